@@ -1919,24 +1919,16 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         RP = 1;
         const int64_t t_max = (int64_t)G * vr.K;
         const int64_t N = (int64_t)ctx->n_cu * slots_per_cu(vr, G);
-        // columns per tile by the cost model: try numbers of column tiles around whole rounds of N
-        const int64_t nct_min = cdiv(E.D0, t_max);
-        int64_t best_cost = -1, best_nct = nct_min;
-        auto consider = [&](int64_t k) {
-            if (k < nct_min) k = nct_min;
-            int64_t tc = cdiv(cdiv(E.D0, k), V) * V;
-            const int64_t tc_min = (int64_t)G * V;      // at least one chunk for every lane
-            if (tc < tc_min) tc = tc_min;
-            if (tc > t_max) return;
-            const int64_t kk = cdiv(E.D0, tc);
-            const int64_t cost = cdiv(E.nrows * kk * copies, N) * (tc + ovh);
-            if (best_cost < 0 || cost < best_cost || (cost == best_cost && kk < best_nct)) { best_cost = cost; best_nct = kk; }
-        };
-        consider(nct_min);
-        const int64_t w0 = cdiv(E.nrows * nct_min * copies, N);
-        for (int64_t w = w0; w < w0 + 8; ++w) consider((w * N) / (E.nrows * copies));
-        int64_t tc = cdiv(cdiv(E.D0, best_nct), V) * V;
-        if (tc < (int64_t)G * V) tc = (int64_t)G * V;
+        // Columns per tile by the cost model, over whole chunk slots only (every lane holds the same number of chunks): a slot
+        // is executed whole whatever part of it is filled, and a tile that ends inside one takes the predicated stores on
+        // every tile instead of on the row's last one.
+        const int64_t slot = (int64_t)G * V;
+        int64_t best_cost = -1, tc = t_max;
+        for (int64_t c = t_max; c >= slot; c -= slot) {
+            const int64_t tiles = E.nrows * cdiv(E.D0, c) * copies;
+            const int64_t cost = tiles >= 3 * N ? tiles * (c + ovh) / N : cdiv(tiles, N) * (c + ovh);
+            if (best_cost < 0 || cost < best_cost) { best_cost = cost; tc = c; }
+        }
         TC = (uint32_t)tc;
         nct = (uint32_t)cdiv(E.D0, tc);
         nvec = (uint32_t)cdiv(cdiv(tc, V), G);
