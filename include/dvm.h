@@ -157,7 +157,8 @@ int  dvm_ctx_set_lds_operands(dvm_ctx *ctx, int enabled);
  * -- the same tiles per workgroup to within one, still static and free of atomics, but the resident workgroups
  * sweep the tensors as one front, which HBM serves faster than N streams that lie far apart.  DVM_ASSIGN_AUTO (the
  * default) is the round-robin order except for programs that keep an operand pinned while consecutive rows share
- * it and whose rows are not whole 128-byte lines, which run blocked.  Results do not depend on the choice. */
+ * it, whose rows are not whole 128-byte lines and whose tensors fit the last-level cache, which run blocked.  Results do not
+ * depend on the choice. */
 typedef enum dvm_assignment { DVM_ASSIGN_BLOCKED = 0, DVM_ASSIGN_INTERLEAVED = 1, DVM_ASSIGN_AUTO = 2 } dvm_assignment;
 int  dvm_ctx_set_assignment(dvm_ctx *ctx, int assignment);
 

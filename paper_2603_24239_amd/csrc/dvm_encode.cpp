@@ -1788,50 +1788,62 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         const int ks[5] = {4, 8, 16, 32, 64};
         int pick = -1;
         uint32_t nv_cap = 0;        // chunks per lane the geometry may use (0: as many as the variant holds)
-        // the largest K that still spreads a row over >= 16 lanes (K = 32: over >= 32 lanes, since that
-        // variant keeps only two waves per SIMD resident); fewer lanes per row mean fewer interpreted
-        // records per element, which measured faster than the higher occupancy of the smaller variants
-        for (int i = 0; i < 5; ++i) {
-            const int K = ks[i];
-            if ((uint32_t)K < V) continue;
-            const int v = find_variant(K);
-            if (v < 0) continue;
-            const int64_t gneed = cdiv(Cr, K / V);
-            if (gneed > VARIANTS[v].max_threads) continue;
-            if (pick < 0 || gneed >= (K >= 32 ? 32 : 16)) pick = v;
-        }
-        // Short rows (a variant exists that holds a row in less than a wave).  What a wave spends on a tile is
-        // mostly fixed -- record decode, addresses, the steps of a reduction across lanes: measured at about four
-        // chunk slots' worth of instructions -- so fewer lanes per row and more chunks per lane mean less work per
-        // row, as long as the waves still fill the machine.  Every (variant, chunks per lane) pair is priced in the
-        // form of the cost model of Section 4.2, ceil(wave tiles / SIMDs) * (4 + chunks per lane), a wave tile
-        // being the part of a tile that one wave holds; the cheapest wins, the smaller variant on a tie.
-        if (pick >= 0 && ctx->dbg_k < (int)V) {
-            int kmax = 0;
-            for (int i = 0; i < 5; ++i)
-                if ((uint32_t)ks[i] >= V && find_variant(ks[i]) >= 0) kmax = ks[i];
-            if (kmax > 0 && cdiv(Cr, kmax / V) < 64) {
-                int64_t best = -1;
-                int prev_k = 0;
-                const int64_t n_simd = 4 * (int64_t)ctx->n_cu;
-                const int64_t nr = E.nrows > 0 ? E.nrows : 1;
+        // Every (variant, chunks per lane) pair is priced in the form of the cost model of Section 4.2, ceil(wave tiles /
+        // SIMDs) * cost of a wave tile, a wave tile being the part of a tile that one wave holds; the cheapest wins, the
+        // smaller variant on a tie.  The cost of a wave tile, in clocks, is fitted to softmax, RMSNorm and LayerNorm over
+        // rows of 16 to 16384 columns in both types:
+        //   - a tile costs 2000 at least (decode, addresses, the steps of the reductions, one latency of memory),
+        //   - a chunk slot costs 880 (fp32; the share of the memory rate) or 1100 (bf16; twice the elements), and 80 for every
+        //     128-byte line its 64 accesses touch where that is more: with G lanes on a row they touch 64 / G * (1 + G / 8)
+        //     lines (fp32 rows of 65 columns: 174 us with 8 lanes x 3 chunks, 296 with 4 x 5, 482 with 2 x 9),
+        //   - over tensors larger than the last-level cache, more than four fp32 chunks or six bf16 chunks in flight per lane buy
+        //     nothing and the variants that hold them keep fewer waves (bf16 rows of 4096: 94 us in (32, 2), 105 in (64, 1);
+        //     within the cache the fewer instructions per element of the wide tile count: 27.7 against 24.4 us at 8192 rows),
+        //   - a row over several waves pays for the exchange between them: it takes as many chunks per lane as its variant holds,
+        //     and a variant below 32 elements per lane only if no wider one takes the row.
+        // Rows that fill a wave at 32 elements per lane take the widest variant that spreads them over 32 lanes or more while
+        // rows are few: one latency per tile is all that counts then, and wider tiles mean fewer waves to exchange with.
+        if (ctx->dbg_k < (int)V) {
+            int64_t best = -1;
+            int prev_k = 0;
+            const int64_t n_simd = 4 * (int64_t)ctx->n_cu;
+            const int64_t nr = E.nrows > 0 ? E.nrows : 1;
+            const int64_t row_bytes = (E.D0 > 0 ? E.D0 : 1) * (V == 8 ? 2 : 4);
+            const bool beyond_cache = 2 * nr * row_bytes * copies > (int64_t)256 << 20;
+            int k_few = 0;
+            if (cdiv(Cr, 32 / V) >= 64 && nr * cdiv(cdiv(Cr, 32 / V), 64) * copies < 8 * n_simd)
                 for (int i = 0; i < 5; ++i) {
-                    const int K = ks[i];
-                    if ((uint32_t)K < V) continue;
-                    const int v = find_variant(K);
-                    if (v < 0) continue;
-                    for (int nv = prev_k / (int)V + 1; nv <= K / (int)V; ++nv) {     // (chunk counts a smaller variant holds were priced with it)
-                        const int64_t gneed = cdiv(Cr, nv);
-                        if (gneed > VARIANTS[v].max_threads) continue;
-                        const int64_t g = gneed <= 64 ? pow2ceil((uint32_t)gneed) : cdiv(gneed, 64) * 64;
-                        if (nv > 1 && g < 2) continue;                               // (keep a few lanes side by side on a row)
-                        const int64_t nvec_g = cdiv(Cr, g);
-                        const int64_t wt = g < 64 ? cdiv(nr, 64 / g) : nr * (g / 64);
-                        const int64_t cost = cdiv(wt * copies, n_simd) * (4 + nvec_g + (g > 64 ? 3 : 0));   // (rows over several waves: a barrier per reduction)
-                        if (best < 0 || cost < best) { best = cost; pick = v; nv_cap = (uint32_t)nv; }
-                    }
-                    prev_k = K;
+                    const int v = (uint32_t)ks[i] < V ? -1 : find_variant(ks[i]);
+                    if (v >= 0 && cdiv(Cr, ks[i] / V) <= VARIANTS[v].max_threads && cdiv(Cr, ks[i] / V) >= 32) k_few = ks[i];
                 }
+            bool wider = false;         // a variant of 32 elements per lane or more takes the row
+            for (int i = 0; i < 5; ++i)
+                if (ks[i] >= 32 && find_variant(ks[i]) >= 0) wider |= cdiv(Cr, ks[i] / V) <= VARIANTS[find_variant(ks[i])].max_threads;
+            for (int i = 0; i < 5; ++i) {
+                const int K = ks[i];
+                if ((uint32_t)K < V || (k_few != 0 && K != k_few)) continue;
+                const int v = find_variant(K);
+                if (v < 0) continue;
+                for (int nv = k_few != 0 ? K / (int)V : prev_k / (int)V + 1; nv <= K / (int)V; ++nv) {     // (chunk counts a smaller variant holds were priced with it)
+                    const int64_t gneed = cdiv(Cr, nv);
+                    if (gneed > VARIANTS[v].max_threads || (gneed > 64 && (nv < K / (int)V || (K < 32 && wider)))) continue;
+                    const int64_t g = gneed <= 64 ? pow2ceil((uint32_t)gneed) : cdiv(gneed, 64) * 64;
+                    const int64_t nvec_g = cdiv(Cr, g);
+                    const int64_t wt = g < 64 ? cdiv(nr, 64 / g) : nr * (g / 64);
+                    int64_t lines = g < 64 ? 64 / g + 8 : 9;
+                    if (g < 64 && 64 / g * row_bytes / 128 + 1 < lines) lines = 64 / g * row_bytes / 128 + 1;     // (short rows share lines)
+                    int64_t slot = V == 8 ? 1100 : 880;
+                    if (80 * lines > slot) slot = 80 * lines;
+                    int64_t tile_cost = nvec_g * slot;
+                    if (beyond_cache && V == 4 && nvec_g > 4) tile_cost = tile_cost * 108 / 100;
+                    if (beyond_cache && K == 64 && (V == 4 || nvec_g > 6)) tile_cost = tile_cost * 115 / 100;
+                    tile_cost += 150;
+                    if (tile_cost < 2000) tile_cost = 2000;
+                    if (g > 64) tile_cost += 100 * (g / 64);
+                    const int64_t cost = cdiv(wt * copies, n_simd) * tile_cost;
+                    if (best < 0 || cost < best) { best = cost; pick = v; nv_cap = (uint32_t)nv; }
+                }
+                prev_k = K;
             }
         }
         if (ctx->dbg_k >= (int)V) {
@@ -2009,13 +2021,15 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     }
     sh[S_TBASE] = 0;
     sh[S_NTENS] = (uint32_t)E.n_acc;
-    // DVM_ASSIGN_AUTO: round-robin, except for a program that keeps an operand pinned while consecutive rows share it
-    // (the reloading part of the prologue) and whose rows are not whole 128-byte lines: there a workgroup that walks
-    // consecutive rows keeps the operand and meets the lines its rows share with their neighbours again at once
-    // (measured 2-8 % faster; with rows of whole lines the round-robin order is 4 % faster).
-    bool interleaved = ctx->assignment == DVM_ASSIGN_INTERLEAVED;
-    if (ctx->assignment == DVM_ASSIGN_AUTO)
-        interleaved = !(E.n_prolog > E.n_prolog_a && (E.D0 * (int64_t)(any_bf16_full ? 2 : 4)) % 128 != 0);
+    // DVM_ASSIGN_AUTO: round-robin, except for a program that keeps an operand pinned while consecutive rows share it (the
+    // reloading part of the prologue), whose rows are not whole 128-byte lines and whose tensors fit the last-level
+    // cache: there a workgroup walks consecutive rows and keeps the operand.  (Within the cache the two orders measure alike,
+    // masked softmax [1, 32, 250, 250] 20.8 us in either; beyond it the round-robin order is faster, [3, 32, 1411, 1411] 343 us
+    // against 357.)
+    bool interleaved = ctx->assignment != DVM_ASSIGN_BLOCKED;
+    const int64_t row_bytes_assign = E.D0 * (int64_t)(any_bf16_full ? 2 : 4);
+    if (ctx->assignment == DVM_ASSIGN_AUTO && E.n_prolog > E.n_prolog_a && row_bytes_assign % 128 != 0 && 2 * E.nrows * row_bytes_assign <= (int64_t)256 << 20)
+        interleaved = false;
     sh[S_FLAGS] = (wgsync ? SF_WGSYNC : 0) | (E.has_cred && E.cstream ? SF_CSTREAM : 0) |
                   (interleaved ? SF_INTERLEAVED : 0) | (E.n_lds > 0 ? SF_LDS : 0) | (long_row ? SF_LONGROW : 0);
     sh[S_PROLOG] = (uint32_t)(E.n_prolog == E.n_ai ? body_words : prolog_words);

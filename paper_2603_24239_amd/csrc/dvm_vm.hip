@@ -47,6 +47,7 @@ struct KArgs {
     uint32_t rotate;                    // 1: every segment deals its tiles out starting at the workgroup after the one the
                                         // segment before stopped at (short segments then do not all land on the first workgroups)
     uint32_t seg_first;                 // this launch runs segments seg_first .. nseg - 1
+    uint32_t aliased;                   // 1: some segment's output shares memory with another tensor of that segment
 };
 
 #define DI __device__ __forceinline__
@@ -323,18 +324,27 @@ template <uint32_t R> DI float wave_allreduce(float v, uint32_t width) {
 // ------------------------------------------------------------------------------------------
 // per-tile geometry
 // ------------------------------------------------------------------------------------------
+// The wave-uniform part lives across the interpreter loop, whose scalar registers are scarce (a value more there is
+// spilled and costs every record): it holds what cannot be derived in a few scalar instructions where it is used.
 struct Geo {
     // wave-uniform
     uint64_t colbase;     // first column of the tile
-    uint32_t ncols;       // valid columns of the tile
+    uint32_t cend;        // chunk slots that start before this column (relative to colbase) are read, reduced and stored whole: the
+                          // tile's width, less the elements of a last chunk that is handled element by element
     uint32_t GV;          // G * V: column distance between two chunks of one lane
-    uint32_t nvec;        // chunks per lane
-    uint32_t nact;        // nvec * V
-    uint32_t part_slot;   // chunk slot that holds the ragged last chunk, or ~0u
-    uint32_t part_lane;   // lane (within the row group) that owns it
-    uint32_t part_col;    // its first column (relative to colbase)
-    uint32_t part_n;      // its number of valid elements
-    uint32_t ragged;      // some lane has invalid columns inside live chunks: reductions must mask
+    uint32_t nact;        // chunks per lane * V
+    uint32_t pk;          // packed: PK_* below
+    static constexpr uint32_t PK_N = 0xF;           // elements of the last chunk a row ends inside of (0: rows of whole chunks)
+    static constexpr uint32_t PK_RAGGED = 0x40;     // some lane has invalid columns inside live chunks: reductions must mask
+    static constexpr uint32_t PK_SLIDE = 0x80;      // the last chunk slides back to end with the row (see tile_cols)
+    static constexpr uint32_t PK_PART = 0x100;      // the last chunk is handled element by element, by ...
+    static constexpr int PK_SLOT = 12, PK_LANE = 20;        // ... the lane (within the row group) PK_LANE in its chunk slot PK_SLOT
+    DI uint32_t ragged() const { return pk & PK_RAGGED; }
+    DI uint32_t slide() const { return pk & PK_SLIDE; }
+    DI uint32_t part() const { return pk & PK_PART; }
+    DI uint32_t part_n() const { return pk & PK_N; }
+    DI uint32_t part_slot() const { return (pk >> PK_SLOT) & 0xFF; }
+    DI uint32_t part_lane() const { return pk >> PK_LANE; }
     // per lane
     uint32_t i1, i2, i3;  // decomposition of the lane's row index over the outer dims
     uint32_t lanecol;     // first column of the lane's chunk 0, relative to colbase: V times the lane's index within the row group
@@ -401,7 +411,7 @@ DI void st_b16(gptr p, uint32_t v, bool ok) {
 // issued, widens the bf16 bits in place and fetches the chunk a ragged row ends in.
 // DT: 0 = fp32, 1 = bf16.  V = chunk width.  `rowp` points at column `colbase` of the lane's row in this tensor
 // (row 0 for a lane whose row is outside the tensor).  A chunk that lies beyond the tile's columns reads the
-// tile's chunk 0 instead: the value is never stored and reductions mask it.  Dtype, chunk width and cache hint
+// tile's last chunk instead: the value is never stored and reductions mask it.  Dtype, chunk width and cache hint
 // are fixed at compile time, so the request needs no per-piece scalar arithmetic.  NT: the data is read once,
 // hint the caches accordingly.
 typedef f32x4 f32x4_a2 __attribute__((aligned(2)));
@@ -411,15 +421,19 @@ template <bool NT> DI f32x4 ld_b128(gcptr q) {
     else return *src;
 }
 
+// First column (relative to the tile's) that the lane's chunk slot J reads and writes.
+template <int V> DI uint32_t chunk_col(const Geo &g, int J) {
+    const uint32_t c0 = g.lanecol + (uint32_t)J * g.GV;
+    const uint32_t cmax = g.cend - V;
+    return c0 < cmax ? c0 : cmax;
+}
 template <int K, int DT, int V, bool NT> DI void request_inplace(Tile<K> &t, gcptr rowp, const Geo &g) {
     constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.ncols >= (uint32_t)V) {       // wave-uniform: the tile has at least one whole chunk
+        if (g.cend != 0) {       // wave-uniform: the tile has at least one whole chunk
             sfor<NJ>([&]<int J>() LI {
-                const uint32_t c0 = g.lanecol + (uint32_t)J * g.GV;
-                const uint32_t cc = c0 + V <= g.ncols ? c0 : 0u;
-                gcptr q = rowp + (uint64_t)cc * ES;
+                gcptr q = rowp + (uint64_t)chunk_col<V>(g, J) * ES;
                 if constexpr (DT == 0) {
                     sfor<V / 4>([&]<int H>() LI { t.q[J * (V / 4) + H] = ld_b128<NT>(q + 16 * H); });
                 } else {
@@ -455,7 +469,7 @@ template <int K, int DT, int V> DI void finish_tile(Tile<K> &t, gcptr rowp, cons
     if constexpr (K < V) tile_zero<K>(t);
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.ncols < (uint32_t)V) {        // narrower than one chunk: only the ragged part below
+        if (g.cend == 0) {        // narrower than one chunk: only the ragged part below
             tile_zero<K>(t);
         } else if constexpr (DT == 1) {
             sfor<NJ>([&]<int J>() LI {
@@ -465,21 +479,21 @@ template <int K, int DT, int V> DI void finish_tile(Tile<K> &t, gcptr rowp, cons
                 t.q[2 * J + 1] = f32x4{bf16_lo(w2), bf16_hi(w2), bf16_lo(w3), bf16_hi(w3)};
             });
         }
-        if (g.part_slot != ~0u) {   // wave-uniform: this tile ends inside a chunk
+        if (g.part() != 0) {   // wave-uniform: this tile ends inside a chunk
             // its elements are read one by one by every lane of the row (one of them keeps them); an element
             // beyond the row reads element 0 again
-            const bool own = g.lanecol == g.part_lane * (uint32_t)V;
+            const bool own = g.lanecol == g.part_lane() * (uint32_t)V;
             float pv[V];
             sfor<V>([&]<int E>() LI {
-                const uint32_t e = (uint32_t)E < g.part_n ? (uint32_t)E : 0u;       // wave-uniform
-                gcptr q = rowp + (uint64_t)(g.part_col + e) * ES;
+                const uint32_t e = (uint32_t)E < g.part_n() ? (uint32_t)E : 0u;       // wave-uniform
+                gcptr q = rowp + (uint64_t)(g.cend + e) * ES;
                 if constexpr (DT == 0) pv[E] = *(const GLOBAL_AS float *)q;
                 else pv[E] = bf16_lo(*(const GLOBAL_AS uint16_t *)q);
             });
             sfor<NJ>([&]<int J>() LI {
-                if ((uint32_t)J == g.part_slot) {       // wave-uniform
+                if ((uint32_t)J == g.part_slot()) {       // wave-uniform
                     sfor<V>([&]<int E>() LI {
-                        const bool ok = own && (uint32_t)E < g.part_n;
+                        const bool ok = own && (uint32_t)E < g.part_n();
                         // (the empty statement keeps this a select between two values: a select between
                         // two register-array elements would be turned into a select of their addresses,
                         // which forces both arrays into memory)
@@ -512,19 +526,17 @@ template <int K, int DT, int V, bool NT> DI void request_staged(Raw<K> &raw, gcp
     constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.ncols >= (uint32_t)V) {
+        if (g.cend != 0) {
             sfor<NJ>([&]<int J>() LI {
-                const uint32_t c0 = g.lanecol + (uint32_t)J * g.GV;
-                const uint32_t cc = c0 + V <= g.ncols ? c0 : 0u;
-                gcptr q = rowp + (uint64_t)cc * ES;
+                gcptr q = rowp + (uint64_t)chunk_col<V>(g, J) * ES;
                 constexpr int PIECES = DT == 0 ? V / 4 : 1;
                 sfor<PIECES>([&]<int H>() LI { raw.q[J * PIECES + H] = ld_b128<NT>(q + 16 * H); });
             });
         }
-        if (g.part_slot != ~0u) {
+        if (g.part() != 0) {
             sfor<V>([&]<int E>() LI {
-                const uint32_t e = (uint32_t)E < g.part_n ? (uint32_t)E : 0u;
-                gcptr q = rowp + (uint64_t)(g.part_col + e) * ES;
+                const uint32_t e = (uint32_t)E < g.part_n() ? (uint32_t)E : 0u;
+                gcptr q = rowp + (uint64_t)(g.cend + e) * ES;
                 if constexpr (DT == 0) raw.pv[E] = *(const GLOBAL_AS uint32_t *)q;
                 else raw.pv[E] = *(const GLOBAL_AS uint16_t *)q;
             });
@@ -552,8 +564,8 @@ template <int K> DI void request_staged_dispatch(Raw<K> &raw, uint32_t dt, uint3
 template <int K, int DT, int V, uint32_t B> DI void combine_staged(Tile<K> &t, const Raw<K> &raw, const Geo &g) {
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.ncols >= (uint32_t)V) {
-            const bool masked = g.ragged != 0;       // wave-uniform
+        if (g.cend != 0) {
+            const bool masked = g.ragged() != 0;       // wave-uniform
             auto chunk = [&]<int J>(bool whole) LI {
                 float x[V];
                 if constexpr (DT == 0) {
@@ -575,11 +587,11 @@ template <int K, int DT, int V, uint32_t B> DI void combine_staged(Tile<K> &t, c
             if (!masked) {
                 sfor<NJ>([&]<int J>() LI { chunk.template operator()<J>(true); });
             } else {
-                sfor<NJ>([&]<int J>() LI { chunk.template operator()<J>(g.lanecol + (uint32_t)J * g.GV + V <= g.ncols); });
+                sfor<NJ>([&]<int J>() LI { chunk.template operator()<J>(g.lanecol + (uint32_t)J * g.GV < g.cend); });
             }
         }
-        if (g.part_slot != ~0u) {
-            const bool own = g.lanecol == g.part_lane * (uint32_t)V;
+        if (g.part() != 0) {
+            const bool own = g.lanecol == g.part_lane() * (uint32_t)V;
             float pv[V];
             sfor<V>([&]<int E>() LI {
                 const uint32_t bits = raw.pv[E];
@@ -587,9 +599,9 @@ template <int K, int DT, int V, uint32_t B> DI void combine_staged(Tile<K> &t, c
                 else pv[E] = bf16_lo(bits);
             });
             sfor<NJ>([&]<int J>() LI {
-                if ((uint32_t)J == g.part_slot) {
+                if ((uint32_t)J == g.part_slot()) {
                     sfor<V>([&]<int E>() LI {
-                        const bool ok = own && (uint32_t)E < g.part_n;
+                        const bool ok = own && (uint32_t)E < g.part_n();
                         float x = pv[E];
                         asm volatile("" : "+v"(x));
                         x = bin_op<B>(TV(t, J * V + E), x);
@@ -613,12 +625,10 @@ template <int K, int DT, int V> DI void store_tile(const Tile<K> &t, gptr rowp, 
     constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        const uint32_t lanecol = g.lanecol;
-        if (g.ncols >= (uint32_t)V) {
+        if (g.cend != 0) {
             sfor<NJ>([&]<int J>() LI {
-                const uint32_t c0 = lanecol + (uint32_t)J * g.GV;
-                const bool ok = g.rowok && c0 + V <= g.ncols;
-                gptr q = rowp + (uint64_t)c0 * ES;
+                const bool ok = g.rowok && g.lanecol + (uint32_t)J * g.GV < g.cend;
+                gptr q = rowp + (uint64_t)chunk_col<V>(g, J) * ES;
                 if constexpr (DT == 0) {
                     sfor<V / 4>([&]<int H>() LI { st_b128(q + 16 * H, t.q[J * (V / 4) + H], ok); });
                 } else {
@@ -628,13 +638,13 @@ template <int K, int DT, int V> DI void store_tile(const Tile<K> &t, gptr rowp, 
                 }
             });
         }
-        if (g.part_slot != ~0u) {
-            const bool own = g.rowok && g.lanecol == g.part_lane * (uint32_t)V;
+        if (g.part() != 0) {
+            const bool own = g.rowok && g.lanecol == g.part_lane() * (uint32_t)V;
             sfor<NJ>([&]<int J>() LI {
-                if ((uint32_t)J == g.part_slot) {
+                if ((uint32_t)J == g.part_slot()) {
                     sfor<V>([&]<int E>() LI {
-                        if ((uint32_t)E < g.part_n) {       // wave-uniform
-                            gptr q = rowp + (uint64_t)(g.part_col + E) * ES;
+                        if ((uint32_t)E < g.part_n()) {       // wave-uniform
+                            gptr q = rowp + (uint64_t)(g.cend + E) * ES;
                             if constexpr (DT == 0) st_b32(q, TV(t, J * V + E), own);
                             else st_b16(q, (uint32_t)pack_bf16(TV(t, J * V + E)), own);
                         }
@@ -665,12 +675,6 @@ struct Wide {
     uint32_t rowok;         // the wave's row lies inside the tensor
 };
 
-// byte offset of chunk J of this lane from the row base; a chunk beyond the tile's columns reads chunk 0 instead
-template <int V, int ES> DI uint32_t chunk_off(const Geo &g, uint32_t lanecol, int J) {
-    const uint32_t c0 = lanecol + (uint32_t)J * g.GV;
-    const uint32_t cc = c0 + V <= g.ncols ? c0 : 0u;
-    return cc * ES;
-}
 template <int K, int DT, int V, bool NT> DI void issue_wide(Tile<K> &t, const char *rowbase, const uint32_t (&vo)[K / V]) {
     constexpr int NJ = K / V;
     sfor<NJ>([&]<int J>() LI {
@@ -688,7 +692,7 @@ template <int K, int DT, int V, bool NT> DI void issue_wide(Tile<K> &t, const ch
 #define DVM_ISSUE_WIDE(DT, V, NT)                                                                   \
     {                                                                                               \
         uint32_t vo[K / V];                                                                         \
-        sfor<K / V>([&]<int J>() LI { vo[J] = chunk_off<V, (DT == 0 ? 4 : 2)>(g, g.lanecol, J); }); \
+        sfor<K / V>([&]<int J>() LI { vo[J] = chunk_col<V>(g, J) * (DT == 0 ? 4 : 2); }); \
         _Pragma("unroll") for (int j_ = 0; j_ < K / V; ++j_) asm volatile("" : "+v"(vo[j_]));       \
         if (ra == SRC_ACC) {                                                                        \
             issue_wide<K, DT, V, NT>(acc, rowbase, vo);                                             \
@@ -697,36 +701,51 @@ template <int K, int DT, int V, bool NT> DI void issue_wide(Tile<K> &t, const ch
         }                                                                                           \
     }
 
-// full tile (no ragged chunk, every chunk inside the row), row inside the tensor: plain 16-byte stores
-template <int K, int DT, int V> DI void store_wide_full(const Tile<K> &t, char *rowbase, const Geo &g) {
+// A row that consists of chunks alone (none handled element by element), row inside the tensor: 16-byte stores from
+// the scalar row base.  FULL: every chunk slot the tile uses lies inside the row.  Otherwise the slots the row ends in
+// switch the lanes behind its end off.
+DI void st_b128_off(char *base, uint32_t off, f32x4 v, bool ok) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(ok);
+    uint64_t sv;
+    asm volatile("s_and_saveexec_b64 %0, %1\n\tglobal_store_dwordx4 %2, %3, %4 nt\n\ts_mov_b64 exec, %0\n\ts_nop 0"
+                 : "=&s"(sv) : "s"(m), "v"(off), "v"(v), "s"(base) : "memory", "scc");
+}
+template <int K, int DT, int V, bool FULL> DI void store_wide(const Tile<K> &t, char *rowbase, const Geo &g) {
     constexpr int ES = DT == 0 ? 4 : 2;
     constexpr int NJ = K / V;
     sfor<NJ>([&]<int J>() LI {
         if (J == 0 || (uint32_t)(J * V) < g.nact) {        // wave-uniform: chunk slots the tile uses
-            const uint32_t vo = (g.lanecol + (uint32_t)J * g.GV) * ES;
-            GLOBAL_AS char *q = (GLOBAL_AS char *)(rowbase + (uint64_t)vo);
+            const uint32_t c0 = g.lanecol + (uint32_t)J * g.GV;
+            const uint32_t vo = (FULL ? c0 : chunk_col<V>(g, J)) * ES;
+            const bool whole = FULL || (uint32_t)(J + 1) * g.GV <= g.cend;      // wave-uniform
+            auto put = [&](f32x4 v, uint32_t at) LI {
+                if (whole) __builtin_nontemporal_store(v, (GLOBAL_AS f32x4 *)(rowbase + (uint64_t)vo + at));
+                else st_b128_off(rowbase, vo + at, v, c0 < g.cend);
+            };
             if constexpr (DT == 0) {
-                sfor<V / 4>([&]<int H>() LI { __builtin_nontemporal_store(t.q[J * (V / 4) + H], (GLOBAL_AS f32x4 *)(q + 16 * H)); });
+                sfor<V / 4>([&]<int H>() LI { put(t.q[J * (V / 4) + H], 16 * H); });
             } else {
                 const f32x4 lo = t.q[2 * J], hi = t.q[2 * J + 1];
                 const u32x4 r = {pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w), pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w)};
-                __builtin_nontemporal_store(__builtin_bit_cast(f32x4, r), (GLOBAL_AS f32x4 *)q);
+                put(__builtin_bit_cast(f32x4, r), 0);
             }
         }
     });
 }
-template <int K> DI void store_wide_full_dispatch(const Tile<K> &t, uint32_t dt, uint32_t V, char *rowbase, const Geo &g) {
+template <int K, bool FULL> DI void store_wide_dispatch(const Tile<K> &t, uint32_t dt, uint32_t V, char *rowbase, const Geo &g) {
     if (dt == 0) {
-        if (V == 4) store_wide_full<K, 0, 4>(t, rowbase, g);
-        else if constexpr (K >= 8) store_wide_full<K, 0, 8>(t, rowbase, g);
+        if (V == 4) store_wide<K, 0, 4, FULL>(t, rowbase, g);
+        else if constexpr (K >= 8) store_wide<K, 0, 8, FULL>(t, rowbase, g);
     } else {
-        if constexpr (K >= 8) store_wide_full<K, 1, 8>(t, rowbase, g);
+        if constexpr (K >= 8) store_wide<K, 1, 8, FULL>(t, rowbase, g);
     }
 }
 
 // in-lane part of a row reduction over the accumulator.  When the tile is ragged, a chunk of a lane
 // is either wholly inside the row, wholly outside, or the one chunk the row ends in: whole chunks
-// are reduced unmasked and selected per chunk, only the last chunk is masked element by element.
+// are reduced unmasked and selected per chunk.  A last chunk that slid back repeats elements of the chunk before it:
+// a maximum or minimum may take them twice, a sum leaves them out (its first elements, as many as it slid by).  A last chunk
+// handled element by element is masked element by element.
 template <int K, uint32_t R, int V> DI float lane_reduce_ragged(const Tile<K> &a, const Geo &g) {
     float v = red_ident<R>();
     if constexpr (K >= V) {
@@ -734,21 +753,30 @@ template <int K, uint32_t R, int V> DI float lane_reduce_ragged(const Tile<K> &a
         constexpr uint32_t RC = R == R_SUMSQ ? R_SUM : R;      // how partial results combine
         sfor<NJ>([&]<int J>() LI {
             if (J == 0 || (uint32_t)(J * V) < g.nact) {        // wave-uniform
+                const uint32_t c0 = g.lanecol + (uint32_t)J * g.GV;
                 float c = red_ident<R>();
-                sfor<V>([&]<int E>() LI {
-                    if constexpr (R == R_SUMSQ) c = f_fma(TV(a, J * V + E), TV(a, J * V + E), c);
-                    else c = red_comb<R>(c, TV(a, J * V + E));
-                });
-                const bool whole = g.lanecol + (uint32_t)J * g.GV + V <= g.ncols;
-                v = red_comb<RC>(v, whole ? c : red_ident<R>());
+                if (R == R_MAX || R == R_MIN || g.slide() == 0 || (uint32_t)(J + 1) * g.GV <= g.cend) {      // wave-uniform
+                    sfor<V>([&]<int E>() LI {
+                        if constexpr (R == R_SUMSQ) c = f_fma(TV(a, J * V + E), TV(a, J * V + E), c);
+                        else c = red_comb<R>(c, TV(a, J * V + E));
+                    });
+                } else {
+                    const uint32_t dup = c0 - chunk_col<V>(g, J);
+                    sfor<V>([&]<int E>() LI {
+                        const float x = (uint32_t)E >= dup ? TV(a, J * V + E) : 0.0f;
+                        if constexpr (R == R_SUMSQ) c = f_fma(x, x, c);
+                        else c = red_comb<R>(c, x);
+                    });
+                }
+                v = red_comb<RC>(v, c0 < g.cend ? c : red_ident<R>());
             }
         });
-        if (g.part_slot != ~0u) {
-            const bool own = g.lanecol == g.part_lane * (uint32_t)V;
+        if (g.part() != 0) {
+            const bool own = g.lanecol == g.part_lane() * (uint32_t)V;
             sfor<NJ>([&]<int J>() LI {
-                if ((uint32_t)J == g.part_slot) {              // wave-uniform
+                if ((uint32_t)J == g.part_slot()) {              // wave-uniform
                     sfor<V>([&]<int E>() LI {
-                        const bool ok = own && (uint32_t)E < g.part_n;
+                        const bool ok = own && (uint32_t)E < g.part_n();
                         if constexpr (R == R_SUMSQ) {
                             const float x = ok ? TV(a, J * V + E) : 0.0f;
                             v = f_fma(x, x, v);
@@ -764,7 +792,7 @@ template <int K, uint32_t R, int V> DI float lane_reduce_ragged(const Tile<K> &a
 }
 template <int K, uint32_t R> DI float lane_reduce(const Tile<K> &a, const Geo &g, uint32_t V) {
     float v = red_ident<R>();
-    if (!g.ragged) {
+    if (g.ragged() == 0) {
         sfor<K / 4>([&]<int Q>() LI {
             if (Q == 0 || (uint32_t)(Q * 4) < g.nact) {
                 sfor<4>([&]<int E>() LI {
@@ -842,23 +870,34 @@ DI uint32_t sdiv_u(uint32_t n, uint32_t m, uint32_t sh) {   // the same on wave-
 // Where a tile of a segment sits.  Columns (wave-uniform): first column and width of column tile
 // `tile_c`, and which chunk the row ends in.  Rows: the lane's row decomposed over the outer
 // iteration dims; `rp` is the row of the tile this lane holds.
-DI void tile_cols(Geo &gt, const uint32_t *sh, uint32_t tile_c, uint32_t G, uint32_t V) {
+DI void tile_cols(Geo &gt, const uint32_t *sh, uint32_t tile_c, uint32_t G, uint32_t V, uint32_t aliased) {
     const uint32_t TC = sh[S_TC];
     const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
     gt.colbase = (uint64_t)tile_c * TC;
     const uint64_t rem = D0 - gt.colbase;
-    gt.ncols = rem < TC ? (uint32_t)rem : TC;
-    const uint32_t full_chunks = V == 8 ? gt.ncols >> 3 : gt.ncols >> 2;      // V is 4 or 8
-    gt.part_n = gt.ncols - full_chunks * V;
-    gt.part_slot = ~0u;
-    gt.part_lane = 0;
-    gt.part_col = full_chunks * V;
-    if (gt.part_n != 0) {
-        gt.part_slot = __builtin_amdgcn_readfirstlane(full_chunks / G);
-        gt.part_lane = full_chunks - gt.part_slot * G;
-    }
+    const uint32_t ncols = rem < TC ? (uint32_t)rem : TC;
+    // A row that ends inside a chunk: that chunk slides back so that it ends with the row and repeats elements of the
+    // chunk before it.  Every operand of the tile is read at the slid columns, so element-wise results are computed
+    // twice alike and stored twice alike, and the row costs whole 16-byte accesses only: reading its last elements one
+    // by one, behind the wait for the chunks, made a second wait for memory per tile (softmax over bf16 rows of 751
+    // columns 188 us that way and 131 us this way).  A program may write its own input: then the chunk before must belong
+    // to the same wave, which reads both before it stores either.  Where it does not, and in rows narrower than a chunk, the
+    // last elements are handled one by one (part_*).
+    const uint32_t full_chunks = V == 8 ? ncols >> 3 : ncols >> 2;      // V is 4 or 8
+    const uint32_t n = ncols - full_chunks * V;
+    gt.cend = full_chunks * V;
     // rows never mix in a reduction, so only invalid columns inside live chunks need a mask
-    gt.ragged = gt.ncols != gt.nact * G;
+    gt.pk = n | (ncols != gt.nact * G ? Geo::PK_RAGGED : 0u);
+    if (n != 0) {
+        const uint32_t slot = __builtin_amdgcn_readfirstlane(full_chunks / G);
+        const uint32_t lane = full_chunks - slot * G;
+        if (full_chunks != 0 && (G <= 64 || (lane & 63u) != 0 || aliased == 0)) {
+            gt.pk |= Geo::PK_SLIDE;
+            gt.cend = ncols;
+        } else {
+            gt.pk |= Geo::PK_PART | (slot << Geo::PK_SLOT) | (lane << Geo::PK_LANE);
+        }
+    }
 }
 DI void tile_rows_at(Geo &gt, const uint32_t *sh, uint32_t row, bool ok) {
     gt.rowok = ok;
@@ -889,7 +928,9 @@ DI void tile_rows(Geo &gt, const uint32_t *sh, uint32_t tile_r, uint32_t rp, uin
 // Copy the first `d0` elements of the tensor at `src` (dtype dt) into an LDS image of n16 16-byte pieces, zero behind
 // the row's end.  All `nthreads` threads of the workgroup take part; every branch is wave-uniform (a thread
 // past the last piece copies the last piece once more).
-DI void lds_copy_row(LDS_AS char *dst, uint32_t n16, gcptr src, uint64_t d0, uint32_t dt, uint32_t tid, uint32_t nthreads) {
+// `full` and `back`: elements from `full` on (a last chunk that slides back, see tile_cols) are read `back` elements
+// before their place; full = d0 and back = 0 where nothing slides.
+DI void lds_copy_row(LDS_AS char *dst, uint32_t n16, gcptr src, uint64_t d0, uint32_t full, uint32_t back, uint32_t dt, uint32_t tid, uint32_t nthreads) {
     const uint32_t es = dt == 0 ? 4u : 2u;
     const uint32_t epp = 16u / es;                        // elements per piece
     const bool aligned = (((uint64_t)(uintptr_t)src) & 15u) == 0;
@@ -897,7 +938,7 @@ DI void lds_copy_row(LDS_AS char *dst, uint32_t n16, gcptr src, uint64_t d0, uin
         const uint32_t want = base + tid;
         const uint32_t i = want < n16 ? want : n16 - 1;
         const uint64_t e0 = (uint64_t)i * epp;
-        const bool whole = aligned && e0 + epp <= d0;
+        const bool whole = aligned && e0 + epp <= full;
         u32x4 v;
         if (__builtin_amdgcn_ballot_w64(!whole) == 0) {     // the usual case: this wave's pieces all lie inside the row
             v = *(const GLOBAL_AS u32x4 *)(src + (uint64_t)i * 16u);
@@ -905,13 +946,15 @@ DI void lds_copy_row(LDS_AS char *dst, uint32_t n16, gcptr src, uint64_t d0, uin
             uint32_t wds[4] = {0u, 0u, 0u, 0u};
             if (dt == 0) {
                 sfor<4>([&]<int E>() LI {
-                    const uint64_t e = e0 + E;
+                    const uint64_t p = e0 + E;
+                    const uint64_t e = p < full ? p : p - back;
                     const uint32_t x = *(const GLOBAL_AS uint32_t *)(src + (e < d0 ? e : 0) * 4u);
                     wds[E] = e < d0 ? x : 0u;
                 });
             } else {
                 sfor<8>([&]<int E>() LI {
-                    const uint64_t e = e0 + E;
+                    const uint64_t p = e0 + E;
+                    const uint64_t e = p < full ? p : p - back;
                     const uint32_t x = *(const GLOBAL_AS uint16_t *)(src + (e < d0 ? e : 0) * 2u);
                     wds[E / 2] |= (e < d0 ? x : 0u) << (16 * (E & 1));
                 });
@@ -936,10 +979,10 @@ template <int K, int V, bool HASA, bool HASB>
 DI void lds_fma(Tile<K> &acc, float s, const LDS_AS char *pa, const LDS_AS char *pb, bool a_bf16, bool b_bf16, uint32_t lanecol, const Geo &g) {
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        const uint32_t ncols_pad = (g.ncols + (uint32_t)V - 1u) / (uint32_t)V * (uint32_t)V;
+        const uint32_t ncols_pad = g.slide() != 0 ? (g.cend + (uint32_t)V - 1u) / (uint32_t)V * (uint32_t)V : g.cend + (g.part() != 0 ? (uint32_t)V : 0u);
         const uint32_t esa = (V == 8 && a_bf16) ? 2u : 4u, esb = (V == 8 && b_bf16) ? 2u : 4u;
         sfor<NJ>([&]<int J>() LI {
-            if ((uint32_t)J < g.nvec) {         // wave-uniform
+            if ((uint32_t)(J * V) < g.nact) {         // wave-uniform
                 const uint32_t c0 = lanecol + (uint32_t)J * g.GV;
                 const uint32_t cc = c0 + V <= ncols_pad ? c0 : 0u;
                 u32x4 a0 = {0u, 0u, 0u, 0u}, a1 = a0, b0 = a0, b1 = a0;
@@ -1009,17 +1052,11 @@ DI void lds_fma(Tile<K> &acc, float s, const LDS_AS char *pa, const LDS_AS char 
     {                                                                                                         \
         uint32_t cb_lo = __builtin_amdgcn_readfirstlane((uint32_t)gt.colbase);                                \
         uint32_t cb_hi = __builtin_amdgcn_readfirstlane((uint32_t)(gt.colbase >> 32));                        \
-        g.ncols = __builtin_amdgcn_readfirstlane(gt.ncols);                                                   \
+        g.cend = __builtin_amdgcn_readfirstlane(gt.cend);                                                     \
         g.GV = __builtin_amdgcn_readfirstlane(gt.GV);                                                         \
-        g.nvec = __builtin_amdgcn_readfirstlane(gt.nvec);                                                     \
         g.nact = __builtin_amdgcn_readfirstlane(gt.nact);                                                     \
-        g.part_slot = __builtin_amdgcn_readfirstlane(gt.part_slot);                                           \
-        g.part_lane = __builtin_amdgcn_readfirstlane(gt.part_lane);                                           \
-        g.part_col = __builtin_amdgcn_readfirstlane(gt.part_col);                                             \
-        g.part_n = __builtin_amdgcn_readfirstlane(gt.part_n);                                                 \
-        g.ragged = __builtin_amdgcn_readfirstlane(gt.ragged);                                                 \
-        asm volatile("" : "+s"(cb_lo), "+s"(cb_hi), "+s"(g.ncols), "+s"(g.GV), "+s"(g.nvec), "+s"(g.nact));   \
-        asm volatile("" : "+s"(g.part_slot), "+s"(g.part_lane), "+s"(g.part_col), "+s"(g.part_n), "+s"(g.ragged)); \
+        g.pk = __builtin_amdgcn_readfirstlane(gt.pk);                                                         \
+        asm volatile("" : "+s"(cb_lo), "+s"(cb_hi), "+s"(g.cend), "+s"(g.GV), "+s"(g.nact), "+s"(g.pk));      \
         g.colbase = (uint64_t)cb_lo | ((uint64_t)cb_hi << 32);                                                \
     }
 
@@ -1091,7 +1128,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 
         Geo gt;
         gt.GV = G * V;
-        gt.nvec = nvec;
         gt.nact = nvec * V;
         const uint32_t rp = tid / G;            // row of the tile held by this lane
         gt.lanecol = (tid - rp * G) * V;
@@ -1176,7 +1212,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
         }
 
         const uint32_t nct = sh[S_NCT];
-        if (nct <= 1) tile_cols(gt, sh, 0, G, V);
+        if (nct <= 1) tile_cols(gt, sh, 0, G, V, args.aliased);
         // A segment that reduces along the penultimate axis counts units (outer index, column tile) in M;
         // the workgroup walks the `inner` rows of a unit RP at a time, one row per wave and step (rin),
         // accumulating in tile registers, and runs the epilogue records after the last step.  Other
@@ -1198,7 +1234,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                 uint32_t tile_r0 = tile;
                 if (nct > 1) {          // (a single column tile was placed once, before the loop)
                     tile_r0 = sdiv_u(tile, shl[S_NCTM], shl[S_NCTSH]);
-                    if (rin == 0) tile_cols(gt, shl, tile - tile_r0 * nct, G, V);      // the steps of a unit share its columns
+                    if (rin == 0) tile_cols(gt, shl, tile - tile_r0 * nct, G, V, args.aliased);      // the steps of a unit share its columns
                 }
                 if (inner != 0) {
                     const uint32_t r = rin * RP + rp;
@@ -1211,10 +1247,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                 // tile prologue: where this tile sits, which of its lanes and chunks are valid
                 uint32_t tile_r = tile;
                 if (longrow) {
-                    tile_cols(gt, sh, lr_c, G, V);
+                    tile_cols(gt, sh, lr_c, G, V, args.aliased);
                 } else if (nct > 1) {   // (a single column tile was placed once, before the loop)
                     tile_r = sdiv_u(tile, sh[S_NCTM], sh[S_NCTSH]);
-                    tile_cols(gt, sh, tile - tile_r * nct, G, V);
+                    tile_cols(gt, sh, tile - tile_r * nct, G, V, args.aliased);
                 }
                 tile_rows(gt, sh, tile_r, rp, tid, RP, seg_threads);
             }
@@ -1263,10 +1299,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                             Geo g = gt;
                             uint32_t gp = cur;
                             u32x4s rw = cw;
-                            const bool slow_finish = g.part_slot != ~0u || g.ncols < V;
+                            const bool slow_finish = g.part() != 0;
                             uint32_t widen = 0;             // bit r + 1: register r (bit 0: ACC) holds raw bf16 bits
                             for (;;) {
-                                asm volatile("" : "+v"(g.lanecol));
+                                asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
                                 const uint32_t r0w = rw.x, w1 = rw.y, r2w = rw.z, r3w = rw.w;
                                 const uint32_t rop = r0w & 0xFF, ra = (r0w >> 16) & 0xFF;
                                 const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
@@ -1277,7 +1313,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                                     off += (int64_t)wd.i2 * DVM_I64(h0, h1) + (int64_t)wd.i3 * DVM_I64(h2, h3);
                                 }
                                 const char *rowbase = (const char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2);
-                                if (g.ncols >= V) {
+                                if (g.cend != 0) {
                                     if ((w1 >> 16) & MF_STREAM) {
                                         if (dt != 0) { if constexpr (K >= 8) DVM_ISSUE_WIDE(1, 8, true) }
                                         else if (V == 4) DVM_ISSUE_WIDE(0, 4, true)
@@ -1297,7 +1333,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                             }
                             if (slow_finish) {          // ragged rows: walk the records again (row address for the last chunk)
                                 for (uint32_t fp = cur; fp < gp;) {
-                                    asm volatile("" : "+v"(g.lanecol));
+                                    asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
                                     const u32x4s fw = fetch4(code, fp);
                                     const uint32_t r0w = fw.x, w1 = fw.y, r2w = fw.z, r3w = fw.w;
                                     const uint32_t rop = r0w & 0xFF, ra = (r0w >> 16) & 0xFF;
@@ -1334,11 +1370,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                         DVM_GEO()
                         uint32_t gp = cur;              // word offset of the record being issued
                         u32x4s rw = cw;
-                        bool finish = g.part_slot != ~0u || g.ncols < V;
+                        bool finish = g.part() != 0;
                         for (;;) {
                             // (the lane's column is made opaque once per record: otherwise the chunk addresses of every
                             // dtype and chunk width are computed ahead of the loop and held in registers throughout)
-                            asm volatile("" : "+v"(g.lanecol));
+                            asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
                             const uint32_t r0w = rw.x, w1 = rw.y, r2w = rw.z, r3w = rw.w;
                             const uint32_t rop = r0w & 0xFF, ra = (r0w >> 16) & 0xFF;
                             const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
@@ -1365,13 +1401,13 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                         }
                         if (finish) {
                             for (uint32_t fp = cur; fp < gp;) {
-                                asm volatile("" : "+v"(g.lanecol));
+                                asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
                                 const u32x4s fw = fetch4(code, fp);
                                 const uint32_t r0w = fw.x, w1 = fw.y, r2w = fw.z, r3w = fw.w;
                                 const uint32_t rop = r0w & 0xFF, ra = (r0w >> 16) & 0xFF;
                                 const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
                                 gcptr rowp = nullptr;
-                                if (g.part_slot != ~0u) {       // (only the ragged chunk needs the address again)
+                                if (g.part() != 0) {       // (only the ragged chunk needs the address again)
                                     int64_t off = (int64_t)g.i1 * DVM_I64(r2w, r3w) + (int64_t)g.colbase;
                                     if (rop == I_VLOAD) {
                                         const u32x4s hw = fetch4(code, fp + 4);
@@ -1396,10 +1432,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                     case I_VSTORE: {
                         if (longrow && lr_phase != n_red) break;    // (only the last pass over a long row stores)
                         if constexpr (WIDE) {
-                            if (gt.part_slot == ~0u && gt.ragged == 0 && gt.ncols >= V) {   // a full tile: plain stores
+                            if (gt.part() == 0) {       // the row consists of chunks
                                 if (wd.rowok) {
                                     Geo g = gt;
-                                    asm volatile("" : "+v"(g.lanecol));
+                                    asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
                                     const uint32_t w1 = cw1;
                                     const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
                                     int64_t off = (int64_t)wd.i1 * DVM_I64(cw2, cw3) + (int64_t)g.colbase;
@@ -1411,9 +1447,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                                     char *rowbase = (char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2);
                                     if (a == SRC_ACC) {
                                         if (b != 0) tile_bins<K, B_MUL>(acc, DVM_GET_S(b - 1));
-                                        store_wide_full_dispatch<K>(acc, dt, V, rowbase, g);
+                                        if (g.ragged() == 0) store_wide_dispatch<K, true>(acc, dt, V, rowbase, g);
+                                        else store_wide_dispatch<K, false>(acc, dt, V, rowbase, g);
+                                    } else if (g.ragged() == 0) {
+                                        DVM_WITH_R(a, rr, (store_wide_dispatch<K, true>(rr, dt, V, rowbase, g)))
                                     } else {
-                                        DVM_WITH_R(a, rr, store_wide_full_dispatch<K>(rr, dt, V, rowbase, g))
+                                        DVM_WITH_R(a, rr, (store_wide_dispatch<K, false>(rr, dt, V, rowbase, g)))
                                     }
                                 }
                                 break;
@@ -1593,8 +1632,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                         // pieces that reach beyond the row's end are put together element by element, zero-filled
                         const uint32_t ti = cw1 & 0xFF, dt = (cw1 >> 8) & 0xFF;
                         gcptr src = (gcptr)DVM_TENSOR(tbase + ti);
-                        const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
-                        lds_copy_row((LDS_AS char *)comb_lds + cw2, cw3 >> 4, src, D0, dt, tid, blockDim.x);
+                        // (a program with LDS images has one column tile: the tile's columns are the row's)
+                        const uint32_t n = gt.part_n();
+                        const uint32_t d0 = gt.slide() != 0 ? gt.cend : gt.cend + n;
+                        const uint32_t full = gt.slide() != 0 ? d0 - n : d0, back = gt.slide() != 0 ? V - n : 0u;
+                        lds_copy_row((LDS_AS char *)comb_lds + cw2, cw3 >> 4, src, d0, full, back, dt, tid, blockDim.x);
                         if (b != 0) __syncthreads();
                         break;
                     }
@@ -1866,7 +1908,8 @@ namespace {
 // One set of tensors against the bytecode's tensor table: no null pointer, the alignment the bytecode was encoded
 // for, equal pointers where it names two entries as the same buffer, and no overlap between a buffer one segment
 // writes and a buffer of another segment unless the bytecode orders them.
-int check_tensor_set(const uint32_t *w, const uint8_t *seg_of, void *const *tensors) {
+// *aliased is set where an output shares memory with another tensor of its own segment.
+int check_tensor_set(const uint32_t *w, const uint8_t *seg_of, void *const *tensors, uint32_t *aliased) {
     const uint32_t ntens = w[PH_NTENS];
     uint64_t addr_of[DVM_MAX_TENSORS], size_of[DVM_MAX_TENSORS];
     for (uint32_t i = 0; i < ntens; ++i) {
@@ -1880,6 +1923,11 @@ int check_tensor_set(const uint32_t *w, const uint8_t *seg_of, void *const *tens
             return dvm_set_error(DVM_E_ARGS, "dvm_run: two entries the bytecode names as the same buffer got different pointers");
         addr_of[i] = addr;
         size_of[i] = (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
+    }
+    for (uint32_t i = 0; i < ntens; ++i) {
+        if (!(w[PH_WORDS_N + i * TT_WORDS + TT_INFO] & TI_OUTPUT)) continue;
+        for (uint32_t j = 0; j < ntens; ++j)
+            if (i != j && seg_of[i] == seg_of[j] && addr_of[i] < addr_of[j] + size_of[j] && addr_of[j] < addr_of[i] + size_of[i]) *aliased = 1;
     }
     if (w[PH_NSEG] > 1) {
         for (uint32_t i = 0; i < ntens; ++i) {
@@ -1947,6 +1995,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     ka.n_tensors = ntens;
     ka.rotate = 0;
     ka.seg_first = 0;
+    ka.aliased = 0;
     ka.nseg = w[PH_NSEG];
     ka.spin_limit = (uint32_t)dvm_ctx_sync_limit(ctx);
 
@@ -1978,7 +2027,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     // Segments of one launch run without order between them unless the bytecode says otherwise: see check_tensor_set
     const int n_sets = batch ? batch->n_sets : 1;
     for (int k = 0; k < n_sets; ++k) {
-        st = check_tensor_set(w, seg_of, tensors + (size_t)k * ntens);
+        st = check_tensor_set(w, seg_of, tensors + (size_t)k * ntens, &ka.aliased);
         if (st != DVM_OK) return st;
     }
     if (batch) {
