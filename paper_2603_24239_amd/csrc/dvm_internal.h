@@ -16,6 +16,20 @@ int dvm_ctx_device(const dvm_ctx *ctx);
 void dvm_ctx_planner_get(const dvm_ctx *ctx, int *n_cu, int *overhead);
 // Bound on the polls of a grid-wide synchronisation point (dvm_ctx_set_sync_limit).
 int64_t dvm_ctx_sync_limit(const dvm_ctx *ctx);
+// A plain reduction along the penultimate axis as its own kernel takes it (dvm_colreduce.hip): sizes and strides in elements.
+typedef struct dvm_colreduce_args {
+    const void *in;
+    void *out;
+    int64_t in_s1, in_s2, in_s3;    // strides of the reduced axis and of the two outer dims
+    int64_t out_s2, out_s3;
+    uint64_t cols;                  // N: at least one 16-byte piece of the input
+    uint32_t size;                  // rows reduced
+    uint32_t d2;                    // extent of the first outer dim (0: the only one)
+    uint32_t col_tiles, log2_lanes; // column tiles of a row; lanes (of 16 bytes) that share a row
+    uint32_t op;                    // R_SUM, R_MAX or R_MIN
+    uint32_t in_bf16, out_bf16, once;
+} dvm_colreduce_args;
+int dvm_colreduce_launch(const dvm_colreduce_args *a, unsigned grid, unsigned block, void *stream);
 // Implemented in the device file so that the encoder object stays free of HIP calls.
 int dvm_ctx_query_device(int hip_device, int *n_cu);
 

@@ -1950,6 +1950,52 @@ int check_tensor_set(const uint32_t *w, const uint8_t *seg_of, void *const *tens
     return DVM_OK;
 }
 
+// A segment that is a plain reduction along the penultimate axis -- one streaming record, the combination of the waves, the
+// store, over rows of one 16-byte piece at least -- as the arguments of the kernel for those.  Grid and block are chosen here:
+// as many lanes on a row as leave two workgroups per compute unit (down to a 128-byte line), and as many waves as fill
+// the machine without leaving a lane fewer than eight rows (but four waves, and sixteen at most).
+bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *tensors, dvm_colreduce_args *a, uint32_t *grid, uint32_t *block) {
+    if (!(sh[S_FLAGS] & SF_CSTREAM) || sh[S_PROLOG] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID))) return false;
+    const uint32_t *r = sh + SH_WORDS;
+    if ((r[0] & 0xFF) != I_CSTREAM || sh[S_EPILOG] != LEN_VLOAD) return false;
+    const uint32_t *cc = r + LEN_VLOAD, *st = cc + LEN_REC;
+    if (sh[S_CODESIZE] < LEN_VLOAD + LEN_REC + LEN_LOAD || (cc[0] & 0xFF) != I_CCOMB || (cc[0] >> 16) != (r[0] >> 16)) return false;
+    const uint32_t sop = st[0] & 0xFF;
+    if (sop != I_STORE && sop != I_VSTORE) return false;
+    if (sh[S_CODESIZE] != LEN_VLOAD + LEN_REC + ((st[0] >> 8) & 0xFF) || ((st[0] >> 16) & 0xFF) != ((r[0] >> 16) & 0xFF) || (st[0] >> 24) != 0) return false;
+    const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
+    auto i64 = [](const uint32_t *w) { return (int64_t)((uint64_t)w[0] | ((uint64_t)w[1] << 32)); };
+    a->in_bf16 = (r[1] >> 8) & 0xFF;
+    a->out_bf16 = (st[1] >> 8) & 0xFF;
+    const uint32_t piece = a->in_bf16 ? 8u : 4u;
+    if (D0 < piece || i64(st + 2) != 0) return false;
+    a->in = (const void *)(uintptr_t)tensors[sh[S_TBASE] + (r[1] & 0xFF)];
+    a->out = (void *)(uintptr_t)tensors[sh[S_TBASE] + (st[1] & 0xFF)];
+    a->once = ((r[1] >> 16) & MF_STREAM) != 0;
+    a->in_s1 = i64(r + 2); a->in_s2 = i64(r + 4); a->in_s3 = i64(r + 6);
+    a->out_s2 = sop == I_VSTORE ? i64(st + 4) : 0;
+    a->out_s3 = sop == I_VSTORE ? i64(st + 6) : 0;
+    a->cols = D0;
+    a->size = sh[S_INNER];
+    a->d2 = sh[S_D2];
+    a->op = r[0] >> 24;
+    int n_cu = 256;
+    dvm_ctx_planner_get(ctx, &n_cu, nullptr);
+    const uint64_t outer = sh[S_NROWS] / sh[S_INNER];
+    uint32_t lg = 6;
+    auto tiles = [&](uint32_t l) { return (D0 + ((uint64_t)piece << l) - 1) / ((uint64_t)piece << l); };
+    while (lg > 3 && outer * tiles(lg) < 2ull * (uint64_t)n_cu) --lg;
+    const uint64_t units = outer * tiles(lg);
+    if (units >= (1ull << 31)) return false;
+    uint32_t waves = 4;
+    while (waves < 16 && units * waves < 16ull * (uint64_t)n_cu && (uint64_t)a->size > 8ull * waves * (64u >> lg)) waves *= 2;
+    a->log2_lanes = lg;
+    a->col_tiles = (uint32_t)tiles(lg);
+    *grid = (uint32_t)units;
+    *block = waves * 64u;
+    return true;
+}
+
 int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *tensors_in, int n_tensors, void *hip_stream, bool static_ws,
              const Batch *batch) {
     if (!ctx || !bytecode || (!tensors_in && n_tensors > 0)) return dvm_set_error(DVM_E_ARGS, "dvm_run: null argument");
@@ -2108,7 +2154,14 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         }
         ka.seg_first = first;
         ka.nseg = end;
-        e = (hipError_t)launch(grid, block, lds_bytes, hip_stream, &ka, nullptr);
+        dvm_colreduce_args ca;
+        uint32_t cgrid = 0, cblock = 0;
+        const uint32_t *first_sh = w + segs_off;
+        for (uint32_t s = 0; s < first; ++s) first_sh += first_sh[S_WORDS];
+        if (cred && end == first + 1 && !batch && plain_colreduce(ctx, first_sh, ka.tensors, &ca, &cgrid, &cblock))
+            e = (hipError_t)dvm_colreduce_launch(&ca, cgrid, cblock, hip_stream);
+        else
+            e = (hipError_t)launch(grid, block, lds_bytes, hip_stream, &ka, nullptr);
         if (e != hipSuccess) {
             t_last_hip_error = (int)e;
             return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
