@@ -180,6 +180,9 @@ enum : uint32_t {
 };
 // reductions R_*
 enum : uint32_t { R_SUM = 0, R_MAX, R_MIN, R_SUMSQ, R_COUNT };
+// In rows longer than a tile, on a maximum S[a] directly followed by acc = exp(acc - S[a]) and the sum of that: the pass that
+// takes the maximum takes the sum as well.
+constexpr uint32_t R_KIND = 0x3F, R_ONLINE = 0x40;
 
 // I_SOP: word1 = kind | srckind << 8 | c << 16 ; word2 = immediate.  kind < 64: B_kind(S[b], x);
 // kind >= 64: U_(kind-64)(S[b]).  srckind 0: x = S[c]; 1: x = immediate.

@@ -2015,6 +2015,14 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     if (long_row) {
         uint32_t n_red = 0;
         for (int i = 0; i < E.n_ai; ++i) n_red += E.ai[i].op == I_RED;
+        // a maximum, the exponential of the difference from it and the sum of that (a softmax) take one pass together
+        for (int i = 0; i + 2 < E.n_ai; ++i) {
+            AI &m = E.ai[i];
+            const AI &x = E.ai[i + 1], &l = E.ai[i + 2];
+            if (m.op == I_RED && m.b == R_MAX && m.kind == U_NONE && m.imm == 1.0f && m.imm2 == 0.0f && x.op == I_BIN && x.b == B_EXPSUB &&
+                x.a == SRC_S0 + m.a && l.op == I_RED && l.b == R_SUM)
+                m.b = R_MAX | R_ONLINE;
+        }
         sh[S_NCTSH] = n_red;
     } else if (nct > 1) {
         magic_u32(nct, &sh[S_NCTM], &sh[S_NCTSH]);
@@ -2329,7 +2337,14 @@ extern "C" int dvm_validate(const void *bytecode, size_t len) {
                     break;
                 case I_RED:
                     ++n_red_seen;
-                    if (l != LEN_REC || !sreg_ok(a) || bb >= R_COUNT) return bad("reduction");
+                    if (l != LEN_REC || !sreg_ok(a) || (bb & R_KIND) >= R_COUNT || (bb & ~(R_KIND | R_ONLINE)) != 0) return bad("reduction");
+                    if (bb & R_ONLINE) {
+                        if (!(sh[S_FLAGS] & SF_LONGROW) || (bb & R_KIND) != R_MAX || w[pc + 1] != U_NONE || w[pc + 2] != bits_f32(1.0f) || w[pc + 3] != 0 ||
+                            pc + 3 * LEN_REC > end)
+                            return bad("reduction in one pass with its sum");
+                        const uint32_t x = w[pc + LEN_REC], s = w[pc + 2 * LEN_REC];
+                        if (x != w0(I_BIN, LEN_REC, SRC_S0 + a, B_EXPSUB) || (s & 0xFF) != I_RED || (s >> 24) != R_SUM) return bad("reduction in one pass with its sum");
+                    }
                     if (w[pc + 1] >= U_COUNT) return bad("reduction post op");
                     break;
                 case I_SOP: {
@@ -2877,9 +2892,9 @@ extern "C" int dvm_disasm(const void *bytecode, size_t len, char *txt, size_t ca
                     break;
                 }
                 case I_RED:
-                    o.put("  %04zu red.%-5s s%u = %s(acc * %.9g + %.9g)%s\n", pc - at - SH_WORDS, RED_NAMES[b], a,
+                    o.put("  %04zu red.%-5s s%u = %s(acc * %.9g + %.9g)%s\n", pc - at - SH_WORDS, RED_NAMES[b & R_KIND], a,
                           w[pc + 1] ? UN_NAMES[w[pc + 1]] : "", (double)f32_bits(w[pc + 2]), (double)f32_bits(w[pc + 3]),
-                          (sh[S_GEOM] & 0xFFFF) > 64 ? "  [workgroup sync]" : "");
+                          (sh[S_GEOM] & 0xFFFF) > 64 ? (b & R_ONLINE ? "  [workgroup sync, in one pass with the sum below]" : "  [workgroup sync]") : "");
                     break;
                 case I_SOP: {
                     const uint32_t w1 = w[pc + 1];

@@ -324,6 +324,13 @@ template <uint32_t R> DI float wave_allreduce(float v, uint32_t width) {
 // ------------------------------------------------------------------------------------------
 // per-tile geometry
 // ------------------------------------------------------------------------------------------
+// (The instantiation for any launch, and the one for reductions along the penultimate axis, handle a last chunk element
+// by element where it may not slide back; the others are launched only where no tile asks for it.)
+#if defined(DVM_VARIANT_K) && !defined(DVM_VARIANT_CRED) && !defined(DVM_VARIANT_ANY)
+constexpr bool HAVE_PART = false;
+#else
+constexpr bool HAVE_PART = true;
+#endif
 // The wave-uniform part lives across the interpreter loop, whose scalar registers are scarce (a value more there is
 // spilled and costs every record): it holds what cannot be derived in a few scalar instructions where it is used.
 struct Geo {
@@ -341,7 +348,8 @@ struct Geo {
     static constexpr int PK_SLOT = 12, PK_LANE = 20;        // ... the lane (within the row group) PK_LANE in its chunk slot PK_SLOT
     DI uint32_t ragged() const { return pk & PK_RAGGED; }
     DI uint32_t slide() const { return pk & PK_SLIDE; }
-    DI uint32_t part() const { return pk & PK_PART; }
+    DI uint32_t part() const { return HAVE_PART ? pk & PK_PART : 0u; }
+    DI bool chunks() const { return !HAVE_PART || cend != 0; }         // the tile has at least one whole chunk
     DI uint32_t part_n() const { return pk & PK_N; }
     DI uint32_t part_slot() const { return (pk >> PK_SLOT) & 0xFF; }
     DI uint32_t part_lane() const { return pk >> PK_LANE; }
@@ -431,7 +439,7 @@ template <int K, int DT, int V, bool NT> DI void request_inplace(Tile<K> &t, gcp
     constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.cend != 0) {       // wave-uniform: the tile has at least one whole chunk
+        if (g.chunks()) {       // wave-uniform: the tile has at least one whole chunk
             sfor<NJ>([&]<int J>() LI {
                 gcptr q = rowp + (uint64_t)chunk_col<V>(g, J) * ES;
                 if constexpr (DT == 0) {
@@ -469,7 +477,7 @@ template <int K, int DT, int V> DI void finish_tile(Tile<K> &t, gcptr rowp, cons
     if constexpr (K < V) tile_zero<K>(t);
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.cend == 0) {        // narrower than one chunk: only the ragged part below
+        if (!g.chunks()) {        // narrower than one chunk: only the ragged part below
             tile_zero<K>(t);
         } else if constexpr (DT == 1) {
             sfor<NJ>([&]<int J>() LI {
@@ -526,7 +534,7 @@ template <int K, int DT, int V, bool NT> DI void request_staged(Raw<K> &raw, gcp
     constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.cend != 0) {
+        if (g.chunks()) {
             sfor<NJ>([&]<int J>() LI {
                 gcptr q = rowp + (uint64_t)chunk_col<V>(g, J) * ES;
                 constexpr int PIECES = DT == 0 ? V / 4 : 1;
@@ -564,7 +572,7 @@ template <int K> DI void request_staged_dispatch(Raw<K> &raw, uint32_t dt, uint3
 template <int K, int DT, int V, uint32_t B> DI void combine_staged(Tile<K> &t, const Raw<K> &raw, const Geo &g) {
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.cend != 0) {
+        if (g.chunks()) {
             const bool masked = g.ragged() != 0;       // wave-uniform
             auto chunk = [&]<int J>(bool whole) LI {
                 float x[V];
@@ -625,7 +633,7 @@ template <int K, int DT, int V> DI void store_tile(const Tile<K> &t, gptr rowp, 
     constexpr int ES = DT == 0 ? 4 : 2;
     if constexpr (K >= V) {
         constexpr int NJ = K / V;
-        if (g.cend != 0) {
+        if (g.chunks()) {
             sfor<NJ>([&]<int J>() LI {
                 const bool ok = g.rowok && g.lanecol + (uint32_t)J * g.GV < g.cend;
                 gptr q = rowp + (uint64_t)chunk_col<V>(g, J) * ES;
@@ -891,7 +899,7 @@ DI void tile_cols(Geo &gt, const uint32_t *sh, uint32_t tile_c, uint32_t G, uint
     if (n != 0) {
         const uint32_t slot = __builtin_amdgcn_readfirstlane(full_chunks / G);
         const uint32_t lane = full_chunks - slot * G;
-        if (full_chunks != 0 && (G <= 64 || (lane & 63u) != 0 || aliased == 0)) {
+        if (!HAVE_PART || (full_chunks != 0 && (G <= 64 || (lane & 63u) != 0 || aliased == 0))) {
             gt.pk |= Geo::PK_SLIDE;
             gt.cend = ncols;
         } else {
@@ -1066,8 +1074,12 @@ DI void lds_fma(Tile<K> &acc, float s, const LDS_AS char *pa, const LDS_AS char 
 // to spare of: 5-10 % on short tiles).
 // WIDE: the instantiation for launches in which every segment spreads a row over at least one whole wave (see
 // "wide rows" above); the other instantiations take any geometry.
-template <int K, int NR, int MAXT, int WAVES, bool CRED, bool WIDE>
+// LONG: the instantiations that also run segments over rows longer than a tile (column tiles, passes); the others carry none
+// of it (its values across the record loop cost softmax over bf16 rows of 751 columns 12 %, RMSNorm 4 %).  The general one
+// with LONG runs any launch without a reduction along the penultimate axis: it also handles last chunks element by element.
+template <int K, int NR, int MAXT, int WAVES, bool CRED, bool WIDE, bool LONG>
 __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES))) dvm_vm_kernel(const KArgs args) {
+    static_assert(!(CRED && LONG), "a launch holds reductions along the penultimate axis or rows longer than a tile");
     static_assert(!(CRED && WIDE), "the instantiation for reductions along the penultimate axis is the general one");
     __shared__ float red_lds[2][16];
     // (sized by the launch: 1 KiB per wave of the widest segment that reduces along the penultimate axis, else nothing)
@@ -1221,10 +1233,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
         // reduction and once more for the rest (lr_phase), each pass column tile after column tile (lr_c): a pass runs
         // the records from the start of the body up to its reduction, skipping the reductions whose value is final and
         // every store; the last pass runs to the end and stores.
-        const bool longrow = (sh[S_FLAGS] & SF_LONGROW) != 0;
+        const bool longrow = LONG && (sh[S_FLAGS] & SF_LONGROW) != 0;
         const uint32_t n_red = longrow ? sh[S_NCTSH] : 0u;
         uint32_t lr_phase = 0, lr_c = 0;
-        float racc = 0.0f;                  // the lane's part of the reduction of the current pass
+        float racc = 0.0f, racc2 = 0.0f;    // the lane's part of the reduction of the current pass (R_ONLINE: maximum and sum)
         uint32_t rin = 0;
         for (uint32_t tile = t_lo; tile < t_hi;) {
             const uint32_t *shl = sh;
@@ -1313,7 +1325,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                                     off += (int64_t)wd.i2 * DVM_I64(h0, h1) + (int64_t)wd.i3 * DVM_I64(h2, h3);
                                 }
                                 const char *rowbase = (const char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2);
-                                if (g.cend != 0) {
+                                if (g.chunks()) {
                                     if ((w1 >> 16) & MF_STREAM) {
                                         if (dt != 0) { if constexpr (K >= 8) DVM_ISSUE_WIDE(1, 8, true) }
                                         else if (V == 4) DVM_ISSUE_WIDE(0, 4, true)
@@ -1431,32 +1443,30 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                     case I_STORE:
                     case I_VSTORE: {
                         if (longrow && lr_phase != n_red) break;    // (only the last pass over a long row stores)
-                        if constexpr (WIDE) {
-                            if (gt.part() == 0) {       // the row consists of chunks
-                                if (wd.rowok) {
-                                    Geo g = gt;
-                                    asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
-                                    const uint32_t w1 = cw1;
-                                    const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
-                                    int64_t off = (int64_t)wd.i1 * DVM_I64(cw2, cw3) + (int64_t)g.colbase;
-                                    if (op == I_VSTORE) {
-                                        const u32x4s hw = fetch4(code, cur + 4);
-                                        const uint32_t h0 = hw.x, h1 = hw.y, h2 = hw.z, h3 = hw.w;
-                                        off += (int64_t)wd.i2 * DVM_I64(h0, h1) + (int64_t)wd.i3 * DVM_I64(h2, h3);
-                                    }
-                                    char *rowbase = (char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2);
-                                    if (a == SRC_ACC) {
-                                        if (b != 0) tile_bins<K, B_MUL>(acc, DVM_GET_S(b - 1));
-                                        if (g.ragged() == 0) store_wide_dispatch<K, true>(acc, dt, V, rowbase, g);
-                                        else store_wide_dispatch<K, false>(acc, dt, V, rowbase, g);
-                                    } else if (g.ragged() == 0) {
-                                        DVM_WITH_R(a, rr, (store_wide_dispatch<K, true>(rr, dt, V, rowbase, g)))
-                                    } else {
-                                        DVM_WITH_R(a, rr, (store_wide_dispatch<K, false>(rr, dt, V, rowbase, g)))
-                                    }
+                        if constexpr (WIDE) {       // (rows consist of chunks in this instantiation)
+                            if (wd.rowok) {
+                                Geo g = gt;
+                                asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
+                                const uint32_t w1 = cw1;
+                                const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
+                                int64_t off = (int64_t)wd.i1 * DVM_I64(cw2, cw3) + (int64_t)g.colbase;
+                                if (op == I_VSTORE) {
+                                    const u32x4s hw = fetch4(code, cur + 4);
+                                    const uint32_t h0 = hw.x, h1 = hw.y, h2 = hw.z, h3 = hw.w;
+                                    off += (int64_t)wd.i2 * DVM_I64(h0, h1) + (int64_t)wd.i3 * DVM_I64(h2, h3);
                                 }
-                                break;
+                                char *rowbase = (char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2);
+                                if (a == SRC_ACC) {
+                                    if (b != 0) tile_bins<K, B_MUL>(acc, DVM_GET_S(b - 1));
+                                    if (g.ragged() == 0) store_wide_dispatch<K, true>(acc, dt, V, rowbase, g);
+                                    else store_wide_dispatch<K, false>(acc, dt, V, rowbase, g);
+                                } else if (g.ragged() == 0) {
+                                    DVM_WITH_R(a, rr, (store_wide_dispatch<K, true>(rr, dt, V, rowbase, g)))
+                                } else {
+                                    DVM_WITH_R(a, rr, (store_wide_dispatch<K, false>(rr, dt, V, rowbase, g)))
+                                }
                             }
+                            break;
                         }
                         DVM_GEO()
                         const uint32_t w1 = cw1;
@@ -1665,29 +1675,59 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                             if (mine < lr_phase) break;         // its value is final: S[a] holds it
                         }
                         DVM_GEO()
+                        // A row that spans gw waves: exchange the per-wave results through LDS.  Two buffers alternate, so
+                        // one barrier per reduction is enough.
+                        auto exchange = [&](float x, uint32_t kind) LI {
+                            if (gw > 1) {
+                                red_lds[red_par][wave & 15] = x;     // every lane of the wave holds the same value
+                                __syncthreads();
+                                x = red_lds[red_par][w0i & 15];
+                                for (uint32_t i = 1; i < gw; ++i) {
+                                    const float o = red_lds[red_par][(w0i + i) & 15];
+                                    x = kind == R_MAX ? f_maxp(x, o) : (kind == R_MIN ? f_minp(x, o) : x + o);
+                                }
+                                red_par ^= 1;
+                            }
+                            return x;
+                        };
                         float v;
                         if (longrow) {
                             // this pass's reduction: the lane's part of this column tile joins those of the tiles before;
                             // after the row's last tile the lanes (and waves) are combined as for a short row
-                            const float part = lane_reduce_dispatch<K>(acc, g, V, b);
-                            racc = lr_c == 0 ? part : (b == R_MAX ? f_maxp(racc, part) : (b == R_MIN ? f_minp(racc, part) : racc + part));
+                            const uint32_t kind = b & R_KIND;
+                            const float part = lane_reduce_dispatch<K>(acc, g, V, kind);
+                            const float before = racc;
+                            racc = lr_c == 0 ? part : (kind == R_MAX ? f_maxp(racc, part) : (kind == R_MIN ? f_minp(racc, part) : racc + part));
                             pcb = this_end * 4;                 // the pass ends here
+                            if (b & R_ONLINE) {
+                                // The sum of exp(x - maximum) in the pass of the maximum: the lane sums against its own maximum
+                                // so far and rescales the sum when that grows, which saves one of the three passes of a softmax
+                                // over the row.  (Nothing but -inf so far: the exponentials are taken against 0 and are 0.)
+                                const float neg = -__builtin_inff();
+                                const float ms = racc == neg ? 0.0f : racc;
+                                tile_bins<K, B_EXPSUB>(acc, ms);
+                                const float add = lane_reduce<K, R_SUM>(acc, g, V);
+                                racc2 = lr_c == 0 ? add : f_fma(racc2, f_exp2((before - ms) * LOG2E), add);
+                                if (lr_c + 1 < nct) break;
+                                v = exchange(wave_allreduce<R_MAX>(racc, width), R_MAX);
+                                const float vs = v == neg ? 0.0f : v;
+                                float sum = exchange(wave_allreduce<R_SUM>(racc2 * f_exp2((racc - vs) * LOG2E), width), R_SUM);
+                                sum = v == neg ? __builtin_nanf("") : sum;      // (a row of -inf alone: -inf - -inf)
+                                DVM_SET_S(a, v);
+                                const u32x4s sr = fetch4(code, cur + 2 * LEN_REC);      // the record of the sum
+                                const uint32_t sw = sr.x, sw1 = sr.y, sw2 = sr.z, sw3 = sr.w;
+                                sum = f_fma(sum, __builtin_bit_cast(float, sw2), __builtin_bit_cast(float, sw3));
+                                if (sw1 != U_NONE) sum = un_dyn(sw1, sum);
+                                DVM_SET_S((sw >> 16) & 0xFF, sum);
+                                ++lr_phase;                     // both reductions are final
+                                break;
+                            }
                             if (lr_c + 1 < nct) break;
-                            v = wave_allreduce_dispatch(racc, b, width);
+                            v = wave_allreduce_dispatch(racc, kind, width);
+                            v = exchange(v, kind);
                         } else {
                             v = reduce_dispatch<K>(acc, g, V, b, width);
-                        }
-                        if (gw > 1) {
-                            // a row spans gw waves: exchange the per-wave results through LDS.  Two
-                            // buffers alternate, so one barrier per reduction is enough.
-                            red_lds[red_par][wave & 15] = v;     // every lane of the wave holds the same value
-                            __syncthreads();
-                            v = red_lds[red_par][w0i & 15];
-                            for (uint32_t i = 1; i < gw; ++i) {
-                                const float o = red_lds[red_par][(w0i + i) & 15];
-                                v = b == R_MAX ? f_maxp(v, o) : (b == R_MIN ? f_minp(v, o) : v + o);
-                            }
-                            red_par ^= 1;
+                            v = exchange(v, b);
                         }
                         // the row-scalar ops folded into this record: U(v * scale + shift)
                         v = f_fma(v, __builtin_bit_cast(float, cw2), __builtin_bit_cast(float, cw3));
@@ -1751,6 +1791,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 #define DVM_CRED_LAUNCHER_NAME(K, NR) DVM_CRED_LAUNCHER_NAME_(K, NR)
 #define DVM_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_w_##K##_##NR
 #define DVM_WIDE_LAUNCHER_NAME(K, NR) DVM_WIDE_LAUNCHER_NAME_(K, NR)
+#define DVM_ANY_LAUNCHER_NAME_(K, NR) dvm_vm_launch_a_##K##_##NR
+#define DVM_ANY_LAUNCHER_NAME(K, NR) DVM_ANY_LAUNCHER_NAME_(K, NR)
+#define DVM_LONG_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_lw_##K##_##NR
+#define DVM_LONG_WIDE_LAUNCHER_NAME(K, NR) DVM_LONG_WIDE_LAUNCHER_NAME_(K, NR)
 
 }  // namespace
 
@@ -1760,13 +1804,19 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 // many workgroups of this size one compute unit holds at a time.  Returns the hipError_t of the calls it made.
 #if defined(DVM_VARIANT_CRED)
 #define DVM_THIS_LAUNCHER DVM_CRED_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
-#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, true, false>
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, true, false, false>
+#elif defined(DVM_VARIANT_LONG) && defined(DVM_VARIANT_WIDE)
+#define DVM_THIS_LAUNCHER DVM_LONG_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, true, true>
+#elif defined(DVM_VARIANT_ANY)
+#define DVM_THIS_LAUNCHER DVM_ANY_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false, true>
 #elif defined(DVM_VARIANT_WIDE)
 #define DVM_THIS_LAUNCHER DVM_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
-#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, true>
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, true, false>
 #else
 #define DVM_THIS_LAUNCHER DVM_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
-#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false>
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false, false>
 #endif
 extern "C" int DVM_THIS_LAUNCHER(unsigned grid, unsigned block, unsigned lds_bytes, void *stream, const void *kargs, int *blocks_per_cu) {
     if (blocks_per_cu) return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, DVM_THIS_KERNEL, (int)block, lds_bytes);
@@ -1779,6 +1829,12 @@ extern "C" int DVM_THIS_LAUNCHER(unsigned grid, unsigned block, unsigned lds_byt
 DVM_VARIANT_LIST(X)
 #undef X
 #define X(K, NR, MAXT, W) extern "C" int DVM_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
+DVM_VARIANT_LIST(X)
+#undef X
+#define X(K, NR, MAXT, W) extern "C" int DVM_ANY_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
+DVM_VARIANT_LIST(X)
+#undef X
+#define X(K, NR, MAXT, W) extern "C" int DVM_LONG_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
 DVM_VARIANT_LIST(X)
 #undef X
 #define X(K, NR, MAXT, W) extern "C" int DVM_CRED_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
@@ -1799,6 +1855,12 @@ const VariantEntry g_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
 #define X(K, NR, MAXT, W) {K, NR, DVM_WIDE_LAUNCHER_NAME(K, NR)},
 const VariantEntry g_wide_variants[] = {DVM_VARIANT_LIST(X)};
+#undef X
+#define X(K, NR, MAXT, W) {K, NR, DVM_ANY_LAUNCHER_NAME(K, NR)},
+const VariantEntry g_any_variants[] = {DVM_VARIANT_LIST(X)};
+#undef X
+#define X(K, NR, MAXT, W) {K, NR, DVM_LONG_WIDE_LAUNCHER_NAME(K, NR)},
+const VariantEntry g_long_wide_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
 #define X(K, NR, MAXT, W) {K, NR, DVM_CRED_LAUNCHER_NAME(K, NR)},
 const VariantEntry g_cred_variants[] = {DVM_CRED_VARIANT_LIST(X)};
@@ -2087,6 +2149,20 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         ka.sets = (uint64_t)(uintptr_t)batch->table;
         ka.n_sets = (uint32_t)n_sets;
     }
+    // A last chunk that is handled element by element (see tile_cols) needs the instantiation that runs any launch.
+    bool part = false;
+    for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
+        const uint32_t *sh = w + at;
+        const uint32_t G = sh[S_GEOM] & 0xFFFF, V = (sh[S_GEOM] >> 16) & 0xFF;
+        const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
+        auto ends_in_part = [&](uint64_t ncols) {
+            const uint64_t full = ncols / V;
+            return ncols % V != 0 && (full == 0 || (G > 64 && ka.aliased != 0 && (full % G) % 64 == 0));
+        };
+        if (sh[S_NTILES] == 0) continue;
+        part |= ends_in_part(D0 - (uint64_t)(sh[S_NCT] - 1) * sh[S_TC]);
+        if (sh[S_NCT] > 1) part |= ends_in_part(sh[S_TC]);
+    }
     // Several segments, or several sets: the tiles of each are dealt out from where the one before stopped.  (Not
     // when a segment relies on its producer's assignment of tiles to workgroups, nor when the segments own shares
     // of the workgroups.)
@@ -2097,12 +2173,10 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     if (cred) {
         for (const VariantEntry &v : g_cred_variants)
             if (v.K == K && v.NR == NR) launch = v.launch;
-    } else if (wide) {
-        for (const VariantEntry &v : g_wide_variants)
-            if (v.K == K && v.NR == NR) launch = v.launch;
     } else {
-        for (const VariantEntry &v : g_variants)
-            if (v.K == K && v.NR == NR) launch = v.launch;
+        const VariantEntry *list = part || (longrow && !wide) ? g_any_variants : (longrow ? g_long_wide_variants : (wide ? g_wide_variants : g_variants));
+        for (int i = 0; i < N_VARIANTS; ++i)
+            if (list[i].K == K && list[i].NR == NR) launch = list[i].launch;
     }
     if (!launch) return dvm_set_error(DVM_E_BADCODE, "dvm_run: no interpreter variant for this bytecode");
     hipError_t e;
