@@ -145,8 +145,11 @@ enum : uint32_t {
     I_LFMA,      // ACC = ACC [* S] [* La] [+ Lb] with La, Lb LDS images (the multiply-add is fused when both are there).
                  // a = La | Lb << 4 as image numbers (LFMA_NONE: absent), b = bit 0: La is bf16, bit 1: Lb is bf16;
                  // word1 = 0 or S index + 1, word2 / word3 = byte offsets of La / Lb in LDS
+    I_MAC,       // ACC = ACC + R[a] * R[b] (word1 = MAC_ADD), ACC - R[a] * R[b] (MAC_SUB) or R[a] * R[b] - ACC (MAC_RSUB): a sum or
+                 // difference with the product of two input tensors, which then needs no register of its own
     I_COUNT
 };
+enum : uint32_t { MAC_ADD = 0, MAC_SUB, MAC_RSUB, MAC_COUNT };
 constexpr uint32_t LFMA_NONE = 0xF;
 constexpr int LDS_SLOTS = 4;                    // LDS images per segment
 constexpr uint32_t LDS_IMAGE_MAX_BYTES = 65536; // all images of a segment together

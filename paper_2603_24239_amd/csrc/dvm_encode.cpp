@@ -594,6 +594,11 @@ struct Enc {
     int reg_of[MAX_NODES], sreg_of[MAX_NODES];
     int regs[NR_MAX], sregs[NS];
     int nr_limit;           // tile registers the program may use
+    int next_reg;
+    bool allow_mac;
+    int n_mac;              // products of two inputs that ride along
+    int mac_of[MAX_NODES];  // the product of two inputs that this sum or difference takes in its record (I_MAC), or -1
+    bool mac[MAX_NODES];    // such a product: not computed by itself
     bool reload_inputs;     // never keep an input tile in a register: load it again at every use
     bool keep_sregs;        // never give a row-scalar register a second value (rows longer than a tile: the body runs once per pass)
     int lds_of[MAX_NODES];  // LDS image (slot) of a row-invariant input that only multiplies or is added, or -1
@@ -664,13 +669,18 @@ struct Enc {
         sreg_of[dst_node] = sr;
     }
     int alloc_reg(int node) {
-        for (int i = 0; i < nr_limit; ++i)
+        for (int k = 0; k < nr_limit; ++k) {
+            // (where inputs are loaded again at each use, registers are taken in turn: one that nothing has touched yet lets
+            // its load join the loads the body starts with)
+            const int i = reload_inputs && nr_limit > 0 ? (next_reg + k) % nr_limit : k;
             if (regs[i] < 0) {
+                next_reg = i + 1;
                 regs[i] = node;
                 reg_of[node] = i;
                 if (i + 1 > nr_used) nr_used = i + 1;
                 return i;
             }
+        }
         fail(DVM_E_UNSUPPORTED, "program needs more live tile registers than available");
         return 0;
     }
@@ -1332,6 +1342,28 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             E.uses[n] += 1 << 20;       // never released
         }
     }
+    // A product of two inputs whose only use is a sum or difference with a computed value rides along with that record: it needs
+    // no register of its own and RoPE fits four tile registers instead of six.
+    E.next_reg = 0;
+    E.n_mac = 0;
+    for (int n = 0; n < NN; ++n) { E.mac_of[n] = -1; E.mac[n] = false; }
+    for (int n = 0; n < NN && E.allow_mac; ++n) {
+        const Node &u = prog->nodes[n];
+        if (u.kind != N_BIN || (u.op != B_ADD && u.op != B_SUB) || E.rows_class[n] || u.a == u.b || E.uses[n] == 0) continue;
+        for (int side = 0; side < 2 && E.mac_of[n] < 0; ++side) {
+            const int m = side == 0 ? u.b : u.a, other = side == 0 ? u.a : u.b;
+            const Node &x = prog->nodes[m];
+            if (x.kind != N_BIN || x.op != B_MUL || E.rows_class[m] || E.uses[m] != 1 || E.mac[m]) continue;
+            if (E.rows_class[other] || prog->nodes[other].kind == N_IN || E.mac[other]) continue;
+            bool ok = true;
+            for (int o = 0; o < prog->n_out; ++o) ok &= prog->out_node[o] != m;
+            for (int q : {(int)x.a, (int)x.b}) ok &= prog->nodes[q].kind == N_IN && !E.rows_class[q] && E.lds_of[q] < 0;
+            if (!ok) continue;
+            E.mac[m] = true;
+            E.mac_of[n] = m;
+            ++E.n_mac;
+        }
+    }
     // The other tile-invariant operands are loaded once per workgroup into a pinned tile register by a
     // prologue that runs before the first tile, instead of once per tile.
     E.n_prolog = 0;
@@ -1438,6 +1470,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             store_outputs(n);       // an input that is also an output: a plain copy
             continue;
         }
+        if (E.mac[n]) continue;     // computed by the record of its only use
         if (E.uses[n] == 0) {       // dead code: still consume the operands
             if (nd.a >= 0) E.use(nd.a);
             if ((nd.kind == N_BIN || nd.kind == N_SEL) && nd.b >= 0) E.use(nd.b);
@@ -1494,6 +1527,23 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                 int a = nd.a, b = nd.b;
                 uint32_t op = nd.op;
                 const bool ra = E.rows_class[a], rb = E.rows_class[b];
+                if (E.mac_of[n] >= 0) {
+                    const int m = E.mac_of[n], other = m == b ? a : b;
+                    const uint32_t kind = op == B_ADD ? MAC_ADD : (m == b ? MAC_SUB : MAC_RSUB);
+                    const int p = prog->nodes[m].a, q = prog->nodes[m].b;
+                    E.to_acc(other);
+                    E.preserve(other, 1);
+                    E.use(other);
+                    const int rp = E.to_reg(p), rq = E.to_reg(q);
+                    E.emit(I_MAC, (uint8_t)rp, (uint8_t)rq, -1, 0.0f, (uint8_t)kind);
+                    for (int x : {p, q})            // (when inputs are not kept, their registers are free again after the record)
+                        if (E.reload_inputs && E.reg_of[x] >= 0 && E.uses[x] > 1 && E.uses[x] < (1 << 20)) { E.regs[E.reg_of[x]] = -1; E.reg_of[x] = -1; }
+                    E.use(p);
+                    E.use(q);
+                    E.uses[m] = 0;
+                    E.in_acc = n;
+                    break;
+                }
                 if (rows) {                         // both operands are row values
                     const int sa = E.sreg(a), sb = E.sreg(b);
                     E.use(a);
@@ -1614,13 +1664,39 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     // first without hoisting, to learn how many tile registers the body needs; then, in row mode,
     // again with as many pinned operands as keep the program within four tile registers
     E.nr_limit = ctx->max_nr < NR_MAX ? ctx->max_nr : NR_MAX;
-    E.reload_inputs = false;
     E.keep_sregs = false;
-    linearize(0);
-    if (E.err) {                // too many live tiles: trade registers for repeated (cached) loads
+    auto linearize_plain = [&](bool mac) {
+        E.allow_mac = mac;
         E.err = nullptr;
-        E.reload_inputs = true;
+        E.reload_inputs = false;
         linearize(0);
+        if (E.err) {                // too many live tiles: trade registers for repeated (cached) loads
+            E.err = nullptr;
+            E.reload_inputs = true;
+            linearize(0);
+        }
+    };
+    linearize_plain(false);
+    // Products that ride along (I_MAC): taken where they let the program run with fewer tile registers, and where the launch is
+    // more than the machine holds at once in the variant of six (64 x 16 elements per wave, three waves per SIMD).  Fewer
+    // registers mean more resident waves (RoPE over 8111 x 32 heads 35 us with six registers, 30 with four); a smaller launch is
+    // resident as a whole either way and keeps its records.
+    if (!E.has_cred && (double)E.nrows * (double)E.D0 * (double)ctx->copies > (double)ctx->n_cu * 4 * 3 * 64 * 16) {
+        auto cls = [](int n) { return n <= 2 ? 2 : (n <= 4 ? 4 : (n <= 6 ? 6 : 8)); };
+        const bool err0 = E.err != nullptr, reload0 = E.reload_inputs;
+        const int regs0 = E.nr_used, n0 = E.n_ai;
+        bool candidate = false;
+        for (int n = 0; n < NN && !candidate; ++n) {
+            const Node &u = prog->nodes[n];
+            candidate = u.kind == N_BIN && (u.op == B_ADD || u.op == B_SUB) && prog->nodes[u.a].kind == N_BIN && prog->nodes[u.b].kind == N_BIN &&
+                        (prog->nodes[u.a].op == B_MUL || prog->nodes[u.b].op == B_MUL);
+        }
+        if (candidate) {
+            linearize_plain(true);
+            const bool better = !E.err && (err0 || (reload0 && !E.reload_inputs) ||
+                                           (reload0 == E.reload_inputs && (cls(E.nr_used) < cls(regs0) || (cls(E.nr_used) == cls(regs0) && E.n_ai < n0))));
+            if (!better) linearize_plain(false);
+        }
     }
     {
         int reg_cap = 4;
@@ -1682,7 +1758,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                 case I_LOAD: case I_STORE: case I_MOVRA: case I_MOVAR: return x.a == r;
                 case I_BIN: return x.a == r;
                 case I_SEL: return x.a == r || x.b == r;
-                case I_FMA: return x.a == r || x.b == r;
+                case I_FMA: case I_MAC: return x.a == r || x.b == r;
                 default: return false;
             }
         };
@@ -1690,6 +1766,16 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         while (top < E.n_ai && (E.ai[top].op == I_LOAD || E.ai[top].op == I_LOADS)) ++top;
         if (top > E.n_prolog) {
             for (int i = top + 1; i < E.n_ai; ++i) {
+                // (a load into the accumulator that is copied to a register at once: load the register and copy it back)
+                if (E.ai[i].op == I_LOAD && E.ai[i].a == SRC_ACC && i + 1 < E.n_ai && E.ai[i + 1].op == I_MOVRA) {
+                    bool free_reg = true;
+                    for (int j = top; j < i && free_reg; ++j) free_reg = !touches(E.ai[j], E.ai[i + 1].a);
+                    for (int j = E.n_prolog; j < top && free_reg; ++j) free_reg = E.ai[j].op != I_LOAD || E.ai[j].a != E.ai[i + 1].a;
+                    if (free_reg) {
+                        E.ai[i].a = E.ai[i + 1].a;
+                        E.ai[i + 1].op = I_MOVAR;
+                    }
+                }
                 if (E.ai[i].op != I_LOAD || E.ai[i].a >= SRC_S0) continue;
                 bool free_reg = true;
                 for (int j = top; j < i && free_reg; ++j) free_reg = !touches(E.ai[j], E.ai[i].a);
@@ -2059,7 +2145,10 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                 *b++ = w0(op, view ? LEN_VLOAD : LEN_LOAD, x.a, x.b);
                 uint32_t mflags = 0;
                 if (x.op == I_LOAD) {
-                    bool once = !A.rows;        // read exactly once: no outer dim is broadcast
+                    bool once = !A.rows;        // read exactly once: no outer dim is broadcast, and one record only
+                    int n_loads = 0;
+                    for (int j = 0; j < E.n_ai; ++j) n_loads += E.ai[j].op == I_LOAD && E.ai[j].tensor == x.tensor;
+                    once &= n_loads == 1;
                     for (int g = 1; g < ng; ++g) once &= !(E.Dg[g] > 1 && A.s[g] == 0);
                     if (once && !long_row) mflags |= MF_STREAM;     // (a long row is read once per pass: keep it cached)
                 }
@@ -2119,9 +2208,9 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                 b[2] = x.srck == 1 ? bits_f32(x.imm) : 0u;
                 b += LEN_SOP;
                 break;
-            case I_FMA:
-                imask |= 1u << I_FMA;
-                b[0] = w0(I_FMA, LEN_REC, x.a, x.b);
+            case I_FMA: case I_MAC:
+                imask |= 1u << x.op;
+                b[0] = w0(x.op, LEN_REC, x.a, x.b);
                 b[1] = x.kind;
                 b += LEN_REC;
                 break;
@@ -2330,6 +2419,9 @@ extern "C" int dvm_validate(const void *bytecode, size_t len) {
                     break;
                 case I_SEL:
                     if (l != LEN_REC || !reg_ok(a, vr) || !reg_ok(bb, vr)) return bad("select");
+                    break;
+                case I_MAC:
+                    if (l != LEN_REC || !reg_ok(a, vr) || !reg_ok(bb, vr) || w[pc + 1] >= MAC_COUNT) return bad("multiply-accumulate");
                     break;
                 case I_FMA:
                     if (l != LEN_REC || !reg_ok(a, vr) || !(reg_ok(bb, vr) || bb == FMA_NO_ADDEND)) return bad("fused multiply-add");
@@ -2882,6 +2974,10 @@ extern "C" int dvm_disasm(const void *bytecode, size_t len, char *txt, size_t ca
                 case I_LDSCOPY:
                     o.put("  %04zu ldscopy L%u = t%u  [%u bytes of LDS at %u%s]\n", pc - at - SH_WORDS, a, w[pc + 1] & 0xFF, w[pc + 3], w[pc + 2],
                           b ? ", then workgroup sync" : "");
+                    break;
+                case I_MAC:
+                    o.put(w[pc + 1] == MAC_RSUB ? "  %04zu mac     acc = r%u * r%u - acc\n" : (w[pc + 1] == MAC_SUB ? "  %04zu mac     acc = acc - r%u * r%u\n" : "  %04zu mac     acc = acc + r%u * r%u\n"),
+                          pc - at - SH_WORDS, a, b);
                     break;
                 case I_LFMA: {
                     char sc[8] = "", mu[8] = "", ad[8] = "";

@@ -1637,6 +1637,16 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                         }
                         break;
                     }
+                    case I_MAC: if constexpr (!(LONG && WIDE)) {       // (long rows with such a record run in the instantiation for any launch)
+                        if (cw1 == MAC_ADD) {
+                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_fma(TV(xa, I), TV(xb, I), TV(acc, I)); })))
+                        } else if (cw1 == MAC_SUB) {
+                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_fma(-TV(xa, I), TV(xb, I), TV(acc, I)); })))
+                        } else {
+                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_fma(TV(xa, I), TV(xb, I), -TV(acc, I)); })))
+                        }
+                    }
+                        break;
                     case I_LDSCOPY: {
                         // every thread of the workgroup copies 16-byte pieces of the tensor's only row into the image;
                         // pieces that reach beyond the row's end are put together element by element, zero-filled
@@ -2114,7 +2124,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     // and LDS for the combination across waves: four floats per lane of every participating wave
     uint32_t lds_bytes = 0;
     bool cred = false, wide = true;     // wide: every segment spreads a row over whole waves
-    bool grid_sync = false, wg_sync = false, longrow = false;
+    bool grid_sync = false, wg_sync = false, longrow = false, mac = false;
     uint8_t seg_of[DVM_MAX_TENSORS];    // the segment a tensor belongs to
     memset(seg_of, 0xFF, sizeof(seg_of));
     for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; ++s) {
@@ -2125,6 +2135,8 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         grid_sync |= (sh[S_FLAGS] & SF_SYNC_GRID) != 0;
         wg_sync |= (sh[S_FLAGS] & SF_SYNC_WG) != 0;
         longrow |= (sh[S_FLAGS] & SF_LONGROW) != 0;
+        if (sh[S_FLAGS] & SF_LONGROW)
+            for (uint32_t pc = SH_WORDS; pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF) mac |= (sh[pc] & 0xFF) == I_MAC;
         if (sh[S_INNER] != 0 && rp > 1 && rp * 64u * 16u > lds_bytes) lds_bytes = rp * 64u * 16u;
         if (sh[S_FLAGS] & SF_LDS)           // the images the prologue copies into LDS
             for (uint32_t pc = SH_WORDS; pc < SH_WORDS + sh[S_PROLOGA]; pc += (sh[pc] >> 8) & 0xFF)
@@ -2174,7 +2186,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         for (const VariantEntry &v : g_cred_variants)
             if (v.K == K && v.NR == NR) launch = v.launch;
     } else {
-        const VariantEntry *list = part || (longrow && !wide) ? g_any_variants : (longrow ? g_long_wide_variants : (wide ? g_wide_variants : g_variants));
+        const VariantEntry *list = part || (longrow && (!wide || mac)) ? g_any_variants : (longrow ? g_long_wide_variants : (wide ? g_wide_variants : g_variants));
         for (int i = 0; i < N_VARIANTS; ++i)
             if (list[i].K == K && list[i].NR == NR) launch = list[i].launch;
     }
