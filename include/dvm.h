@@ -317,6 +317,10 @@ int  dvm_code_info_get(const void *bytecode, size_t len, dvm_code_info *info);
 int  dvm_code_tensor(const void *bytecode, size_t len, int index,
                      int64_t *min_bytes, int *is_output, int *dtype, int *align_bytes);
 
+/* Minimum sizes in bytes of the buffers behind tensors[0 .. n-1], as dvm_code_tensor reports them one by one; n must not
+ * exceed the tensors the bytecode lists (DVM_E_ARGS). */
+int  dvm_code_min_bytes(const void *bytecode, size_t len, int64_t *min_bytes, int n);
+
 /* The tile-size rule on a one-dimensional space (Section 4.2, hardware_align_div): among tile
  * sizes 1..t_max the one minimising ceil(ceil(total/t)/n_cores) * (t + overhead), ties to the
  * larger tile, then rounded up to a multiple of `align` without exceeding t_max.

@@ -6,8 +6,11 @@ PyTorch is used by callers for device memory and streams; this module only reads
 """
 from __future__ import annotations
 
+import array
 import ctypes as C
+import itertools
 import os
+import struct
 from typing import Dict, List, Optional, Sequence, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -99,6 +102,7 @@ def load() -> C.CDLL:
         "dvm_disasm": (i, [vp, sz, C.c_char_p, sz]),
         "dvm_code_info_get": (i, [vp, sz, P(dvm_code_info)]),
         "dvm_code_tensor": (i, [vp, sz, i, P(C.c_int64), P(i), P(i), P(i)]),
+        "dvm_code_min_bytes": (i, [vp, sz, P(C.c_int64), i]),
         "dvm_plan": (i, [C.c_int64, i, C.c_int64, i, i, P(C.c_int64), P(C.c_int64), P(C.c_int64)]),
         "dvm_run": (i, [vp, vp, sz, P(vp), i, vp]),
         "dvm_run_static": (i, [vp, vp, sz, P(vp), i, vp]),
@@ -131,7 +135,7 @@ EXPORTED = ["dvm_shape_contiguous", "dvm_ctx_create", "dvm_ctx_destroy", "dvm_ct
             "dvm_prog_input", "dvm_prog_op", "dvm_prog_output", "dvm_prog_finish", "dvm_prog_num_inputs",
             "dvm_prog_num_outputs", "dvm_prog_destroy", "dvm_encode", "dvm_stack", "dvm_stack_spatial", "dvm_stack_dependent",
             "dvm_ctx_set_sync_limit", "dvm_workspace_status", "dvm_validate", "dvm_disasm",
-            "dvm_code_info_get", "dvm_code_tensor", "dvm_plan", "dvm_run", "dvm_run_static", "dvm_run_batched", "dvm_encode_timed", "dvm_copy_kernel", "dvm_strerror", "dvm_last_error_detail",
+            "dvm_code_info_get", "dvm_code_tensor", "dvm_code_min_bytes", "dvm_plan", "dvm_run", "dvm_run_static", "dvm_run_batched", "dvm_encode_timed", "dvm_copy_kernel", "dvm_strerror", "dvm_last_error_detail",
             "dvm_last_hip_error", "dvm_fuser_create", "dvm_fuser_destroy", "dvm_fuser_set_workspace", "dvm_fuser_tensor", "dvm_fuser_op",
             "dvm_fuser_release", "dvm_fuser_flush", "dvm_fuser_stats", "dvm_fuser_last_code"]
 
@@ -168,6 +172,27 @@ def _ptr_align(ptr: int) -> int:
 
 def shape_of_tensor(t) -> dvm_shape:
     return make_shape(tuple(t.shape), tuple(t.stride()), _ptr_align(t.data_ptr()))
+
+
+# One call packs a whole dvm_shape: setting its fields one by one through ctypes was most of the host time of a launch.
+_SHAPE = struct.Struct(f"=ii{DVM_MAX_RANK}q{DVM_MAX_RANK}q")
+_PAD = [(0,) * (DVM_MAX_RANK - r) for r in range(DVM_MAX_RANK + 1)]
+
+
+def _shapes_of(tensors: Sequence):
+    """An array of dvm_shape for torch tensors (shape_of_tensor of each)."""
+    arr = (dvm_shape * max(len(tensors), 1))()
+    at = 0
+    for t in tensors:
+        dims = t.shape
+        r = len(dims)
+        if r > DVM_MAX_RANK:
+            raise DvmError(-3, "make_shape")
+        pad = _PAD[r]
+        p = t.data_ptr()
+        _SHAPE.pack_into(arr, at, r, p & -p if p & 15 else 16, *dims, *pad, *t.stride(), *pad)
+        at += _SHAPE.size
+    return arr
 
 
 class Context:
@@ -258,7 +283,6 @@ class Program:
 class Bytecode:
     def __init__(self, raw: bytes, out_shapes: List[Tuple[int, ...]]):
         self.raw = raw
-        self._buf = C.create_string_buffer(raw, len(raw))
         self.out_shapes = out_shapes
 
     def __len__(self):
@@ -266,7 +290,7 @@ class Bytecode:
 
     @property
     def ptr(self):
-        return C.cast(self._buf, C.c_void_p)
+        return C.cast(C.c_char_p(self.raw), C.c_void_p)     # (valid while this object lives)
 
     def info(self) -> dvm_code_info:
         inf = dvm_code_info()
@@ -302,18 +326,30 @@ _ENC_CAP = 8192
 
 def dvm_encode(ctx: Context, prog: Program, in_shapes: Sequence[dvm_shape],
                out_layout: Optional[Sequence[dvm_shape]] = None) -> Bytecode:
-    lib = load()
     n = len(in_shapes)
     arr = (dvm_shape * max(n, 1))(*in_shapes)
     outl = None
     if out_layout is not None:
         outl = (dvm_shape * max(len(out_layout), 1))(*out_layout)
-    buf = C.create_string_buffer(_ENC_CAP)
+    return _encode(ctx, prog, arr, n, outl)
+
+
+_EncBuf = C.c_char * _ENC_CAP
+
+
+def _encode(ctx: Context, prog: Program, arr, n: int, outl) -> Bytecode:
+    buf = _EncBuf()
     ln = C.c_size_t()
-    outs = (dvm_shape * max(prog.n_out, 1))()
-    _check(lib.dvm_encode(ctx._h, prog._h, arr, n, outl, buf, _ENC_CAP, C.byref(ln), outs), "dvm_encode")
-    shapes = [tuple(outs[i].dim[k] for k in range(outs[i].rank)) for i in range(prog.n_out)]
-    return Bytecode(buf.raw[: ln.value], shapes)
+    n_out = prog.n_out
+    outs = (dvm_shape * max(n_out, 1))()
+    status = load().dvm_encode(ctx._h, prog._h, arr, n, outl, buf, _ENC_CAP, ln, outs)
+    if status != 0:
+        raise DvmError(status, "dvm_encode")
+    shapes = []
+    for k in range(n_out):
+        v = _SHAPE.unpack_from(outs, k * _SHAPE.size)
+        shapes.append(v[2: 2 + v[0]])
+    return Bytecode(buf[: ln.value], shapes)
 
 
 def dvm_stack(codes: Sequence[Bytecode], spatial: bool = False) -> Bytecode:
@@ -365,8 +401,10 @@ def workspace_gave_up(workspace_ptr: int, stream: int = 0) -> bool:
 
 def dvm_run(ctx: Context, code: Bytecode, tensor_ptrs: Sequence[int], stream: int = 0) -> None:
     n = len(tensor_ptrs)
-    arr = (C.c_void_p * max(n, 1))(*tensor_ptrs)
-    _check(load().dvm_run(ctx._h, code.ptr, len(code), arr, n, C.c_void_p(stream)), "dvm_run")
+    raw = code.raw
+    status = load().dvm_run(ctx._h, raw, len(raw), (C.c_void_p * max(n, 1))(*tensor_ptrs), n, stream)
+    if status != 0:
+        raise DvmError(status, "dvm_run")
 
 
 def dvm_run_batched(ctx: Context, code: Bytecode, tensor_ptr_sets: Sequence[Sequence[int]], table_ptr: int, table_bytes: int,
@@ -374,9 +412,9 @@ def dvm_run_batched(ctx: Context, code: Bytecode, tensor_ptr_sets: Sequence[Sequ
     """One launch over several sets of tensors (device pointers); `table_ptr`: device memory for the address table."""
     n_sets = len(tensor_ptr_sets)
     n = len(tensor_ptr_sets[0])
-    flat = [p for s_ in tensor_ptr_sets for p in s_]
+    flat = array.array("Q", itertools.chain.from_iterable(tensor_ptr_sets))
     assert len(flat) == n * n_sets
-    arr = (C.c_void_p * len(flat))(*flat)
+    arr = (C.c_void_p * len(flat)).from_buffer(flat)
     _check(load().dvm_run_batched(ctx._h, code.ptr, len(code), arr, n, n_sets, C.c_void_p(table_ptr), table_bytes, C.c_void_p(stream)),
            "dvm_run_batched")
 
@@ -450,15 +488,17 @@ def dvm_plan(total: int, n_cores: int, t_max: int, align: int, overhead: int = 2
 
 def encode_for(ctx: Context, prog: Program, inputs: Sequence, outputs: Optional[Sequence] = None) -> Bytecode:
     """Encode `prog` for the shapes/strides of the given torch tensors (and output views, if any)."""
-    in_shapes = [shape_of_tensor(t) for t in inputs]
-    out_layout = [shape_of_tensor(t) for t in outputs] if outputs is not None else None
-    return dvm_encode(ctx, prog, in_shapes, out_layout)
+    return _encode(ctx, prog, _shapes_of(inputs), len(inputs), _shapes_of(outputs) if outputs is not None else None)
 
 
 def check_buffers(code: Bytecode, tensors: Sequence) -> None:
     """Host-side guard: every tensor's storage must cover what the bytecode will touch."""
-    for i, t in enumerate(tensors):
-        need, _is_out, _dt, _al = code.tensor(i)
+    n = len(tensors)
+    needs = (C.c_int64 * max(n, 1))()
+    _check(load().dvm_code_min_bytes(code.raw, len(code.raw), needs, n), "dvm_code_min_bytes")
+    for i, (need, t) in enumerate(zip(needs, tensors)):
+        if need <= t.nbytes and t.is_contiguous():      # (its storage holds at least its elements)
+            continue
         have = (t.untyped_storage().nbytes() - t.storage_offset() * t.element_size()) if t.numel() else 0
         if need > have:
             raise DvmError(-1, f"tensor {i}: bytecode touches {need} bytes, storage holds {have}")

@@ -2544,6 +2544,18 @@ extern "C" int dvm_code_info_get(const void *bytecode, size_t len, dvm_code_info
     return DVM_OK;
 }
 
+extern "C" int dvm_code_min_bytes(const void *bytecode, size_t len, int64_t *min_bytes, int n) {
+    const int st = dvm_validate(bytecode, len);
+    if (st != DVM_OK) return st;
+    const uint32_t *w = (const uint32_t *)bytecode;
+    if (n < 0 || (uint32_t)n > w[PH_NTENS] || (n > 0 && !min_bytes)) return dvm_set_error(DVM_E_ARGS, "dvm_code_min_bytes: tensor count");
+    for (int i = 0; i < n; ++i) {
+        const uint32_t *te = w + PH_WORDS_N + i * TT_WORDS;
+        min_bytes[i] = (int64_t)((uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32));
+    }
+    return DVM_OK;
+}
+
 extern "C" int dvm_code_tensor(const void *bytecode, size_t len, int index, int64_t *min_bytes, int *is_output,
                                int *dtype, int *align_bytes) {
     int st = dvm_validate(bytecode, len);
