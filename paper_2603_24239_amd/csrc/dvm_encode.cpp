@@ -595,6 +595,7 @@ struct Enc {
     int regs[NR_MAX], sregs[NS];
     int nr_limit;           // tile registers the program may use
     int next_reg;
+    bool stale[NR_MAX];     // the register still holds an input that will be loaded again if something else takes the register
     bool allow_mac;
     int n_mac;              // products of two inputs that ride along
     int mac_of[MAX_NODES];  // the product of two inputs that this sum or difference takes in its record (I_MAC), or -1
@@ -669,18 +670,21 @@ struct Enc {
         sreg_of[dst_node] = sr;
     }
     int alloc_reg(int node) {
-        for (int k = 0; k < nr_limit; ++k) {
-            // (where inputs are loaded again at each use, registers are taken in turn: one that nothing has touched yet lets
-            // its load join the loads the body starts with)
-            const int i = reload_inputs && nr_limit > 0 ? (next_reg + k) % nr_limit : k;
-            if (regs[i] < 0) {
-                next_reg = i + 1;
-                regs[i] = node;
-                reg_of[node] = i;
-                if (i + 1 > nr_used) nr_used = i + 1;
-                return i;
+        for (int pass = 0; pass < 2; ++pass)
+            for (int k = 0; k < nr_limit; ++k) {
+                // (where inputs are loaded again at each use, registers are taken in turn: one that nothing has touched yet lets
+                // its load join the loads the body starts with)
+                const int i = reload_inputs && nr_limit > 0 ? (next_reg + k) % nr_limit : k;
+                if (pass == 1 && regs[i] >= 0 && stale[i]) { reg_of[regs[i]] = -1; regs[i] = -1; }
+                if (regs[i] < 0) {
+                    next_reg = i + 1;
+                    regs[i] = node;
+                    reg_of[node] = i;
+                    stale[i] = false;
+                    if (i + 1 > nr_used) nr_used = i + 1;
+                    return i;
+                }
             }
-        }
         fail(DVM_E_UNSUPPORTED, "program needs more live tile registers than available");
         return 0;
     }
@@ -742,7 +746,10 @@ struct Enc {
         emit(I_MOVRA, (uint8_t)r);
     }
     int to_reg(int n) {                 // make sure a tile value sits in some R register
-        if (reg_of[n] >= 0) return reg_of[n];
+        if (reg_of[n] >= 0) {
+            stale[reg_of[n]] = false;
+            return reg_of[n];
+        }
         if (rows_class[n] && in_acc != n) {     // a row value needed as a tile: broadcast it through the accumulator
             to_acc(n);
         }
@@ -1297,7 +1304,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     }
     for (int i = 0; i < prog->n_out; ++i) E.uses[prog->out_node[i]]++;
     for (int n = 0; n < NN; ++n) { E.reg_of[n] = -1; E.sreg_of[n] = -1; }
-    for (int i = 0; i < NR_MAX; ++i) E.regs[i] = -1;
+    for (int i = 0; i < NR_MAX; ++i) { E.regs[i] = -1; E.stale[i] = false; }
     for (int i = 0; i < NS; ++i) E.sregs[i] = -1;
     E.in_acc = -1;
     E.n_ai = 0;
@@ -1537,7 +1544,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                     const int rp = E.to_reg(p), rq = E.to_reg(q);
                     E.emit(I_MAC, (uint8_t)rp, (uint8_t)rq, -1, 0.0f, (uint8_t)kind);
                     for (int x : {p, q})            // (when inputs are not kept, their registers are free again after the record)
-                        if (E.reload_inputs && E.reg_of[x] >= 0 && E.uses[x] > 1 && E.uses[x] < (1 << 20)) { E.regs[E.reg_of[x]] = -1; E.reg_of[x] = -1; }
+                        if (E.reload_inputs && E.reg_of[x] >= 0 && E.uses[x] > 1 && E.uses[x] < (1 << 20)) E.stale[E.reg_of[x]] = true;
                     E.use(p);
                     E.use(q);
                     E.uses[m] = 0;
@@ -1605,7 +1612,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                         // the loads before it); when inputs are not kept, the register is free again after the op
                         const int r = E.to_reg(b);
                         E.emit(I_BIN, (uint8_t)r, (uint8_t)op);
-                        if (E.reload_inputs && E.uses[b] > 1) { E.regs[r] = -1; E.reg_of[b] = -1; }
+                        if (E.reload_inputs && E.uses[b] > 1) E.stale[r] = true;
                     } else {
                         E.fail(DVM_E_UNSUPPORTED, "internal: operand lost during linearisation");
                     }
