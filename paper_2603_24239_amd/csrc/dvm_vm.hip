@@ -44,8 +44,11 @@ struct KArgs {
     uint64_t sets;                      // batched launch: device array of n_sets * n_tensors addresses (0: `tensors` above)
     uint32_t n_sets;                    // times the program runs, each time on the next set of tensors (at least 1)
     uint32_t n_tensors;
-    uint32_t rotate;                    // 1: every segment deals its tiles out starting at the workgroup after the one the
-                                        // segment before stopped at (short segments then do not all land on the first workgroups)
+    uint32_t rotate;                    // not 0: every segment deals its tiles out starting at the workgroup after the one the
+                                        // segment before stopped at (short segments then do not all land on the first workgroups);
+                                        // 1: all of them round-robin, so that workgroup b runs the tiles b, b + N, b + 2N, .. of the
+                                        // whole launch, counted over its segments and sets
+    uint32_t set_tiles;                 // rotate = 1: tiles of one set (of this launch's segments)
     uint32_t seg_first;                 // this launch runs segments seg_first .. nseg - 1
     uint32_t aliased;                   // 1: some segment's output shares memory with another tensor of that segment
 };
@@ -330,6 +333,15 @@ template <uint32_t R> DI float wave_allreduce(float v, uint32_t width) {
 constexpr bool HAVE_PART = false;
 #else
 constexpr bool HAVE_PART = true;
+#endif
+// Passing over the sets and segments that hold none of a workgroup's tiles (rotate = 1) is left out of the instantiations for
+// launches of one segment and one set: two more values across the record loop cost the 12-op chain 12 % and masked softmax
+// 6-15 %.  (Their loops over segments and sets stay: without them the compiler reloads the segment header inside the record
+// loop, and the chain is 5 % slower, masked softmax 3 %.)
+#if defined(DVM_VARIANT_SINGLE)
+constexpr bool SKIP = false;
+#else
+constexpr bool SKIP = true;
 #endif
 // The wave-uniform part lives across the interpreter loop, whose scalar registers are scarce (a value more there is
 // spilled and costs every record): it holds what cannot be derived in a few scalar instructions where it is used.
@@ -1097,7 +1109,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
     const uint32_t ngrid = gridDim.x;
     uint32_t red_par = 0;
     uint32_t n_sync = 0;                    // grid-wide synchronisation points passed so far
-    uint32_t rot = 0;                       // first workgroup of the next segment's tiles (rotating assignment)
+    uint32_t rot = 0;                       // rotate = 2: first workgroup of the next segment's tiles
+    uint32_t gbase = 0, gnext = bid;        // rotate = 1: tiles of the launch before this segment; this workgroup's next tile
     const uint32_t *code = args.code;
     // the launch's tensor addresses, one per lane: a memory record reads the one it needs with a single lane read
     // (the index is wave-uniform) instead of a scalar load whose latency it would have to wait for
@@ -1109,7 +1122,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
     }
     // A batched launch runs the whole program once per set of tensors, the sets one after the other; the workgroups
     // pass from one set to the next without waiting for each other (the sets are independent).
+    // A set or segment that holds none of a workgroup's tiles is passed over at once: going through it (its addresses, its
+    // header, the divisions of its geometry) took 1.1 us, 173 us of a 32-layer step whatever its size (a step of 11 tokens 221 us
+    // that way and 64 now, of 107 tokens 280 and 132, of 512 tokens 639 and 604).
     for (uint32_t set = 0; set < args.n_sets; ++set) {
+    if (SKIP && args.rotate == 1 && gnext - gbase >= args.set_tiles) {
+        gbase += args.set_tiles;
+        continue;
+    }
     if (args.sets != 0) {
         const uint32_t slot = tid & (DVM_MAX_TENSORS - 1);
         const uint32_t idx = set * args.n_tensors + (slot < args.n_tensors ? slot : 0u);
@@ -1129,8 +1149,13 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
             seg += seg_words;
             continue;
         }
-        const uint32_t code_size = sh[S_CODESIZE];
         const uint32_t M = sh[S_NTILES];
+        if (SKIP && args.rotate == 1 && gnext - gbase >= M) {
+            gbase += M;
+            seg += seg_words;
+            continue;
+        }
+        const uint32_t code_size = sh[S_CODESIZE];
         const uint32_t geom = sh[S_GEOM];
         const uint32_t G = geom & 0xFFFF, V = (geom >> 16) & 0xFF, nvec = geom >> 24;
         const uint32_t RP = sh[S_RP] & 0xFFFF, seg_threads = sh[S_RP] >> 16;
@@ -1196,7 +1221,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
         // Algorithm 2: m = ceil(M / N); this workgroup runs tiles [m*id, min(M, m*(id+1))).  In a
         // spatially stacked launch N and id count the workgroups of this segment's share only.
         uint32_t sbid = bid, sgrid = ngrid;
-        if (args.rotate != 0) {
+        if (SKIP && args.rotate == 1) sbid = gnext - gbase;     // (below M: the first of its tiles here)
+        if (args.rotate == 2) {
             sbid = bid >= rot ? bid - rot : bid + ngrid - rot;
             rot += M % ngrid;
             if (rot >= ngrid) rot -= ngrid;
@@ -1209,18 +1235,20 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                 continue;
             }
         }
-        const uint32_t m = (M + sgrid - 1) / sgrid;
-        const uint64_t t_lo64 = (uint64_t)m * sbid;
-        uint32_t t_lo = t_lo64 < M ? (uint32_t)t_lo64 : M;
-        uint32_t t_hi = (M - t_lo) < m ? M : t_lo + m;
-        uint32_t t_step = 1;
         // Interleaved assignment: workgroup id runs tiles id, id + N, id + 2N, ...  At any moment the resident
         // workgroups then work on one contiguous stretch of the tensors, which the memory system of this
         // machine serves measurably faster than N streams that are far apart (the blocked ranges).
+        uint32_t t_lo, t_hi, t_step;
         if (sh[S_FLAGS] & SF_INTERLEAVED) {
             t_lo = sbid < M ? sbid : M;
             t_hi = M;
             t_step = sgrid;
+        } else {
+            const uint32_t m = (M + sgrid - 1) / sgrid;
+            const uint64_t t_lo64 = (uint64_t)m * sbid;
+            t_lo = t_lo64 < M ? (uint32_t)t_lo64 : M;
+            t_hi = (M - t_lo) < m ? M : t_lo + m;
+            t_step = 1;
         }
 
         const uint32_t nct = sh[S_NCT];
@@ -1780,6 +1808,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                 tile += t_step;
             }
         }
+        if (SKIP && args.rotate == 1) {         // (one past the last tile this workgroup ran here, in steps of the grid)
+            gnext += (M - sbid + ngrid - 1) / ngrid * ngrid;
+            gbase += M;
+        }
         seg += seg_words;
     }
     }   // (sets)
@@ -1808,6 +1840,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 #define DVM_WIDE_LAUNCHER_NAME(K, NR) DVM_WIDE_LAUNCHER_NAME_(K, NR)
 #define DVM_ANY_LAUNCHER_NAME_(K, NR) dvm_vm_launch_a_##K##_##NR
 #define DVM_ANY_LAUNCHER_NAME(K, NR) DVM_ANY_LAUNCHER_NAME_(K, NR)
+#define DVM_ONE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_1_##K##_##NR
+#define DVM_ONE_LAUNCHER_NAME(K, NR) DVM_ONE_LAUNCHER_NAME_(K, NR)
+#define DVM_ONE_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_1w_##K##_##NR
+#define DVM_ONE_WIDE_LAUNCHER_NAME(K, NR) DVM_ONE_WIDE_LAUNCHER_NAME_(K, NR)
 #define DVM_LONG_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_lw_##K##_##NR
 #define DVM_LONG_WIDE_LAUNCHER_NAME(K, NR) DVM_LONG_WIDE_LAUNCHER_NAME_(K, NR)
 
@@ -1826,6 +1862,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 #elif defined(DVM_VARIANT_ANY)
 #define DVM_THIS_LAUNCHER DVM_ANY_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
 #define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false, true>
+#elif defined(DVM_VARIANT_WIDE) && defined(DVM_VARIANT_SINGLE)
+#define DVM_THIS_LAUNCHER DVM_ONE_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, true, false>
+#elif defined(DVM_VARIANT_SINGLE)
+#define DVM_THIS_LAUNCHER DVM_ONE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
+#define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false, false>
 #elif defined(DVM_VARIANT_WIDE)
 #define DVM_THIS_LAUNCHER DVM_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
 #define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, true, false>
@@ -1852,6 +1894,12 @@ DVM_VARIANT_LIST(X)
 #define X(K, NR, MAXT, W) extern "C" int DVM_LONG_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
 DVM_VARIANT_LIST(X)
 #undef X
+#define X(K, NR, MAXT, W) extern "C" int DVM_ONE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
+DVM_VARIANT_LIST(X)
+#undef X
+#define X(K, NR, MAXT, W) extern "C" int DVM_ONE_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
+DVM_VARIANT_LIST(X)
+#undef X
 #define X(K, NR, MAXT, W) extern "C" int DVM_CRED_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
 DVM_CRED_VARIANT_LIST(X)
 #undef X
@@ -1876,6 +1924,12 @@ const VariantEntry g_any_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
 #define X(K, NR, MAXT, W) {K, NR, DVM_LONG_WIDE_LAUNCHER_NAME(K, NR)},
 const VariantEntry g_long_wide_variants[] = {DVM_VARIANT_LIST(X)};
+#undef X
+#define X(K, NR, MAXT, W) {K, NR, DVM_ONE_LAUNCHER_NAME(K, NR)},
+const VariantEntry g_one_variants[] = {DVM_VARIANT_LIST(X)};
+#undef X
+#define X(K, NR, MAXT, W) {K, NR, DVM_ONE_WIDE_LAUNCHER_NAME(K, NR)},
+const VariantEntry g_one_wide_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
 #define X(K, NR, MAXT, W) {K, NR, DVM_CRED_LAUNCHER_NAME(K, NR)},
 const VariantEntry g_cred_variants[] = {DVM_CRED_VARIANT_LIST(X)};
@@ -2117,6 +2171,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     ka.n_sets = 1;
     ka.n_tensors = ntens;
     ka.rotate = 0;
+    ka.set_tiles = 0;
     ka.seg_first = 0;
     ka.aliased = 0;
     ka.nseg = w[PH_NSEG];
@@ -2183,7 +2238,15 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     // Several segments, or several sets: the tiles of each are dealt out from where the one before stopped.  (Not
     // when a segment relies on its producer's assignment of tiles to workgroups, nor when the segments own shares
     // of the workgroups.)
-    ka.rotate = (w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL ? 1u : 0u;
+    if ((w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL) {
+        uint64_t total = 0;
+        bool round_robin = true;
+        for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
+            total += w[at + S_NTILES];
+            round_robin &= (w[at + S_FLAGS] & SF_INTERLEAVED) != 0;
+        }
+        ka.rotate = round_robin && !grid_sync && total * (uint64_t)n_sets < (1ull << 31) ? 1u : 2u;     // (every workgroup arrives at a grid-wide wait)
+    }
     if (cred && longrow)
         return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: a launch holds both a reduction along the penultimate axis and rows longer than a tile");
     vm_launch_t launch = nullptr;
@@ -2191,7 +2254,11 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         for (const VariantEntry &v : g_cred_variants)
             if (v.K == K && v.NR == NR) launch = v.launch;
     } else {
-        const VariantEntry *list = part || (longrow && (!wide || mac)) ? g_any_variants : (longrow ? g_long_wide_variants : (wide ? g_wide_variants : g_variants));
+        const bool one = w[PH_NSEG] == 1 && n_sets == 1;
+        const VariantEntry *list = part || (longrow && (!wide || mac || !one)) ? g_any_variants
+                                   : longrow                                   ? g_long_wide_variants
+                                   : one                                       ? (wide ? g_one_wide_variants : g_one_variants)
+                                                                               : (wide ? g_wide_variants : g_variants);
         for (int i = 0; i < N_VARIANTS; ++i)
             if (list[i].K == K && list[i].NR == NR) launch = list[i].launch;
     }
@@ -2245,6 +2312,9 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         }
         ka.seg_first = first;
         ka.nseg = end;
+        ka.set_tiles = 0;
+        for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s)
+            if (s >= first) ka.set_tiles += w[at + S_NTILES];
         dvm_colreduce_args ca;
         uint32_t cgrid = 0, cblock = 0;
         const uint32_t *first_sh = w + segs_off;
