@@ -25,6 +25,11 @@ SQ = ["SQ_WAVES", "SQ_BUSY_CU_CYCLES", "SQ_WAVE_CYCLES", "SQ_INSTS_VALU", "SQ_IN
       "SQ_ACTIVE_INST_ANY"]
 
 
+def _ours(name: str) -> bool:
+    """The interpreter, and the kernel of plain reductions along the penultimate axis."""
+    return "dvm_vm_kernel" in name or "dvm_colreduce" in name
+
+
 def _short(name: str, n: int = 78) -> str:
     return (name[:n] + "...") if len(name) > n else name
 
@@ -41,7 +46,7 @@ def _counter(dirname: str, counter: str):
             key = (f, r["Dispatch_Id"])
             per[key] += float(r["Counter_Value"])
             k = r["Kernel_Name"]
-            kind[key] = "vm" if "dvm_vm_kernel" in k else ("copy" if "copyBuffer" in k else ("dvm_copy" if "dvm_copy_tiles" in k else "x"))
+            kind[key] = "vm" if _ours(k) else ("copy" if "copyBuffer" in k else ("dvm_copy" if "dvm_copy_tiles" in k else "x"))
     out = collections.defaultdict(list)
     for key, v in per.items():
         out[kind[key]].append(v)
@@ -70,8 +75,8 @@ def main() -> int:
     out.append("## Kernel trace\n")
     out.append(f"    rocprofv3 --kernel-trace --stats --output-format csv -d <dir>/kt -o kt -- {cmd} --steps 2 --warmup 1 --no-cpu-baseline --skip-unstacked\n")
     out.append("| kernel | calls | total ms | avg us | min us | max us | % of GPU time |\n|---|---|---|---|---|---|---|")
-    vm = [r for r in rows if "dvm_vm_kernel" in r["Name"]]
-    for r in vm + [r for r in rows if "dvm_vm_kernel" not in r["Name"]][:3]:
+    vm = [r for r in rows if _ours(r["Name"])]
+    for r in vm + [r for r in rows if not _ours(r["Name"])][:3]:
         out.append("| `%s` | %s | %.2f | %.2f | %.2f | %.2f | %s |" % (_short(r["Name"]), r["Calls"], float(r["TotalDurationNs"]) / 1e6,
                                                                     float(r["AverageNs"]) / 1e3, float(r["MinNs"]) / 1e3, float(r["MaxNs"]) / 1e3,
                                                                     r["Percentage"]))
