@@ -335,8 +335,8 @@ constexpr bool HAVE_PART = false;
 constexpr bool HAVE_PART = true;
 #endif
 // Passing over the sets and segments that hold none of a workgroup's tiles (rotate = 1) is left out of the instantiations for
-// launches of one segment and one set: two more values across the record loop cost the 12-op chain 12 % and masked softmax
-// 6-15 %.  (Their loops over segments and sets stay: without them the compiler reloads the segment header inside the record
+// launches of few segments and sets for their size: two more values across the record loop cost the 12-op chain 12 %, masked softmax
+// 6-15 % and a stack of eight large RMSNorms 15 %.  (Their loops over segments and sets stay: without them the compiler reloads the segment header inside the record
 // loop, and the chain is 5 % slower, masked softmax 3 %.)
 #if defined(DVM_VARIANT_SINGLE)
 constexpr bool SKIP = false;
@@ -2247,6 +2247,15 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         }
         ka.rotate = round_robin && !grid_sync && total * (uint64_t)n_sets < (1ull << 31) ? 1u : 2u;     // (every workgroup arrives at a grid-wide wait)
     }
+    // The instantiations that pass over foreign sets and segments are some 8 % slower per tile; the others spend 1.1 us on each.
+    // They pay where that is more than 8 % of the time the launch's bytes take at 5 TB/s, i.e. below 69 MB per segment and set
+    // (32 layers of five programs at 512 tokens, 18 MB each: 604 us against 639; eight RMSNorms of 285 MB: the other way round).
+    bool skip = false;
+    if (ka.rotate == 1) {
+        uint64_t bytes = 0;
+        for (uint32_t i = 0; i < ntens; ++i) bytes += (uint64_t)w[PH_WORDS_N + i * TT_WORDS + TT_BYTES_LO] | ((uint64_t)w[PH_WORDS_N + i * TT_WORDS + TT_BYTES_HI] << 32);
+        skip = bytes < (uint64_t)w[PH_NSEG] * (69ull << 20);
+    }
     if (cred && longrow)
         return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: a launch holds both a reduction along the penultimate axis and rows longer than a tile");
     vm_launch_t launch = nullptr;
@@ -2255,10 +2264,10 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             if (v.K == K && v.NR == NR) launch = v.launch;
     } else {
         const bool one = w[PH_NSEG] == 1 && n_sets == 1;
-        const VariantEntry *list = part || (longrow && (!wide || mac || !one)) ? g_any_variants
-                                   : longrow                                   ? g_long_wide_variants
-                                   : one                                       ? (wide ? g_one_wide_variants : g_one_variants)
-                                                                               : (wide ? g_wide_variants : g_variants);
+        const bool any = part || (longrow && (!wide || mac || !one));
+        if (!any && !skip && ka.rotate == 1) ka.rotate = 2;         // (they know the other way of counting only)
+        const VariantEntry *list = any ? g_any_variants : longrow ? g_long_wide_variants
+                                   : skip ? (wide ? g_wide_variants : g_variants) : (wide ? g_one_wide_variants : g_one_variants);
         for (int i = 0; i < N_VARIANTS; ++i)
             if (list[i].K == K && list[i].NR == NR) launch = list[i].launch;
     }
