@@ -120,7 +120,9 @@ int  dvm_ctx_set_planner(dvm_ctx *ctx, int n_compute_units, int tile_overhead_el
  * a program that needs more tile registers than allowed makes dvm_encode return DVM_E_UNSUPPORTED.  The default
  * bounds are 32 elements and 6 registers; the variant with 64 elements exists with one tile register only (programs
  * with long rows that need no more: a row of up to 4096 elements is then held by one wave; flat element-wise
- * programs keep 32 elements) and is planned for only when the bound is raised to 64. */
+ * programs keep 32 elements) and is planned for only when the bound is raised to 64.  Under 64 a program's rows decide:
+ * few rows, or tensors within the last-level cache, take it, long rows beyond the cache stay at 32.  A caller that stacks
+ * parts of such different sizes keeps the bound at 32, or every part runs in the wide variant. */
 int  dvm_ctx_set_limits(dvm_ctx *ctx, int max_elems_per_lane, int max_tile_regs);
 
 /* Force parts of the tile plan instead of letting the cost model choose (tests and tuning walk plans the
