@@ -175,7 +175,13 @@ int  dvm_prog_input(dvm_prog *p, int dtype, int *value_id);
 int  dvm_prog_op(dvm_prog *p, int opcode, const int *arg_ids, int n_args,
                  const double *imm, int n_imm, int *value_id);
 /* Mark a value as the next output with storage dtype `dtype`.  Outputs follow the inputs in
- * `tensors[]`, in the order of these calls. */
+ * `tensors[]`, in the order of these calls.
+ * A call may pass the buffer of an input as an output too: the output then has the input's dtype, shape and strides, and no
+ * operator issued after the one that computes it takes that input (an operator only renamed by DVM_OP_COPY or a cast to fp32
+ * counts as issued where its argument was).  Every load of the input then precedes the store.  What any other overlap of an output with
+ * an input of the same program gives depends on the plan.  (Under a bound on the tile registers so tight that a difference
+ * under an exponential, a square under a sum or a product under a sum fits only where it is used, such an operator counts as
+ * issued there.) */
 int  dvm_prog_output(dvm_prog *p, int value_id, int dtype);
 /* Decompose compound ops into basic ops and freeze the program. */
 int  dvm_prog_finish(dvm_prog *p);

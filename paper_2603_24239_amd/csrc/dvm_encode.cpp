@@ -238,6 +238,10 @@ struct dvm_prog {
     UserOp value_op[MAX_VALUES];
     int value_node[MAX_VALUES];
     Node nodes[MAX_NODES];
+    // fused nodes whose operands are loaded behind the store of an output that came after the operand's own use (dvm_prog_finish)
+    struct Late { int16_t node, from; Node node_form, from_form; };    // (as they are before the fusion)
+    int n_late;
+    Late late[MAX_NODES];
 };
 
 extern "C" int dvm_prog_create(dvm_prog **out) {
@@ -439,6 +443,19 @@ extern "C" int dvm_prog_finish(dvm_prog *p) {
     }
     for (int i = 0; i < p->n_out; ++i) p->out_node[i] = p->value_node[p->out_value[i]];
 
+    // The peepholes below evaluate a node in place of the later node that uses it, and so load its inputs later.  A call may write an
+    // output over an input that no later operator takes: where the store of an output lies in between, both forms are noted, and
+    // dvm_encode takes the fused one only if the other does not fit the registers.
+    p->n_late = 0;
+    auto fuse = [&](int from, int n, const Node &fused) {
+        const Node x = p->nodes[from], own = p->nodes[n];
+        bool late = false;
+        if (p->nodes[x.a].kind == N_IN || (x.kind == N_BIN && p->nodes[x.b].kind == N_IN))
+            for (int o = 0; o < p->n_out; ++o) late |= p->out_node[o] > from && p->out_node[o] < n;
+        if (late) p->late[p->n_late++] = dvm_prog::Late{(int16_t)n, (int16_t)from, own, x};
+        p->nodes[n] = fused;
+        p->nodes[from].kind = N_DEAD;
+    };
     // peephole: sum(square(x)) or sum(x * x), the square used nowhere else -> one sum-of-squares
     int uses[MAX_NODES];
     memset(uses, 0, sizeof(uses));
@@ -453,26 +470,27 @@ extern "C" int dvm_prog_finish(dvm_prog *p) {
     for (int n = 0; n < p->n_nodes; ++n) {
         Node &nd = p->nodes[n];
         if (nd.kind != N_RED || nd.op != R_SUM) continue;
-        Node &sq = p->nodes[nd.a];
+        const Node &sq = p->nodes[nd.a];
         const bool is_sq = (sq.kind == N_UN && sq.op == U_SQUARE) || (sq.kind == N_BIN && sq.op == B_MUL && sq.a == sq.b);
         if (is_sq && uses[nd.a] == 1) {
-            nd.op = R_SUMSQ;
-            nd.a = sq.a;
-            sq.kind = N_DEAD;
+            Node f = nd;
+            f.op = R_SUMSQ;
+            f.a = sq.a;
+            fuse(nd.a, n, f);
         }
     }
     // peephole: exp(a - b), the difference used nowhere else -> one fused op (the softmax core)
     for (int n = 0; n < p->n_nodes; ++n) {
         Node &nd = p->nodes[n];
         if (nd.kind != N_UN || nd.op != U_EXP) continue;
-        Node &d = p->nodes[nd.a];
+        const Node &d = p->nodes[nd.a];
         if (d.kind == N_BIN && d.op == B_SUB && uses[nd.a] == 1) {
-            const int16_t da = d.a, db = d.b;
-            d.kind = N_DEAD;
-            nd.kind = N_BIN;
-            nd.op = B_EXPSUB;
-            nd.a = da;
-            nd.b = db;
+            Node f = nd;
+            f.kind = N_BIN;
+            f.op = B_EXPSUB;
+            f.a = d.a;
+            f.b = d.b;
+            fuse(nd.a, n, f);
         }
     }
     p->finished = true;
@@ -596,7 +614,7 @@ struct Enc {
     int nr_limit;           // tile registers the program may use
     int next_reg;
     bool stale[NR_MAX];     // the register still holds an input that will be loaded again if something else takes the register
-    bool allow_mac;
+    int allow_mac;          // 0: none, 1: those that load no input behind a store it came before, 2: all
     int n_mac;              // products of two inputs that ride along
     int mac_of[MAX_NODES];  // the product of two inputs that this sum or difference takes in its record (I_MAC), or -1
     bool mac[MAX_NODES];    // such a product: not computed by itself
@@ -967,6 +985,17 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     if (!ctx || !prog || !len || (n_in > 0 && !in_shapes)) return dvm_set_error(DVM_E_ARGS, "dvm_encode: null argument");
     if (!prog->finished) return dvm_set_error(DVM_E_STATE, "dvm_encode: program not finished");
     if (n_in != prog->n_in) return dvm_set_error(DVM_E_ARGS, "dvm_encode: number of input shapes");
+    if (prog->n_late > 0) {         // first without the fusions that load an input behind a store it came before
+        dvm_prog in_order = *prog;
+        for (int i = 0; i < prog->n_late; ++i) {
+            in_order.nodes[prog->late[i].node] = prog->late[i].node_form;
+            in_order.nodes[prog->late[i].from] = prog->late[i].from_form;
+        }
+        in_order.n_late = 0;
+        const int st_order = dvm_encode(ctx, &in_order, in_shapes, n_in, out_layout, bytecode, cap, len, out_shapes);
+        if (st_order != DVM_E_UNSUPPORTED) return st_order;
+        t_detail[0] = 0;
+    }
     Enc E;
     E.p = prog;
     E.err = nullptr;
@@ -1350,11 +1379,12 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         }
     }
     // A product of two inputs whose only use is a sum or difference with a computed value rides along with that record: it needs
-    // no register of its own and RoPE fits four tile registers instead of six.
+    // no register of its own and RoPE fits four tile registers instead of six.  (Its inputs are then loaded at the sum: past the
+    // store of an output in between, which may be written over one of them, only where the program fits no other way.)
     E.next_reg = 0;
     E.n_mac = 0;
     for (int n = 0; n < NN; ++n) { E.mac_of[n] = -1; E.mac[n] = false; }
-    for (int n = 0; n < NN && E.allow_mac; ++n) {
+    for (int n = 0; n < NN && E.allow_mac != 0; ++n) {
         const Node &u = prog->nodes[n];
         if (u.kind != N_BIN || (u.op != B_ADD && u.op != B_SUB) || E.rows_class[n] || u.a == u.b || E.uses[n] == 0) continue;
         for (int side = 0; side < 2 && E.mac_of[n] < 0; ++side) {
@@ -1363,7 +1393,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             if (x.kind != N_BIN || x.op != B_MUL || E.rows_class[m] || E.uses[m] != 1 || E.mac[m]) continue;
             if (E.rows_class[other] || prog->nodes[other].kind == N_IN || E.mac[other]) continue;
             bool ok = true;
-            for (int o = 0; o < prog->n_out; ++o) ok &= prog->out_node[o] != m;
+            for (int o = 0; o < prog->n_out; ++o) ok &= prog->out_node[o] != m && (E.allow_mac == 2 || prog->out_node[o] < m || prog->out_node[o] >= n);
             for (int q : {(int)x.a, (int)x.b}) ok &= prog->nodes[q].kind == N_IN && !E.rows_class[q] && E.lds_of[q] < 0;
             if (!ok) continue;
             E.mac[m] = true;
@@ -1672,7 +1702,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     // again with as many pinned operands as keep the program within four tile registers
     E.nr_limit = ctx->max_nr < NR_MAX ? ctx->max_nr : NR_MAX;
     E.keep_sregs = false;
-    auto linearize_plain = [&](bool mac) {
+    auto linearize_plain = [&](int mac) {
         E.allow_mac = mac;
         E.err = nullptr;
         E.reload_inputs = false;
@@ -1683,7 +1713,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             linearize(0);
         }
     };
-    linearize_plain(false);
+    linearize_plain(0);
     // Products that ride along (I_MAC): taken where they let the program run with fewer tile registers, and where the launch is
     // more than the machine holds at once in the variant of six (64 x 16 elements per wave, three waves per SIMD).  Fewer
     // registers mean more resident waves (RoPE over 8111 x 32 heads 35 us with six registers, 30 with four); a smaller launch is
@@ -1699,10 +1729,11 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                         (prog->nodes[u.a].op == B_MUL || prog->nodes[u.b].op == B_MUL);
         }
         if (candidate) {
-            linearize_plain(true);
+            linearize_plain(1);
+            if (err0 && E.err) linearize_plain(2);
             const bool better = !E.err && (err0 || (reload0 && !E.reload_inputs) ||
                                            (reload0 == E.reload_inputs && (cls(E.nr_used) < cls(regs0) || (cls(E.nr_used) == cls(regs0) && E.n_ai < n0))));
-            if (!better) linearize_plain(false);
+            if (!better) linearize_plain(0);
         }
     }
     {
