@@ -476,7 +476,10 @@ extern "C" int dvm_prog_finish(dvm_prog *p) {
             Node f = nd;
             f.op = R_SUMSQ;
             f.a = sq.a;
-            fuse(nd.a, n, f);
+            const int from = nd.a;
+            fuse(from, n, f);
+            for (int m = n + 1; m < p->n_nodes; ++m)        // (a mean of squares divides by the extent of what was squared: the square has no shape now)
+                if (p->nodes[m].kind == N_BINI && p->nodes[m].immkind == IMM_INV_H && p->nodes[m].b == from) p->nodes[m].b = f.a;
         }
     }
     // peephole: exp(a - b), the difference used nowhere else -> one fused op (the softmax core)

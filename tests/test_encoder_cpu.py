@@ -477,3 +477,12 @@ def test_copies_in_flight_make_the_planner_keep_tiles_large():
     for bad in (0, -1, 5000):
         with pytest.raises(B.DvmError):
             shared.set_copies_in_flight(bad)
+
+
+def test_a_mean_of_squares_divides_by_the_row_length(ctx):
+    """The square is folded into the reduction and has no shape of its own then."""
+    for square in (("p", "square", ["a"], {}), ("p", "mul", ["a", "a"], {})):
+        desc = W._p("rms_by_hand", [("a", "f32")], [square, ("m", "mean", ["p"], {}), ("r", "sub", ["a", "m"], {})], [("r", "f32")])
+        for _ in range(2):
+            text = B.dvm_encode(ctx, B.Program(desc), [B.make_shape((64, 1024))]).disasm()
+            assert "red.sumsq s0 = (acc * 0.0009765625 + 0)" in text, text

@@ -251,3 +251,11 @@ def test_operand_pinned_along_the_fastest_outer_dim():
         _, code, _ = H.check_program(desc, {"z": z, "mask": mask}, ctx=inter)
         assert "again whenever the second outer index changes" in code.disasm()
         H.check_program(desc, {"z": z, "mask": mask})
+
+
+@pytest.mark.parametrize("shape", [(5, 7), (40, 1000), (3, 20001)])
+def test_mean_of_squares_written_out(shape):
+    say("x * rsqrt(mean(square(x)) + eps) by single ops", shape)
+    desc = W._p("rms_by_hand", [("x", "f32")], [("q", "square", ["x"], {}), ("m", "mean", ["q"], {}), ("e", "adds", ["m"], {"imm": 1e-6}), ("s", "rsqrt", ["e"], {}),
+                                                ("y", "mul", ["x", "s"], {})], [("y", "f32")])
+    H.check_program(desc, {"x": gen.randn(shape, 91, DEV)})
