@@ -1063,11 +1063,21 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     // ---- 2. classes ---------------------------------------------------------------------------
     E.row_axis = E.dom[R - 1] > 1;
     E.has_red = false;
+    bool taken[MAX_NODES];          // (a reduction that nothing takes is not evaluated: it does not make a row long)
+    for (int n = 0; n < NN; ++n) taken[n] = false;
+    for (int n = 0; n < NN; ++n) {
+        const Node &nd = prog->nodes[n];
+        if (nd.kind == N_IN || nd.kind == N_DEAD) continue;
+        taken[nd.a] = true;
+        if (nd.kind == N_BIN || nd.kind == N_SEL) taken[nd.b] = true;
+        if (nd.kind == N_SEL) taken[nd.c] = true;
+    }
+    for (int o = 0; o < prog->n_out; ++o) taken[prog->out_node[o]] = true;
     for (int n = 0; n < NN; ++n) {
         const Node &nd = prog->nodes[n];
         if (nd.kind == N_DEAD) continue;
         E.rows_class[n] = E.row_axis && E.shape[n][R - 1] == 1;
-        if (nd.kind == N_RED && !E.rows_class[nd.a] && E.row_axis) E.has_red = true;
+        if (nd.kind == N_RED && taken[n] && !E.rows_class[nd.a] && E.row_axis) E.has_red = true;
     }
     // Reductions along the penultimate axis.  The values computed from one (`post`) exist once per unit
     // (outer index, column tile) and are evaluated by an epilogue after the unit's last row; everything

@@ -486,3 +486,11 @@ def test_a_mean_of_squares_divides_by_the_row_length(ctx):
         for _ in range(2):
             text = B.dvm_encode(ctx, B.Program(desc), [B.make_shape((64, 1024))]).disasm()
             assert "red.sumsq s0 = (acc * 0.0009765625 + 0)" in text, text
+
+
+def test_a_reduction_nothing_takes_is_not_evaluated(ctx):
+    desc = W._p("unused", [("x", "f32"), ("b", "f32")], [("m", "sum", ["x"], {}), ("y", "add", ["x", "b"], {})], [("y", "f32")])
+    for cols in (100, 40000):
+        code = B.dvm_encode(ctx, B.Program(desc), [B.make_shape((30, cols)), B.make_shape((cols,))])
+        code.validate()
+        assert "red." not in code.disasm()
