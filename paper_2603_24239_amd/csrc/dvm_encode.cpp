@@ -1940,7 +1940,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         //     and a variant below 32 elements per lane only if no wider one takes the row.
         // Rows that fill a wave at 32 elements per lane take the widest variant that spreads them over 32 lanes or more while
         // rows are few: one latency per tile is all that counts then, and wider tiles mean fewer waves to exchange with.
-        if (ctx->dbg_k < (int)V) {
+        {
             int64_t best = -1;
             int prev_k = 0;
             const int64_t n_simd = 4 * (int64_t)ctx->n_cu;
@@ -1985,15 +1985,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         }
         if (ctx->dbg_k >= (int)V) {
             const int v = find_variant(ctx->dbg_k);
-            if (v >= 0 && cdiv(Cr, ctx->dbg_k / V) <= VARIANTS[v].max_threads) pick = v;
-        }
-        if (pick < 0) {                         // long rows: more elements per lane
-            for (int i = 0; i < 5 && pick < 0; ++i) {
-                const int K = ks[i];
-                if ((uint32_t)K < V) continue;
-                const int v = find_variant(K);
-                if (v >= 0 && cdiv(Cr, K / V) <= VARIANTS[v].max_threads) pick = v;
-            }
+            if (v >= 0 && cdiv(Cr, ctx->dbg_k / V) <= VARIANTS[v].max_threads) { pick = v; nv_cap = 0; }      // (else the planner's choice stands)
         }
         if (pick < 0 && (E.has_red || has_rows_output)) {
             // Rows longer than the widest tile: the row is cut into column tiles and the workgroup passes over it

@@ -494,3 +494,15 @@ def test_a_reduction_nothing_takes_is_not_evaluated(ctx):
         code = B.dvm_encode(ctx, B.Program(desc), [B.make_shape((30, cols)), B.make_shape((cols,))])
         code.validate()
         assert "red." not in code.disasm()
+
+
+def test_a_plan_override_that_cannot_be_honoured_leaves_the_planners_choice():
+    """64 elements per lane under the default bound of 32; 16 where a row needs more lanes than that variant's workgroup has."""
+    prog = B.Program(W.get_program("softmax_f32"))
+    for elems, shape in ((64, (64, 4096)), (64, (9, 300)), (16, (64, 32768))):
+        c, plain = B.Context(-1), B.Context(-1)
+        c.set_plan_override(elems, 0, 0)
+        assert B.dvm_encode(c, prog, [B.make_shape(shape)]).raw == B.dvm_encode(plain, prog, [B.make_shape(shape)]).raw
+    c = B.Context(-1)
+    c.set_plan_override(8, 0, 0)
+    assert B.dvm_encode(c, prog, [B.make_shape((64, 4096))]).info().variant_k == 8
