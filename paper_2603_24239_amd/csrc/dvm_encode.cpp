@@ -242,6 +242,7 @@ struct dvm_prog {
     struct Late { int16_t node, from; Node node_form, from_form; };    // (as they are before the fusion)
     int n_late;
     Late late[MAX_NODES];
+    bool products;          // some sum or difference of computed values has a product of two inputs for an operand (dvm_prog_finish)
 };
 
 extern "C" int dvm_prog_create(dvm_prog **out) {
@@ -496,6 +497,15 @@ extern "C" int dvm_prog_finish(dvm_prog *p) {
             fuse(nd.a, n, f);
         }
     }
+    p->products = false;
+    for (int n = 0; n < p->n_nodes && !p->products; ++n) {
+        const Node &u = p->nodes[n];
+        if (u.kind != N_BIN || (u.op != B_ADD && u.op != B_SUB) || p->nodes[u.a].kind != N_BIN || p->nodes[u.b].kind != N_BIN) continue;
+        for (int q : {(int)u.a, (int)u.b}) {
+            const Node &x = p->nodes[q];
+            p->products |= x.op == B_MUL && uses[q] == 1 && p->nodes[x.a].kind == N_IN && p->nodes[x.b].kind == N_IN;
+        }
+    }
     p->finished = true;
     return DVM_OK;
 }
@@ -618,7 +628,6 @@ struct Enc {
     int next_reg;
     bool stale[NR_MAX];     // the register still holds an input that will be loaded again if something else takes the register
     int allow_mac;          // 0: none, 1: those that load no input behind a store it came before, 2: all
-    int n_mac;              // products of two inputs that ride along
     int mac_of[MAX_NODES];  // the product of two inputs that this sum or difference takes in its record (I_MAC), or -1
     bool mac[MAX_NODES];    // such a product: not computed by itself
     bool reload_inputs;     // never keep an input tile in a register: load it again at every use
@@ -1395,7 +1404,6 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     // no register of its own and RoPE fits four tile registers instead of six.  (Its inputs are then loaded at the sum: past the
     // store of an output in between, which may be written over one of them, only where the program fits no other way.)
     E.next_reg = 0;
-    E.n_mac = 0;
     for (int n = 0; n < NN; ++n) { E.mac_of[n] = -1; E.mac[n] = false; }
     for (int n = 0; n < NN && E.allow_mac != 0; ++n) {
         const Node &u = prog->nodes[n];
@@ -1411,7 +1419,6 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             if (!ok) continue;
             E.mac[m] = true;
             E.mac_of[n] = m;
-            ++E.n_mac;
         }
     }
     // The other tile-invariant operands are loaded once per workgroup into a pinned tile register by a
@@ -1731,23 +1738,15 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     // more than the machine holds at once in the variant of six (64 x 16 elements per wave, three waves per SIMD).  Fewer
     // registers mean more resident waves (RoPE over 8111 x 32 heads 35 us with six registers, 30 with four); a smaller launch is
     // resident as a whole either way and keeps its records.
-    if (!E.has_cred && (double)E.nrows * (double)E.D0 * (double)ctx->copies > (double)ctx->n_cu * 4 * 3 * 64 * 16) {
+    if (prog->products && !E.has_cred && (double)E.nrows * (double)E.D0 * (double)ctx->copies > (double)ctx->n_cu * 4 * 3 * 64 * 16) {
         auto cls = [](int n) { return n <= 2 ? 2 : (n <= 4 ? 4 : (n <= 6 ? 6 : 8)); };
         const bool err0 = E.err != nullptr, reload0 = E.reload_inputs;
         const int regs0 = E.nr_used, n0 = E.n_ai;
-        bool candidate = false;
-        for (int n = 0; n < NN && !candidate; ++n) {
-            const Node &u = prog->nodes[n];
-            candidate = u.kind == N_BIN && (u.op == B_ADD || u.op == B_SUB) && prog->nodes[u.a].kind == N_BIN && prog->nodes[u.b].kind == N_BIN &&
-                        (prog->nodes[u.a].op == B_MUL || prog->nodes[u.b].op == B_MUL);
-        }
-        if (candidate) {
-            linearize_plain(1);
-            if (err0 && E.err) linearize_plain(2);
-            const bool better = !E.err && (err0 || (reload0 && !E.reload_inputs) ||
-                                           (reload0 == E.reload_inputs && (cls(E.nr_used) < cls(regs0) || (cls(E.nr_used) == cls(regs0) && E.n_ai < n0))));
-            if (!better) linearize_plain(0);
-        }
+        linearize_plain(1);
+        if (err0 && E.err) linearize_plain(2);
+        const bool better = !E.err && (err0 || (reload0 && !E.reload_inputs) ||
+                                       (reload0 == E.reload_inputs && (cls(E.nr_used) < cls(regs0) || (cls(E.nr_used) == cls(regs0) && E.n_ai < n0))));
+        if (!better) linearize_plain(0);
     }
     {
         int reg_cap = 4;
