@@ -1260,7 +1260,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
         // A segment over rows longer than a tile (SF_LONGROW) counts rows in M; the workgroup passes over a row once per
         // reduction and once more for the rest (lr_phase), each pass column tile after column tile (lr_c): a pass runs
         // the records from the start of the body up to its reduction, skipping the reductions whose value is final and
-        // every store; the last pass runs to the end and stores.  Every pass runs the other way round than the one before: the
+        // every store; the last pass runs to the end and stores.  Every pass over a row runs the other way round than the one
+        // before (each row's first from its start, so that a row's bits do not depend on where in the launch it stands): the
         // rows in flight together are about as large as the last-level cache, and a pass that starts where the one before
         // ended finds part of its row there (RMSNorm bf16 [671, 100000] 85.4 us with all passes from the start, 81.5 so; softmax fp32
         // [671, 100003] 145.6 and 142.4).
@@ -1802,7 +1803,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                 if (++lr_c == nct) {
                     lr_c = 0;
                     lr_back ^= 1;
-                    if (++lr_phase > n_red) { lr_phase = 0; tile += t_step; }
+                    if (++lr_phase > n_red) { lr_phase = 0; lr_back = 0; tile += t_step; }      // (nothing of the next row is cached)
                 }
             } else {
                 tile += t_step;
