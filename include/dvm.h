@@ -82,7 +82,8 @@ typedef enum dvm_opcode {
     /* Table 1's Sum / Max / Min in their general form: [M, size, N] reduced along `size`, the penultimate
      * axis (kept, extent 1).  A program holds reductions along one axis only; a value reduced this way may
      * feed further ops of its own shape ([M, 1, N] and tensors that broadcast into it), not full-size ones.
-     * The `size` rows are accumulated in order by one workgroup per (M index, column tile), in fp32. */
+     * The `size` rows are accumulated by one workgroup per (M index, column tile), in fp32 and in an order that is part of the
+     * bytecode: the same bytecode gives the same bits alone, in a stack and in a batched launch, whatever context runs it. */
     DVM_OP_CSUM = 72, DVM_OP_CMAX, DVM_OP_CMIN,
     /* compound ops, decomposed by dvm_prog_finish */
     DVM_OP_SOFTMAX = 80,    /* args = (z)                                    */
@@ -141,7 +142,7 @@ int  dvm_ctx_set_plan_override(dvm_ctx *ctx, int elems_per_lane, int rows_per_ti
  * (dvm_code_tensor: is_output = 2, min_bytes = what this program needs); the caller passes that much 256-byte
  * aligned device memory as the last entry of tensors[] (or calls dvm_run_static, whose array then serves, up to
  * DVM_STATIC_WORKSPACE_BYTES).  The result does not depend on the number of compute units running: S and the order
- * are fixed by the shapes.  Such bytecode cannot be a part of dvm_stack / dvm_stack_dependent or run batched. */
+ * are fixed by the bytecode.  Such bytecode cannot be a part of dvm_stack / dvm_stack_dependent or run batched. */
 int  dvm_ctx_set_workspace_limit(dvm_ctx *ctx, int64_t bytes);
 /* Tell the planner that `copies` copies of every program encoded with this context share a launch: the tensor sets
  * of a dvm_run_batched call, or like parts of a stack (Section 5.1).  In the cost model of Section 4.2,

@@ -134,10 +134,13 @@ enum : uint32_t {
     I_CACC,      // R[a] = first row of the unit ? ACC : R_b(R[a], ACC): accumulates a reduction along the
                  // penultimate axis (Table 1: Sum / Max / Min over [M, size, N] with N > 1)
     I_CCOMB,     // epilogue only: combine R[a] over the waves of the workgroup with R_b (each wave accumulated its
-                 // own share of the unit's rows), through LDS; afterwards only the first wave stores
+                 // own share of the unit's rows), through LDS; afterwards only the first wave stores.  word1 = 0: in the
+                 // order of the waves; 1: in pairs (waves 0 and 1, 2 and 3, ..., then 0 and 2, ..., then 0 and 4, ...)
     I_CSTREAM,   // R[a] = R_b over the rows of the unit that fall to this wave, of a tensor (memory record with three
                  // strides): the whole per-row part of a segment that only reduces input tensors along the
-                 // penultimate axis (SF_CSTREAM), with several rows in flight per wave instead of one per step
+                 // penultimate axis (SF_CSTREAM), with several rows in flight per wave instead of one per step.  Bits 24-31
+                 // of word1: the number q of partial results of a wave (0: one); its k-th row belongs to partial k mod q,
+                 // and the partials are combined in their order
     I_LDSCOPY,   // prologue only: copy a row-invariant tensor (every outer stride 0) into the workgroup's LDS, as it
                  // lies in memory, zero-filled up to the tile width.  word1 = tensor | dtype << 8, word2 = byte offset
                  // of the image in LDS, word3 = its size in bytes (a multiple of 16); b != 0: the workgroup

@@ -8,8 +8,9 @@
 //   - a wave spreads over 64 / L rows by L lanes of 16 bytes (L = 64 down to 8: a row piece is never below a 128-byte
 //     line), L being the widest that leaves enough workgroups,
 //   - every lane keeps eight loads in flight, the next one issued as one is used,
-//   - rows are combined in row order within a lane, then over the lanes that share a column (fixed tree), then over
-//     the waves in wave order through LDS: the result depends on the shapes and the number of compute units only.
+//   - L lanes hold one partial result: the segment has `waves` * `partials` of them, number w + j * waves being the j-th partial of
+//     wave w in the interpreter's terms.  Partial p adds the rows p, p + waves * partials, .. in order; through LDS the partials of a
+//     wave are combined in their order, then the waves in pairs.  The order is the segment's, whatever L is.
 // Measured (rotating inputs, whole call): bias gradient bf16 [8192, 4096] in two launches 46 -> 25 us (the launches 46 -> 20 us; the
 // rest is host time), fp32 [9238, 8192] in one (no divisor to split by) 317 -> 62 us, [38, 535, 2048] 54 -> 32 us (5.3 TB/s).
 #include <hip/hip_runtime.h>
@@ -61,24 +62,24 @@ template <int BF16, uint32_t R>
 __global__ void __launch_bounds__(1024) dvm_colreduce(const dvm_colreduce_args a) {
     constexpr int E = BF16 ? 8 : 4;         // columns of a 16-byte piece
     constexpr int ES = BF16 ? 2 : 4;
-    extern __shared__ float lds[];          // [wave][column of the tile]
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, waves = blockDim.x >> 6;
-    const uint32_t L = 1u << a.log2_lanes, rows_per_wave = 64u >> a.log2_lanes;
+    extern __shared__ float lds[];          // [partial result][column of the tile]
+    const uint32_t tid = threadIdx.x;
+    const uint32_t L = 1u << a.log2_lanes, slot = tid & (L - 1u);
+    const uint32_t step = a.waves * a.partials, first = tid >> a.log2_lanes;    // this lane's partial result (step and above: none)
     const uint32_t outer = blockIdx.x / a.col_tiles, tile = blockIdx.x - outer * a.col_tiles;
     const uint32_t o2 = a.d2 != 0 ? outer % a.d2 : outer, o3 = a.d2 != 0 ? outer / a.d2 : 0u;
     // The row's last piece slides back to end with the row (the caller made sure that it has a whole one).
-    const uint64_t c0 = ((uint64_t)tile * L + (lane & (L - 1u))) * E;
+    const uint64_t c0 = ((uint64_t)tile * L + slot) * E;
     const uint64_t cmax = a.cols - E;
     const uint64_t c = c0 < cmax ? c0 : cmax;
-    const uint32_t first = wave * rows_per_wave + (lane >> a.log2_lanes), step = waves * rows_per_wave;
-    const uint32_t n = first < a.size ? (a.size - first + step - 1) / step : 0u;        // rows of this lane
+    const uint32_t n = first < step && first < a.size ? (a.size - first + step - 1) / step : 0u;        // rows of this lane
     const char *p = (const char *)a.in + ((int64_t)o2 * a.in_s2 + (int64_t)o3 * a.in_s3 + (int64_t)c) * ES;
     const int64_t row = a.in_s1 * ES;
     float acc[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] = ident<R>();
     // (a lane that has run out of rows reads its first row again, or row 0, and takes nothing from it)
-    const uint32_t r0 = first < a.size ? first : 0u;
+    const uint32_t r0 = n != 0 ? first : 0u;
     u32x4 buf[U];
     const uint32_t n_max = (a.size + step - 1) / step;      // the same for every lane of the launch
 #pragma unroll
@@ -99,24 +100,37 @@ __global__ void __launch_bounds__(1024) dvm_colreduce(const dvm_colreduce_args a
             }
         }
     }
-    // the lanes of the wave that hold the same columns
-    for (uint32_t m = L; m < 64u; m <<= 1) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[e] = comb<R>(acc[e], __shfl_xor(acc[e], (int)m));
-    }
     const uint32_t width = L * E;
-    if ((lane >> a.log2_lanes) == 0) {
+    if (first < step) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) lds[wave * width + lane * E + e] = acc[e];
+        for (int e = 0; e < E; ++e) lds[first * width + slot * E + e] = acc[e];
     }
     __syncthreads();
+    // partials of a wave in their order (all waves side by side), then the waves in pairs
+    if (a.partials > 1) {
+        const uint32_t all = a.waves * width;
+        for (uint32_t j = tid; j < all; j += blockDim.x) {
+            float v = lds[j];
+#pragma unroll 4
+            for (uint32_t k = 1; k < a.partials; ++k) v = comb<R>(v, lds[k * all + j]);
+            lds[j] = v;
+        }
+        __syncthreads();
+    }
     for (uint32_t j = tid; j < width; j += blockDim.x) {
         const uint64_t col = (uint64_t)tile * width + j;
         if (col >= a.cols) break;
         const uint64_t piece = col - j % E;
         const uint32_t at = j + (piece > cmax ? (uint32_t)(piece - cmax) : 0u);     // (where the slid piece holds this column)
-        float v = lds[at];
-        for (uint32_t w = 1; w < waves; ++w) v = comb<R>(v, lds[w * width + at]);
+        float x[16];                // (a wave the segment does not have: the neutral value)
+#pragma unroll
+        for (int w = 0; w < 16; ++w) x[w] = (uint32_t)w < a.waves ? lds[(uint32_t)w * width + at] : ident<R>();
+#pragma unroll
+        for (int s = 1; s < 16; s *= 2) {
+#pragma unroll
+            for (int w = 0; w < 16; w += 2 * s) x[w] = comb<R>(x[w], x[w + s]);
+        }
+        const float v = x[0];
         const int64_t off = (int64_t)o2 * a.out_s2 + (int64_t)o3 * a.out_s3 + (int64_t)col;
         if (a.out_bf16) {
             const __bf16 h = (__bf16)v;
@@ -130,7 +144,7 @@ __global__ void __launch_bounds__(1024) dvm_colreduce(const dvm_colreduce_args a
 }  // namespace
 
 extern "C" int dvm_colreduce_launch(const dvm_colreduce_args *a, unsigned grid, unsigned block, void *stream) {
-    const unsigned lds = (block / 64u) * ((1u << a->log2_lanes) * (a->in_bf16 ? 8u : 4u)) * 4u;
+    const unsigned lds = a->waves * a->partials * ((1u << a->log2_lanes) * (a->in_bf16 ? 8u : 4u)) * 4u;
     const hipStream_t s = (hipStream_t)stream;
 #define GO(B, R) hipLaunchKernelGGL((dvm_colreduce<B, R>), dim3(grid), dim3(block), lds, s, *a)
     if (a->in_bf16) {

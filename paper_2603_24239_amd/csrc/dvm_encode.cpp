@@ -934,6 +934,9 @@ static int encode_split_reduction(const dvm_ctx *ctx, const dvm_prog *prog, cons
         p2.out_node[o] = map[prog->out_node[o]];
         p2.out_dtype[o] = prog->out_dtype[o];
     }
+    // (a reduction of an input with nothing behind it: both parts are plain ones, whose kernel takes workgroups of its own, and the
+    // second has few rows to spread)
+    if (ctx->dbg_rp == 0 && nn == 2 && p2.nodes[1].kind == N_CRED && prog->nodes[prog->nodes[c].a].kind == N_IN) sub.dbg_rp = 8;
     st = dvm_encode(&sub, &p2, sh2, p2.n_in, out_layout, code2, sizeof(code2), &len2, out_shapes);
     if (st != DVM_OK) return st;
     // ---- join: stack the two, then fold their tensor tables into [inputs, outputs, workspace]
@@ -1873,6 +1876,15 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     for (int t = prog->n_in; t < E.n_acc; ++t) has_rows_output |= E.acc[t].rows;
     if (has_rows_output) column_mode = false;
     const int64_t cred_outer = E.has_cred && E.Dg[1] > 0 ? E.nrows / E.Dg[1] : 0;
+    uint32_t partials = 1;          // partial results per wave of a plain reduction along the penultimate axis
+    uint32_t pairwise = 0;          // 1: its waves are combined in pairs
+    bool plain_cred = E.has_cred && prog->n_out == 1 && E.cred_real[prog->out_node[0]], plain_bf16 = false;
+    if (plain_cred) {
+        for (int n = 0; n < NN; ++n) plain_cred &= !E.cred_real[n] || n == prog->out_node[0];
+        const Node &in = prog->nodes[prog->nodes[prog->out_node[0]].a];
+        plain_cred &= in.kind == N_IN;
+        plain_bf16 = plain_cred && E.acc[in.input].dtype == DVM_BF16;
+    }
     if (E.has_cred) {
         // Reduction along the penultimate axis: a unit of work is (outer index, column tile); one wave
         // walks the `size` rows of a unit and accumulates in a tile register.  The tile is as wide as
@@ -1902,6 +1914,26 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             const int64_t units = cred_outer * cdiv(E.D0 > 0 ? E.D0 : 1, 64 * vr.K);
             const int64_t want = cdiv((int64_t)ctx->n_cu * slots_per_cu(vr, 64), (units > 0 ? units : 1) * copies);
             RP = (uint32_t)(want < 1 ? 1 : (want > rp_max ? rp_max : want));
+            // A plain reduction, which as a launch of its own runs in the kernel for those (dvm_colreduce.hip), keeps as many partial
+            // results as that kernel has use for: as many waves of 64 / (lanes on a row) rows each as fill the machine without
+            // leaving a lane fewer than eight rows, but four waves and sixteen at most -- and with P of them over n rows
+            // P * P >= n / 2 up to sixteen, because the error grows with the chains of n / P additions.  They are fixed here, so that
+            // the sums have the same bits wherever the bytecode runs.
+            if (E.cstream && plain_cred && vr.K <= 8) {
+                pairwise = 1;
+                const int64_t size = E.Dg[1], piece = plain_bf16 ? 8 : 4, outer = cred_outer * copies, cols = E.D0 > 0 ? E.D0 : 1;
+                int lg = 6;
+                while (lg > 3 && outer * cdiv(cols, piece << lg) < 2 * (int64_t)ctx->n_cu) --lg;
+                int64_t waves = 4;
+                while (waves < 16 && outer * cdiv(cols, piece << lg) * waves < 16 * (int64_t)ctx->n_cu && size > 8 * waves * (64 >> lg)) waves *= 2;
+                int64_t want_partials = waves * (64 >> lg);
+                while (ctx->dbg_rp == 0 && want_partials < 16 && 2 * want_partials * want_partials < size) want_partials *= 2;
+                if (RP > want_partials) RP = (uint32_t)want_partials;
+                if (pow2ceil(RP) <= rp_max) RP = pow2ceil(RP);
+                if (ctx->dbg_rp > 0 && ctx->dbg_rp <= rp_max) RP = (uint32_t)ctx->dbg_rp;
+                partials = (uint32_t)cdiv(want_partials, RP);       // (more than one where units are few)
+                while (partials > 1 && (partials > cdiv(size, RP) || (((int64_t)RP * partials) << lg) > 1024)) --partials;
+            }
             if (ctx->dbg_rp > 0 && ctx->dbg_rp <= rp_max) RP = (uint32_t)ctx->dbg_rp;
         }
         nvec = (uint32_t)(VARIANTS[vi].K / V);
@@ -2205,7 +2237,7 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                 *b++ = w0(I_CSTREAM, LEN_VLOAD, x.a, x.b);
                 bool once = true;       // read exactly once: no outer dim is broadcast
                 for (int g = 1; g < ng; ++g) once &= !(E.Dg[g] > 1 && A.s[g] == 0);
-                *b++ = (uint32_t)x.tensor | ((uint32_t)A.dtype << 8) | ((once ? MF_STREAM : 0u) << 16);
+                *b++ = (uint32_t)x.tensor | ((uint32_t)A.dtype << 8) | ((once ? MF_STREAM : 0u) << 16) | ((partials > 1 ? partials : 0u) << 24);
                 put_i64(A.s[1]); put_i64(A.s[2]); put_i64(A.s[3]);
                 break;
             }
@@ -2262,6 +2294,12 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
                 b[1] = x.kind;                  // post unary op (U_NONE: none)
                 b[2] = bits_f32(x.imm);         // scale
                 b[3] = bits_f32(x.imm2);        // shift
+                b += LEN_REC;
+                break;
+            case I_CCOMB:
+                imask |= 1u << I_CCOMB;
+                b[0] = w0(I_CCOMB, LEN_REC, x.a, x.b);
+                b[1] = pairwise;
                 b += LEN_REC;
                 break;
             default:
@@ -2500,15 +2538,16 @@ extern "C" int dvm_validate(const void *bytecode, size_t len) {
                     if (sh[S_INNER] == 0 || !(sh[S_FLAGS] & SF_CSTREAM) || pc >= at + SH_WORDS + sh[S_EPILOG])
                         return bad("streaming reduction outside the per-row part of a segment marked for it");
                     const uint32_t w1 = w[pc + 1];
+                    if ((w1 >> 24) * RP > 128) return bad("partial results of a streaming reduction");
                     if ((w1 & 0xFF) >= nt) return bad("tensor index");
                     const uint32_t info = w[PH_WORDS_N + (tbase + (w1 & 0xFF)) * TT_WORDS + TT_INFO];
                     if (((w1 >> 8) & 0xFF) != (info & 0xFF)) return bad("dtype differs from the tensor table");
                     if (((w1 >> 8) & 0xFF) == DVM_BF16 && V != 8) return bad("bf16 tile with 4-element chunks");
-                    if ((w1 >> 16) & ~MF_STREAM) return bad("memory flags");
+                    if (((w1 >> 16) & 0xFF) & ~MF_STREAM) return bad("memory flags");
                     break;
                 }
                 case I_CCOMB:
-                    if (l != LEN_REC || !reg_ok(a, vr) || bb > R_MIN) return bad("combine");
+                    if (l != LEN_REC || !reg_ok(a, vr) || bb > R_MIN || w[pc + 1] > 1) return bad("combine");
                     if (sh[S_INNER] == 0 || pc < at + SH_WORDS + sh[S_EPILOG]) return bad("combine outside the epilogue of a reducing segment");
                     break;
                 case I_LDSCOPY: {
@@ -3013,10 +3052,14 @@ extern "C" int dvm_disasm(const void *bytecode, size_t len, char *txt, size_t ca
                     break;
                 case I_SEL: o.put("  %04zu select  acc = acc ? r%u : r%u\n", pc - at - SH_WORDS, a, b); break;
                 case I_CSTREAM:
-                    o.put("  %04zu stream.%-3s r%u = %s over this wave's rows of t%u strides=[%lld,%lld,%lld]%s\n", pc - at - SH_WORDS, RED_NAMES[b], a,
+                    o.put("  %04zu stream.%-3s r%u = %s over this wave's rows of t%u strides=[%lld,%lld,%lld]%s", pc - at - SH_WORDS, RED_NAMES[b], a,
                           RED_NAMES[b], w[pc + 1] & 0xFF, i64(pc + 2), i64(pc + 4), i64(pc + 6), ((w[pc + 1] >> 16) & MF_STREAM) ? "  [read once]" : "");
+                    if (w[pc + 1] >> 24) o.put("  [%u partial results]", w[pc + 1] >> 24);
+                    o.put("\n");
                     break;
-                case I_CCOMB: o.put("  %04zu comb.%-3s r%u = %s of r%u over the workgroup's waves\n", pc - at - SH_WORDS, RED_NAMES[b], a, RED_NAMES[b], a); break;
+                case I_CCOMB:
+                    o.put("  %04zu comb.%-3s r%u = %s of r%u over the workgroup's waves%s\n", pc - at - SH_WORDS, RED_NAMES[b], a, RED_NAMES[b], a, w[pc + 1] ? " in pairs" : "");
+                    break;
                 case I_CACC: o.put("  %04zu acc.%-4s r%u = first row ? acc : %s(r%u, acc)\n", pc - at - SH_WORDS, RED_NAMES[b], a, RED_NAMES[b], a); break;
                 case I_FMA: {
                     char sc[8] = "", ad[8] = "";

@@ -26,6 +26,7 @@ typedef struct dvm_colreduce_args {
     uint32_t size;                  // rows reduced
     uint32_t d2;                    // extent of the first outer dim (0: the only one)
     uint32_t col_tiles, log2_lanes; // column tiles of a row; lanes (of 16 bytes) that share a row
+    uint32_t waves, partials;       // the segment's waves per unit and partial results per wave: they fix the order of the rows
     uint32_t op;                    // R_SUM, R_MAX or R_MIN
     uint32_t in_bf16, out_bf16, once;
 } dvm_colreduce_args;

@@ -1603,26 +1603,34 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                         const uint32_t inner_n = sh[S_INNER];
                         const float ident = b == R_SUM ? 0.0f : (b == R_MAX ? -__builtin_inff() : __builtin_inff());
                         constexpr int U = K <= 4 ? 6 : 4;       // (as many as the registers hold)
-                        DVM_WITH_R(a, rr, {
-                            sfor<K>([&]<int I>() LI { TV(rr, I) = ident; });
-                            if (wave < RP) {
-                                for (uint32_t r = wave; r < inner_n; r += RP * U) {
-                                    Raw<K> raw[U];
-                                    sfor<U>([&]<int J>() LI {
-                                        const uint32_t ru = r + (uint32_t)J * RP;
-                                        const uint32_t rc = ru < inner_n ? ru : r;      // past the end: read row r again, unused
-                                        request_staged_dispatch<K>(raw[J], dt, V, nt, base + (off0 + (int64_t)rc * st1) * es, g);
-                                    });
-                                    sfor<U>([&]<int J>() LI {
-                                        if (r + (uint32_t)J * RP < inner_n) {
-                                            if (b == R_SUM) combine_staged_dispatch<K, B_ADD>(rr, raw[J], dt, V, g);
-                                            else if (b == R_MAX) combine_staged_dispatch<K, B_MAX>(rr, raw[J], dt, V, g);
-                                            else combine_staged_dispatch<K, B_MIN>(rr, raw[J], dt, V, g);
-                                        }
-                                    });
-                                }
+                        // (the order of the rows is the one dvm_colreduce takes for the same segment as a launch of its own)
+                        const uint32_t q = (w1 >> 24) > 1 ? w1 >> 24 : 1u, step = RP * q;
+                        Tile<K> sum;
+                        sfor<K>([&]<int I>() LI { TV(sum, I) = ident; });
+                        for (uint32_t first_r = wave, j = 0; wave < RP && j < q; ++j, first_r += RP) {
+                            Tile<K> part;
+                            sfor<K>([&]<int I>() LI { TV(part, I) = ident; });
+                            for (uint32_t r = first_r; r < inner_n; r += step * U) {
+                                Raw<K> raw[U];
+                                sfor<U>([&]<int J>() LI {
+                                    const uint32_t ru = r + (uint32_t)J * step;
+                                    const uint32_t rc = ru < inner_n ? ru : r;      // past the end: read row r again, unused
+                                    request_staged_dispatch<K>(raw[J], dt, V, nt, base + (off0 + (int64_t)rc * st1) * es, g);
+                                });
+                                sfor<U>([&]<int J>() LI {
+                                    if (r + (uint32_t)J * step < inner_n) {
+                                        if (b == R_SUM) combine_staged_dispatch<K, B_ADD>(part, raw[J], dt, V, g);
+                                        else if (b == R_MAX) combine_staged_dispatch<K, B_MAX>(part, raw[J], dt, V, g);
+                                        else combine_staged_dispatch<K, B_MIN>(part, raw[J], dt, V, g);
+                                    }
+                                });
                             }
-                        })
+                            if (j == 0) sum = part;
+                            else if (b == R_SUM) tile_bin<K, B_ADD>(sum, part);
+                            else if (b == R_MAX) tile_bin<K, B_MAX>(sum, part);
+                            else tile_bin<K, B_MIN>(sum, part);
+                        }
+                        DVM_WITH_R(a, rr, rr = sum)
                     }
                         break;
                     case I_CCOMB:       // every wave ends up with the combination, taken in wave order; the first wave stores
@@ -1635,8 +1643,21 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                                     mine[0] = TV(rr, 4 * Q); mine[1] = TV(rr, 4 * Q + 1); mine[2] = TV(rr, 4 * Q + 2); mine[3] = TV(rr, 4 * Q + 3);
                                 }
                                 __syncthreads();
+                                // (in pairs: a wave writes its own slot in the steps in which no other wave reads it)
+                                if (cw1 != 0) {
+                                    for (uint32_t s = 1; s < RP; s <<= 1) {
+                                        if (wave < RP && (wave & (2u * s - 1u)) == 0 && wave + s < RP) {
+                                            float *mine = &comb_lds[(wave * 64u + lane) * 4u];
+                                            const float *p = mine + s * 256u;
+                                            if (b == R_SUM) { mine[0] += p[0]; mine[1] += p[1]; mine[2] += p[2]; mine[3] += p[3]; }
+                                            else if (b == R_MAX) { mine[0] = f_maxp(mine[0], p[0]); mine[1] = f_maxp(mine[1], p[1]); mine[2] = f_maxp(mine[2], p[2]); mine[3] = f_maxp(mine[3], p[3]); }
+                                            else { mine[0] = f_minp(mine[0], p[0]); mine[1] = f_minp(mine[1], p[1]); mine[2] = f_minp(mine[2], p[2]); mine[3] = f_minp(mine[3], p[3]); }
+                                        }
+                                        __syncthreads();
+                                    }
+                                }
                                 float c0 = comb_lds[lane * 4u], c1 = comb_lds[lane * 4u + 1], c2 = comb_lds[lane * 4u + 2], c3 = comb_lds[lane * 4u + 3];
-                                for (uint32_t o = 1; o < RP; ++o) {
+                                for (uint32_t o = 1; cw1 == 0 && o < RP; ++o) {
                                     const float *p = &comb_lds[(o * 64u + lane) * 4u];
                                     if (b == R_SUM) { c0 += p[0]; c1 += p[1]; c2 += p[2]; c3 += p[3]; }
                                     else if (b == R_MAX) { c0 = f_maxp(c0, p[0]); c1 = f_maxp(c1, p[1]); c2 = f_maxp(c2, p[2]); c3 = f_maxp(c3, p[3]); }
@@ -2083,15 +2104,17 @@ int check_tensor_set(const uint32_t *w, const uint8_t *seg_of, void *const *tens
 }
 
 // A segment that is a plain reduction along the penultimate axis -- one streaming record, the combination of the waves, the
-// store, over rows of one 16-byte piece at least -- as the arguments of the kernel for those.  Grid and block are chosen here:
-// as many lanes on a row as leave two workgroups per compute unit (down to a 128-byte line), and as many waves as fill
-// the machine without leaving a lane fewer than eight rows (but four waves, and sixteen at most).
+// store, over rows of one 16-byte piece at least -- as the arguments of the kernel for those.  Which rows are added to which
+// partial result, and in which order those are combined, is the segment's (its waves and their partial results): the bits are
+// the interpreter's for the same segment in a stack or a batched launch.  Only the lanes that share a row are chosen here: as many
+// as leave two workgroups per compute unit (down to a 128-byte line) and a workgroup of 1024 threads at most, 256 where a lane has
+// few rows ([256, 64, 1024] fp32 in 8 partials 17.6 us in workgroups of 512 threads, 11.8 in 256; over longer columns no difference).
 bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *tensors, dvm_colreduce_args *a, uint32_t *grid, uint32_t *block) {
     if (!(sh[S_FLAGS] & SF_CSTREAM) || sh[S_PROLOG] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID))) return false;
     const uint32_t *r = sh + SH_WORDS;
     if ((r[0] & 0xFF) != I_CSTREAM || sh[S_EPILOG] != LEN_VLOAD) return false;
     const uint32_t *cc = r + LEN_VLOAD, *st = cc + LEN_REC;
-    if (sh[S_CODESIZE] < LEN_VLOAD + LEN_REC + LEN_LOAD || (cc[0] & 0xFF) != I_CCOMB || (cc[0] >> 16) != (r[0] >> 16)) return false;
+    if (sh[S_CODESIZE] < LEN_VLOAD + LEN_REC + LEN_LOAD || (cc[0] & 0xFF) != I_CCOMB || cc[1] == 0 || (cc[0] >> 16) != (r[0] >> 16)) return false;
     const uint32_t sop = st[0] & 0xFF;
     if (sop != I_STORE && sop != I_VSTORE) return false;
     if (sh[S_CODESIZE] != LEN_VLOAD + LEN_REC + ((st[0] >> 8) & 0xFF) || ((st[0] >> 16) & 0xFF) != ((r[0] >> 16) & 0xFF) || (st[0] >> 24) != 0) return false;
@@ -2116,15 +2139,17 @@ bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *ten
     const uint64_t outer = sh[S_NROWS] / sh[S_INNER];
     uint32_t lg = 6;
     auto tiles = [&](uint32_t l) { return (D0 + ((uint64_t)piece << l) - 1) / ((uint64_t)piece << l); };
-    while (lg > 3 && outer * tiles(lg) < 2ull * (uint64_t)n_cu) --lg;
+    a->waves = sh[S_RP] & 0xFFFF;
+    a->partials = (r[1] >> 24) > 1 ? r[1] >> 24 : 1u;
+    const uint32_t parts = a->waves * a->partials;
+    while (lg > 3 && (outer * tiles(lg) < 2ull * (uint64_t)n_cu || parts << lg > 1024u)) --lg;
+    while (lg > 4 && a->size < 32u * parts && parts << lg > 256u) --lg;
     const uint64_t units = outer * tiles(lg);
-    if (units >= (1ull << 31)) return false;
-    uint32_t waves = 4;
-    while (waves < 16 && units * waves < 16ull * (uint64_t)n_cu && (uint64_t)a->size > 8ull * waves * (64u >> lg)) waves *= 2;
+    if (units >= (1ull << 31) || parts << lg > 1024u) return false;
     a->log2_lanes = lg;
     a->col_tiles = (uint32_t)tiles(lg);
     *grid = (uint32_t)units;
-    *block = waves * 64u;
+    *block = ((parts << lg) + 63u) / 64u * 64u;
     return true;
 }
 
