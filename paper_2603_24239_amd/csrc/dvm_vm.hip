@@ -2109,7 +2109,9 @@ int check_tensor_set(const uint32_t *w, const uint8_t *seg_of, void *const *tens
 // the interpreter's for the same segment in a stack or a batched launch.  Only the lanes that share a row are chosen here: as many
 // as leave two workgroups per compute unit (down to a 128-byte line) and a workgroup of 1024 threads at most, 256 where a lane has
 // few rows ([256, 64, 1024] fp32 in 8 partials 17.6 us in workgroups of 512 threads, 11.8 in 256; over longer columns no difference).
-bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *tensors, dvm_colreduce_args *a, uint32_t *grid, uint32_t *block) {
+// An output written over a row of the input stays with the interpreter where a row's last piece slides back into columns that another
+// workgroup stores.
+bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *tensors, bool aliased, dvm_colreduce_args *a, uint32_t *grid, uint32_t *block) {
     if (!(sh[S_FLAGS] & SF_CSTREAM) || sh[S_PROLOG] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID))) return false;
     const uint32_t *r = sh + SH_WORDS;
     if ((r[0] & 0xFF) != I_CSTREAM || sh[S_EPILOG] != LEN_VLOAD) return false;
@@ -2146,6 +2148,7 @@ bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *ten
     while (lg > 4 && a->size < 32u * parts && parts << lg > 256u) --lg;
     const uint64_t units = outer * tiles(lg);
     if (units >= (1ull << 31) || parts << lg > 1024u) return false;
+    if (aliased && D0 % piece != 0 && ((D0 / piece) & ((1u << lg) - 1u)) == 0) return false;
     a->log2_lanes = lg;
     a->col_tiles = (uint32_t)tiles(lg);
     *grid = (uint32_t)units;
@@ -2354,7 +2357,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         uint32_t cgrid = 0, cblock = 0;
         const uint32_t *first_sh = w + segs_off;
         for (uint32_t s = 0; s < first; ++s) first_sh += first_sh[S_WORDS];
-        if (cred && end == first + 1 && !batch && plain_colreduce(ctx, first_sh, ka.tensors, &ca, &cgrid, &cblock))
+        if (cred && end == first + 1 && !batch && plain_colreduce(ctx, first_sh, ka.tensors, ka.aliased != 0, &ca, &cgrid, &cblock))
             e = (hipError_t)dvm_colreduce_launch(&ca, cgrid, cblock, hip_stream);
         else
             e = (hipError_t)launch(grid, block, lds_bytes, hip_stream, &ka, nullptr);

@@ -59,3 +59,15 @@ def test_strided_operands_and_special_values(dt):
     x[1, 150, 12] = float("-inf")
     for op in ("csum", "cmax", "cmin"):
         check(op, dt, "f32", x)
+
+
+@pytest.mark.parametrize("shape", [(300, 20, 257), (300, 20, 256), (40, 300, 129), (1, 900, 33), (2, 64, 515)])
+def test_written_over_the_first_row_of_the_input(shape):
+    """Also where the row's last 16-byte piece slides back into the column tile before (257 fp32 columns in tiles of 256)."""
+    for dt in ("f32", "bf16"):
+        print(f"[case] column sum over row 0 of its input {dt} {shape}", flush=True)
+        x = gen.randn(shape, 54, DEV, dt)
+        ref, _ = H.run_vm(one("csum", dt, dt), {"x": x})
+        mine = x.clone()
+        H.run_vm(one("csum", dt, dt), {"x": mine}, outputs={"s": mine[:, :1, :]})
+        assert torch.equal(mine[:, :1, :], ref["s"]) and torch.equal(mine[:, 1:, :], x[:, 1:, :])
