@@ -2147,7 +2147,7 @@ bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *ten
     while (lg > 3 && (outer * tiles(lg) < 2ull * (uint64_t)n_cu || parts << lg > 1024u)) --lg;
     while (lg > 4 && a->size < 32u * parts && parts << lg > 256u) --lg;
     const uint64_t units = outer * tiles(lg);
-    if (units >= (1ull << 31) || parts << lg > 1024u) return false;
+    if (units == 0 || units >= (1ull << 31) || parts << lg > 1024u) return false;
     if (aliased && D0 % piece != 0 && ((D0 / piece) & ((1u << lg) - 1u)) == 0) return false;
     a->log2_lanes = lg;
     a->col_tiles = (uint32_t)tiles(lg);

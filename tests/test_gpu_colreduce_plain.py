@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2603_24239_amd import binding as B
 from workloads import gen
 from workloads.programs import _p
 
@@ -71,3 +72,19 @@ def test_written_over_the_first_row_of_the_input(shape):
         mine = x.clone()
         H.run_vm(one("csum", dt, dt), {"x": mine}, outputs={"s": mine[:, :1, :]})
         assert torch.equal(mine[:, :1, :], ref["s"]) and torch.equal(mine[:, 1:, :], x[:, 1:, :])
+
+
+def test_bytecode_without_outer_indices():
+    """Valid bytecode over [0, 7, 64] that keeps the row length: nothing to do, and no launch of an empty grid."""
+    print("[case] plain column reduction of no units", flush=True)
+    x, s = gen.randn((3, 7, 64), 55, DEV), torch.full((3, 1, 64), -7.0, device=DEV)
+    code = B.encode_for(H.gpu_ctx(), H.program(one("csum", "f32", "f32")), [x])
+    w = np.frombuffer(code.raw, dtype=np.uint32).copy()
+    seg = 8 + 3 * 2                     # behind the program header and two tensor entries
+    assert w[seg + 9] == 21 and w[seg + 26] == 7
+    w[seg + 2] = w[seg + 9] = 0         # tiles, rows
+    empty = B.Bytecode(w.tobytes(), code.out_shapes)
+    empty.validate()
+    B.run_on(H.gpu_ctx(), empty, [x, s])
+    torch.cuda.synchronize()
+    assert bool((s == -7.0).all())
