@@ -172,7 +172,9 @@ int  dvm_prog_create(dvm_prog **out);
 /* Declare the next input; *value_id receives its SSA id.  Inputs are numbered in declaration order
  * and that is their order in `in_shapes[]` and at the front of `tensors[]`. */
 int  dvm_prog_input(dvm_prog *p, int dtype, int *value_id);
-/* Append an op.  `arg_ids` are SSA ids of earlier values, `imm` the immediates the opcode takes. */
+/* Append an op.  `arg_ids` are SSA ids of earlier values, `imm` the immediates the opcode takes.  A multiplication directly
+ * followed by an addition may be evaluated with one rounding instead of two, where the plan (and so the register limits and the
+ * size of the launch) provides for it; a product that is subtracted, or subtracted from, is rounded first. */
 int  dvm_prog_op(dvm_prog *p, int opcode, const int *arg_ids, int n_args,
                  const double *imm, int n_imm, int *value_id);
 /* Mark a value as the next output with storage dtype `dtype`.  Outputs follow the inputs in

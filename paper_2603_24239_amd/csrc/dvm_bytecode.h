@@ -149,7 +149,8 @@ enum : uint32_t {
                  // a = La | Lb << 4 as image numbers (LFMA_NONE: absent), b = bit 0: La is bf16, bit 1: Lb is bf16;
                  // word1 = 0 or S index + 1, word2 / word3 = byte offsets of La / Lb in LDS
     I_MAC,       // ACC = ACC + R[a] * R[b] (word1 = MAC_ADD), ACC - R[a] * R[b] (MAC_SUB) or R[a] * R[b] - ACC (MAC_RSUB): a sum or
-                 // difference with the product of two input tensors, which then needs no register of its own
+                 // difference with the product of two input tensors, which then needs no register of its own.  MAC_ADD rounds
+                 // once, the others round the product first
     I_COUNT
 };
 enum : uint32_t { MAC_ADD = 0, MAC_SUB, MAC_RSUB, MAC_COUNT };

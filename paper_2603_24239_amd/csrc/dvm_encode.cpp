@@ -1405,7 +1405,9 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
     }
     // A product of two inputs whose only use is a sum or difference with a computed value rides along with that record: it needs
     // no register of its own and RoPE fits four tile registers instead of six.  (Its inputs are then loaded at the sum: past the
-    // store of an output in between, which may be written over one of them, only where the program fits no other way.)
+    // store of an output in between, which may be written over one of them, only where the program fits no other way.)  The
+    // rounding is that of the records it replaces: a difference rounds the product first; of the sums only those directly behind
+    // their product of two tensors are taken, which are one fused record (I_FMA) otherwise.
     E.next_reg = 0;
     for (int n = 0; n < NN; ++n) { E.mac_of[n] = -1; E.mac[n] = false; }
     for (int n = 0; n < NN && E.allow_mac != 0; ++n) {
@@ -1417,6 +1419,11 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             if (x.kind != N_BIN || x.op != B_MUL || E.rows_class[m] || E.uses[m] != 1 || E.mac[m]) continue;
             if (E.rows_class[other] || prog->nodes[other].kind == N_IN || E.mac[other]) continue;
             bool ok = true;
+            if (u.op == B_ADD && E.allow_mac == 1) {
+                int before = n - 1;
+                while (before > m && (prog->nodes[before].kind == N_IN || prog->nodes[before].kind == N_DEAD || E.uses[before] == 0)) --before;
+                ok = before == m && x.a != x.b;
+            }
             for (int o = 0; o < prog->n_out; ++o) ok &= prog->out_node[o] != m && (E.allow_mac == 2 || prog->out_node[o] < m || prog->out_node[o] >= n);
             for (int q : {(int)x.a, (int)x.b}) ok &= prog->nodes[q].kind == N_IN && !E.rows_class[q] && E.lds_of[q] < 0;
             if (!ok) continue;

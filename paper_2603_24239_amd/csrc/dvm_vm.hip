@@ -73,6 +73,16 @@ DI float f_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
 DI float f_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 DI float f_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 DI float f_fma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+DI float f_mul_sub(float a, float b, float c) {        // a * b rounded, then - c
+#pragma clang fp contract(off)
+    const float p = a * b;
+    return p - c;
+}
+DI float f_sub_mul(float c, float a, float b) {        // c - a * b, the product rounded
+#pragma clang fp contract(off)
+    const float p = a * b;
+    return c - p;
+}
 // Table 1's Max / Min are read as propagating a NaN operand (what NumPy's maximum / minimum and the frameworks
 // this VM serves do).  gfx950 has that operation as one instruction (v_maximum3_f32 / v_minimum3_f32), which the
 // compiler selects for the IEEE-754-2019 maximum / minimum builtins: element-wise ops and every stage of a
@@ -1691,13 +1701,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                         }
                         break;
                     }
+                    // (the sum rounds once and the differences twice, as the records do that a program without I_MAC has: see the encoder)
                     case I_MAC: if constexpr (!(LONG && WIDE)) {       // (long rows with such a record run in the instantiation for any launch)
                         if (cw1 == MAC_ADD) {
                             DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_fma(TV(xa, I), TV(xb, I), TV(acc, I)); })))
                         } else if (cw1 == MAC_SUB) {
-                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_fma(-TV(xa, I), TV(xb, I), TV(acc, I)); })))
+                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_sub_mul(TV(acc, I), TV(xa, I), TV(xb, I)); })))
                         } else {
-                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_fma(TV(xa, I), TV(xb, I), -TV(acc, I)); })))
+                            DVM_WITH_R(a, xa, DVM_WITH_R2(b, xb, sfor<K>([&]<int I>() LI { TV(acc, I) = f_mul_sub(TV(xa, I), TV(xb, I), TV(acc, I)); })))
                         }
                     }
                         break;

@@ -2,6 +2,8 @@
 few (inputs loaded again), views, ragged rows, both types, against the oracle; and programs that must not lose a plan to it."""
 from __future__ import annotations
 
+from dataclasses import replace
+
 import pytest
 import torch
 
@@ -11,6 +13,7 @@ from workloads import programs as W
 from workloads.programs import _p
 
 from . import harness as H
+from .test_written_inputs_cpu import make
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -57,6 +60,43 @@ def test_rope(limits):
     out = torch.empty((37, 32, 128), dtype=torch.bfloat16, device=DEV)
     _, code, _ = H.check_program(W.get_program("c5_rope"), d, outputs={"y1": out[..., :64], "y2": out[..., 64:]}, ctx=_ctx(*limits))
     assert " mac " in code.disasm() and code.info().variant_nr <= 4
+
+
+def equal_bits(desc, d):
+    """The program planned for a launch of its own and for one that fills the machine."""
+    alone, _ = H.run_vm(desc, d, ctx=B.Context(torch.cuda.current_device()))
+    full, code = H.run_vm(desc, d, ctx=_ctx(32, 6))
+    for n, t in alone.items():
+        a, b = (x.view(torch.int16 if x.dtype == torch.bfloat16 else torch.int32) for x in (t, full[n]))
+        assert torch.equal(a, b), (desc.name, n)
+    return code
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_the_size_of_the_launch_does_not_change_the_rounding(dt):
+    print(f"[case] products that ride along, alone and in a full launch {dt}", flush=True)
+    d = {n: gen.randn((33, 64), 70 + i, DEV, dt) for i, n in enumerate("abcd")}
+    f32 = [replace(f, outputs=tuple((o, "f32") for o, _ in f.outputs)) for f in forms(dt) if f.name != "norm"]
+    ab_cd = [("p", "mul", ["a", "b"], {}), ("q", "mul", ["c", "d"], {})]
+    swapped = _p("swapped", f32[0].inputs, ab_cd + [("y", "add", ["q", "p"], {})], [("y", "f32")])
+    between = _p("between", f32[0].inputs, ab_cd + [("t", "tanh", ["a"], {}), ("s", "add", ["p", "q"], {}), ("y", "add", ["s", "t"], {})], [("y", "f32")])
+    texts = [equal_bits(f, d).disasm() for f in f32 + [swapped, between]]
+    assert sum(" mac " in t for t in texts) >= 3
+    # a difference of equal products is zero
+    zero, code = H.run_vm(f32[1], {"a": d["a"], "b": d["b"], "c": d["a"], "d": d["b"]}, ctx=_ctx(32, 6))
+    assert " mac " in code.disasm() and not zero["y"].any()
+
+
+def test_random_programs_round_alike_in_every_launch():
+    ran = 0
+    for seed in range(120):
+        desc = make(seed)
+        if any(o.name in ("rmax", "sum") for o in desc.ops):        # (row plans may differ in the order of a sum)
+            continue
+        print(f"[case] random program {seed}, alone and in a full launch", flush=True)
+        equal_bits(desc, {n: gen.randn((33, 512), 500 + 7 * seed + i, DEV, dt, std=0.5) for i, (n, dt) in enumerate(desc.inputs)})
+        ran += 1
+    assert ran > 30
 
 
 def test_one_register_is_still_enough():
