@@ -784,7 +784,7 @@ def run(args, names, cpu) -> int:
         ctx.set_limits(k_, nr_)
     else:
         # parts of very different sizes share a launch here: under a bound of 64 the small ones are planned for the 64-element
-        # variant and the large ones for 32, and their stack runs all of them in the former (config 2: 4.6 TB/s against 5.4)
+        # variant and the large ones for 32, and a stack of them is two launches (config 2: 5.32 TB/s against 5.41 so; config 3 alike)
         ctx.set_limits(32, 6)
     placement = condition_memory(torch, dev, args.shuffle_memory_gib, args.shuffle_chunk_mib)
     if args.workload == "if_else_add":

@@ -122,8 +122,8 @@ int  dvm_ctx_set_planner(dvm_ctx *ctx, int n_compute_units, int tile_overhead_el
  * bounds are 32 elements and 6 registers; the variant with 64 elements exists with one tile register only (programs
  * with long rows that need no more: a row of up to 4096 elements is then held by one wave; flat element-wise
  * programs keep 32 elements) and is planned for only when the bound is raised to 64.  Under 64 a program's rows decide:
- * few rows, or tensors within the last-level cache, take it, long rows beyond the cache stay at 32.  A caller that stacks
- * parts of such different sizes keeps the bound at 32, or every part runs in the wide variant. */
+ * few rows, or tensors within the last-level cache, take it, long rows beyond the cache stay at 32.  dvm_stack runs large
+ * parts of the second kind in a kernel launch of their own, behind the others. */
 int  dvm_ctx_set_limits(dvm_ctx *ctx, int max_elems_per_lane, int max_tile_regs);
 
 /* Force parts of the tile plan instead of letting the cost model choose (tests and tuning walk plans the
@@ -211,7 +211,8 @@ int  dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog,
  * program's tensor list is the concatenation of the parts' tensor lists, in order.  The parts
  * must be independent of each other (no part reads what another writes): dvm_run refuses a launch
  * in which a buffer one part writes overlaps a buffer of another part (DVM_E_ARGS).  For parts that
- * depend on each other use dvm_stack_dependent. */
+ * depend on each other use dvm_stack_dependent.  Parts planned for the variant of 64 elements beside others whose tensors exceed 256 MB in
+ * all make two kernel launches of one dvm_run (dvm_code_info.n_launches): each kind runs in its own variant. */
 int  dvm_stack(const void *const *codes, const size_t *lens, int n,
                void *out, size_t cap, size_t *len);
 

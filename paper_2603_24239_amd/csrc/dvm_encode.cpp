@@ -2743,6 +2743,21 @@ static int stack_impl(const void *const *codes, const size_t *lens, int n, const
         }
     }
     if (!vr) return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_stack: no interpreter variant fits all parts");
+    // Parts planned for 32 elements per lane or fewer beside parts for 64 would run in the wide variant, which holds fewer waves
+    // and whose tile registers they half fill.  Where they are large they become a kernel launch of their own, behind the wide
+    // ones', in the variant of 32 (dvm_run): eight RMSNorms of 9 to 900 MB under a bound of 64 elements 371 us in one launch
+    // and 321 in two (398 and 316, 462 and 378 for two other eights); a boundary costs some 6 us, as much as 18 % of the time 175 MB take, and these are taken apart from 256 MB.
+    bool apart = false;
+    if (!spatial && !same_as && vr->K == 64 && NR <= 2 && block <= 256 && !need_cred) {
+        uint64_t narrow_bytes = 0;
+        int n_wide = 0;
+        for (int i = 0; i < n; ++i) {
+            const uint32_t *c = (const uint32_t *)codes[i];
+            if ((c[PH_VARIANT] & 0xFF) > 32) { ++n_wide; continue; }
+            for (uint32_t t = 0; t < c[PH_NTENS]; ++t) narrow_bytes += (uint64_t)c[PH_WORDS_N + t * TT_WORDS + TT_BYTES_LO] | ((uint64_t)c[PH_WORDS_N + t * TT_WORDS + TT_BYTES_HI] << 32);
+        }
+        apart = n_wide < n && narrow_bytes >= ((uint64_t)256 << 20);
+    }
     // (a dependent stack may need the workspace entry: reserve its place, drop it again if no segment waits grid-wide)
     const uint32_t ntens_parts = ntens;
     if (same_as) {
@@ -2768,34 +2783,40 @@ static int stack_impl(const void *const *codes, const size_t *lens, int n, const
     w[PH_NTENS] = ntens;
     uint32_t *tt = w + PH_WORDS_N;
     uint32_t *sg = w + PH_WORDS_N + ntens * TT_WORDS;
-    uint32_t tbase = 0;
-    for (int i = 0; i < n; ++i) {
-        const uint32_t *c = (const uint32_t *)codes[i];
-        const uint32_t nt = c[PH_NTENS];
-        memcpy(tt, c + PH_WORDS_N, (size_t)nt * TT_WORDS * 4);
-        tt += nt * TT_WORDS;
-        const uint32_t off = PH_WORDS_N + nt * TT_WORDS;
-        const uint32_t sw = c[PH_WORDS] - off;
-        memcpy(sg, c + off, (size_t)sw * 4);
-        // rebase the tensor indices of the copied segments, and re-tile row-mode segments to the
-        // launch's workgroup size: a part planned for fewer threads takes more rows per tile
-        // instead of leaving the other threads of the common workgroup idle
-        uint32_t at = 0;
-        for (uint32_t s = 0; s < c[PH_NSEG]; ++s) {
-            uint32_t *sh = sg + at;
-            sh[S_TBASE] += tbase;
-            const uint32_t G = sh[S_GEOM] & 0xFFFF, RP = sh[S_RP] & 0xFFFF;
-            if (sh[S_NCT] == 1 && G <= block && sh[S_NROWS] > 0 && sh[S_INNER] == 0) {
-                const uint32_t rp_new = block / G;
-                if (rp_new > RP && rp_new <= 0xFFFF) {
-                    sh[S_RP] = rp_new | ((rp_new * G) << 16);
-                    sh[S_NTILES] = (sh[S_NROWS] + rp_new - 1) / rp_new;
+    for (int group = 0; group < (apart ? 2 : 1); ++group) {
+        uint32_t tbase = 0;
+        bool first_of_group = group != 0;
+        for (int i = 0; i < n; ++i) {
+            const uint32_t *c = (const uint32_t *)codes[i];
+            const uint32_t nt = c[PH_NTENS];
+            if (group == 0) memcpy(tt + tbase * TT_WORDS, c + PH_WORDS_N, (size_t)nt * TT_WORDS * 4);
+            if (!apart || ((c[PH_VARIANT] & 0xFF) <= 32) == (group == 1)) {
+                const uint32_t off = PH_WORDS_N + nt * TT_WORDS;
+                const uint32_t sw = c[PH_WORDS] - off;
+                memcpy(sg, c + off, (size_t)sw * 4);
+                // rebase the tensor indices of the copied segments, and re-tile row-mode segments to the
+                // launch's workgroup size: a part planned for fewer threads takes more rows per tile
+                // instead of leaving the other threads of the common workgroup idle
+                uint32_t at = 0;
+                for (uint32_t s = 0; s < c[PH_NSEG]; ++s) {
+                    uint32_t *sh = sg + at;
+                    sh[S_TBASE] += tbase;
+                    const uint32_t G = sh[S_GEOM] & 0xFFFF, RP = sh[S_RP] & 0xFFFF;
+                    if (sh[S_NCT] == 1 && G <= block && sh[S_NROWS] > 0 && sh[S_INNER] == 0) {
+                        const uint32_t rp_new = block / G;
+                        if (rp_new > RP && rp_new <= 0xFFFF) {
+                            sh[S_RP] = rp_new | ((rp_new * G) << 16);
+                            sh[S_NTILES] = (sh[S_NROWS] + rp_new - 1) / rp_new;
+                        }
+                    }
+                    at += sh[S_WORDS];
                 }
+                if (first_of_group) sg[S_FLAGS] |= SF_NEW_LAUNCH;
+                first_of_group = false;
+                sg += sw;
             }
-            at += sh[S_WORDS];
+            tbase += nt;
         }
-        sg += sw;
-        tbase += nt;
     }
     if (same_as) {
         // Dependences between the parts follow from the buffers they share: a part that touches a buffer an

@@ -2218,7 +2218,6 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     ka.spin_limit = (uint32_t)dvm_ctx_sync_limit(ctx);
 
     const int K = (int)(w[PH_VARIANT] & 0xFF), NR = (int)((w[PH_VARIANT] >> 8) & 0xFF);
-    uint32_t grid = w[PH_GRID];
     const uint32_t block = w[PH_BLOCK];
     // A segment that reduces along the penultimate axis needs the instantiation that runs such segments,
     // and LDS for the combination across waves: four floats per lane of every participating wave
@@ -2275,83 +2274,20 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         part |= ends_in_part(D0 - (uint64_t)(sh[S_NCT] - 1) * sh[S_TC]);
         if (sh[S_NCT] > 1) part |= ends_in_part(sh[S_TC]);
     }
-    // Several segments, or several sets: the tiles of each are dealt out from where the one before stopped.  (Not
-    // when a segment relies on its producer's assignment of tiles to workgroups, nor when the segments own shares
-    // of the workgroups.)
-    if ((w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL) {
-        uint64_t total = 0;
-        bool round_robin = true;
-        for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
-            total += w[at + S_NTILES];
-            round_robin &= (w[at + S_FLAGS] & SF_INTERLEAVED) != 0;
-        }
-        ka.rotate = round_robin && !grid_sync && total * (uint64_t)n_sets < (1ull << 31) ? 1u : 2u;     // (every workgroup arrives at a grid-wide wait)
-    }
-    // The instantiations that pass over foreign sets and segments are some 8 % slower per tile; the others spend 1.1 us on each.
-    // They pay where that is more than 8 % of the time the launch's bytes take at 5 TB/s, i.e. below 69 MB per segment and set
-    // (32 layers of five programs at 512 tokens, 18 MB each: 604 us against 639; eight RMSNorms of 285 MB: the other way round).
-    bool skip = false;
-    if (ka.rotate == 1) {
-        uint64_t bytes = 0;
-        for (uint32_t i = 0; i < ntens; ++i) bytes += (uint64_t)w[PH_WORDS_N + i * TT_WORDS + TT_BYTES_LO] | ((uint64_t)w[PH_WORDS_N + i * TT_WORDS + TT_BYTES_HI] << 32);
-        skip = bytes < (uint64_t)w[PH_NSEG] * (69ull << 20);
-    }
     if (cred && longrow)
         return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: a launch holds both a reduction along the penultimate axis and rows longer than a tile");
-    vm_launch_t launch = nullptr;
-    if (cred) {
-        for (const VariantEntry &v : g_cred_variants)
-            if (v.K == K && v.NR == NR) launch = v.launch;
-    } else {
-        const bool one = w[PH_NSEG] == 1 && n_sets == 1;
-        const bool any = part || (longrow && (!wide || mac || !one));
-        if (!any && !skip && ka.rotate == 1) ka.rotate = 2;         // (they know the other way of counting only)
-        const VariantEntry *list = any ? g_any_variants : longrow ? g_long_wide_variants
-                                   : skip ? (wide ? g_wide_variants : g_variants) : (wide ? g_one_wide_variants : g_one_variants);
-        for (int i = 0; i < N_VARIANTS; ++i)
-            if (list[i].K == K && list[i].NR == NR) launch = list[i].launch;
+    // Segments planned for 32 elements per lane or fewer that have a launch to themselves in a program of the 64-element variant
+    // (dvm_stack sets large ones apart) run in the one of 32: more resident waves, and no idle half of every tile register.
+    bool apart = false;
+    for (uint32_t s = 0, at = segs_off, k_max = 64; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
+        const uint32_t k = (w[at + S_GEOM] >> 24) * ((w[at + S_GEOM] >> 16) & 0xFF);
+        k_max = w[at + S_FLAGS] & SF_NEW_LAUNCH ? k : (k > k_max ? k : k_max);
+        const bool last = s + 1 == w[PH_NSEG] || (w[at + w[at + S_WORDS] + S_FLAGS] & SF_NEW_LAUNCH);
+        apart |= last && k_max <= 32 && K == 64 && NR <= 2 && block <= 256 && !cred;
     }
-    if (!launch) return dvm_set_error(DVM_E_BADCODE, "dvm_run: no interpreter variant for this bytecode");
+    const bool rotates = (w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL;
+    if (grid_sync) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws);
     hipError_t e;
-    if (grid_sync) {
-        // every workgroup waits for all the others: the whole grid has to be resident at once
-        int per_cu = 0, n_cu = 0;
-        e = (hipError_t)resident_per_cu(launch, block, lds_bytes, &per_cu);
-        if (e != hipSuccess) {
-            t_last_hip_error = (int)e;
-            return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
-        }
-        dvm_ctx_planner_get(ctx, &n_cu, nullptr);
-        // (the parts were planned one by one, some for interpreter variants that hold more waves than the
-        // launch's common one: the interpreter deals the tiles out over whatever grid it finds itself in)
-        if (per_cu < 1 || n_cu < 1)
-            return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: the device holds no workgroup of this launch's size");
-        if ((uint64_t)grid > (uint64_t)per_cu * (uint64_t)n_cu) grid = (uint32_t)per_cu * (uint32_t)n_cu;
-        hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws);
-    }
-    // A launch whose segments (and sets) deal their tiles out in rotation keeps as many workgroups busy as it has
-    // tiles in all: the grid grows from what the largest segment alone asked for to that, up to what the device holds
-    // at once (short segments of many sets then run side by side instead of one after the other on a few workgroups).
-    if (ka.rotate != 0 && !grid_sync) {
-        uint64_t total = 0;
-        for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; ++s) {
-            total += w[at + S_NTILES];
-            at += w[at + S_WORDS];
-        }
-        total *= (uint64_t)n_sets;
-        if (total > grid) {
-            int per_cu = 0, n_cu = 0;
-            e = (hipError_t)resident_per_cu(launch, block, lds_bytes, &per_cu);
-            if (e != hipSuccess) {
-                t_last_hip_error = (int)e;
-                return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
-            }
-            dvm_ctx_planner_get(ctx, &n_cu, nullptr);
-            const uint64_t cap = (uint64_t)(per_cu > 0 ? per_cu : 1) * (uint64_t)(n_cu > 0 ? n_cu : 1);
-            const uint64_t want = total < cap ? total : cap;
-            if (want > grid) grid = (uint32_t)want;
-        }
-    }
     // one kernel launch per run of segments up to the next one that asks for a launch of its own
     for (uint32_t first = 0; first < w[PH_NSEG];) {
         uint32_t end = first + 1;
@@ -2362,8 +2298,73 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         ka.seg_first = first;
         ka.nseg = end;
         ka.set_tiles = 0;
-        for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s)
-            if (s >= first) ka.set_tiles += w[at + S_NTILES];
+        uint64_t total = 0, bytes = 0;      // of this launch
+        uint32_t k_need = 0;                // elements per lane its segments use
+        bool round_robin = true;
+        for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s) {
+            if (s < first) continue;
+            const uint32_t *sh = w + at;
+            total += sh[S_NTILES];
+            round_robin &= (sh[S_FLAGS] & SF_INTERLEAVED) != 0;
+            const uint32_t k = (sh[S_GEOM] >> 24) * ((sh[S_GEOM] >> 16) & 0xFF);
+            if (k > k_need) k_need = k;
+            for (uint32_t i = 0; i < sh[S_NTENS]; ++i) {
+                const uint32_t *te = w + PH_WORDS_N + (sh[S_TBASE] + i) * TT_WORDS;
+                bytes += (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
+            }
+        }
+        ka.set_tiles = (uint32_t)total;
+        total *= (uint64_t)n_sets;
+        // Several segments, or several sets: the tiles of each are dealt out from where the one before stopped.  (Not
+        // when a segment relies on its producer's assignment of tiles to workgroups, nor when the segments own shares
+        // of the workgroups.)
+        ka.rotate = !rotates ? 0u : round_robin && !grid_sync && total < (1ull << 31) ? 1u : 2u;        // (every workgroup arrives at a grid-wide wait)
+        // The instantiations that pass over foreign sets and segments are some 8 % slower per tile; the others spend 1.1 us on each.
+        // They pay where that is more than 8 % of the time the launch's bytes take at 5 TB/s, i.e. below 69 MB per segment and set
+        // (32 layers of five programs at 512 tokens, 18 MB each: 604 us against 639; eight RMSNorms of 285 MB: the other way round).
+        const bool skip = ka.rotate == 1 && bytes < (uint64_t)(end - first) * (69ull << 20);
+        const bool narrow = apart && k_need <= 32;
+        const int K_l = narrow ? 32 : K, NR_l = narrow ? 2 : NR;
+        vm_launch_t launch = nullptr;
+        if (cred) {
+            for (const VariantEntry &v : g_cred_variants)
+                if (v.K == K && v.NR == NR) launch = v.launch;
+        } else {
+            const bool one = w[PH_NSEG] == 1 && n_sets == 1;
+            const bool any = part || (longrow && (!wide || mac || !one));
+            if (!any && !skip && ka.rotate == 1) ka.rotate = 2;         // (they know the other way of counting only)
+            const VariantEntry *list = any ? g_any_variants : longrow ? g_long_wide_variants
+                                       : skip ? (wide ? g_wide_variants : g_variants) : (wide ? g_one_wide_variants : g_one_variants);
+            for (int i = 0; i < N_VARIANTS; ++i)
+                if (list[i].K == K_l && list[i].NR == NR_l) launch = list[i].launch;
+        }
+        if (!launch) return dvm_set_error(DVM_E_BADCODE, "dvm_run: no interpreter variant for this bytecode");
+        uint32_t grid = w[PH_GRID];
+        if (grid_sync || (ka.rotate != 0 && (total > grid || apart))) {
+            int per_cu = 0, n_cu = 0;
+            e = (hipError_t)resident_per_cu(launch, block, lds_bytes, &per_cu);
+            if (e != hipSuccess) {
+                t_last_hip_error = (int)e;
+                return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
+            }
+            dvm_ctx_planner_get(ctx, &n_cu, nullptr);
+            if (grid_sync) {
+                // every workgroup waits for all the others: the whole grid has to be resident at once
+                // (the parts were planned one by one, some for interpreter variants that hold more waves than the
+                // launch's common one: the interpreter deals the tiles out over whatever grid it finds itself in)
+                if (per_cu < 1 || n_cu < 1)
+                    return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: the device holds no workgroup of this launch's size");
+                if ((uint64_t)grid > (uint64_t)per_cu * (uint64_t)n_cu) grid = (uint32_t)per_cu * (uint32_t)n_cu;
+            } else {
+                // A launch whose segments (and sets) deal their tiles out in rotation keeps as many workgroups busy as it has
+                // tiles in all: the grid grows from what the largest segment alone asked for to that, up to what the device holds
+                // at once (short segments of many sets then run side by side instead of one after the other on a few workgroups).
+                // Where launches differ in variant, each gets the grid of its own.
+                const uint64_t cap = (uint64_t)(per_cu > 0 ? per_cu : 1) * (uint64_t)(n_cu > 0 ? n_cu : 1);
+                const uint64_t want = total < cap ? total : cap;
+                if (want > grid || (apart && want > 0)) grid = (uint32_t)want;
+            }
+        }
         dvm_colreduce_args ca;
         uint32_t cgrid = 0, cblock = 0;
         const uint32_t *first_sh = w + segs_off;

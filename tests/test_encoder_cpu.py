@@ -506,3 +506,18 @@ def test_a_plan_override_that_cannot_be_honoured_leaves_the_planners_choice():
     c = B.Context(-1)
     c.set_plan_override(8, 0, 0)
     assert B.dvm_encode(c, prog, [B.make_shape((64, 4096))]).info().variant_k == 8
+
+
+def test_a_stack_sets_large_parts_of_the_narrow_variant_apart():
+    c = B.Context(-1)
+    c.set_limits(64, 6)
+    small, large = [_encode(c, "c2_rmsnorm", [(n, 4096), (4096,)]) for n in (700, 40000)]
+    assert small.info().variant_k == 64 and large.info().variant_k == 32
+    both = B.dvm_stack([large, small, large])
+    both.validate()
+    assert both.info().n_launches == 2 and both.info().variant_k == 64 and both.info().n_tensors == 9
+    # the small part's segment comes first and names its own tensors (entries 3 to 5)
+    assert re.findall(r"rows=(\d+) ", both.disasm()) == ["700", "40000", "40000"]
+    assert re.findall(r"tensor_base=(\d+)", both.disasm()) == ["3", "0", "6"]
+    for parts in ([large, large], [small, small], [_encode(c, "c2_rmsnorm", [(700, 4096), (4096,)]), _encode(c, "softmax_bf16", [(2000, 300)])]):
+        assert B.dvm_stack(parts).info().n_launches == 1

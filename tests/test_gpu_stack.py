@@ -118,3 +118,35 @@ def test_stack_limits():
     code = B.encode_for(ctx, prog, [d["x"], d["w"]])
     with pytest.raises(B.DvmError):
         B.dvm_stack([code] * 11)        # 33 tensors: beyond the launch's tensor table
+
+
+def test_parts_of_two_variants():
+    """Under a bound of 64 elements small RMSNorms are planned for it and large ones for 32: two launches, the bits of single runs."""
+    ctx = B.Context(torch.cuda.current_device())
+    ctx.set_limits(64, 6)
+    prog = H.program(W.get_program("c2_rmsnorm"))
+    w = gen.randn((4096,), 95, DEV, "bf16", mean=1.0, std=0.1)
+    for rows, launches in (((700, 20011, 33), 2), ((20011, 20012), 1), ((700, 33), 1), ((17000, 33, 2000, 17001), 2)):
+        print(f"[case] stacked RMSNorms of {rows} rows under a bound of 64 elements", flush=True)
+        xs = [gen.randn((n, 4096), 96 + i, DEV, "bf16") for i, n in enumerate(rows)]
+        codes = [B.encode_for(ctx, prog, [x, w]) for x in xs]
+        refs = [torch.empty_like(x) for x in xs]
+        for code, x, y in zip(codes, xs, refs):
+            B.run_on(ctx, code, [x, w, y])
+        stack = B.dvm_stack(codes)
+        assert stack.info().n_launches == launches, (rows, stack.info().n_launches)
+        stream = torch.cuda.current_stream().cuda_stream
+        outs = [torch.full_like(x, -7.0) for x in xs]
+        B.dvm_run(ctx, stack, [t.data_ptr() for x, y in zip(xs, outs) for t in (x, w, y)], stream)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, refs)), rows
+        if len(rows) == 3:
+            sets, other = [], [torch.full_like(x, -7.0) for x in xs]
+            for ys in (outs, other):
+                for y in ys:
+                    y.fill_(-7.0)
+                sets.append([t.data_ptr() for x, y in zip(xs, ys) for t in (x, w, y)])
+            table = torch.empty(2 * len(sets[0]), dtype=torch.int64, device=DEV)
+            B.dvm_run_batched(ctx, stack, sets, table.data_ptr(), table.numel() * 8, stream)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for ys in (outs, other) for a, b in zip(ys, refs)), rows
