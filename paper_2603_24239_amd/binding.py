@@ -497,11 +497,12 @@ def check_buffers(code: Bytecode, tensors: Sequence) -> None:
     needs = (C.c_int64 * max(n, 1))()
     _check(load().dvm_code_min_bytes(code.raw, len(code.raw), needs, n), "dvm_code_min_bytes")
     for i, (need, t) in enumerate(zip(needs, tensors)):
-        if need <= t.nbytes and t.is_contiguous():      # (its storage holds at least its elements)
-            continue
-        have = (t.untyped_storage().nbytes() - t.storage_offset() * t.element_size()) if t.numel() else 0
-        if need > have:
-            raise DvmError(-1, f"tensor {i}: bytecode touches {need} bytes, storage holds {have}")
+        have = t.untyped_storage().nbytes()     # (a storage may have been resized below what its tensor's shape says)
+        offset = t.storage_offset()
+        if offset != 0:
+            have -= offset * t.element_size()
+        if need > have or (need > 0 and t.numel() == 0):
+            raise DvmError(-1, f"tensor {i}: bytecode touches {need} bytes, storage holds {have if t.numel() else 0}")
 
 
 def run_on(ctx: Context, code: Bytecode, tensors: Sequence, stream: Optional[int] = None) -> None:

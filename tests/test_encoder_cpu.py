@@ -521,3 +521,21 @@ def test_a_stack_sets_large_parts_of_the_narrow_variant_apart():
     assert re.findall(r"tensor_base=(\d+)", both.disasm()) == ["3", "0", "6"]
     for parts in ([large, large], [small, small], [_encode(c, "c2_rmsnorm", [(700, 4096), (4096,)]), _encode(c, "softmax_bf16", [(2000, 300)])]):
         assert B.dvm_stack(parts).info().n_launches == 1
+
+
+def test_the_buffer_guard_looks_at_the_storage(ctx):
+    import torch
+    desc = W.get_program("c1_gelu_erf")
+    x, a, b, y = torch.empty(4, 1000), torch.empty(1000), torch.empty(1000), torch.empty(4, 1000)
+    code = B.encode_for(ctx, B.Program(desc), [x, a, b])
+    B.check_buffers(code, [x, a, b, y])
+    shrunk = torch.empty(4, 1000)
+    shrunk.untyped_storage().resize_(4000)          # still contiguous, still 16000 bytes by its shape
+    tail = torch.empty(5000)[1001:]                 # 3999 elements of its storage left
+    for bad in (shrunk, tail, torch.empty(4, 999), torch.empty(20000)[:0]):
+        for at in (0, 3):
+            tensors = [x, a, b, y]
+            tensors[at] = bad
+            with pytest.raises(B.DvmError):
+                B.check_buffers(code, tensors)
+    B.check_buffers(code, [torch.empty(5000)[1000:], a, b, y])
