@@ -412,9 +412,13 @@ def dvm_run_batched(ctx: Context, code: Bytecode, tensor_ptr_sets: Sequence[Sequ
     """One launch over several sets of tensors (device pointers); `table_ptr`: device memory for the address table."""
     n_sets = len(tensor_ptr_sets)
     n = len(tensor_ptr_sets[0])
-    flat = array.array("Q", itertools.chain.from_iterable(tensor_ptr_sets))
+    try:
+        flat = array.array("Q", itertools.chain.from_iterable(tensor_ptr_sets))
+        arr = (C.c_void_p * len(flat)).from_buffer(flat)
+    except TypeError:                   # (None or c_void_p among the addresses)
+        flat = list(itertools.chain.from_iterable(tensor_ptr_sets))
+        arr = (C.c_void_p * len(flat))(*flat)
     assert len(flat) == n * n_sets
-    arr = (C.c_void_p * len(flat)).from_buffer(flat)
     _check(load().dvm_run_batched(ctx._h, code.ptr, len(code), arr, n, n_sets, C.c_void_p(table_ptr), table_bytes, C.c_void_p(stream)),
            "dvm_run_batched")
 
@@ -488,6 +492,7 @@ def dvm_plan(total: int, n_cores: int, t_max: int, align: int, overhead: int = 2
 
 def encode_for(ctx: Context, prog: Program, inputs: Sequence, outputs: Optional[Sequence] = None) -> Bytecode:
     """Encode `prog` for the shapes/strides of the given torch tensors (and output views, if any)."""
+    inputs, outputs = tuple(inputs), outputs if outputs is None else tuple(outputs)
     return _encode(ctx, prog, _shapes_of(inputs), len(inputs), _shapes_of(outputs) if outputs is not None else None)
 
 

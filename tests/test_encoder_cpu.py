@@ -539,3 +539,16 @@ def test_the_buffer_guard_looks_at_the_storage(ctx):
             with pytest.raises(B.DvmError):
                 B.check_buffers(code, tensors)
     B.check_buffers(code, [torch.empty(5000)[1000:], a, b, y])
+
+
+def test_the_binding_takes_iterables_of_tensors_and_null_addresses(ctx):
+    import torch
+    desc = W.get_program("c2_rmsnorm")
+    x, w = torch.empty(8, 512, dtype=torch.bfloat16), torch.empty(512, dtype=torch.bfloat16)
+    prog = B.Program(desc)
+    assert B.encode_for(ctx, prog, (t for t in (x, w))).raw == B.encode_for(ctx, prog, [x, w]).raw
+    code = B.encode_for(ctx, prog, [x, w])
+    table = (ctypes.c_int64 * 6)()
+    for sets in ([[None, 16, 32], [16, 32, 48]], [[16, ctypes.c_void_p(32), 48], [16, 32, 48]]):
+        with pytest.raises(B.DvmError):         # (a context without a device: refused by the library, not by the packing)
+            B.dvm_run_batched(ctx, code, sets, ctypes.addressof(table), 48)
