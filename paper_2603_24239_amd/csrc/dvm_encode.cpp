@@ -3028,7 +3028,13 @@ extern "C" int dvm_disasm(const void *bytecode, size_t len, char *txt, size_t ca
               (unsigned long long)((uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32)), sh[S_GEOM] & 0xFFFF,
               (sh[S_GEOM] >> 16) & 0xFF, sh[S_GEOM] >> 24, sh[S_RP] & 0xFFFF, sh[S_NCT], sh[S_TC], sh[S_D1], sh[S_D2], sh[S_TBASE],
               (sh[S_FLAGS] & SF_INTERLEAVED) ? "interleaved" : "blocked");
-        if (sh[S_FLAGS] & SF_LONGROW) o.put("  ; rows longer than a tile: %u passes over a row, %u column tiles each\n", sh[S_NCTSH] + 1, sh[S_NCT]);
+        if (sh[S_FLAGS] & SF_LONGROW) {
+            uint32_t joint = 0;         // (maxima whose pass takes the sum behind them as well)
+            for (uint32_t pc = SH_WORDS; pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF) joint += (sh[pc] & 0xFF) == I_RED && ((sh[pc] >> 24) & R_ONLINE) != 0;
+            char together[48] = "";
+            if (joint) snprintf(together, sizeof together, " (%u of them with the one before)", joint);
+            o.put("  ; rows longer than a tile: %u passes over a row%s, %u column tiles each\n", sh[S_NCTSH] + 1, together, sh[S_NCT]);
+        }
         if (sh[S_FLAGS] & SF_NEW_LAUNCH) o.put("  ; a kernel launch of its own: starts when the segments before are complete\n");
         if (sh[S_FLAGS] & SF_SYNC_GRID) o.put("  ; waits until every workgroup has finished the segments before\n");
         else if (sh[S_FLAGS] & SF_SYNC_WG) o.put("  ; waits for this workgroup's own stores of the segments before\n");
@@ -3115,7 +3121,7 @@ extern "C" int dvm_disasm(const void *bytecode, size_t len, char *txt, size_t ca
                 case I_RED:
                     o.put("  %04zu red.%-5s s%u = %s(acc * %.9g + %.9g)%s\n", pc - at - SH_WORDS, RED_NAMES[b & R_KIND], a,
                           w[pc + 1] ? UN_NAMES[w[pc + 1]] : "", (double)f32_bits(w[pc + 2]), (double)f32_bits(w[pc + 3]),
-                          (sh[S_GEOM] & 0xFFFF) > 64 ? (b & R_ONLINE ? "  [workgroup sync, in one pass with the sum below]" : "  [workgroup sync]") : "");
+                          b & R_ONLINE ? "  [workgroup sync, in one pass with the sum below]" : ((sh[S_GEOM] & 0xFFFF) > 64 ? "  [workgroup sync]" : ""));
                     break;
                 case I_SOP: {
                     const uint32_t w1 = w[pc + 1];

@@ -552,3 +552,12 @@ def test_the_binding_takes_iterables_of_tensors_and_null_addresses(ctx):
     for sets in ([[None, 16, 32], [16, 32, 48]], [[16, ctypes.c_void_p(32), 48], [16, 32, 48]]):
         with pytest.raises(B.DvmError):         # (a context without a device: refused by the library, not by the packing)
             B.dvm_run_batched(ctx, code, sets, ctypes.addressof(table), 48)
+
+
+def test_the_disassembly_names_the_passes_over_a_long_row(ctx):
+    """A softmax takes its maximum and its sum in one pass, a LayerNorm its two sums in one each."""
+    text = _encode(ctx, "softmax_f32", [(9, 50000)]).disasm()
+    assert "rows longer than a tile: 3 passes over a row (1 of them with the one before)" in text
+    assert "in one pass with the sum below" in text
+    text = _encode(ctx, "layernorm_f32", [(9, 50000), (50000,), (50000,)]).disasm()
+    assert "rows longer than a tile: 3 passes over a row, " in text and "in one pass" not in text
