@@ -56,13 +56,13 @@ def build(verbose: bool = True) -> str:
         jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-c", vm], os.path.join(CSRC, f"dvm_vm_w_k{k}_r{nr}.o")))
     for k, nr, maxt, waves in variants():       # (launches that hold rows longer than a tile; the instantiation for any launch)
         defs = [f"-DDVM_VARIANT_K={k}", f"-DDVM_VARIANT_NR={nr}", f"-DDVM_VARIANT_MAXT={maxt}", f"-DDVM_VARIANT_WAVES={waves}"]
-        jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-DDVM_VARIANT_LONG=1", "-DDVM_VARIANT_WIDE=1", "-DDVM_VARIANT_SINGLE=1", "-c", vm], os.path.join(CSRC, f"dvm_vm_lw_k{k}_r{nr}.o")))
+        jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-DDVM_VARIANT_LONG=1", "-DDVM_VARIANT_WIDE=1", "-DDVM_VARIANT_VISIT=1", "-c", vm], os.path.join(CSRC, f"dvm_vm_lw_k{k}_r{nr}.o")))
         jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-DDVM_VARIANT_ANY=1", "-c", vm], os.path.join(CSRC, f"dvm_vm_a_k{k}_r{nr}.o")))
-    for k, nr, maxt, waves in variants():       # (launches of one segment and one set of tensors, in both forms)
+    for k, nr, maxt, waves in variants():       # (both forms without passing over foreign sets and segments: launches of one of each, or of large ones)
         defs = [f"-DDVM_VARIANT_K={k}", f"-DDVM_VARIANT_NR={nr}", f"-DDVM_VARIANT_MAXT={maxt}", f"-DDVM_VARIANT_WAVES={waves}",
-                "-DDVM_VARIANT_SINGLE=1"]
-        jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-c", vm], os.path.join(CSRC, f"dvm_vm_1_k{k}_r{nr}.o")))
-        jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-DDVM_VARIANT_WIDE=1", "-c", vm], os.path.join(CSRC, f"dvm_vm_1w_k{k}_r{nr}.o")))
+                "-DDVM_VARIANT_VISIT=1"]
+        jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-c", vm], os.path.join(CSRC, f"dvm_vm_v_k{k}_r{nr}.o")))
+        jobs.append(([hipcc, *COMMON, *DEVICE, *defs, "-DDVM_VARIANT_WIDE=1", "-c", vm], os.path.join(CSRC, f"dvm_vm_vw_k{k}_r{nr}.o")))
     for k, nr, maxt, waves in variants("DVM_CRED_VARIANT_LIST"):
         defs = [f"-DDVM_VARIANT_K={k}", f"-DDVM_VARIANT_NR={nr}", f"-DDVM_VARIANT_MAXT={maxt}", f"-DDVM_VARIANT_WAVES={waves}",
                 "-DDVM_VARIANT_CRED=1"]
@@ -70,7 +70,7 @@ def build(verbose: bool = True) -> str:
 
     # the variants with the most registers take the longest to compile: start them first
     def weight(job):
-        m = re.search(r"dvm_vm(?:_c|_w|_a|_lw|_1|_1w)?_k(\d+)_r(\d+)\.o$", job[1])
+        m = re.search(r"dvm_vm(?:_c|_w|_a|_lw|_v|_vw)?_k(\d+)_r(\d+)\.o$", job[1])
         return -(int(m.group(1)) * int(m.group(2))) if m else 0
     jobs.sort(key=weight)
 

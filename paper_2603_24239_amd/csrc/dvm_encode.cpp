@@ -2390,6 +2390,7 @@ extern "C" int dvm_validate(const void *bytecode, size_t len) {
         const uint32_t nct = sh[S_NCT], TC = sh[S_TC];
         if (nct == 0) return bad("column tiles");
         if (TC > G * nvec * V) return bad("tile wider than the lanes can hold");
+        if (nct > 1 && TC % V != 0) return bad("tile width is not whole chunks");
         const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
         const uint64_t nrows = sh[S_NROWS];
         const uint64_t M = sh[S_NTILES];

@@ -348,7 +348,7 @@ constexpr bool HAVE_PART = true;
 // launches of few segments and sets for their size: two more values across the record loop cost the 12-op chain 12 %, masked softmax
 // 6-15 % and a stack of eight large RMSNorms 15 %.  (Their loops over segments and sets stay: without them the compiler reloads the segment header inside the record
 // loop, and the chain is 5 % slower, masked softmax 3 %.)
-#if defined(DVM_VARIANT_SINGLE)
+#if defined(DVM_VARIANT_VISIT)
 constexpr bool SKIP = false;
 #else
 constexpr bool SKIP = true;
@@ -1354,7 +1354,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                             Geo g = gt;
                             uint32_t gp = cur;
                             u32x4s rw = cw;
-                            const bool slow_finish = g.part() != 0;
                             uint32_t widen = 0;             // bit r + 1: register r (bit 0: ACC) holds raw bf16 bits
                             for (;;) {
                                 asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
@@ -1386,28 +1385,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                                 const uint32_t nop = rw.x & 0xFF;
                                 if (nop != I_LOAD && nop != I_VLOAD) break;
                             }
-                            if (slow_finish) {          // ragged rows: walk the records again (row address for the last chunk)
-                                for (uint32_t fp = cur; fp < gp;) {
-                                    asm volatile("" : "+v"(g.lanecol), "+s"(g.pk), "+s"(g.cend));
-                                    const u32x4s fw = fetch4(code, fp);
-                                    const uint32_t r0w = fw.x, w1 = fw.y, r2w = fw.z, r3w = fw.w;
-                                    const uint32_t rop = r0w & 0xFF, ra = (r0w >> 16) & 0xFF;
-                                    const uint32_t ti = w1 & 0xFF, dt = (w1 >> 8) & 0xFF;
-                                    int64_t off = (int64_t)wd.i1 * DVM_I64(r2w, r3w) + (int64_t)g.colbase;
-                                    if (rop == I_VLOAD) {
-                                        const u32x4s hw = fetch4(code, fp + 4);
-                                        const uint32_t h0 = hw.x, h1 = hw.y, h2 = hw.z, h3 = hw.w;
-                                        off += (int64_t)wd.i2 * DVM_I64(h0, h1) + (int64_t)wd.i3 * DVM_I64(h2, h3);
-                                    }
-                                    gcptr rowp = (gcptr)((const char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2));
-                                    if (ra == SRC_ACC) {
-                                        finish_dispatch<K>(acc, dt, V, rowp, g);
-                                    } else {
-                                        DVM_WITH_R(ra, rr, (finish_dispatch<K>(rr, dt, V, rowp, g)))
-                                    }
-                                    fp += (r0w >> 8) & 0xFF;
-                                }
-                            } else if (widen != 0) {    // full rows: only the bf16 registers need their second half
+                            if (widen != 0) {           // the bf16 registers need their second half
                                 if constexpr (K >= 8) {
                                     if (widen & 1u) finish_tile<K, 1, 8>(acc, nullptr, g);
                                     if (widen & 2u) finish_tile<K, 1, 8>(r0, nullptr, g);
@@ -1873,10 +1851,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 #define DVM_WIDE_LAUNCHER_NAME(K, NR) DVM_WIDE_LAUNCHER_NAME_(K, NR)
 #define DVM_ANY_LAUNCHER_NAME_(K, NR) dvm_vm_launch_a_##K##_##NR
 #define DVM_ANY_LAUNCHER_NAME(K, NR) DVM_ANY_LAUNCHER_NAME_(K, NR)
-#define DVM_ONE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_1_##K##_##NR
-#define DVM_ONE_LAUNCHER_NAME(K, NR) DVM_ONE_LAUNCHER_NAME_(K, NR)
-#define DVM_ONE_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_1w_##K##_##NR
-#define DVM_ONE_WIDE_LAUNCHER_NAME(K, NR) DVM_ONE_WIDE_LAUNCHER_NAME_(K, NR)
+#define DVM_VISIT_LAUNCHER_NAME_(K, NR) dvm_vm_launch_v_##K##_##NR
+#define DVM_VISIT_LAUNCHER_NAME(K, NR) DVM_VISIT_LAUNCHER_NAME_(K, NR)
+#define DVM_VISIT_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_vw_##K##_##NR
+#define DVM_VISIT_WIDE_LAUNCHER_NAME(K, NR) DVM_VISIT_WIDE_LAUNCHER_NAME_(K, NR)
 #define DVM_LONG_WIDE_LAUNCHER_NAME_(K, NR) dvm_vm_launch_lw_##K##_##NR
 #define DVM_LONG_WIDE_LAUNCHER_NAME(K, NR) DVM_LONG_WIDE_LAUNCHER_NAME_(K, NR)
 
@@ -1895,11 +1873,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
 #elif defined(DVM_VARIANT_ANY)
 #define DVM_THIS_LAUNCHER DVM_ANY_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
 #define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false, true>
-#elif defined(DVM_VARIANT_WIDE) && defined(DVM_VARIANT_SINGLE)
-#define DVM_THIS_LAUNCHER DVM_ONE_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
+#elif defined(DVM_VARIANT_WIDE) && defined(DVM_VARIANT_VISIT)
+#define DVM_THIS_LAUNCHER DVM_VISIT_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
 #define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, true, false>
-#elif defined(DVM_VARIANT_SINGLE)
-#define DVM_THIS_LAUNCHER DVM_ONE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
+#elif defined(DVM_VARIANT_VISIT)
+#define DVM_THIS_LAUNCHER DVM_VISIT_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
 #define DVM_THIS_KERNEL dvm_vm_kernel<DVM_VARIANT_K, DVM_VARIANT_NR, DVM_VARIANT_MAXT, DVM_VARIANT_WAVES, false, false, false>
 #elif defined(DVM_VARIANT_WIDE)
 #define DVM_THIS_LAUNCHER DVM_WIDE_LAUNCHER_NAME(DVM_VARIANT_K, DVM_VARIANT_NR)
@@ -1927,10 +1905,10 @@ DVM_VARIANT_LIST(X)
 #define X(K, NR, MAXT, W) extern "C" int DVM_LONG_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
 DVM_VARIANT_LIST(X)
 #undef X
-#define X(K, NR, MAXT, W) extern "C" int DVM_ONE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
+#define X(K, NR, MAXT, W) extern "C" int DVM_VISIT_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
 DVM_VARIANT_LIST(X)
 #undef X
-#define X(K, NR, MAXT, W) extern "C" int DVM_ONE_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
+#define X(K, NR, MAXT, W) extern "C" int DVM_VISIT_WIDE_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
 DVM_VARIANT_LIST(X)
 #undef X
 #define X(K, NR, MAXT, W) extern "C" int DVM_CRED_LAUNCHER_NAME(K, NR)(unsigned, unsigned, unsigned, void *, const void *, int *);
@@ -1958,11 +1936,11 @@ const VariantEntry g_any_variants[] = {DVM_VARIANT_LIST(X)};
 #define X(K, NR, MAXT, W) {K, NR, DVM_LONG_WIDE_LAUNCHER_NAME(K, NR)},
 const VariantEntry g_long_wide_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
-#define X(K, NR, MAXT, W) {K, NR, DVM_ONE_LAUNCHER_NAME(K, NR)},
-const VariantEntry g_one_variants[] = {DVM_VARIANT_LIST(X)};
+#define X(K, NR, MAXT, W) {K, NR, DVM_VISIT_LAUNCHER_NAME(K, NR)},
+const VariantEntry g_visit_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
-#define X(K, NR, MAXT, W) {K, NR, DVM_ONE_WIDE_LAUNCHER_NAME(K, NR)},
-const VariantEntry g_one_wide_variants[] = {DVM_VARIANT_LIST(X)};
+#define X(K, NR, MAXT, W) {K, NR, DVM_VISIT_WIDE_LAUNCHER_NAME(K, NR)},
+const VariantEntry g_visit_wide_variants[] = {DVM_VARIANT_LIST(X)};
 #undef X
 #define X(K, NR, MAXT, W) {K, NR, DVM_CRED_LAUNCHER_NAME(K, NR)},
 const VariantEntry g_cred_variants[] = {DVM_CRED_VARIANT_LIST(X)};
@@ -2272,7 +2250,6 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         };
         if (sh[S_NTILES] == 0) continue;
         part |= ends_in_part(D0 - (uint64_t)(sh[S_NCT] - 1) * sh[S_TC]);
-        if (sh[S_NCT] > 1) part |= ends_in_part(sh[S_TC]);
     }
     if (cred && longrow)
         return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: a launch holds both a reduction along the penultimate axis and rows longer than a tile");
@@ -2334,7 +2311,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             const bool any = part || (longrow && (!wide || mac || !one));
             if (!any && !skip && ka.rotate == 1) ka.rotate = 2;         // (they know the other way of counting only)
             const VariantEntry *list = any ? g_any_variants : longrow ? g_long_wide_variants
-                                       : skip ? (wide ? g_wide_variants : g_variants) : (wide ? g_one_wide_variants : g_one_variants);
+                                       : skip ? (wide ? g_wide_variants : g_variants) : (wide ? g_visit_wide_variants : g_visit_variants);
             for (int i = 0; i < N_VARIANTS; ++i)
                 if (list[i].K == K_l && list[i].NR == NR_l) launch = list[i].launch;
         }
