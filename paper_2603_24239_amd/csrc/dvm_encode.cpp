@@ -837,7 +837,9 @@ static int encode_split_reduction(const dvm_ctx *ctx, const dvm_prog *prog, cons
     dvm_ctx sub = *ctx;
     sub.workspace_limit = 0;
     if (sub.max_k > 8) sub.max_k = 8;       // (the streaming form of the reduction runs in the variants up to 8 elements per lane)
-    if (sub.dbg_rp == 0) sub.dbg_rp = 4;    // four waves per unit: workgroups of 256 threads, four of them per compute unit
+    // (a reduction of an input with nothing behind it: both parts are plain ones, whose kernel takes workgroups of its own)
+    const bool plain = n_out == 1 && prog->out_node[0] == c && prog->nodes[prog->nodes[c].a].kind == N_IN;
+    if (sub.dbg_rp == 0 && !plain) sub.dbg_rp = 4;      // four waves per unit: workgroups of 256 threads, four of them per compute unit
     // ---- part 1
     dvm_prog p1;
     memset(&p1, 0, sizeof(p1));
@@ -934,9 +936,6 @@ static int encode_split_reduction(const dvm_ctx *ctx, const dvm_prog *prog, cons
         p2.out_node[o] = map[prog->out_node[o]];
         p2.out_dtype[o] = prog->out_dtype[o];
     }
-    // (a reduction of an input with nothing behind it: both parts are plain ones, whose kernel takes workgroups of its own, and the
-    // second has few rows to spread)
-    if (ctx->dbg_rp == 0 && nn == 2 && p2.nodes[1].kind == N_CRED && prog->nodes[prog->nodes[c].a].kind == N_IN) sub.dbg_rp = 8;
     st = dvm_encode(&sub, &p2, sh2, p2.n_in, out_layout, code2, sizeof(code2), &len2, out_shapes);
     if (st != DVM_OK) return st;
     // ---- join: stack the two, then fold their tensor tables into [inputs, outputs, workspace]

@@ -28,7 +28,7 @@ typedef struct dvm_colreduce_args {
     uint32_t col_tiles, log2_lanes; // column tiles of a row; lanes (of 16 bytes) that share a row
     uint32_t waves, partials;       // the segment's waves per unit and partial results per wave: they fix the order of the rows
     uint32_t op;                    // R_SUM, R_MAX or R_MIN
-    uint32_t in_bf16, out_bf16, once;
+    uint32_t in_bf16, out_bf16;
 } dvm_colreduce_args;
 int dvm_colreduce_launch(const dvm_colreduce_args *a, unsigned grid, unsigned block, void *stream);
 // Implemented in the device file so that the encoder object stays free of HIP calls.

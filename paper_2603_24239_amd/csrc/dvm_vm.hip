@@ -2117,7 +2117,6 @@ bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *ten
     if (D0 < piece || i64(st + 2) != 0) return false;
     a->in = (const void *)(uintptr_t)tensors[sh[S_TBASE] + (r[1] & 0xFF)];
     a->out = (void *)(uintptr_t)tensors[sh[S_TBASE] + (st[1] & 0xFF)];
-    a->once = ((r[1] >> 16) & MF_STREAM) != 0;
     a->in_s1 = i64(r + 2); a->in_s2 = i64(r + 4); a->in_s3 = i64(r + 6);
     a->out_s2 = sop == I_VSTORE ? i64(st + 4) : 0;
     a->out_s3 = sop == I_VSTORE ? i64(st + 6) : 0;
