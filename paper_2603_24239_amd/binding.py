@@ -335,6 +335,9 @@ def dvm_encode(ctx: Context, prog: Program, in_shapes: Sequence[dvm_shape],
 
 
 _EncBuf = C.c_char * _ENC_CAP
+# arrays for the tensors of a launch (32 at most)
+_Sizes = [C.c_int64 * max(k, 1) for k in range(33)]
+_Pointers = [C.c_void_p * max(k, 1) for k in range(33)]
 
 
 def _encode(ctx: Context, prog: Program, arr, n: int, outl) -> Bytecode:
@@ -402,7 +405,7 @@ def workspace_gave_up(workspace_ptr: int, stream: int = 0) -> bool:
 def dvm_run(ctx: Context, code: Bytecode, tensor_ptrs: Sequence[int], stream: int = 0) -> None:
     n = len(tensor_ptrs)
     raw = code.raw
-    status = load().dvm_run(ctx._h, raw, len(raw), (C.c_void_p * max(n, 1))(*tensor_ptrs), n, stream)
+    status = load().dvm_run(ctx._h, raw, len(raw), (_Pointers[n] if n < len(_Pointers) else C.c_void_p * n)(*tensor_ptrs), n, stream)
     if status != 0:
         raise DvmError(status, "dvm_run")
 
@@ -499,14 +502,18 @@ def encode_for(ctx: Context, prog: Program, inputs: Sequence, outputs: Optional[
 def check_buffers(code: Bytecode, tensors: Sequence) -> None:
     """Host-side guard: every tensor's storage must cover what the bytecode will touch."""
     n = len(tensors)
-    needs = (C.c_int64 * max(n, 1))()
-    _check(load().dvm_code_min_bytes(code.raw, len(code.raw), needs, n), "dvm_code_min_bytes")
-    for i, (need, t) in enumerate(zip(needs, tensors)):
+    needs = _Sizes[n]() if n < len(_Sizes) else (C.c_int64 * n)()
+    raw = code.raw
+    status = load().dvm_code_min_bytes(raw, len(raw), needs, n)
+    if status != 0:
+        raise DvmError(status, "dvm_code_min_bytes")
+    for need, t in zip(needs, tensors):
         have = t.untyped_storage().nbytes()     # (a storage may have been resized below what its tensor's shape says)
         offset = t.storage_offset()
         if offset != 0:
             have -= offset * t.element_size()
-        if need > have or (need > 0 and t.numel() == 0):
+        if need > have or (not t.numel() and need > 0):
+            i = next(k for k, u in enumerate(tensors) if u is t)
             raise DvmError(-1, f"tensor {i}: bytecode touches {need} bytes, storage holds {have if t.numel() else 0}")
 
 
