@@ -838,7 +838,7 @@ static int encode_split_reduction(const dvm_ctx *ctx, const dvm_prog *prog, cons
     sub.workspace_limit = 0;
     if (sub.max_k > 8) sub.max_k = 8;       // (the streaming form of the reduction runs in the variants up to 8 elements per lane)
     // (a reduction of an input with nothing behind it: both parts are plain ones, whose kernel takes workgroups of its own)
-    const bool plain = n_out == 1 && prog->out_node[0] == c && prog->nodes[prog->nodes[c].a].kind == N_IN;
+    const bool plain = n_out == 1 && prog->out_node[0] == c && prog->nodes[prog->nodes[c].a].kind == N_IN && dom[R - 1] >= 8;
     if (sub.dbg_rp == 0 && !plain) sub.dbg_rp = 4;      // four waves per unit: workgroups of 256 threads, four of them per compute unit
     // ---- part 1
     dvm_prog p1;
