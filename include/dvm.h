@@ -212,7 +212,9 @@ int  dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog,
  * must be independent of each other (no part reads what another writes): dvm_run refuses a launch
  * in which a buffer one part writes overlaps a buffer of another part (DVM_E_ARGS).  For parts that
  * depend on each other use dvm_stack_dependent.  Parts planned for the variant of 64 elements beside others whose tensors exceed 256 MB in
- * all make two kernel launches of one dvm_run (dvm_code_info.n_launches): each kind runs in its own variant. */
+ * all make two kernel launches of one dvm_run (dvm_code_info.n_launches): each kind runs in its own variant.
+ * A softmax along the row that moves 16 MB or more (over rows longer than a tile: 2 MB) runs in a kernel of its own, as a launch of
+ * its own in its place among the parts, here, in dvm_stack_dependent and in dvm_run_batched; n_launches does not count those. */
 int  dvm_stack(const void *const *codes, const size_t *lens, int n,
                void *out, size_t cap, size_t *len);
 
@@ -228,7 +230,7 @@ int  dvm_stack(const void *const *codes, const size_t *lens, int n,
  *   - otherwise, with order_by = DVM_ORDER_BY_LAUNCH, dvm_run starts a kernel launch of its own at that part (everything
  *     before it is then complete and visible; no workspace, no wait on the device; on this hardware the cheaper of
  *     the two: a few microseconds per boundary);
- *   - or, with order_by = DVM_ORDER_IN_KERNEL, the whole program stays ONE kernel launch and every workgroup waits
+ *   - or, with order_by = DVM_ORDER_IN_KERNEL, the whole program (but for large softmax parts, see dvm_stack) stays ONE kernel launch and every workgroup waits
  *     until all have finished the earlier parts (its cost grows with the number of workgroups: each makes its
  *     stores visible beyond its own second-level cache).  That needs
  *     DVM_WORKSPACE_BYTES of device memory the caller lends to the launch: the stacked program then lists one
@@ -320,7 +322,7 @@ typedef struct dvm_code_info {
     int32_t  n_instructions;   /* over all segments                                               */
     int64_t  n_tiles;          /* over all segments (the M of Algorithm 2, summed)                */
     int64_t  code_bytes;       /* over all segments (CodeSize, summed)                            */
-    int32_t  n_launches;       /* kernel launches dvm_run issues for this bytecode (1 unless parts ask for their own) */
+    int32_t  n_launches;       /* kernel launches dvm_run issues for this bytecode (1 unless parts ask for their own; see dvm_stack) */
     int32_t  reserved;
 } dvm_code_info;
 int  dvm_code_info_get(const void *bytecode, size_t len, dvm_code_info *info);

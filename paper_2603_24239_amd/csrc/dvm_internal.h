@@ -31,6 +31,27 @@ typedef struct dvm_colreduce_args {
     uint32_t in_bf16, out_bf16;
 } dvm_colreduce_args;
 int dvm_colreduce_launch(const dvm_colreduce_args *a, unsigned grid, unsigned block, void *stream);
+// A softmax along the row, of one tensor or of the sum of two, as its own kernel takes it (dvm_softmax.hip): sizes and strides in elements.
+typedef struct dvm_softmax_args {
+    const void *a, *b;              // b: the second tensor of the sum (null: none)
+    void *y;
+    uint64_t sets;                  // batched launch: device array of n_sets * n_tensors addresses (0: the three above)
+    uint32_t n_tensors, ia, ib, iy; // and where the three stand in a set
+    uint32_t bf16;                  // the dtype of all three: bf16 or fp32
+    int64_t a_s[3], b_s[3], y_s[3]; // strides of the outer dims, the first of them varying fastest from row to row
+    uint32_t d1, m1, sh1, d2, m2, sh2;      // extents of the first two and the multiply-shift constants that divide by them
+    uint32_t limit;                 // blocked order (0: none): the third index counts blocks of d1 along one dim, of this extent
+    uint32_t rows, cols;            // rows of a set (blocked order: with those that the last block has too many), columns
+    uint32_t tiles;                 // of all sets
+    uint32_t set_tiles, set_m, set_sh;      // of one set
+    uint32_t lanes;                 // lanes on a row: a power of two from 8 to 1024
+    uint32_t in_long;               // 1: the kernel for long rows (lanes: 512 or 1024)
+    uint32_t slots;                 // 16-byte chunks of a lane
+    uint32_t tail;                  // a row may end in this slot of chunks or behind it
+    uint32_t shifted;               // some row does not start on a 128-byte line of the output
+} dvm_softmax_args;
+constexpr int64_t DVM_SOFTMAX_MIN_BYTES = 16 << 20;
+int dvm_softmax_launch(const dvm_softmax_args *a, unsigned grid, void *stream);
 // Implemented in the device file so that the encoder object stays free of HIP calls.
 int dvm_ctx_query_device(int hip_device, int *n_cu);
 

@@ -1972,10 +1972,10 @@ int scratch_setup(int device) {
     return DVM_OK;
 }
 
-// clears the synchronisation area of a launch's workspace (a kernel rather than a memset node, so that the
-// clearing may be captured into a HIP graph with the launch it precedes)
-__global__ void dvm_ws_clear(uint32_t *ws) {
-    if (threadIdx.x < WS_SYNC_WORDS) ws[threadIdx.x] = 0;
+// clears the first words of the synchronisation area of a launch's workspace (a kernel rather than a memset node, so that
+// the clearing may be captured into a HIP graph with the launch it precedes)
+__global__ void dvm_ws_clear(uint32_t *ws, uint32_t words) {
+    if (threadIdx.x < words) ws[threadIdx.x] = 0;
 }
 
 }  // namespace
@@ -2144,6 +2144,167 @@ bool plain_colreduce(const dvm_ctx *ctx, const uint32_t *sh, const uint64_t *ten
     return true;
 }
 
+// Multiply-shift constants of magic_div (Granlund & Montgomery): n / d for every 32-bit n.
+void magic_of(uint32_t d, uint32_t *m, uint32_t *sh) {
+    uint32_t l = 0;
+    while (l < 32 && (1ull << l) < d) ++l;
+    *m = (uint32_t)(((1ull << 32) * ((1ull << l) - d)) / d + 1);
+    *sh = (l < 1 ? l : 1u) | (l > 1 ? l - 1 : 0u) << 8;
+}
+
+// A segment that is a softmax along the row, of one tensor or of the sum of two, as the arguments of the kernel for those: load [, load,
+// add], max, exp of the difference, reciprocal of the sum, store of the product.  It takes segments that read and write at least
+// DVM_SOFTMAX_MIN_BYTES (rows longer than a tile, which the interpreter reads twice: an eighth of that): below, a launch is bound by its own
+// cost, and in a stack an extra one (2 us) would cost more than it gives.  Rows of less than a line stay too (fp32 [400000, 9] 12.4 us
+// there and 18.0 here).  The rule looks at the segment alone, so that its bits are the same alone, in a stack and in a batched launch (in a
+// spatial stack, whose parts share one launch, it stays with the interpreter).
+// Lanes on a row: those that leave the fewest idle, lanes * chunks being what a row costs, over up to 8 chunks of 16 bytes a lane (bf16: 6,
+// for the registers).  More than 4 cost an eighth for the waves they displace (not in fp32 rows of one wave), a row of several waves a
+// sixteenth for its barriers: bf16 [64000, 2000] 141 us in 256 lanes of 2 chunks, 99 in 128 of 3, 82 in 64 of 5; fp32 [31250, 4096] 169 in 128 of
+// 8, 161 in 256 of 4.  Longer rows go to the kernel that keeps one per workgroup.
+bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tensors, int n_sets, uint32_t n_tensors, dvm_softmax_args *a) {
+    if (sh[S_INNER] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_LDS | SF_CSTREAM)) || sh[S_NROWS] == 0) return false;
+    const uint32_t *r = sh + SH_WORDS, *end = r + sh[S_CODESIZE];
+    auto op_of = [&]() { return r < end ? r[0] & 0xFF : (uint32_t)I_COUNT; };
+    auto ra = [&]() { return (r[0] >> 16) & 0xFF; };
+    auto rb = [&]() { return r[0] >> 24; };
+    auto next = [&]() { r += (r[0] >> 8) & 0xFF; };
+    auto is_load = [&]() { return op_of() == I_LOAD || op_of() == I_VLOAD; };
+    constexpr uint32_t ONE = 0x3F800000u;
+    const uint32_t *la = nullptr, *lb = nullptr, *st;
+    uint32_t reg = 0;
+    for (int i = 0; i < 2 && is_load(); ++i, next()) {
+        if (ra() == SRC_ACC && !la) la = r;
+        else if (ra() != SRC_ACC && !lb) { lb = r; reg = ra(); }
+        else return false;
+    }
+    if (!la) return false;
+    if (lb) {
+        if (op_of() != I_BIN || ra() != reg || rb() != B_ADD) return false;
+        next();
+    }
+    if (op_of() != I_RED || (rb() & R_KIND) != R_MAX || r[1] != U_NONE || r[2] != ONE || r[3] != 0) return false;
+    const uint32_t smax = ra();
+    next();
+    if (op_of() != I_BIN || ra() != SRC_S0 + smax || rb() != B_EXPSUB) return false;
+    next();
+    if (op_of() != I_RED || rb() != R_SUM || r[1] != U_RCP || r[2] != ONE || r[3] != 0) return false;
+    const uint32_t ssum = ra();
+    next();
+    if ((op_of() != I_STORE && op_of() != I_VSTORE) || ra() != SRC_ACC || rb() != ssum + 1) return false;
+    st = r;
+    next();
+    if (r != end) return false;
+    const uint32_t dt = (la[1] >> 8) & 0xFF;
+    if (((st[1] >> 8) & 0xFF) != dt || (lb && ((lb[1] >> 8) & 0xFF) != dt)) return false;
+    const uint32_t es = dt ? 2 : 4, V = 16 / es, line = 128 / es;
+    const uint64_t cols = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
+    const uint64_t rows = sh[S_NROWS];
+    if (cols < line || cols > (1u << 24) || (int64_t)(rows * cols * es * 2) < (sh[S_FLAGS] & SF_LONGROW ? DVM_SOFTMAX_MIN_BYTES / 8 : DVM_SOFTMAX_MIN_BYTES)) return false;
+    // the outer dims and the strides along them, in the order of the output's strides: rows that follow each other in memory do so in the grid
+    uint32_t ext[3] = {(uint32_t)rows, 1, 1};
+    if (sh[S_D1] != 0) {
+        ext[0] = sh[S_D1];
+        ext[1] = (uint32_t)(rows / sh[S_D1]);
+        if (sh[S_D2] != 0) {
+            ext[2] = ext[1] / sh[S_D2];
+            ext[1] = sh[S_D2];
+        }
+    }
+    auto stride = [&](const uint32_t *rec, int k) {
+        const bool view = (rec[0] & 0xFF) == I_VLOAD || (rec[0] & 0xFF) == I_VSTORE;
+        return k == 0 || view ? (int64_t)((uint64_t)rec[2 + 2 * k] | ((uint64_t)rec[3 + 2 * k] << 32)) : (int64_t)0;
+    };
+    int dim[3] = {0, 1, 2};
+    auto weight = [&](int k) { return ext[k] == 1 ? INT64_MAX : (stride(st, k) < 0 ? -stride(st, k) : stride(st, k)); };
+    for (int i = 1; i < 3; ++i)
+        for (int j = i; j > 0 && weight(dim[j]) < weight(dim[j - 1]); --j) { const int t = dim[j]; dim[j] = dim[j - 1]; dim[j - 1] = t; }
+    bool even = true;               // every row starts where the first does in its line
+    for (int k = 0; k < 3; ++k) {
+        a->a_s[k] = stride(la, dim[k]);
+        a->b_s[k] = lb ? stride(lb, dim[k]) : 0;
+        a->y_s[k] = stride(st, dim[k]);
+        even &= ext[dim[k]] == 1 || a->y_s[k] % (int64_t)line == 0;
+    }
+    // (masked softmax fp32 [96, 1411, 1411] 293 -> 267 us by the filling up; [64, 1800, 1800] 344 us in rows as they come, 315 in
+    // blocks, 283 filled up; the blocks pay beyond 24 MB of mask: [32, 2500, 2500] 280 and 282, [32, 3500, 3500] 560 and 651)
+    // A second tensor that all indices of the second dim share (a mask under batch * heads) is read again from the cache of the die that
+    // read it before, if the same rows go to the same die every time: workgroups are dealt to the eight dies in turn, so the rows
+    // of an index are filled up to a multiple of eight workgroups.  A mask larger than the dies' caches hold is taken in blocks of rows, each for
+    // all indices before the next block.
+    a->limit = 0;
+    uint64_t all = rows;
+    uint32_t block = ext[dim[0]];
+    if (lb && ext[dim[2]] == 1 && ext[dim[1]] > 1 && block > 256 && a->b_s[1] == 0 && a->b_s[0] != 0) {
+        a->limit = block;
+        block = (uint64_t)block * cols * es <= (24u << 20) ? (block + 31) / 32 * 32 : 256 * cols * es < (4u << 20) ? 256 : 64;
+        all = (uint64_t)((a->limit + block - 1) / block) * block * ext[dim[1]];
+        a->a_s[2] = a->a_s[0] * block;
+        a->b_s[2] = a->b_s[0] * block;
+        a->y_s[2] = a->y_s[0] * block;
+    }
+    a->d1 = block;
+    a->d2 = ext[dim[1]];
+    magic_of(a->d1, &a->m1, &a->sh1);
+    magic_of(a->d2, &a->m2, &a->sh2);
+    a->ia = sh[S_TBASE] + (la[1] & 0xFF);
+    a->ib = lb ? sh[S_TBASE] + (lb[1] & 0xFF) : 0;
+    a->iy = sh[S_TBASE] + (st[1] & 0xFF);
+    // An output may be an input, element for element: a row is read before it is stored.  Any other overlap stays with the interpreter.
+    uint32_t shift = 0;
+    for (int k = 0; k < n_sets; ++k) {
+        void *const *t = tensors + (size_t)k * n_tensors;
+        auto span = [&](uint32_t i, uint64_t *lo, uint64_t *hi) {
+            const uint32_t *te = table + i * TT_WORDS;
+            *lo = (uint64_t)(uintptr_t)t[i];
+            *hi = *lo + ((uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32));
+        };
+        uint64_t ylo, yhi, lo, hi;
+        span(a->iy, &ylo, &yhi);
+        if (ylo % es != 0) return false;
+        for (int i = 0; i < (lb ? 2 : 1); ++i) {
+            span(i ? a->ib : a->ia, &lo, &hi);
+            if (lo % es != 0) return false;
+            if (lo >= yhi || ylo >= hi) continue;
+            for (int d = 0; d < 3; ++d)
+                if (lo != ylo || (ext[d] > 1 && stride(i ? lb : la, d) != stride(st, d))) return false;
+        }
+        const uint32_t at = (uint32_t)(ylo % 128) / es;
+        if (at > shift) shift = at;
+    }
+    if (!even) shift = line - 1;
+    a->shifted = shift != 0;
+    auto need = [&](uint32_t lanes) { return (uint32_t)((cols + shift + (uint64_t)lanes * V - 1) / ((uint64_t)lanes * V)); };
+    a->lanes = 0;
+    uint64_t best = UINT64_MAX;
+    for (uint32_t lanes = 8; lanes <= 1024; lanes *= 2) {
+        const uint32_t n = need(lanes);
+        if (n > (lanes == 1024 ? (dt ? 3u : 4u) : dt ? 6u : 8u)) continue;
+        const uint64_t cost = (uint64_t)lanes * n * (n > 4 && (dt || lanes != 64) ? 18 : 16) * (lanes > 64 ? 17 : 16);
+        if (cost < best) {
+            best = cost;
+            a->lanes = lanes;
+        }
+    }
+    a->in_long = a->lanes == 0;
+    if (a->in_long != 0) a->lanes = need(512) <= (dt ? 16u : 24u) ? 512 : 1024;
+    a->slots = need(a->lanes);
+    if (a->slots > (dt ? 20u : 33u)) return false;
+    a->tail = (uint32_t)(cols / ((uint64_t)a->lanes * V));
+    const uint64_t rp = a->lanes >= 256 ? 1 : 256 / a->lanes, tiles = (all + rp - 1) / rp;
+    if (all >= (1ull << 32) || tiles * (uint64_t)n_sets >= (1ull << 31)) return false;
+    a->rows = (uint32_t)all;
+    a->cols = (uint32_t)cols;
+    a->bf16 = dt;
+    a->set_tiles = (uint32_t)tiles;
+    magic_of(a->set_tiles, &a->set_m, &a->set_sh);
+    a->tiles = (uint32_t)(tiles * (uint64_t)n_sets);
+    a->a = tensors[a->ia];
+    a->b = lb ? tensors[a->ib] : nullptr;
+    a->y = tensors[a->iy];
+    return true;
+}
+
 int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *tensors_in, int n_tensors, void *hip_stream, bool static_ws,
              const Batch *batch) {
     if (!ctx || !bytecode || (!tensors_in && n_tensors > 0)) return dvm_set_error(DVM_E_ARGS, "dvm_run: null argument");
@@ -2262,14 +2423,39 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         apart |= last && k_max <= 32 && K == 64 && NR <= 2 && block <= 256 && !cred;
     }
     const bool rotates = (w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL;
-    if (grid_sync) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws);
+    if (grid_sync) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, (uint32_t)WS_SYNC_WORDS);
     hipError_t e;
-    // one kernel launch per run of segments up to the next one that asks for a launch of its own
+    // one kernel launch per run of segments up to the next one that asks for a launch of its own, or is a softmax that gets one
+    dvm_softmax_args sm;
+    uint32_t sm_at = 0;                 // the segment that `sm` describes + 1
+    auto is_softmax = [&](uint32_t s, const uint32_t *sh) {
+        if (!plain_softmax(sh, w + PH_WORDS_N, tensors, n_sets, ntens, &sm)) return false;
+        sm_at = s + 1;
+        return true;
+    };
     for (uint32_t first = 0; first < w[PH_NSEG];) {
         uint32_t end = first + 1;
+        bool softmax = false;
         for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; ++s) {
-            if (s > first && s == end && !(w[at + S_FLAGS] & SF_NEW_LAUNCH)) ++end;
+            if (s == first) softmax = sm_at == s + 1 || is_softmax(s, w + at);
+            if (s > first && s == end && !softmax && !(w[at + S_FLAGS] & SF_NEW_LAUNCH) && !is_softmax(s, w + at)) ++end;
             at += w[at + S_WORDS];
+        }
+        if (softmax) {              // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
+            int n_cu = 256;
+            dvm_ctx_planner_get(ctx, &n_cu, nullptr);
+            sm.sets = ka.sets;
+            sm.n_tensors = ntens;
+            // (the kernel for long rows loads a workgroup's next row while it stores the one before: as many workgroups as are resident)
+            const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
+            const uint32_t grid = sm.in_long != 0 && sm.tiles > most ? most : sm.tiles;
+            e = (hipError_t)dvm_softmax_launch(&sm, grid, hip_stream);
+            if (e != hipSuccess) {
+                t_last_hip_error = (int)e;
+                return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
+            }
+            first = end;
+            continue;
         }
         ka.seg_first = first;
         ka.nseg = end;
@@ -2341,6 +2527,8 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
                 if (want > grid || (apart && want > 0)) grid = (uint32_t)want;
             }
         }
+        // (every launch counts its arrivals at grid-wide waits from zero; the status word stays)
+        if (grid_sync && first != 0) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, 1u);
         dvm_colreduce_args ca;
         uint32_t cgrid = 0, cblock = 0;
         const uint32_t *first_sh = w + segs_off;
