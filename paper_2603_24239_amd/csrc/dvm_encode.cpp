@@ -2067,7 +2067,10 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
             // (with plenty of rows a workgroup of four waves is the smallest candidate: tiles of 8 KiB and more per
             // tensor measured 3-4 % faster than the same rows dealt out two waves at a time)
             uint32_t rp_first = step;
-            if (rp_max > step && E.nrows * copies >= (int64_t)8 * ctx->n_cu * rp_max) rp_first = rp_max;
+            // (several copies share a launch whose workgroups are those of its largest program, four waves: a tile of one wave leaves
+            // three idle, so four as long as every compute unit gets one)
+            if (rp_max > step && (E.nrows * copies >= (int64_t)8 * ctx->n_cu * rp_max || (copies > 1 && E.nrows * copies >= (int64_t)ctx->n_cu * rp_max)))
+                rp_first = rp_max;
             int64_t best_cost = -1;
             RP = rp_first;
             for (uint32_t rp = rp_first; rp <= (rp_max > step ? rp_max : step); rp += step) {
@@ -2100,11 +2103,12 @@ extern "C" int dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog, const dvm_sh
         // Columns per tile by the cost model, over whole chunk slots only (every lane holds the same number of chunks): a slot
         // is executed whole whatever part of it is filled, and a tile that ends inside one takes the predicated stores on
         // every tile instead of on the row's last one.
-        const int64_t slot = (int64_t)G * V;
+        // A tile's fixed part (decode, addresses, one latency of memory) costs what a slot does at the default overhead.
+        const int64_t slot = (int64_t)G * V, fixed = ovh * slot / 512;
         int64_t best_cost = -1, tc = t_max;
         for (int64_t c = t_max; c >= slot; c -= slot) {
             const int64_t tiles = E.nrows * cdiv(E.D0, c) * copies;
-            const int64_t cost = tiles >= 3 * N ? tiles * (c + ovh) / N : cdiv(tiles, N) * (c + ovh);
+            const int64_t cost = tiles >= 3 * N ? tiles * (c + fixed) / N : cdiv(tiles, N) * (c + fixed);
             if (best_cost < 0 || cost < best_cost) { best_cost = cost; tc = c; }
         }
         TC = (uint32_t)tc;
