@@ -48,6 +48,7 @@ typedef struct dvm_softmax_args {
     uint32_t in_long;               // 1: the kernel for long rows (lanes: 512 or 1024)
     uint32_t slots;                 // 16-byte chunks of a lane
     uint32_t tail;                  // a row may end in this slot of chunks or behind it
+    uint32_t stream;                // 1: larger than the last-level cache holds, read past it
     uint32_t shifted;               // some row does not start on a 128-byte line of the output
 } dvm_softmax_args;
 constexpr int64_t DVM_SOFTMAX_MIN_BYTES = 16 << 20;

@@ -85,6 +85,9 @@ template <int BF16> DI u32x4 narrow(const float *v, float scale) {
     }
     return r;
 }
+// (closes a branch of loads with the streaming hint, which the compiler would otherwise merge with the branch of those without it, dropping
+// the hint)
+#define STREAMING() asm volatile("; streaming" ::: "memory")
 template <bool NT> DI u32x4 load16(const char *p) {
     if constexpr (NT) return __builtin_nontemporal_load((const GLOBAL_AS u32x4_a2 *)p);
     else return *(const GLOBAL_AS u32x4_a2 *)p;
@@ -214,9 +217,16 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
         const int c_first = at - r.shift;
         auto col = [&](int c0) { const int c = c0 < cmax ? c0 : cmax; return c > 0 ? c : 0; };
         u32x4 raw[NR], rawb[MASK ? NR : 1];
+        if (s.stream != 0) {        // (the same for every lane)
 #pragma unroll
-        for (int j = 0; j < NR; ++j)
-            if (j < NR / 2 || j < (int)s.slots) raw[j] = load16<true>(r.a + (int64_t)col(c_first + j * W) * ES);
+            for (int j = 0; j < NR; ++j)
+                if (j < NR / 2 || j < (int)s.slots) raw[j] = load16<true>(r.a + (int64_t)col(c_first + j * W) * ES);
+            STREAMING();
+        } else {
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (j < NR / 2 || j < (int)s.slots) raw[j] = load16<false>(r.a + (int64_t)col(c_first + j * W) * ES);
+        }
         if constexpr (MASK) {
 #pragma unroll
             for (int j = 0; j < NR; ++j)

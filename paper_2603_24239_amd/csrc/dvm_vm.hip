@@ -445,6 +445,9 @@ DI void st_b16(gptr p, uint32_t v, bool ok) {
 // tile's last chunk instead: the value is never stored and reductions mask it.  Dtype, chunk width and cache hint
 // are fixed at compile time, so the request needs no per-piece scalar arithmetic.  NT: the data is read once,
 // hint the caches accordingly.
+// DVM_STREAMING closes a branch of loads with the streaming hint: the compiler would merge it with the branch of the same loads without
+// the hint and drop the hint (all of them in the general instantiation, those of fp32 tensors in the wide one): fp32 add over 45M elements 104 us so merged, 97 apart.
+#define DVM_STREAMING() asm volatile("; streaming" ::: "memory")
 typedef f32x4 f32x4_a2 __attribute__((aligned(2)));
 template <bool NT> DI f32x4 ld_b128(gcptr q) {
     const GLOBAL_AS f32x4_a2 *src = (const GLOBAL_AS f32x4_a2 *)q;
@@ -471,6 +474,7 @@ template <int K, int DT, int V, bool NT> DI void request_inplace(Tile<K> &t, gcp
                     t.q[K / 8 + J] = ld_b128<NT>(q);        // raw bits, widened by finish_tile
                 }
             });
+            if constexpr (NT) DVM_STREAMING();
         }
     }
 }
@@ -716,6 +720,7 @@ template <int K, int DT, int V, bool NT> DI void issue_wide(Tile<K> &t, const ch
             t.q[K / 8 + J] = ld_b128<NT>(q);
         }
     });
+    if constexpr (NT) DVM_STREAMING();
 }
 // The offsets are computed before the destination register is selected: inside the selected case nothing but
 // the load instructions may write a register, or the compiler would compute addresses in the registers the
@@ -2329,6 +2334,11 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     return true;
 }
 
+// Loads take the streaming hint in launches that touch more than the last-level cache holds.  Within it, what the program before wrote
+// or this one read last time may still be there: RMSNorm bf16 [11000, 4096] (180 MB) 30.8 us without the hint, 36.5 with it, RoPE over 8111 tokens
+// (133 MB) 31.6 and 38.1; beyond it the hint pays (a 32-layer step of 512 tokens 603 us without, 592 with it).
+constexpr uint64_t STREAM_MIN_BYTES = 256ull << 20;
+
 int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *tensors_in, int n_tensors, void *hip_stream, bool static_ws,
              const Batch *batch) {
     if (!ctx || !bytecode || (!tensors_in && n_tensors > 0)) return dvm_set_error(DVM_E_ARGS, "dvm_run: null argument");
@@ -2470,6 +2480,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             int n_cu = 256;
             dvm_ctx_planner_get(ctx, &n_cu, nullptr);
             sm.sets = ka.sets;
+            sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 4u : 8u) * (uint64_t)n_sets >= STREAM_MIN_BYTES;
             sm.n_tensors = ntens;
             // (the kernel for long rows loads a workgroup's next row while it stores the one before: as many workgroups as are resident)
             const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
@@ -2485,7 +2496,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         ka.seg_first = first;
         ka.nseg = end;
         ka.set_tiles = 0;
-        uint64_t total = 0, bytes = 0;      // of this launch
+        uint64_t total = 0, bytes = 0, touched = 0;     // of this launch (touched: without what lies between the rows of views)
         uint32_t k_need = 0;                // elements per lane its segments use
         bool round_robin = true;
         for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s) {
@@ -2497,7 +2508,19 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             if (k > k_need) k_need = k;
             for (uint32_t i = 0; i < sh[S_NTENS]; ++i) {
                 const uint32_t *te = w + PH_WORDS_N + (sh[S_TBASE] + i) * TT_WORDS;
-                bytes += (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
+                const uint64_t span = (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
+                const uint64_t whole = (uint64_t)sh[S_NROWS] * ((uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32)) * ((te[TT_INFO] & 0xFF) == DVM_BF16 ? 2u : 4u);
+                bytes += span;
+                touched += whole < span ? whole : span;
+            }
+        }
+        // (streaming loads go past the last-level cache)
+        const bool stream = touched * (uint64_t)n_sets >= STREAM_MIN_BYTES;
+        for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s) {
+            if (s < first) continue;
+            for (uint32_t pc = at + SH_WORDS; pc < at + w[at + S_WORDS]; pc += (w[pc] >> 8) & 0xFF) {
+                const uint32_t op = w[pc] & 0xFF;
+                if (op == I_LOAD || op == I_VLOAD) ka.code[pc + 1 - segs_off] = stream ? w[pc + 1] : w[pc + 1] & ~(MF_STREAM << 16);
             }
         }
         ka.set_tiles = (uint32_t)total;
@@ -2563,6 +2586,15 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         uint32_t cgrid = 0, cblock = 0;
         const uint32_t *first_sh = w + segs_off;
         for (uint32_t s = 0; s < first; ++s) first_sh += first_sh[S_WORDS];
+        // A large launch of one segment spreads its tiles over eight times the workgroups that are resident: those that walk many tiles
+        // drift apart, and the memory in use with them, while the dispatcher starts the next ones in order (fp32 add over 45M elements 93.6 -> 87.2 us,
+        // RMSNorm bf16 [42648, 4096] 127 -> 119).  A prologue (pinned operands) runs in every workgroup: each of its records wants two and a
+        // half tiles behind it (LayerNorm bf16 [163840, 2048] 250 -> 241, but [81920, 1024], with one tile behind two, 63 -> 68).
+        if (w[PH_NSEG] == 1 && n_sets == 1 && !cred && !longrow && stream && (first_sh[S_FLAGS] & SF_INTERLEAVED) && !(first_sh[S_FLAGS] & SF_LDS)) {
+            uint32_t records = 0;
+            for (uint32_t pc = SH_WORDS; pc < SH_WORDS + first_sh[S_PROLOG]; pc += (first_sh[pc] >> 8) & 0xFF) ++records;
+            if (records == 0 || 2 * total >= 5ull * records * 8u * grid) grid = total < 8ull * grid ? (uint32_t)total : 8u * grid;
+        }
         if (cred && end == first + 1 && !batch && plain_colreduce(ctx, first_sh, ka.tensors, ka.aliased != 0, &ca, &cgrid, &cblock))
             e = (hipError_t)dvm_colreduce_launch(&ca, cgrid, cblock, hip_stream);
         else
