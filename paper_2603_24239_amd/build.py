@@ -46,7 +46,8 @@ def build(verbose: bool = True) -> str:
             ([hipcc, *COMMON, *DEVICE, "-c", vm], os.path.join(CSRC, "dvm_vm_host.o")),
             ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_bench.hip")], os.path.join(CSRC, "dvm_bench.o")),
             ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_colreduce.hip")], os.path.join(CSRC, "dvm_colreduce.o")),
-            ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_softmax.hip")], os.path.join(CSRC, "dvm_softmax.o"))]
+            ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_softmax.hip")], os.path.join(CSRC, "dvm_softmax.o")),
+            ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_rotary.hip")], os.path.join(CSRC, "dvm_rotary.o"))]
     # every interpreter variant is a translation unit of its own, compiled side by side
     for k, nr, maxt, waves in variants():
         defs = [f"-DDVM_VARIANT_K={k}", f"-DDVM_VARIANT_NR={nr}", f"-DDVM_VARIANT_MAXT={maxt}", f"-DDVM_VARIANT_WAVES={waves}"]

@@ -53,6 +53,23 @@ typedef struct dvm_softmax_args {
 } dvm_softmax_args;
 constexpr int64_t DVM_SOFTMAX_MIN_BYTES = 16 << 20;
 int dvm_softmax_launch(const dvm_softmax_args *a, unsigned grid, void *stream);
+// A rotation of pairs over short rows as its own kernel takes it (dvm_rotary.hip): tensors in the order x1, x2, c, s, y1, y2; strides in elements.
+typedef struct dvm_rotary_args {
+    uint64_t p[6];                  // addresses
+    uint64_t sets;                  // batched launch: device array of n_sets * n_tensors addresses (0: `p`)
+    int64_t s[6][3];                // strides of the outer dims, the first of them varying fastest from row to row
+    uint32_t at[6], n_tensors;      // where the six stand in a set
+    uint32_t d1, m1, sh1, d2, m2, sh2;      // extents of the first two outer dims and the multiply-shift constants that divide by them
+    uint32_t rows;                  // of a set
+    uint32_t groups;                // waves' shares of rows, of all sets
+    uint32_t set_groups, set_m, set_sh;     // of one set
+    uint32_t log2_lanes;            // lanes on a row, of 16 bytes of x each
+    uint32_t rows_per_lane;         // 4: rows of one index of the dims behind the first, along which the tables do not change; else 1
+    uint32_t fused;                 // y2: 0: both products rounded, 1: x2 c fused into the sum, 2: x1 s
+    uint32_t x_bf16, t_bf16;        // x1, x2, y1, y2; c, s
+    uint32_t stream;                // 1: larger than the last-level cache holds, read past it
+} dvm_rotary_args;
+int dvm_rotary_launch(const dvm_rotary_args *a, void *stream);
 // Implemented in the device file so that the encoder object stays free of HIP calls.
 int dvm_ctx_query_device(int hip_device, int *n_cu);
 

@@ -2334,6 +2334,151 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     return true;
 }
 
+// A segment that is a rotation of pairs, y1 = x1 c - x2 s and y2 = x2 c + x1 s, over rows of a power of two of 16-byte chunks (64 at most), as
+// the arguments of the kernel for those.  The records may come in many forms (registers, products that ride along, inputs loaded twice), so
+// they are evaluated on symbols first; the kernel rounds where the form does, and its bits are the interpreter's.
+bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const *tensors, int n_sets, uint32_t n_tensors, dvm_rotary_args *a) {
+    if (sh[S_INNER] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_LDS | SF_CSTREAM | SF_LONGROW)) || sh[S_NTENS] != 6 || sh[S_NCT] != 1) return false;
+    const uint64_t cols = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
+    if (cols > 512 || cols == 0) return false;
+    struct Expr { uint8_t kind, a, b, c; };         // kind: 0 nothing, 1 tensor a, 2 a * b, 3 a - b, 4 a + b, 5 fma(a, b, c)
+    Expr e[64] = {};
+    uint32_t n_e = 1, reg[8] = {};                  // (value 0: nothing known); registers 0 .. 5 and, last, the accumulator
+    constexpr uint32_t ACC = 7;
+    const uint32_t *rec_of[6] = {};                 // a record that loads or stores each tensor
+    uint32_t out_expr[2] = {}, out_tensor[2] = {}, n_out = 0;
+    auto make = [&](uint8_t k, uint32_t x, uint32_t y, uint32_t z) { e[n_e] = Expr{k, (uint8_t)x, (uint8_t)y, (uint8_t)z}; return n_e++; };
+    auto slot = [&](uint32_t r) { return r == SRC_ACC ? ACC : r; };
+    for (const uint32_t *r = sh + SH_WORDS, *end = r + sh[S_CODESIZE]; r < end; r += (r[0] >> 8) & 0xFF) {
+        const uint32_t op = r[0] & 0xFF, ra = (r[0] >> 16) & 0xFF, rb = r[0] >> 24;
+        if (n_e + 2 > 64) return false;
+        if (op == I_LOAD || op == I_VLOAD) {
+            const uint32_t t = r[1] & 0xFF;
+            if (t >= 6 || (ra != SRC_ACC && ra > 5)) return false;
+            if (rec_of[t] && memcmp(rec_of[t] + 2, r + 2, ((r[0] >> 8) & 0xFF) * 4 - 8) != 0) return false;
+            rec_of[t] = r;
+            reg[slot(ra)] = make(1, t, 0, 0);
+        } else if (op == I_STORE || op == I_VSTORE) {
+            if (n_out == 2 || rb != 0 || (ra != SRC_ACC && ra > 5)) return false;
+            rec_of[r[1] & 0xFF] = r;
+            out_tensor[n_out] = r[1] & 0xFF;
+            out_expr[n_out++] = reg[slot(ra)];
+        } else if (op == I_MOVRA && ra < 6) {
+            reg[ra] = reg[ACC];
+        } else if (op == I_MOVAR && ra < 6) {
+            reg[ACC] = reg[ra];
+        } else if (op == I_BIN && ra < 6 && (rb == B_MUL || rb == B_SUB || rb == B_RSUB || rb == B_ADD)) {
+            reg[ACC] = rb == B_RSUB ? make(3, reg[ra], reg[ACC], 0) : make(rb == B_MUL ? 2 : rb == B_SUB ? 3 : 4, reg[ACC], reg[ra], 0);
+        } else if (op == I_MAC && ra < 6 && rb < 6) {
+            if (r[1] == MAC_ADD) {
+                reg[ACC] = make(5, reg[ra], reg[rb], reg[ACC]);
+            } else {
+                const uint32_t p = make(2, reg[ra], reg[rb], 0);
+                reg[ACC] = r[1] == MAC_SUB ? make(3, reg[ACC], p, 0) : make(3, p, reg[ACC], 0);
+            }
+        } else if (op == I_FMA && ra < 6 && r[1] == 0 && rb < 6 && rb != FMA_NO_ADDEND) {
+            reg[ACC] = nr <= 4 ? make(5, reg[ACC], reg[ra], reg[rb]) : make(4, make(2, reg[ACC], reg[ra], 0), reg[rb], 0);     // (as the variants take it)
+        } else {
+            return false;
+        }
+    }
+    if (n_out != 2 || out_tensor[0] == out_tensor[1]) return false;
+    for (int k = 0; k < 6; ++k)
+        if (!rec_of[k]) return false;
+    // the two products of a sum or difference, as pairs of tensors
+    auto product = [&](uint32_t x, uint32_t *p) {
+        if (e[x].kind != 2 || e[e[x].a].kind != 1 || e[e[x].b].kind != 1) return false;
+        p[0] = e[e[x].a].a;
+        p[1] = e[e[x].b].a;
+        return true;
+    };
+    int one = e[out_expr[0]].kind == 3 ? 0 : 1;
+    const Expr d = e[out_expr[one]], s = e[out_expr[1 - one]];
+    uint32_t p[2], q[2], u[2], w[2];
+    if (d.kind != 3 || !product(d.a, p) || !product(d.b, q)) return false;
+    uint32_t fused = 0;
+    if (s.kind == 4) {
+        if (!product(s.a, u) || !product(s.b, w)) return false;
+    } else if (s.kind == 5) {
+        if (e[s.a].kind != 1 || e[s.b].kind != 1 || !product(s.c, w)) return false;
+        u[0] = e[s.a].a;
+        u[1] = e[s.b].a;
+        fused = 1;
+    } else {
+        return false;
+    }
+    auto is = [](const uint32_t *x, uint32_t y, uint32_t z) { return (x[0] == y && x[1] == z) || (x[0] == z && x[1] == y); };
+    bool found = false;
+    uint32_t x1 = 0, x2 = 0, c = 0, sn = 0;
+    for (int k = 0; k < 4 && !found; ++k) {
+        x1 = p[k & 1]; c = p[1 - (k & 1)]; x2 = q[k >> 1]; sn = q[1 - (k >> 1)];
+        if (is(u, x2, c) && is(w, x1, sn)) found = true;
+        else if (is(u, x1, sn) && is(w, x2, c)) { found = true; fused *= 2; }
+    }
+    if (!found || x1 == x2 || c == sn || x1 == sn || x2 == c) return false;
+    const uint32_t t[6] = {x1, x2, c, sn, out_tensor[one], out_tensor[1 - one]};
+    auto dtype = [&](int k) { return (rec_of[t[k]][1] >> 8) & 0xFF; };
+    a->x_bf16 = dtype(0);
+    a->t_bf16 = dtype(2);
+    if (dtype(1) != a->x_bf16 || dtype(4) != a->x_bf16 || dtype(5) != a->x_bf16 || dtype(3) != a->t_bf16 || (a->t_bf16 && !a->x_bf16)) return false;
+    const uint32_t V = a->x_bf16 ? 8 : 4, es = a->x_bf16 ? 2 : 4;
+    if (cols % V != 0 || (cols / V & (cols / V - 1)) != 0 || cols / V > 64) return false;
+    a->log2_lanes = 0;
+    while ((V << a->log2_lanes) < cols) ++a->log2_lanes;
+    const uint64_t rows = sh[S_NROWS];
+    uint32_t ext[3] = {(uint32_t)rows, 1, 1};
+    if (sh[S_D1] != 0) {
+        ext[0] = sh[S_D1];
+        ext[1] = (uint32_t)(rows / sh[S_D1]);
+        if (sh[S_D2] != 0) {
+            ext[2] = ext[1] / sh[S_D2];
+            ext[1] = sh[S_D2];
+        }
+    }
+    if (rows == 0) return false;
+    for (int k = 0; k < 6; ++k) {
+        const uint32_t *r = rec_of[t[k]];
+        const bool view = (r[0] & 0xFF) == I_VLOAD || (r[0] & 0xFF) == I_VSTORE;
+        for (int i = 0; i < 3; ++i) a->s[k][i] = i == 0 || view ? (int64_t)((uint64_t)r[2 + 2 * i] | ((uint64_t)r[3 + 2 * i] << 32)) : 0;
+        a->at[k] = sh[S_TBASE] + t[k];
+        a->p[k] = (uint64_t)(uintptr_t)tensors[a->at[k]];
+    }
+    // Outputs apart from the inputs, and from each other (two halves of the same rows are)
+    for (int k = 0; k < n_sets; ++k) {
+        uint64_t lo[6], hi[6];
+        for (int i = 0; i < 6; ++i) {
+            const uint32_t *te = table + a->at[i] * TT_WORDS;
+            lo[i] = (uint64_t)(uintptr_t)tensors[(size_t)k * n_tensors + a->at[i]];
+            hi[i] = lo[i] + ((uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32));
+            if (lo[i] % (dtype(i) ? 2 : 4) != 0) return false;
+        }
+        for (int o = 4; o < 6; ++o)
+            for (int i = 0; i < 4; ++i)
+                if (lo[i] < hi[o] && lo[o] < hi[i]) return false;
+        if (lo[4] < hi[5] && lo[5] < hi[4]) {
+            const uint64_t apart = lo[4] < lo[5] ? lo[5] - lo[4] : lo[4] - lo[5];
+            if (apart < cols * es) return false;
+            for (int i = 0; i < 3; ++i)
+                if (a->s[4][i] != a->s[5][i] || (ext[i] > 1 && (a->s[4][i] < 0 || (uint64_t)a->s[4][i] * es < apart + cols * es))) return false;
+        }
+    }
+    a->d1 = ext[0];
+    a->d2 = ext[1];
+    magic_of(a->d1, &a->m1, &a->sh1);
+    magic_of(a->d2, &a->m2, &a->sh2);
+    const uint32_t rw = 64u >> a->log2_lanes;
+    a->rows_per_lane = ext[0] % (4 * rw) == 0 && a->s[2][0] == 0 && a->s[3][0] == 0 ? 4 : 1;
+    const uint64_t per = (uint64_t)rw * a->rows_per_lane, groups = (rows + per - 1) / per;
+    if (groups * (uint64_t)n_sets >= (1ull << 31)) return false;
+    a->rows = (uint32_t)rows;
+    a->set_groups = (uint32_t)groups;
+    magic_of(a->set_groups, &a->set_m, &a->set_sh);
+    a->groups = (uint32_t)(groups * (uint64_t)n_sets);
+    a->fused = fused;
+    a->n_tensors = n_tensors;
+    return true;
+}
+
 // Loads take the streaming hint in launches that touch more than the last-level cache holds.  Within it, what the program before wrote
 // or this one read last time may still be there: RMSNorm bf16 [11000, 4096] (180 MB) 30.8 us without the hint, 36.5 with it, RoPE over 8111 tokens
 // (133 MB) 31.6 and 38.1; beyond it the hint pays (a 32-layer step of 512 tokens 603 us without, 592 with it).
@@ -2468,6 +2613,17 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         sm_at = s + 1;
         return true;
     };
+    dvm_rotary_args ra;
+    if (w[PH_NSEG] == 1 && plain_rotary(w + segs_off, NR, w + PH_WORDS_N, tensors, n_sets, ntens, &ra)) {
+        ra.sets = ka.sets;
+        ra.stream = (uint64_t)ra.rows * (uint64_t)(((uint64_t)w[segs_off + S_D0LO]) * (ra.x_bf16 ? 8u : 16u)) * (uint64_t)n_sets >= STREAM_MIN_BYTES;
+        e = (hipError_t)dvm_rotary_launch(&ra, hip_stream);
+        if (e != hipSuccess) {
+            t_last_hip_error = (int)e;
+            return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
+        }
+        return DVM_OK;
+    }
     for (uint32_t first = 0; first < w[PH_NSEG];) {
         uint32_t end = first + 1;
         bool softmax = false;
