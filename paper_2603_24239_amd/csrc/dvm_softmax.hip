@@ -422,6 +422,128 @@ __global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_args s) 
     }
 }
 
+// ---- rows as the interpreter lays them out --------------------------------------------------------------------------------
+// Smaller programs with a launch to themselves (bf16 [3200, 13] 12.6 -> 11.6 us a call, [32000, 120] 12.6 -> 11.5: less to fetch and no decoding).  The chunks of a row start with the row, G lanes hold it as in the segment's plan, and everything is
+// added in the interpreter's order -- a lane's elements one after the other (where the row does not fill the tile: chunk by chunk), then the lanes --
+// so that the bits are the interpreter's, whichever of the two a launch runs in.  G: 1 to 64.  PART: rows narrower than a chunk, one lane each.
+template <int BF16, int NR, bool MASK, bool PART>
+__global__ void __launch_bounds__(256) dvm_softmax_exact(const dvm_softmax_args s) {
+    constexpr int V = BF16 ? 8 : 4, ES = BF16 ? 2 : 4;
+    const uint32_t G = s.lanes, lg = s.log2_lanes;
+    const uint32_t g = threadIdx.x >> lg, l = threadIdx.x & (G - 1u), RP = 256u >> lg;
+    const int cols = (int)s.cols, cmax = cols - V, W = (int)G * V;
+    auto value = [&](const char *p) {       // one element
+        if constexpr (BF16) return bf16_lo(*(const GLOBAL_AS uint16_t *)p);
+        else return *(const GLOBAL_AS float *)p;
+    };
+    auto all = [&]<bool MAX>(float v) {     // over the G lanes of a row
+        if (G >= 2) v = comb<MAX>(v, dpp<0xB1>(v));
+        if (G >= 4) v = comb<MAX>(v, dpp<0x4E>(v));
+        if (G >= 8) v = comb<MAX>(v, dpp<0x141>(v));
+        if (G >= 16) v = comb<MAX>(v, dpp<0x140>(v));
+        if (G >= 32) v = comb<MAX>(v, __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F)));
+        if (G >= 64) v = comb<MAX>(lane_of(v, 0), lane_of(v, 32));
+        return v;
+    };
+    for (uint32_t tile = blockIdx.x; tile < s.tiles; tile += gridDim.x) {
+        const uint32_t set = s.sets != 0 ? magic_div(tile, s.set_m, s.set_sh) : 0u;
+        uint32_t row = (tile - set * s.set_tiles) * RP + g;
+        const bool ok = row < s.rows;
+        row = ok ? row : s.rows - 1u;
+        const Row r = place<BF16, MASK>(s, set, row);
+        float v[NR][V];
+        if constexpr (PART) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[0][e] = value(r.a + (e < cols ? e : 0) * ES);
+            if constexpr (MASK) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[0][e] += value(r.b + (e < cols ? e : 0) * ES);
+            }
+        } else {
+            u32x4 raw[NR], rawb[MASK ? NR : 1];
+            auto at = [&](int j) { const int c = (int)l * V + j * W; return (int64_t)(c < cmax ? c : cmax) * ES; };
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (j < NR / 2 || j < (int)s.slots) raw[j] = load16<false>(r.a + at(j));
+            if constexpr (MASK) {
+#pragma unroll
+                for (int j = 0; j < NR; ++j)
+                    if (j < NR / 2 || j < (int)s.slots) rawb[j] = load16<false>(r.b + at(j));
+            }
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (j < NR / 2 || j < (int)s.slots) {
+                    widen<BF16>(v[j], raw[j]);
+                    if constexpr (MASK) {
+                        float b[V];
+                        widen<BF16>(b, rawb[j]);
+#pragma unroll
+                        for (int e = 0; e < V; ++e) v[j][e] += b[e];
+                    }
+                }
+        }
+        float m = NEG_INF;
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+            if (j < NR / 2 || j < (int)s.slots) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) m = maxp(m, PART && e >= cols ? NEG_INF : v[j][e]);
+            }
+        m = all.template operator()<true>(m);
+        float sum = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+            if (j < NR / 2 || j < (int)s.slots) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[j][e] = __builtin_amdgcn_exp2f((v[j][e] - m) * LOG2E);
+                if constexpr (PART) {
+#pragma unroll
+                    for (int e = 0; e < V; ++e) sum += e < cols ? v[j][e] : 0.0f;
+                } else if (s.ragged == 0) {         // (the same for every lane)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) sum += v[j][e];
+                } else {
+                    const int c0 = (int)l * V + j * W, dup = c0 - cmax;         // elements that a chunk which slid back repeats
+                    float c = 0.0f;
+                    if (j < (int)s.tail) {          // (a slot that lies inside the row)
+#pragma unroll
+                        for (int e = 0; e < V; ++e) c += v[j][e];
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < V; ++e) c += e >= dup ? v[j][e] : 0.0f;
+                    }
+                    sum += c0 < cols ? c : 0.0f;
+                }
+            }
+        const float scale = __builtin_amdgcn_rcpf(all.template operator()<false>(sum));
+        if constexpr (PART) {
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (ok && e < cols) {
+                    if constexpr (BF16) *(GLOBAL_AS uint16_t *)(r.y + e * ES) = (uint16_t)pack_bf16x2(v[0][e] * scale, 0.0f);
+                    else *(GLOBAL_AS float *)(r.y + e * ES) = v[0][e] * scale;
+                }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NR; ++j)
+                if (j < NR / 2 || j < (int)s.slots) {
+                    const int c0 = (int)l * V + j * W;
+                    if (ok && c0 < cols) store16(r.y + (int64_t)(c0 < cmax ? c0 : cmax) * ES, narrow<BF16>(v[j], scale));
+                }
+        }
+    }
+}
+template <int BF16, bool MASK> int launch_exact(const dvm_softmax_args &s, unsigned grid, hipStream_t q) {
+#define GO(NR, PART) hipLaunchKernelGGL((dvm_softmax_exact<BF16, NR, MASK, PART>), dim3(grid), dim3(256), 0, q, s)
+    if (s.cols < (BF16 ? 8u : 4u)) GO(1, true);
+    else if (s.slots <= 1) GO(1, false);
+    else if (s.slots <= 2) GO(2, false);
+    else if (s.slots <= 4) GO(4, false);
+    else GO(8, false);
+#undef GO
+    return (int)hipGetLastError();
+}
+
 template <int BF16, int T, bool MASK> int launch_rows(const dvm_softmax_args &s, unsigned grid, hipStream_t q) {
     constexpr unsigned BLOCK = T < 256 ? 256 : T;
     if (s.slots <= 2) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 2, MASK>), dim3(grid), dim3(BLOCK), 0, q, s);
@@ -460,6 +582,10 @@ template <int BF16, bool MASK> int launch_any(const dvm_softmax_args &s, unsigne
 
 extern "C" int dvm_softmax_launch(const dvm_softmax_args *s, unsigned grid, void *stream) {
     const hipStream_t q = (hipStream_t)stream;
+    if (s->exact) {
+        if (s->bf16) return s->b ? launch_exact<1, true>(*s, grid, q) : launch_exact<1, false>(*s, grid, q);
+        return s->b ? launch_exact<0, true>(*s, grid, q) : launch_exact<0, false>(*s, grid, q);
+    }
     if (s->bf16) return s->b ? launch_any<1, true>(*s, grid, q) : launch_any<1, false>(*s, grid, q);
     return s->b ? launch_any<0, true>(*s, grid, q) : launch_any<0, false>(*s, grid, q);
 }

@@ -34,9 +34,10 @@ using namespace dvmbc;
 namespace {
 
 constexpr int CODE_WORDS = DVM_CODE_MAX_BYTES / 4;
+constexpr int MAX_SEGMENTS = CODE_WORDS / SH_WORDS;
 
 struct KArgs {
-    uint32_t code[CODE_WORDS];          // the segments of the program (headers + bodies)
+    uint32_t code[CODE_WORDS];          // the segments of this launch (headers + bodies)
     uint64_t tensors[DVM_MAX_TENSORS];  // device addresses
     uint64_t ws;                        // the launch's workspace (0: none)
     uint32_t nseg;
@@ -50,7 +51,6 @@ struct KArgs {
                                         // whole launch, counted over its segments and sets
     uint32_t set_tiles;                 // rotate = 1: tiles of one set (of this launch's segments), and the multiply-shift constants
     uint32_t set_m, set_sh;             // that divide by it
-    uint32_t seg_first;                 // this launch runs segments seg_first .. nseg - 1
     uint32_t aliased;                   // 1: some segment's output shares memory with another tensor of that segment
 };
 
@@ -1163,10 +1163,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
     for (uint32_t si = 0; si < args.nseg; ++si) {
         const uint32_t *sh = &code[seg];
         const uint32_t seg_words = sh[S_WORDS];
-        if (si < args.seg_first) {          // (a segment of an earlier launch of this program)
-            seg += seg_words;
-            continue;
-        }
         const uint32_t M = sh[S_NTILES];
         if (SKIP && args.rotate == 1 && gnext - gbase >= M) {
             gbase += M;
@@ -2183,7 +2179,7 @@ void magic_of(uint32_t d, uint32_t *m, uint32_t *sh) {
 
 // A segment that is a softmax along the row, of one tensor or of the sum of two, as the arguments of the kernel for those: load [, load,
 // add], max, exp of the difference, reciprocal of the sum, store of the product.  It takes segments that read and write at least
-// DVM_SOFTMAX_MIN_BYTES (rows longer than a tile, which the interpreter reads twice: an eighth of that): below, a launch is bound by its own
+// DVM_SOFTMAX_MIN_BYTES in a layout of its own (rows longer than a tile, which the interpreter reads twice: an eighth of that): below, a launch is bound by its own
 // cost, and in a stack an extra one (2 us) would cost more than it gives.  Rows of less than a line stay too (fp32 [400000, 9] 12.4 us
 // there and 18.0 here).  The rule looks at the segment alone, so that its bits are the same alone, in a stack and in a batched launch (in a
 // spatial stack, whose parts share one launch, it stays with the interpreter).
@@ -2191,7 +2187,8 @@ void magic_of(uint32_t d, uint32_t *m, uint32_t *sh) {
 // for the registers).  More than 4 cost an eighth for the waves they displace (not in fp32 rows of one wave), a row of several waves a
 // sixteenth for its barriers: bf16 [64000, 2000] 141 us in 256 lanes of 2 chunks, 99 in 128 of 3, 82 in 64 of 5; fp32 [31250, 4096] 169 in 128 of
 // 8, 161 in 256 of 4.  Longer rows go to the kernel that keeps one per workgroup.
-bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tensors, int n_sets, uint32_t n_tensors, dvm_softmax_args *a) {
+bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tensors, int n_sets, uint32_t n_tensors, bool may_exact,
+                   dvm_softmax_args *a) {
     if (sh[S_INNER] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_LDS | SF_CSTREAM)) || sh[S_NROWS] == 0) return false;
     const uint32_t *r = sh + SH_WORDS, *end = r + sh[S_CODESIZE];
     auto op_of = [&]() { return r < end ? r[0] & 0xFF : (uint32_t)I_COUNT; };
@@ -2229,7 +2226,19 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     const uint32_t es = dt ? 2 : 4, V = 16 / es, line = 128 / es;
     const uint64_t cols = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
     const uint64_t rows = sh[S_NROWS];
-    if (cols < line || cols > (1u << 24) || (int64_t)(rows * cols * es * 2) < (sh[S_FLAGS] & SF_LONGROW ? DVM_SOFTMAX_MIN_BYTES / 8 : DVM_SOFTMAX_MIN_BYTES)) return false;
+    if (cols > (1u << 24)) return false;
+    const int64_t bytes = (int64_t)(rows * cols * es * 2);
+    a->exact = cols < line || bytes < (sh[S_FLAGS] & SF_LONGROW ? DVM_SOFTMAX_MIN_BYTES / 8 : DVM_SOFTMAX_MIN_BYTES);
+    if (a->exact) {         // the interpreter's order: a choice of speed alone
+        const uint32_t G = sh[S_GEOM] & 0xFFFF, nvec = sh[S_GEOM] >> 24;
+        if (!may_exact || (sh[S_FLAGS] & SF_LONGROW) || sh[S_NCT] != 1 || ((sh[S_GEOM] >> 16) & 0xFF) != V || G > 64 || (G & (G - 1)) != 0 ||
+            nvec > 8 || (cols < V && G != 1)) return false;
+        a->lanes = G;
+        a->slots = nvec;
+        a->log2_lanes = 0;
+        while ((1u << a->log2_lanes) < G) ++a->log2_lanes;
+        a->ragged = cols != (uint64_t)G * nvec * V;
+    }
     // the outer dims and the strides along them, in the order of the output's strides: rows that follow each other in memory do so in the grid
     uint32_t ext[3] = {(uint32_t)rows, 1, 1};
     if (sh[S_D1] != 0) {
@@ -2264,7 +2273,7 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     a->limit = 0;
     uint64_t all = rows;
     uint32_t block = ext[dim[0]];
-    if (lb && ext[dim[2]] == 1 && ext[dim[1]] > 1 && block > 256 && a->b_s[1] == 0 && a->b_s[0] != 0) {
+    if (!a->exact && lb && ext[dim[2]] == 1 && ext[dim[1]] > 1 && block > 256 && a->b_s[1] == 0 && a->b_s[0] != 0) {
         a->limit = block;
         block = (uint64_t)block * cols * es <= (24u << 20) ? (block + 31) / 32 * 32 : 256 * cols * es < (4u << 20) ? 256 : 64;
         all = (uint64_t)((a->limit + block - 1) / block) * block * ext[dim[1]];
@@ -2304,8 +2313,8 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     if (!even) shift = line - 1;
     a->shifted = shift != 0;
     auto need = [&](uint32_t lanes) { return (uint32_t)((cols + shift + (uint64_t)lanes * V - 1) / ((uint64_t)lanes * V)); };
-    a->lanes = 0;
-    uint64_t best = UINT64_MAX;
+    if (!a->exact) a->lanes = 0;
+    uint64_t best = a->exact ? 0 : UINT64_MAX;
     for (uint32_t lanes = 8; lanes <= 1024; lanes *= 2) {
         const uint32_t n = need(lanes);
         if (n > (lanes == 1024 ? (dt ? 3u : 4u) : dt ? 6u : 8u)) continue;
@@ -2317,7 +2326,7 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     }
     a->in_long = a->lanes == 0;
     if (a->in_long != 0) a->lanes = need(512) <= (dt ? 16u : 24u) ? 512 : 1024;
-    a->slots = need(a->lanes);
+    if (!a->exact) a->slots = need(a->lanes);
     if (a->slots > (dt ? 20u : 33u)) return false;
     a->tail = (uint32_t)(cols / ((uint64_t)a->lanes * V));
     const uint64_t rp = a->lanes >= 256 ? 1 : 256 / a->lanes, tiles = (all + rp - 1) / rp;
@@ -2515,7 +2524,6 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     if (w[PH_GRID] == 0) return DVM_OK;   // an empty iteration space: nothing to launch, pointers may be null
 
     KArgs ka;
-    memcpy(ka.code, w + segs_off, (size_t)seg_words * 4);
     ka.ws = 0;
     for (uint32_t i = 0; i < ntens; ++i) {
         ka.tensors[i] = (uint64_t)(uintptr_t)tensors[i];
@@ -2530,37 +2538,39 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     ka.rotate = 0;
     ka.set_tiles = 0;
     ka.set_m = ka.set_sh = 0;
-    ka.seg_first = 0;
     ka.aliased = 0;
     ka.nseg = w[PH_NSEG];
     ka.spin_limit = (uint32_t)dvm_ctx_sync_limit(ctx);
 
     const int K = (int)(w[PH_VARIANT] & 0xFF), NR = (int)((w[PH_VARIANT] >> 8) & 0xFF);
     const uint32_t block = w[PH_BLOCK];
-    // A segment that reduces along the penultimate axis needs the instantiation that runs such segments,
-    // and LDS for the combination across waves: four floats per lane of every participating wave
-    uint32_t lds_bytes = 0;
-    bool cred = false, wide = true;     // wide: every segment spreads a row over whole waves
-    bool grid_sync = false, wg_sync = false, longrow = false, mac = false;
+    // What decides which instantiation a launch of some of the segments takes
+    struct Needs {
+        uint32_t lds_bytes = 0;         // the combination across waves of a reduction along the penultimate axis: four floats per lane of
+                                        // every participating wave; the images that prologues copy into LDS
+        bool longrow = false, mac = false, part = false;
+    };
+    bool wide = true;                   // every segment of the program spreads a row over whole waves
+    bool cred = false;                  // a segment that reduces along the penultimate axis needs the instantiation that runs such segments
+    bool grid_sync = false, wg_sync = false, longrow = false;
+    uint32_t seg_at[MAX_SEGMENTS];      // where the segments start
     uint8_t seg_of[DVM_MAX_TENSORS];    // the segment a tensor belongs to
     memset(seg_of, 0xFF, sizeof(seg_of));
+    if (w[PH_NSEG] > (uint32_t)MAX_SEGMENTS) return dvm_set_error(DVM_E_LIMIT, "dvm_run: bytecode exceeds the kernel-argument budget");
+    bool ordered = (w[PH_TYPE] & 0xFFFF) == KT_STACK_SPATIAL || ka.ws != 0;      // segments may depend on each other
     for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; ++s) {
         const uint32_t *sh = w + at;
-        const uint32_t rp = sh[S_RP] & 0xFFFF;
-        cred |= sh[S_INNER] != 0;
+        seg_at[s] = at;
         wide &= (sh[S_GEOM] & 0xFFFF) >= 64;
+        cred |= sh[S_INNER] != 0;
         grid_sync |= (sh[S_FLAGS] & SF_SYNC_GRID) != 0;
         wg_sync |= (sh[S_FLAGS] & SF_SYNC_WG) != 0;
         longrow |= (sh[S_FLAGS] & SF_LONGROW) != 0;
-        if (sh[S_FLAGS] & SF_LONGROW)
-            for (uint32_t pc = SH_WORDS; pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF) mac |= (sh[pc] & 0xFF) == I_MAC;
-        if (sh[S_INNER] != 0 && rp > 1 && rp * 64u * 16u > lds_bytes) lds_bytes = rp * 64u * 16u;
-        if (sh[S_FLAGS] & SF_LDS)           // the images the prologue copies into LDS
-            for (uint32_t pc = SH_WORDS; pc < SH_WORDS + sh[S_PROLOGA]; pc += (sh[pc] >> 8) & 0xFF)
-                if ((sh[pc] & 0xFF) == I_LDSCOPY && sh[pc + 2] + sh[pc + 3] > lds_bytes) lds_bytes = sh[pc + 2] + sh[pc + 3];
+        ordered |= (sh[S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID | SF_NEW_LAUNCH)) != 0;
         for (uint32_t t = 0; t < sh[S_NTENS]; ++t) seg_of[sh[S_TBASE] + t] = (uint8_t)s;
         at += sh[S_WORDS];
     }
+    for (uint32_t i = 0; i < ntens; ++i) ordered |= (w[PH_WORDS_N + i * TT_WORDS + TT_INFO] >> 24) != 0;
     // Segments of one launch run without order between them unless the bytecode says otherwise: see check_tensor_set
     const int n_sets = batch ? batch->n_sets : 1;
     for (int k = 0; k < n_sets; ++k) {
@@ -2578,19 +2588,20 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         ka.sets = (uint64_t)(uintptr_t)batch->table;
         ka.n_sets = (uint32_t)n_sets;
     }
-    // A last chunk that is handled element by element (see tile_cols) needs the instantiation that runs any launch.
-    bool part = false;
-    for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
-        const uint32_t *sh = w + at;
-        const uint32_t G = sh[S_GEOM] & 0xFFFF, V = (sh[S_GEOM] >> 16) & 0xFF;
-        const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32);
-        auto ends_in_part = [&](uint64_t ncols) {
-            const uint64_t full = ncols / V;
-            return ncols % V != 0 && (full == 0 || (G > 64 && ka.aliased != 0 && (full % G) % 64 == 0));
-        };
-        if (sh[S_NTILES] == 0) continue;
-        part |= ends_in_part(D0 - (uint64_t)(sh[S_NCT] - 1) * sh[S_TC]);
-    }
+    auto add_needs = [&](const uint32_t *sh, Needs *n) {
+        const uint32_t rp = sh[S_RP] & 0xFFFF, G = sh[S_GEOM] & 0xFFFF, V = (sh[S_GEOM] >> 16) & 0xFF;
+        n->longrow |= (sh[S_FLAGS] & SF_LONGROW) != 0;
+        if (sh[S_FLAGS] & SF_LONGROW)
+            for (uint32_t pc = SH_WORDS; pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF) n->mac |= (sh[pc] & 0xFF) == I_MAC;
+        if (sh[S_INNER] != 0 && rp > 1 && rp * 64u * 16u > n->lds_bytes) n->lds_bytes = rp * 64u * 16u;
+        if (sh[S_FLAGS] & SF_LDS)
+            for (uint32_t pc = SH_WORDS; pc < SH_WORDS + sh[S_PROLOGA]; pc += (sh[pc] >> 8) & 0xFF)
+                if ((sh[pc] & 0xFF) == I_LDSCOPY && sh[pc + 2] + sh[pc + 3] > n->lds_bytes) n->lds_bytes = sh[pc + 2] + sh[pc + 3];
+        // A last chunk that is handled element by element (see tile_cols) needs the instantiation that runs any launch.
+        if (sh[S_NTILES] == 0) return;
+        const uint64_t D0 = (uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32), ncols = D0 - (uint64_t)(sh[S_NCT] - 1) * sh[S_TC], full = ncols / V;
+        n->part |= ncols % V != 0 && (full == 0 || (G > 64 && ka.aliased != 0 && (full % G) % 64 == 0));
+    };
     if (cred && longrow)
         return dvm_set_error(DVM_E_UNSUPPORTED, "dvm_run: a launch holds both a reduction along the penultimate axis and rows longer than a tile");
     // Segments planned for 32 elements per lane or fewer that have a launch to themselves in a program of the 64-element variant
@@ -2605,13 +2616,10 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     const bool rotates = (w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL;
     if (grid_sync) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, (uint32_t)WS_SYNC_WORDS);
     hipError_t e;
-    // one kernel launch per run of segments up to the next one that asks for a launch of its own, or is a softmax that gets one
-    dvm_softmax_args sm;
-    uint32_t sm_at = 0;                 // the segment that `sm` describes + 1
-    auto is_softmax = [&](uint32_t s, const uint32_t *sh) {
-        if (!plain_softmax(sh, w + PH_WORDS_N, tensors, n_sets, ntens, &sm)) return false;
-        sm_at = s + 1;
-        return true;
+    // A softmax that runs apart (plain_softmax).  A smaller one, whose bits are the interpreter's, only where it is the whole program: in a batched
+    // stack its arithmetic hides behind the traffic of the other parts (a 32-layer step of 200 tokens 213 us, 219 with it apart).
+    auto softmax_of = [&](uint32_t s, dvm_softmax_args *sm) {
+        return plain_softmax(w + seg_at[s], w + PH_WORDS_N, tensors, n_sets, ntens, w[PH_NSEG] == 1, sm);
     };
     dvm_rotary_args ra;
     if (w[PH_NSEG] == 1 && plain_rotary(w + segs_off, NR, w + PH_WORDS_N, tensors, n_sets, ntens, &ra)) {
@@ -2624,15 +2632,32 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         }
         return DVM_OK;
     }
-    for (uint32_t first = 0; first < w[PH_NSEG];) {
-        uint32_t end = first + 1;
-        bool softmax = false;
-        for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; ++s) {
-            if (s == first) softmax = sm_at == s + 1 || is_softmax(s, w + at);
-            if (s > first && s == end && !softmax && !(w[at + S_FLAGS] & SF_NEW_LAUNCH) && !is_softmax(s, w + at)) ++end;
-            at += w[at + S_WORDS];
+    // The kernel launches: segments in a run share one.  A segment starts a run of its own where it asks for one, and a softmax that runs apart is
+    // one.  Segments that are independent of each other go first, all but those, in one launch.
+    uint32_t list[MAX_SEGMENTS], run_at[MAX_SEGMENTS + 1], n_runs = 0, n_list = 0;
+    bool apart_run[MAX_SEGMENTS];
+    dvm_softmax_args sm;
+    auto push = [&](uint32_t s, bool fresh, bool softmax) {
+        if (fresh || n_runs == 0) { apart_run[n_runs] = softmax; run_at[n_runs++] = n_list; }
+        list[n_list++] = s;
+    };
+    {
+        bool soft[MAX_SEGMENTS];
+        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) soft[s] = softmax_of(s, &sm);
+        if (ordered) {
+            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) push(s, soft[s] || (s > 0 && soft[s - 1]) || (w[seg_at[s] + S_FLAGS] & SF_NEW_LAUNCH), soft[s]);
+        } else {
+            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!soft[s]) push(s, false, false);
+            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (soft[s]) push(s, true, true);
         }
-        if (softmax) {              // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
+    }
+    run_at[n_runs] = n_list;
+    uint32_t vm_runs = 0;
+    for (uint32_t run = 0; run < n_runs; ++run) {
+        const uint32_t *segs = list + run_at[run];
+        const uint32_t n_segs = run_at[run + 1] - run_at[run];
+        if (apart_run[run]) {       // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
+            softmax_of(segs[0], &sm);
             int n_cu = 256;
             dvm_ctx_planner_get(ctx, &n_cu, nullptr);
             sm.sets = ka.sets;
@@ -2646,24 +2671,23 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
                 t_last_hip_error = (int)e;
                 return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
             }
-            first = end;
             continue;
         }
-        ka.seg_first = first;
-        ka.nseg = end;
+        ka.nseg = n_segs;
         ka.set_tiles = 0;
+        Needs need;
         uint64_t total = 0, bytes = 0, touched = 0;     // of this launch (touched: without what lies between the rows of views)
         uint32_t k_need = 0;                // elements per lane its segments use
         bool round_robin = true;
-        for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s) {
-            if (s < first) continue;
-            const uint32_t *sh = w + at;
+        for (uint32_t i = 0; i < n_segs; ++i) {
+            const uint32_t *sh = w + seg_at[segs[i]];
+            add_needs(sh, &need);
             total += sh[S_NTILES];
             round_robin &= (sh[S_FLAGS] & SF_INTERLEAVED) != 0;
             const uint32_t k = (sh[S_GEOM] >> 24) * ((sh[S_GEOM] >> 16) & 0xFF);
             if (k > k_need) k_need = k;
-            for (uint32_t i = 0; i < sh[S_NTENS]; ++i) {
-                const uint32_t *te = w + PH_WORDS_N + (sh[S_TBASE] + i) * TT_WORDS;
+            for (uint32_t t = 0; t < sh[S_NTENS]; ++t) {
+                const uint32_t *te = w + PH_WORDS_N + (sh[S_TBASE] + t) * TT_WORDS;
                 const uint64_t span = (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
                 const uint64_t whole = (uint64_t)sh[S_NROWS] * ((uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32)) * ((te[TT_INFO] & 0xFF) == DVM_BF16 ? 2u : 4u);
                 bytes += span;
@@ -2672,18 +2696,15 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         }
         // (streaming loads go past the last-level cache)
         const bool stream = touched * (uint64_t)n_sets >= STREAM_MIN_BYTES;
-        for (uint32_t s = 0, at = segs_off; s < end; at += w[at + S_WORDS], ++s) {
-            if (s < first) continue;
-            for (uint32_t pc = at + SH_WORDS; pc < at + w[at + S_WORDS]; pc += (w[pc] >> 8) & 0xFF) {
-                const uint32_t op = w[pc] & 0xFF;
-                if (op == I_LOAD || op == I_VLOAD) ka.code[pc + 1 - segs_off] = stream ? w[pc + 1] : w[pc + 1] & ~(MF_STREAM << 16);
-            }
+        for (uint32_t i = 0, to = 0; i < n_segs; ++i) {
+            const uint32_t *sh = w + seg_at[segs[i]];
+            memcpy(ka.code + to, sh, (size_t)sh[S_WORDS] * 4);
+            for (uint32_t pc = SH_WORDS; !stream && pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF)
+                if ((sh[pc] & 0xFF) == I_LOAD || (sh[pc] & 0xFF) == I_VLOAD) ka.code[to + pc + 1] &= ~(MF_STREAM << 16);
+            to += sh[S_WORDS];
         }
         ka.set_tiles = (uint32_t)total;
-        if (total == 0) {               // (its segments are empty)
-            first = end;
-            continue;
-        }
+        if (total == 0) continue;       // (its segments are empty)
         if (total < (1ull << 31)) magic_of(ka.set_tiles, &ka.set_m, &ka.set_sh);
         total *= (uint64_t)n_sets;
         // Several segments, or several sets: the tiles of each are dealt out from where the one before stopped.  (Not
@@ -2693,7 +2714,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         // The instantiations that pass over foreign sets and segments are some 8 % slower per tile; the others spend 1.1 us on each.
         // They pay where that is more than 8 % of the time the launch's bytes take at 5 TB/s, i.e. below 69 MB per segment and set
         // (32 layers of five programs at 512 tokens, 18 MB each: 604 us against 639; eight RMSNorms of 285 MB: the other way round).
-        const bool skip = ka.rotate == 1 && bytes < (uint64_t)(end - first) * (69ull << 20);
+        const bool skip = ka.rotate == 1 && bytes < (uint64_t)n_segs * (69ull << 20);
         const bool narrow = apart && k_need <= 32;
         const int K_l = narrow ? 32 : K, NR_l = narrow ? 2 : NR;
         vm_launch_t launch = nullptr;
@@ -2701,10 +2722,10 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             for (const VariantEntry &v : g_cred_variants)
                 if (v.K == K && v.NR == NR) launch = v.launch;
         } else {
-            const bool one = w[PH_NSEG] == 1 && n_sets == 1;
-            const bool any = part || (longrow && (!wide || mac || !one));
+            const bool one = n_segs == 1 && n_sets == 1;
+            const bool any = need.part || (need.longrow && (!wide || need.mac || !one));
             if (!any && !skip && ka.rotate == 1) ka.rotate = 2;         // (they know the other way of counting only)
-            const VariantEntry *list = any ? g_any_variants : longrow ? g_long_wide_variants
+            const VariantEntry *list = any ? g_any_variants : need.longrow ? g_long_wide_variants
                                        : skip ? (wide ? g_wide_variants : g_variants) : (wide ? g_visit_wide_variants : g_visit_variants);
             for (int i = 0; i < N_VARIANTS; ++i)
                 if (list[i].K == K_l && list[i].NR == NR_l) launch = list[i].launch;
@@ -2713,7 +2734,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         uint32_t grid = w[PH_GRID];
         if (grid_sync || (ka.rotate != 0 && (total > grid || apart))) {
             int per_cu = 0, n_cu = 0;
-            e = (hipError_t)resident_per_cu(launch, block, lds_bytes, &per_cu);
+            e = (hipError_t)resident_per_cu(launch, block, need.lds_bytes, &per_cu);
             if (e != hipSuccess) {
                 t_last_hip_error = (int)e;
                 return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
@@ -2737,11 +2758,10 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             }
         }
         // (every launch counts its arrivals at grid-wide waits from zero; the status word stays)
-        if (grid_sync && first != 0) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, 1u);
+        if (grid_sync && vm_runs++ != 0) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, 1u);
         dvm_colreduce_args ca;
         uint32_t cgrid = 0, cblock = 0;
-        const uint32_t *first_sh = w + segs_off;
-        for (uint32_t s = 0; s < first; ++s) first_sh += first_sh[S_WORDS];
+        const uint32_t *first_sh = w + seg_at[segs[0]];
         // A large launch of one segment spreads its tiles over eight times the workgroups that are resident: those that walk many tiles
         // drift apart, and the memory in use with them, while the dispatcher starts the next ones in order (fp32 add over 45M elements 93.6 -> 87.2 us,
         // RMSNorm bf16 [42648, 4096] 127 -> 119).  A prologue (pinned operands) runs in every workgroup: each of its records wants two and a
@@ -2751,15 +2771,14 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             for (uint32_t pc = SH_WORDS; pc < SH_WORDS + first_sh[S_PROLOG]; pc += (first_sh[pc] >> 8) & 0xFF) ++records;
             if (records == 0 || 2 * total >= 5ull * records * 8u * grid) grid = total < 8ull * grid ? (uint32_t)total : 8u * grid;
         }
-        if (cred && end == first + 1 && !batch && plain_colreduce(ctx, first_sh, ka.tensors, ka.aliased != 0, &ca, &cgrid, &cblock))
+        if (cred && n_segs == 1 && !batch && plain_colreduce(ctx, first_sh, ka.tensors, ka.aliased != 0, &ca, &cgrid, &cblock))
             e = (hipError_t)dvm_colreduce_launch(&ca, cgrid, cblock, hip_stream);
         else
-            e = (hipError_t)launch(grid, block, lds_bytes, hip_stream, &ka, nullptr);
+            e = (hipError_t)launch(grid, block, need.lds_bytes, hip_stream, &ka, nullptr);
         if (e != hipSuccess) {
             t_last_hip_error = (int)e;
             return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
         }
-        first = end;
     }
     return DVM_OK;
 }

@@ -137,3 +137,31 @@ def test_stack_and_batch(dt):
         torch.cuda.synchronize()
         want = (a.float() + c.float()).to(a.dtype)
         assert all(torch.equal(p, q) for p, q in zip(outs, refs)) and all(torch.equal(p, want) for p in sums)
+
+
+@pytest.mark.parametrize("limits", [(64, 1), (64, 6), (32, 2), (8, 6)])
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_small_programs_have_the_interpreters_bits(dt, limits):
+    """Alone and batched they run in a kernel that adds in the interpreter's order; in a stack in the interpreter."""
+    ctx = B.Context(torch.cuda.current_device())
+    ctx.set_limits(*limits)
+    stream = torch.cuda.current_stream().cuda_stream
+    a = gen.randn((33,), 40, DEV)
+    other = B.encode_for(ctx, H.program(W.single_op_program("abs", 1, "f32")), [a])
+    for rows, cols in ((1, 3), (777, 1), (777, 3), (500, 7), (63, 8), (64, 9), (65, 26), (1000, 32), (300, 65), (257, 100), (129, 250), (130, 257), (40, 512), (33, 1000), (5, 2049), (3, 4096)):
+        for masked in (False, True):
+            if masked and limits[1] < 2:
+                continue
+            print(f"[case] softmax {dt} [{rows}, {cols}] {limits}{', masked' if masked else ''}", flush=True)
+            z = gen.randn((3, rows, cols), 41, DEV, dt, std=3.0)
+            z[:, 0, cols // 2] = -INF
+            ins = [z] + ([gen.randn((rows, cols), 42, DEV, dt)] if masked else [])
+            names = [n for n, _ in desc(dt, masked).inputs]
+            alone = H.run_vm(desc(dt, masked), dict(zip(names, ins)), ctx=ctx)[0]["p"]
+            check(alone, z.float() + ins[1].float() if masked else z, dt, (rows, cols))
+            code = B.encode_for(ctx, H.program(desc(dt, masked)), ins)
+            y, o = torch.empty_like(z), torch.empty_like(a)
+            B.dvm_run(ctx, B.dvm_stack([code, other]), [t.data_ptr() for t in ins + [y, a, o]], stream)
+            torch.cuda.synchronize()
+            bits = [t.view(torch.int32 if dt == "f32" else torch.int16) for t in (alone, y)]
+            assert torch.equal(*bits), (rows, cols, masked)
