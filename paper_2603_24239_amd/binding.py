@@ -6,12 +6,14 @@ PyTorch is used by callers for device memory and streams; this module only reads
 """
 from __future__ import annotations
 
-import array
 import ctypes as C
-import itertools
 import os
-import struct
 from typing import Dict, List, Optional, Sequence, Tuple
+
+try:
+    from . import _dvm          # (dvm_py.c: the calls a launch goes through; load() says what is missing)
+except ImportError:
+    _dvm = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdvm.so")
@@ -70,6 +72,8 @@ def load() -> C.CDLL:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`")
+    if _dvm is None:
+        raise RuntimeError(f"the extension module _dvm beside {_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`")
     lib = C.CDLL(_LIB_PATH)
     vp, i, sz = C.c_void_p, C.c_int, C.c_size_t
     P = C.POINTER
@@ -126,6 +130,8 @@ def load() -> C.CDLL:
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
+    _dvm.bind(*[C.cast(f, C.c_void_p).value for f in (lib.dvm_encode, lib.dvm_stack, lib.dvm_stack_spatial, lib.dvm_run, lib.dvm_run_batched,
+                                                      lib.dvm_code_min_bytes, lib.dvm_code_info_get, lib.dvm_code_tensor)])
     _lib = lib
     return lib
 
@@ -172,27 +178,6 @@ def _ptr_align(ptr: int) -> int:
 
 def shape_of_tensor(t) -> dvm_shape:
     return make_shape(tuple(t.shape), tuple(t.stride()), _ptr_align(t.data_ptr()))
-
-
-# One call packs a whole dvm_shape: setting its fields one by one through ctypes was most of the host time of a launch.
-_SHAPE = struct.Struct(f"=ii{DVM_MAX_RANK}q{DVM_MAX_RANK}q")
-_PAD = [(0,) * (DVM_MAX_RANK - r) for r in range(DVM_MAX_RANK + 1)]
-
-
-def _shapes_of(tensors: Sequence):
-    """An array of dvm_shape for torch tensors (shape_of_tensor of each)."""
-    arr = (dvm_shape * max(len(tensors), 1))()
-    at = 0
-    for t in tensors:
-        dims = t.shape
-        r = len(dims)
-        if r > DVM_MAX_RANK:
-            raise DvmError(-3, "make_shape")
-        pad = _PAD[r]
-        p = t.data_ptr()
-        _SHAPE.pack_into(arr, at, r, p & -p if p & 15 else 16, *dims, *pad, *t.stride(), *pad)
-        at += _SHAPE.size
-    return arr
 
 
 class Context:
@@ -305,12 +290,12 @@ class Bytecode:
 
     def needs_workspace(self) -> bool:
         """True if the launch's last tensor is its workspace (a dependent stack with a grid-wide synchronisation point)."""
-        n = self.info().n_tensors
-        if n == 0:
-            return False
-        io = C.c_int()
-        _check(load().dvm_code_tensor(self.ptr, len(self.raw), n - 1, None, C.byref(io), None, None), "dvm_code_tensor")
-        return io.value == 2
+        if _lib is None:
+            load()
+        r = _dvm.needs_workspace(self.raw)
+        if r is not True and r is not False:
+            raise DvmError(r, "dvm_code_info_get")
+        return r
 
     def disasm(self) -> str:
         buf = C.create_string_buffer(1 << 16)
@@ -326,48 +311,28 @@ _ENC_CAP = 8192
 
 def dvm_encode(ctx: Context, prog: Program, in_shapes: Sequence[dvm_shape],
                out_layout: Optional[Sequence[dvm_shape]] = None) -> Bytecode:
-    n = len(in_shapes)
-    arr = (dvm_shape * max(n, 1))(*in_shapes)
-    outl = None
-    if out_layout is not None:
-        outl = (dvm_shape * max(len(out_layout), 1))(*out_layout)
-    return _encode(ctx, prog, arr, n, outl)
+    return _encoded(_dvm.encode(ctx._h, prog._h, in_shapes, out_layout, prog.n_out, 1))
 
 
-_EncBuf = C.c_char * _ENC_CAP
-# arrays for the tensors of a launch (32 at most)
-_Sizes = [C.c_int64 * max(k, 1) for k in range(33)]
-_Pointers = [C.c_void_p * max(k, 1) for k in range(33)]
-
-
-def _encode(ctx: Context, prog: Program, arr, n: int, outl) -> Bytecode:
-    buf = _EncBuf()
-    ln = C.c_size_t()
-    n_out = prog.n_out
-    outs = (dvm_shape * max(n_out, 1))()
-    status = load().dvm_encode(ctx._h, prog._h, arr, n, outl, buf, _ENC_CAP, ln, outs)
-    if status != 0:
-        raise DvmError(status, "dvm_encode")
-    shapes = []
-    for k in range(n_out):
-        v = _SHAPE.unpack_from(outs, k * _SHAPE.size)
-        shapes.append(v[2: 2 + v[0]])
-    return Bytecode(buf[: ln.value], shapes)
+def _encoded(r) -> Bytecode:
+    if type(r) is tuple:
+        return Bytecode(*r)
+    if r is None:
+        raise DvmError(-3, "make_shape")
+    raise DvmError(r, "dvm_encode")
 
 
 def dvm_stack(codes: Sequence[Bytecode], spatial: bool = False) -> Bytecode:
-    lib = load()
-    n = len(codes)
-    ptrs = (C.c_void_p * n)(*[c.ptr for c in codes])
-    lens = (C.c_size_t * n)(*[len(c) for c in codes])
-    buf = C.create_string_buffer(_ENC_CAP)
-    ln = C.c_size_t()
-    fn = lib.dvm_stack_spatial if spatial else lib.dvm_stack
-    _check(fn(ptrs, lens, n, buf, _ENC_CAP, C.byref(ln)), "dvm_stack_spatial" if spatial else "dvm_stack")
+    if _lib is None:
+        load()
+    codes = list(codes)
+    r = _dvm.stack([c.raw for c in codes], spatial)
+    if type(r) is int:
+        raise DvmError(r, "dvm_stack_spatial" if spatial else "dvm_stack")
     shapes: List[Tuple[int, ...]] = []
     for c in codes:
         shapes.extend(c.out_shapes)
-    return Bytecode(buf.raw[: ln.value], shapes)
+    return Bytecode(r, shapes)
 
 
 def dvm_stack_spatial(codes: Sequence[Bytecode]) -> Bytecode:
@@ -403,9 +368,7 @@ def workspace_gave_up(workspace_ptr: int, stream: int = 0) -> bool:
 
 
 def dvm_run(ctx: Context, code: Bytecode, tensor_ptrs: Sequence[int], stream: int = 0) -> None:
-    n = len(tensor_ptrs)
-    raw = code.raw
-    status = load().dvm_run(ctx._h, raw, len(raw), (_Pointers[n] if n < len(_Pointers) else C.c_void_p * n)(*tensor_ptrs), n, stream)
+    status = _dvm.run(ctx._h, code.raw, tensor_ptrs, stream)
     if status != 0:
         raise DvmError(status, "dvm_run")
 
@@ -413,17 +376,11 @@ def dvm_run(ctx: Context, code: Bytecode, tensor_ptrs: Sequence[int], stream: in
 def dvm_run_batched(ctx: Context, code: Bytecode, tensor_ptr_sets: Sequence[Sequence[int]], table_ptr: int, table_bytes: int,
                     stream: int = 0) -> None:
     """One launch over several sets of tensors (device pointers); `table_ptr`: device memory for the address table."""
-    n_sets = len(tensor_ptr_sets)
-    n = len(tensor_ptr_sets[0])
-    try:
-        flat = array.array("Q", itertools.chain.from_iterable(tensor_ptr_sets))
-        arr = (C.c_void_p * len(flat)).from_buffer(flat)
-    except TypeError:                   # (None or c_void_p among the addresses)
-        flat = list(itertools.chain.from_iterable(tensor_ptr_sets))
-        arr = (C.c_void_p * len(flat))(*flat)
-    assert len(flat) == n * n_sets
-    _check(load().dvm_run_batched(ctx._h, code.ptr, len(code), arr, n, n_sets, C.c_void_p(table_ptr), table_bytes, C.c_void_p(stream)),
-           "dvm_run_batched")
+    tensor_ptr_sets[0]              # (at least one set)
+    status = _dvm.run_batched(ctx._h, code.raw, tensor_ptr_sets, table_ptr, table_bytes, stream)
+    assert status is not None       # (sets of equal size)
+    if status != 0:
+        raise DvmError(status, "dvm_run_batched")
 
 
 def dvm_run_static(ctx: Context, code: Bytecode, tensor_ptrs: Sequence[int], stream: int = 0) -> None:
@@ -495,31 +452,25 @@ def dvm_plan(total: int, n_cores: int, t_max: int, align: int, overhead: int = 2
 
 def encode_for(ctx: Context, prog: Program, inputs: Sequence, outputs: Optional[Sequence] = None) -> Bytecode:
     """Encode `prog` for the shapes/strides of the given torch tensors (and output views, if any)."""
-    inputs, outputs = tuple(inputs), outputs if outputs is None else tuple(outputs)
-    return _encode(ctx, prog, _shapes_of(inputs), len(inputs), _shapes_of(outputs) if outputs is not None else None)
+    return _encoded(_dvm.encode(ctx._h, prog._h, tuple(inputs), outputs if outputs is None else tuple(outputs), prog.n_out, 0))
 
 
 def check_buffers(code: Bytecode, tensors: Sequence) -> None:
     """Host-side guard: every tensor's storage must cover what the bytecode will touch."""
-    n = len(tensors)
-    needs = _Sizes[n]() if n < len(_Sizes) else (C.c_int64 * n)()
-    raw = code.raw
-    status = load().dvm_code_min_bytes(raw, len(raw), needs, n)
-    if status != 0:
-        raise DvmError(status, "dvm_code_min_bytes")
-    for need, t in zip(needs, tensors):
-        have = t.untyped_storage().nbytes()     # (a storage may have been resized below what its tensor's shape says)
-        offset = t.storage_offset()
-        if offset != 0:
-            have -= offset * t.element_size()
-        if need > have or (not t.numel() and need > 0):
-            i = next(k for k, u in enumerate(tensors) if u is t)
-            raise DvmError(-1, f"tensor {i}: bytecode touches {need} bytes, storage holds {have if t.numel() else 0}")
+    if _lib is None:
+        load()
+    r = _dvm.check(code.raw, tensors)
+    if r is None:
+        return
+    if type(r) is int:
+        raise DvmError(r, "dvm_code_min_bytes")
+    i, need, have = r
+    raise DvmError(-1, f"tensor {i}: bytecode touches {need} bytes, storage holds {have}")
 
 
 def run_on(ctx: Context, code: Bytecode, tensors: Sequence, stream: Optional[int] = None) -> None:
-    import torch
     check_buffers(code, tensors)
     if stream is None:
+        import torch
         stream = torch.cuda.current_stream().cuda_stream
     dvm_run(ctx, code, [t.data_ptr() for t in tensors], stream)

@@ -15,10 +15,12 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdvm.so")
+EXT = os.path.join(HERE, "_dvm" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 COMMON = ["-O3", "-std=c++20", "-fPIC", "-Wall", "-Wno-unused-function", "-Wno-unused-command-line-argument"]
 DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -48,6 +50,10 @@ def build(verbose: bool = True) -> str:
             ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_colreduce.hip")], os.path.join(CSRC, "dvm_colreduce.o")),
             ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_softmax.hip")], os.path.join(CSRC, "dvm_softmax.o")),
             ([hipcc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, "dvm_rotary.hip")], os.path.join(CSRC, "dvm_rotary.o"))]
+    # the extension module of the binding (host C only; it takes the library's functions by address)
+    gcc = os.environ.get("CC", "gcc")
+    py = [gcc, "-O2", "-std=c11", "-fPIC", "-Wall", "-shared", f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, "dvm_py.c")]
+    jobs.append((py, EXT))
     # every interpreter variant is a translation unit of its own, compiled side by side
     for k, nr, maxt, waves in variants():
         defs = [f"-DDVM_VARIANT_K={k}", f"-DDVM_VARIANT_NR={nr}", f"-DDVM_VARIANT_MAXT={maxt}", f"-DDVM_VARIANT_WAVES={waves}"]
@@ -92,7 +98,7 @@ def build(verbose: bool = True) -> str:
     workers = max(1, min(len(jobs), os.cpu_count() or 1, int(os.environ.get("MAX_JOBS", "16"))))
     with concurrent.futures.ThreadPoolExecutor(max_workers=workers) as pool:
         objs = list(pool.map(run, jobs))
-    cmd = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
+    cmd = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *[o for o in objs if o != EXT], "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

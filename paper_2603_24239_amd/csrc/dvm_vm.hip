@@ -2488,10 +2488,13 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
     return true;
 }
 
-// Loads take the streaming hint in launches that touch more than the last-level cache holds.  Within it, what the program before wrote
-// or this one read last time may still be there: RMSNorm bf16 [11000, 4096] (180 MB) 30.8 us without the hint, 36.5 with it, RoPE over 8111 tokens
-// (133 MB) 31.6 and 38.1; beyond it the hint pays (a 32-layer step of 512 tokens 603 us without, 592 with it).
-constexpr uint64_t STREAM_MIN_BYTES = 256ull << 20;
+// Loads take the streaming hint in launches that read more than this.  Less may still be in the last-level cache (256 MB) from the program that
+// wrote it or the one that read it last, beside what others use; the hint then costs (RMSNorm bf16 [11000, 4096], 90 MB read, 30.8 us
+// without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
+// 2245 rows of 8192, 110 MB, 40.1 and 36.7).
+constexpr uint64_t STREAM_MIN_READS = 96ull << 20;
+constexpr uint64_t LARGE_MIN_BYTES = 256ull << 20;      // launches larger than the last-level cache
+constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut into column tiles
 
 int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *tensors_in, int n_tensors, void *hip_stream, bool static_ws,
              const Batch *batch) {
@@ -2624,7 +2627,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     dvm_rotary_args ra;
     if (w[PH_NSEG] == 1 && plain_rotary(w + segs_off, NR, w + PH_WORDS_N, tensors, n_sets, ntens, &ra)) {
         ra.sets = ka.sets;
-        ra.stream = (uint64_t)ra.rows * (uint64_t)(((uint64_t)w[segs_off + S_D0LO]) * (ra.x_bf16 ? 8u : 16u)) * (uint64_t)n_sets >= STREAM_MIN_BYTES;
+        ra.stream = (uint64_t)ra.rows * (uint64_t)(((uint64_t)w[segs_off + S_D0LO]) * (ra.x_bf16 ? 4u : 8u)) * (uint64_t)n_sets >= STREAM_MIN_READS;
         e = (hipError_t)dvm_rotary_launch(&ra, hip_stream);
         if (e != hipSuccess) {
             t_last_hip_error = (int)e;
@@ -2661,7 +2664,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             int n_cu = 256;
             dvm_ctx_planner_get(ctx, &n_cu, nullptr);
             sm.sets = ka.sets;
-            sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 4u : 8u) * (uint64_t)n_sets >= STREAM_MIN_BYTES;
+            sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets >= STREAM_MIN_READS;
             sm.n_tensors = ntens;
             // (the kernel for long rows loads a workgroup's next row while it stores the one before: as many workgroups as are resident)
             const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
@@ -2676,7 +2679,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         ka.nseg = n_segs;
         ka.set_tiles = 0;
         Needs need;
-        uint64_t total = 0, bytes = 0, touched = 0;     // of this launch (touched: without what lies between the rows of views)
+        uint64_t total = 0, bytes = 0, touched = 0, reads = 0;     // of this launch (the last two: without what lies between the rows of views)
         uint32_t k_need = 0;                // elements per lane its segments use
         bool round_robin = true;
         for (uint32_t i = 0; i < n_segs; ++i) {
@@ -2692,10 +2695,11 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
                 const uint64_t whole = (uint64_t)sh[S_NROWS] * ((uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32)) * ((te[TT_INFO] & 0xFF) == DVM_BF16 ? 2u : 4u);
                 bytes += span;
                 touched += whole < span ? whole : span;
+                if (!(te[TT_INFO] & TI_OUTPUT)) reads += whole < span ? whole : span;
             }
         }
         // (streaming loads go past the last-level cache)
-        const bool stream = touched * (uint64_t)n_sets >= STREAM_MIN_BYTES;
+        const bool stream = reads * (uint64_t)n_sets >= STREAM_MIN_READS;
         for (uint32_t i = 0, to = 0; i < n_segs; ++i) {
             const uint32_t *sh = w + seg_at[segs[i]];
             memcpy(ka.code + to, sh, (size_t)sh[S_WORDS] * 4);
@@ -2765,8 +2769,9 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         // A large launch of one segment spreads its tiles over eight times the workgroups that are resident: those that walk many tiles
         // drift apart, and the memory in use with them, while the dispatcher starts the next ones in order (fp32 add over 45M elements 93.6 -> 87.2 us,
         // RMSNorm bf16 [42648, 4096] 127 -> 119).  A prologue (pinned operands) runs in every workgroup: each of its records wants two and a
-        // half tiles behind it (LayerNorm bf16 [163840, 2048] 250 -> 241, but [81920, 1024], with one tile behind two, 63 -> 68).
-        if (w[PH_NSEG] == 1 && n_sets == 1 && !cred && !longrow && stream && (first_sh[S_FLAGS] & SF_INTERLEAVED) && !(first_sh[S_FLAGS] & SF_LDS)) {
+        // half tiles behind it (LayerNorm bf16 [163840, 2048] 250 -> 241, but [81920, 1024], with one tile behind two, 63 -> 68).  Flat programs, whose tiles
+        // cost the same, gain from 64 MB on, where their last round is not full (fp32 add over 15M elements 34.0 -> 31.9, over 10M 23.1 -> 23.3).
+        if (w[PH_NSEG] == 1 && n_sets == 1 && !cred && !longrow && touched >= (first_sh[S_NCT] > 1 ? FLAT_MIN_BYTES : LARGE_MIN_BYTES) && (first_sh[S_FLAGS] & SF_INTERLEAVED) && !(first_sh[S_FLAGS] & SF_LDS)) {
             uint32_t records = 0;
             for (uint32_t pc = SH_WORDS; pc < SH_WORDS + first_sh[S_PROLOG]; pc += (first_sh[pc] >> 8) & 0xFF) ++records;
             if (records == 0 || 2 * total >= 5ull * records * 8u * grid) grid = total < 8ull * grid ? (uint32_t)total : 8u * grid;
