@@ -1,0 +1,65 @@
+"""The extension module of the binding: the argument forms that the calls take, and what they refuse."""
+from __future__ import annotations
+
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_24239_amd import binding as B
+from workloads import programs as W
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = B.Context(-1)
+    c.set_planner(256)
+    return c
+
+
+@pytest.mark.parametrize("shape,offset,dt", [((4, 1000), 0, "f32"), ((7,), 3, "f32"), ((3, 5, 64), 1, "bf16"), ((0, 8), 0, "f32")])
+def test_tensors_and_shapes_encode_alike(ctx, shape, offset, dt):
+    n = int(np.prod(shape))
+    t = torch.zeros(n + 8, dtype=torch.float32 if dt == "f32" else torch.bfloat16)[offset: offset + n].view(shape)
+    prog = B.Program(W.single_op_program("add", 2, dt))
+    a = B.encode_for(ctx, prog, [t, t])
+    b = B.dvm_encode(ctx, prog, [B.shape_of_tensor(t)] * 2)
+    assert a.raw == b.raw and list(a.out_shapes) == list(b.out_shapes) == [tuple(shape)]
+    assert a.needs_workspace() is False and B.encode_for(ctx, prog, iter([t, t]), iter([t])).info().n_tensors == 3
+
+
+def test_refusals(ctx):
+    prog = B.Program(W.single_op_program("abs", 1, "f32"))
+    code = B.encode_for(ctx, prog, [torch.zeros(16)])
+    with pytest.raises(B.DvmError, match=r"\(-3\)"):
+        B.encode_for(ctx, prog, [torch.zeros((1,) * 7)])
+    with pytest.raises(B.DvmError, match="dvm_encode"):
+        B.encode_for(ctx, prog, [torch.zeros(3)] * 40)
+    with pytest.raises(B.DvmError, match="dvm_encode"):
+        B.encode_for(ctx, prog, [torch.zeros(3)], [])
+    with pytest.raises(TypeError):
+        B.dvm_encode(ctx, prog, [b"no shape"])
+    for ptrs in ([0, None], [C.c_void_p(64), np.int64(64)], [64] * 40, ()):      # (a context without a device launches nothing)
+        with pytest.raises(B.DvmError, match="dvm_run"):
+            B.dvm_run(ctx, code, ptrs)
+    for sets in ([[64, 64]], [(np.uint64(64), None)] * 3):
+        with pytest.raises(B.DvmError, match="dvm_run_batched"):
+            B.dvm_run_batched(ctx, code, sets, 64, 4096)
+    with pytest.raises(AssertionError):
+        B.dvm_run_batched(ctx, code, [[64, 64], [64]], 64, 4096)
+    with pytest.raises(IndexError):
+        B.dvm_run_batched(ctx, code, [], 64, 4096)
+    with pytest.raises(B.DvmError, match="dvm_stack"):
+        B.dvm_stack([])
+    assert B.dvm_stack([code, code]).info().n_segments == 2
+
+
+def test_buffers_are_checked(ctx):
+    code = B.encode_for(ctx, B.Program(W.single_op_program("abs", 1, "f32")), [torch.zeros(16)])
+    whole = torch.zeros(32)
+    B.check_buffers(code, [whole[:16], whole[16:]])
+    with pytest.raises(B.DvmError, match="tensor 1: bytecode touches 64 bytes, storage holds 60"):
+        B.check_buffers(code, [whole, whole[17:]])
+    with pytest.raises(B.DvmError, match="tensor 0: bytecode touches 64 bytes, storage holds 0"):
+        B.check_buffers(code, (whole[:0], whole))
