@@ -1372,7 +1372,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(WAVES
                                 }
                                 const char *rowbase = (const char *)DVM_TENSOR(tbase + ti) + off * (dt == 0 ? 4 : 2);
                                 if (g.chunks()) {
-                                    if ((w1 >> 16) & MF_STREAM) {
+                                    if (!LONG && ((w1 >> 16) & MF_STREAM)) {      // (long rows are read once per pass: no hint)
                                         if (dt != 0) { if constexpr (K >= 8) DVM_ISSUE_WIDE(1, 8, true) }
                                         else if (V == 4) DVM_ISSUE_WIDE(0, 4, true)
                                         else { if constexpr (K >= 8) DVM_ISSUE_WIDE(0, 8, true) }
