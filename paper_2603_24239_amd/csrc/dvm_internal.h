@@ -52,7 +52,10 @@ typedef struct dvm_softmax_args {
     uint32_t tail;                  // a row may end in this slot of chunks or behind it
     uint32_t stream;                // 1: larger than the last-level cache holds, read past it
     uint32_t shifted;               // some row does not start on a 128-byte line of the output
+    uint64_t parts[3 * 16];         // sets = DVM_SOFTMAX_PARTS: the addresses of up to 16 alike parts of a stack (n_tensors 3, in the order 0, 1, 2)
 } dvm_softmax_args;
+constexpr uint64_t DVM_SOFTMAX_PARTS = 1;
+constexpr uint32_t DVM_SOFTMAX_MAX_PARTS = 16;
 constexpr int64_t DVM_SOFTMAX_MIN_BYTES = 16 << 20;
 int dvm_softmax_launch(const dvm_softmax_args *a, unsigned grid, void *stream);
 // A rotation of pairs over short rows as its own kernel takes it (dvm_rotary.hip): tensors in the order x1, x2, c, s, y1, y2; strides in elements.

@@ -19,6 +19,7 @@
 // combined.  The two chunks that reach over the ends of a row slide back inside (every access stays in the row) and hand each class its
 // element by a barrel shift.
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "dvm_bytecode.h"
@@ -131,7 +132,10 @@ template <int BF16, bool MASK> DI Row place(const dvm_softmax_args &s, uint32_t 
     i1 = ok ? i1 : s.limit - 1u - i3 * s.d1;
     uint64_t pa = (uint64_t)(uintptr_t)s.a, pb = (uint64_t)(uintptr_t)s.b, py = (uint64_t)(uintptr_t)s.y;
     if (s.sets != 0) {
-        const GLOBAL_AS uint64_t *t = (const GLOBAL_AS uint64_t *)s.sets + (uint64_t)set * s.n_tensors;
+        // (the addresses of a stack's parts are in the argument block, which is memory like any other)
+        uint64_t table = s.sets;
+        if (table == DVM_SOFTMAX_PARTS) table = (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(dvm_softmax_args, parts);
+        const GLOBAL_AS uint64_t *t = (const GLOBAL_AS uint64_t *)table + (uint64_t)set * s.n_tensors;
         pa = t[s.ia];
         if constexpr (MASK) pb = t[s.ib];
         py = t[s.iy];

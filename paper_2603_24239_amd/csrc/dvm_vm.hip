@@ -2179,9 +2179,10 @@ void magic_of(uint32_t d, uint32_t *m, uint32_t *sh) {
 
 // A segment that is a softmax along the row, of one tensor or of the sum of two, as the arguments of the kernel for those: load [, load,
 // add], max, exp of the difference, reciprocal of the sum, store of the product.  It takes segments that read and write at least
-// DVM_SOFTMAX_MIN_BYTES in a layout of its own (rows longer than a tile, which the interpreter reads twice: an eighth of that): below, a launch is bound by its own
-// cost, and in a stack an extra one (2 us) would cost more than it gives.  Rows of less than a line stay too (fp32 [400000, 9] 12.4 us
-// there and 18.0 here).  The rule looks at the segment alone, so that its bits are the same alone, in a stack and in a batched launch (in a
+// DVM_SOFTMAX_MIN_BYTES in a layout of its own (rows longer than a tile, which the interpreter reads twice: an eighth of that): below, a launch
+// is bound by its own cost, and in a stack an extra one (2 us) would cost more than it gives.  Rows of less than a line and smaller segments
+// go to the kernel with the interpreter's bits where they are the whole program (fp32 [400000, 9] 12.4 us in the interpreter and 18.0 in the
+// layout here).  The rule looks at the segment alone, so that its bits are the same alone, in a stack and in a batched launch (in a
 // spatial stack, whose parts share one launch, it stays with the interpreter).
 // Lanes on a row: those that leave the fewest idle, lanes * chunks being what a row costs, over up to 8 chunks of 16 bytes a lane (bf16: 6,
 // for the registers).  More than 4 cost an eighth for the waves they displace (not in fp32 rows of one wave), a row of several waves a
@@ -2636,7 +2637,9 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         return DVM_OK;
     }
     // The kernel launches: segments in a run share one.  A segment starts a run of its own where it asks for one, and a softmax that runs apart is
-    // one.  Segments that are independent of each other go first, all but those, in one launch.
+    // one.  Segments that are independent of each other go first, all but those, in one launch; softmaxes alike in all but their addresses share a
+    // launch, since few rows leave most of the chip idle (eight in a stack, one launch each and one for all, us: bf16 [32, 17000] 43 and 7, fp32 [128, 17000]
+    // 60 and 27, bf16 [6000, 751] 51 and 24; in the interpreter 20, 40 and 42).
     uint32_t list[MAX_SEGMENTS], run_at[MAX_SEGMENTS + 1], n_runs = 0, n_list = 0;
     bool apart_run[MAX_SEGMENTS];
     dvm_softmax_args sm;
@@ -2651,7 +2654,21 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             for (uint32_t s = 0; s < w[PH_NSEG]; ++s) push(s, soft[s] || (s > 0 && soft[s - 1]) || (w[seg_at[s] + S_FLAGS] & SF_NEW_LAUNCH), soft[s]);
         } else {
             for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!soft[s]) push(s, false, false);
-            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (soft[s]) push(s, true, true);
+            dvm_softmax_args last;
+            uint32_t n = 0;         // in the present run
+            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) {
+                if (!soft[s]) continue;
+                memset(&sm, 0, sizeof sm);
+                softmax_of(s, &sm);
+                sm.a = sm.y = nullptr;
+                if (sm.b) sm.b = w;         // (there is one)
+                sm.ia = sm.ib = sm.iy = 0;
+                const bool joins = n > 0 && n < DVM_SOFTMAX_MAX_PARTS && n_sets == 1 && memcmp(&sm, &last, sizeof sm) == 0 &&
+                                   (uint64_t)sm.tiles * (n + 1) < (1ull << 31);
+                n = joins ? n + 1 : 1;
+                push(s, !joins, true);
+                last = sm;
+            }
         }
     }
     run_at[n_runs] = n_list;
@@ -2664,8 +2681,21 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             int n_cu = 256;
             dvm_ctx_planner_get(ctx, &n_cu, nullptr);
             sm.sets = ka.sets;
-            sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets >= STREAM_MIN_READS;
             sm.n_tensors = ntens;
+            if (n_segs > 1) {
+                for (uint32_t i = 0; i < n_segs; ++i) {
+                    dvm_softmax_args one;
+                    softmax_of(segs[i], &one);
+                    sm.parts[3 * i] = (uint64_t)(uintptr_t)one.a;
+                    sm.parts[3 * i + 1] = (uint64_t)(uintptr_t)one.b;
+                    sm.parts[3 * i + 2] = (uint64_t)(uintptr_t)one.y;
+                }
+                sm.sets = DVM_SOFTMAX_PARTS;
+                sm.n_tensors = 3;
+                sm.ia = 0, sm.ib = 1, sm.iy = 2;
+                sm.tiles *= n_segs;
+            }
+            sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets * n_segs >= STREAM_MIN_READS;
             // (the kernel for long rows loads a workgroup's next row while it stores the one before: as many workgroups as are resident)
             const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
             const uint32_t grid = sm.in_long != 0 && sm.tiles > most ? most : sm.tiles;

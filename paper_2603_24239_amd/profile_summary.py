@@ -26,8 +26,8 @@ SQ = ["SQ_WAVES", "SQ_BUSY_CU_CYCLES", "SQ_WAVE_CYCLES", "SQ_INSTS_VALU", "SQ_IN
 
 
 def _ours(name: str) -> bool:
-    """The interpreter, and the kernel of plain reductions along the penultimate axis."""
-    return "dvm_vm_kernel" in name or "dvm_colreduce" in name
+    """The interpreter, and the kernels of plain reductions along the penultimate axis, softmaxes and rotations."""
+    return any(k in name for k in ("dvm_vm_kernel", "dvm_colreduce", "dvm_softmax", "dvm_rotary"))
 
 
 def _short(name: str, n: int = 78) -> str:
