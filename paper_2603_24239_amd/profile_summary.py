@@ -64,7 +64,7 @@ def main() -> int:
     roof = bench["roofline"]
     cmd = f"python3 bench.py --workload {W}{extra}"
     out = []
-    out.append(f"# rocprofv3 summaries: interpreter kernel, `bench.py --workload {W}{extra}`\n")
+    out.append(f"# rocprofv3 summaries: kernels of the library, `bench.py --workload {W}{extra}`\n")
     out.append(f"Workload: {pc['workload']}; {pc['instances']} instances, {pc['instances_per_launch']} per launch, "
                f"{pc['launches_per_pass']} launches per pass over the stream.")
     out.append("All commands run from the repository root on the MI355X box; raw output stays outside the repository.\n")
@@ -85,7 +85,7 @@ def main() -> int:
     avg_us = tot_ns / calls / 1e3
     bpl = roof["bytes_per_launch"]
     out.append("")
-    out.append("Interpreter launches (all instantiations together): %d, average %.2f us.  Algorithmic bytes per launch (mean over the launches;"
+    out.append("Launches of the library (all instantiations together): %d, average %.2f us.  Algorithmic bytes per launch (mean over the launches;"
                % (calls, avg_us))
     out.append("one read of every input element and one write of every output element): %.1f MB -> %.2f TB/s, %.1f %% of the 8 TB/s HBM peak."
                % (bpl / 1e6, bpl / avg_us / 1e6, 100 * bpl / avg_us / 1e6 / 8))
