@@ -7,13 +7,11 @@ PyTorch is used by callers for device memory and streams; this module only reads
 from __future__ import annotations
 
 import ctypes as C
+import importlib
 import os
 from typing import Dict, List, Optional, Sequence, Tuple
 
-try:
-    from . import _dvm          # (dvm_py.c: the calls a launch goes through; load() says what is missing)
-except ImportError:
-    _dvm = None
+_dvm = None         # the extension module (dvm_py.c: the calls a launch goes through).  load() imports it: the build imports this package first
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdvm.so")
@@ -67,13 +65,16 @@ _lib = None
 def load() -> C.CDLL:
     """Load libdvm.so from the package directory.  There is no fallback: without the built
     library nothing in this package can run."""
-    global _lib
+    global _lib, _dvm
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`")
-    if _dvm is None:
-        raise RuntimeError(f"the extension module _dvm beside {_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`")
+    importlib.invalidate_caches()           # (it may have been built since the package was imported)
+    try:
+        _dvm = importlib.import_module("._dvm", __package__)
+    except ImportError as e:
+        raise RuntimeError(f"the extension module _dvm beside {_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`") from e
     lib = C.CDLL(_LIB_PATH)
     vp, i, sz = C.c_void_p, C.c_int, C.c_size_t
     P = C.POINTER

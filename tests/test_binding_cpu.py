@@ -2,6 +2,11 @@
 from __future__ import annotations
 
 import ctypes as C
+import glob
+import os
+import shutil
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -63,3 +68,20 @@ def test_buffers_are_checked(ctx):
         B.check_buffers(code, [whole, whole[17:]])
     with pytest.raises(B.DvmError, match="tensor 0: bytecode touches 64 bytes, storage holds 0"):
         B.check_buffers(code, (whole[:0], whole))
+
+
+def test_a_build_in_the_process_that_uses_it(tmp_path):
+    """A clean tree's build imports the package, compiles, and loads what it compiled, all in one process."""
+    here = os.path.dirname(B.__file__)
+    pkg = tmp_path / os.path.basename(here)
+    pkg.mkdir()
+    for f in glob.glob(os.path.join(here, "*.py")):
+        shutil.copy(f, pkg)
+    script = ("import glob, shutil\n"
+              "from paper_2603_24239_amd import binding as B\n"
+              f"for f in glob.glob({os.path.join(here, '*.so')!r}): shutil.copy(f, {str(pkg)!r})\n"
+              "B.load()\n"
+              f"assert B.__file__.startswith({str(pkg)!r})\n"
+              "assert B.Context(-1).device == -1\n")
+    r = subprocess.run([sys.executable, "-c", script], cwd=tmp_path, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
