@@ -11,7 +11,9 @@ import importlib
 import os
 from typing import Dict, List, Optional, Sequence, Tuple
 
-_dvm = None         # the extension module (dvm_py.c: the calls a launch goes through).  load() imports it: the build imports this package first
+# The calls a launch goes through: the extension module _dvm (dvm_py.c), or where its build found no headers of the Python interpreter
+# marshal_ctypes.py.  load() imports it: the build imports this package first.
+_dvm = None
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdvm.so")
@@ -70,11 +72,6 @@ def load() -> C.CDLL:
         return _lib
     if not os.path.exists(_LIB_PATH):
         raise RuntimeError(f"{_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`")
-    importlib.invalidate_caches()           # (it may have been built since the package was imported)
-    try:
-        _dvm = importlib.import_module("._dvm", __package__)
-    except ImportError as e:
-        raise RuntimeError(f"the extension module _dvm beside {_LIB_PATH} is missing: build it with `python -m paper_2603_24239_amd.build`") from e
     lib = C.CDLL(_LIB_PATH)
     vp, i, sz = C.c_void_p, C.c_int, C.c_size_t
     P = C.POINTER
@@ -131,8 +128,14 @@ def load() -> C.CDLL:
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
-    _dvm.bind(*[C.cast(f, C.c_void_p).value for f in (lib.dvm_encode, lib.dvm_stack, lib.dvm_stack_spatial, lib.dvm_run, lib.dvm_run_batched,
-                                                      lib.dvm_code_min_bytes, lib.dvm_code_info_get, lib.dvm_code_tensor)])
+    importlib.invalidate_caches()           # (it may have been built since the package was imported)
+    try:
+        _dvm = importlib.import_module("._dvm", __package__)
+        _dvm.bind(*[C.cast(f, C.c_void_p).value for f in (lib.dvm_encode, lib.dvm_stack, lib.dvm_stack_spatial, lib.dvm_run, lib.dvm_run_batched,
+                                                          lib.dvm_code_min_bytes, lib.dvm_code_info_get, lib.dvm_code_tensor)])
+    except ModuleNotFoundError:
+        _dvm = importlib.import_module(".marshal_ctypes", __package__)
+        _dvm.bind(lib)
     _lib = lib
     return lib
 

@@ -1,4 +1,5 @@
-"""The extension module of the binding: the argument forms that the calls take, and what they refuse."""
+"""The calls of the binding that a launch goes through, in the extension module and through ctypes: the argument forms that they take, and
+what they refuse."""
 from __future__ import annotations
 
 import ctypes as C
@@ -13,13 +14,19 @@ import pytest
 import torch
 
 from paper_2603_24239_amd import binding as B
+from paper_2603_24239_amd import marshal_ctypes
 from workloads import programs as W
 
 
-@pytest.fixture(scope="module")
-def ctx():
+@pytest.fixture(params=["module", "ctypes"])
+def ctx(request, monkeypatch):
     c = B.Context(-1)
     c.set_planner(256)
+    if request.param == "module":
+        assert B._dvm.__name__.endswith("._dvm")
+    else:
+        marshal_ctypes.bind(B.load())
+        monkeypatch.setattr(B, "_dvm", marshal_ctypes)
     return c
 
 
@@ -70,8 +77,9 @@ def test_buffers_are_checked(ctx):
         B.check_buffers(code, (whole[:0], whole))
 
 
-def test_a_build_in_the_process_that_uses_it(tmp_path):
-    """A clean tree's build imports the package, compiles, and loads what it compiled, all in one process."""
+@pytest.mark.parametrize("built", ["*.so", "libdvm.so"])
+def test_a_build_in_the_process_that_uses_it(tmp_path, built):
+    """A clean tree's build imports the package, compiles, and loads what it compiled, all in one process; without the extension module too."""
     here = os.path.dirname(B.__file__)
     pkg = tmp_path / os.path.basename(here)
     pkg.mkdir()
@@ -79,9 +87,10 @@ def test_a_build_in_the_process_that_uses_it(tmp_path):
         shutil.copy(f, pkg)
     script = ("import glob, shutil\n"
               "from paper_2603_24239_amd import binding as B\n"
-              f"for f in glob.glob({os.path.join(here, '*.so')!r}): shutil.copy(f, {str(pkg)!r})\n"
+              f"for f in glob.glob({os.path.join(here, built)!r}): shutil.copy(f, {str(pkg)!r})\n"
               "B.load()\n"
               f"assert B.__file__.startswith({str(pkg)!r})\n"
+              f"assert B._dvm.__name__.endswith({'._dvm' if built == '*.so' else '.marshal_ctypes'!r})\n"
               "assert B.Context(-1).device == -1\n")
     r = subprocess.run([sys.executable, "-c", script], cwd=tmp_path, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
