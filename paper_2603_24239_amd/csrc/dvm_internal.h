@@ -75,6 +75,15 @@ typedef struct dvm_rotary_args {
     uint32_t stream;                // 1: larger than the last-level cache holds, read past it
 } dvm_rotary_args;
 int dvm_rotary_launch(const dvm_rotary_args *a, void *stream);
+// One kernel launch of a run, as far as it is known without the device (the interpreter's grid is not).
+typedef struct dvm_launch {
+    uint32_t kind;                  // DVM_LAUNCH_*
+    uint32_t first_segment, n_segments;
+    uint32_t grid, block;
+    uint32_t lanes, slots;          // a softmax: lanes on a row, 16-byte chunks of a lane
+} dvm_launch;
+enum { DVM_LAUNCH_INTERPRETER = 0, DVM_LAUNCH_SOFTMAX, DVM_LAUNCH_SOFTMAX_LONG, DVM_LAUNCH_SOFTMAX_EXACT, DVM_LAUNCH_ROTARY };
+int dvm_launch_plan(const void *bytecode, size_t len, void *const *tensors, int n_sets, int n_cu, dvm_launch *out, int cap, int *n);
 // Implemented in the device file so that the encoder object stays free of HIP calls.
 int dvm_ctx_query_device(int hip_device, int *n_cu);
 

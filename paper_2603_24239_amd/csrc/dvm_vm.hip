@@ -2289,7 +2289,10 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     a->ia = sh[S_TBASE] + (la[1] & 0xFF);
     a->ib = lb ? sh[S_TBASE] + (lb[1] & 0xFF) : 0;
     a->iy = sh[S_TBASE] + (st[1] & 0xFF);
-    // An output may be an input, element for element: a row is read before it is stored.  Any other overlap stays with the interpreter.
+    // An output may be an input, element for element: a row is read before it is stored.  Any other overlap stays with the interpreter, and so
+    // does a long bf16 row written over the second tensor, which that kernel reads once more beside its stores (the last chunk of a row slides back over
+    // columns that another wave stores).
+    bool over_b = false;
     uint32_t shift = 0;
     for (int k = 0; k < n_sets; ++k) {
         void *const *t = tensors + (size_t)k * n_tensors;
@@ -2307,6 +2310,7 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
             if (lo >= yhi || ylo >= hi) continue;
             for (int d = 0; d < 3; ++d)
                 if (lo != ylo || (ext[d] > 1 && stride(i ? lb : la, d) != stride(st, d))) return false;
+            over_b |= i == 1;
         }
         const uint32_t at = (uint32_t)(ylo % 128) / es;
         if (at > shift) shift = at;
@@ -2326,6 +2330,7 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
         }
     }
     a->in_long = a->lanes == 0;
+    if (a->in_long != 0 && dt && over_b) return false;
     if (a->in_long != 0) a->lanes = need(512) <= (dt ? 16u : 24u) ? 512 : 1024;
     if (!a->exact) a->slots = need(a->lanes);
     if (a->slots > (dt ? 20u : 33u)) return false;
@@ -2489,6 +2494,69 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
     return true;
 }
 
+// A softmax that runs apart (plain_softmax): the segment at word `at`.  A smaller one, whose bits are the interpreter's, only where it is the whole
+// program: in a batched stack its arithmetic hides behind the traffic of the other parts (a 32-layer step of 200 tokens 213 us, 219 with it apart).
+bool runs_apart(const uint32_t *w, uint32_t at, void *const *tensors, int n_sets, dvm_softmax_args *sm) {
+    return plain_softmax(w + at, w + PH_WORDS_N, tensors, n_sets, w[PH_NTENS], w[PH_NSEG] == 1, sm);
+}
+// Workgroups of its launch.  The kernel for long rows loads a workgroup's next row while it stores the one before: as many as are resident.
+uint32_t softmax_grid(const dvm_softmax_args &sm, int n_cu) {
+    const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
+    return sm.in_long != 0 && sm.tiles > most ? most : sm.tiles;
+}
+
+// The kernel launches: segments in a run share one.  A segment starts a run of its own where it asks for one, and a softmax that runs apart is
+// one.  Segments that are independent of each other go first, all but those, in one launch; softmaxes alike in all but their addresses share a
+// launch, since few rows leave most of the chip idle (eight in a stack, one launch each and one for all, us: bf16 [32, 17000] 43 and 7, fp32 [128, 17000]
+// 60 and 27, bf16 [6000, 751] 51 and 24; in the interpreter 20, 40 and 42).
+struct Runs {
+    uint32_t n = 0, n_list = 0;
+    uint32_t list[MAX_SEGMENTS], at[MAX_SEGMENTS + 1];      // segments, run after run, and where the runs start
+    bool softmax[MAX_SEGMENTS];                             // the run is a softmax that runs apart
+    void push(uint32_t s, bool fresh, bool soft) {
+        if (fresh || n == 0) { softmax[n] = soft; at[n++] = n_list; }
+        list[n_list++] = s;
+    }
+};
+void plan_runs(const uint32_t *w, void *const *tensors, int n_sets, bool ordered, Runs *runs) {
+    uint32_t seg_at[MAX_SEGMENTS];
+    bool soft[MAX_SEGMENTS];
+    dvm_softmax_args sm;
+    for (uint32_t s = 0, at = PH_WORDS_N + w[PH_NTENS] * TT_WORDS; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
+        seg_at[s] = at;
+        soft[s] = runs_apart(w, at, tensors, n_sets, &sm);
+    }
+    if (ordered) {
+        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) runs->push(s, soft[s] || (s > 0 && soft[s - 1]) || (w[seg_at[s] + S_FLAGS] & SF_NEW_LAUNCH), soft[s]);
+    } else {
+        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!soft[s]) runs->push(s, false, false);
+        dvm_softmax_args last;
+        uint32_t n = 0;         // in the present run
+        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) {
+            if (!soft[s]) continue;
+            memset(&sm, 0, sizeof sm);
+            runs_apart(w, seg_at[s], tensors, n_sets, &sm);
+            sm.a = sm.y = nullptr;
+            if (sm.b) sm.b = w;         // (there is one)
+            sm.ia = sm.ib = sm.iy = 0;
+            const bool joins = n > 0 && n < DVM_SOFTMAX_MAX_PARTS && n_sets == 1 && memcmp(&sm, &last, sizeof sm) == 0 &&
+                               (uint64_t)sm.tiles * (n + 1) < (1ull << 31);
+            n = joins ? n + 1 : 1;
+            runs->push(s, !joins, true);
+            last = sm;
+        }
+    }
+    runs->at[runs->n] = runs->n_list;
+}
+// Segments that may depend on each other
+bool is_ordered(const uint32_t *w) {
+    bool r = (w[PH_TYPE] & 0xFFFF) == KT_STACK_SPATIAL;
+    for (uint32_t i = 0; i < w[PH_NTENS]; ++i) r |= (w[PH_WORDS_N + i * TT_WORDS + TT_INFO] & TI_WORKSPACE) != 0 || (w[PH_WORDS_N + i * TT_WORDS + TT_INFO] >> 24) != 0;
+    for (uint32_t s = 0, at = PH_WORDS_N + w[PH_NTENS] * TT_WORDS; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s)
+        r |= (w[at + S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID | SF_NEW_LAUNCH)) != 0;
+    return r;
+}
+
 // Loads take the streaming hint in launches that read more than this.  Less may still be in the last-level cache (256 MB) from the program that
 // wrote it or the one that read it last, beside what others use; the hint then costs (RMSNorm bf16 [11000, 4096], 90 MB read, 30.8 us
 // without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
@@ -2561,7 +2629,6 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     uint8_t seg_of[DVM_MAX_TENSORS];    // the segment a tensor belongs to
     memset(seg_of, 0xFF, sizeof(seg_of));
     if (w[PH_NSEG] > (uint32_t)MAX_SEGMENTS) return dvm_set_error(DVM_E_LIMIT, "dvm_run: bytecode exceeds the kernel-argument budget");
-    bool ordered = (w[PH_TYPE] & 0xFFFF) == KT_STACK_SPATIAL || ka.ws != 0;      // segments may depend on each other
     for (uint32_t s = 0, at = segs_off; s < w[PH_NSEG]; ++s) {
         const uint32_t *sh = w + at;
         seg_at[s] = at;
@@ -2570,11 +2637,9 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         grid_sync |= (sh[S_FLAGS] & SF_SYNC_GRID) != 0;
         wg_sync |= (sh[S_FLAGS] & SF_SYNC_WG) != 0;
         longrow |= (sh[S_FLAGS] & SF_LONGROW) != 0;
-        ordered |= (sh[S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID | SF_NEW_LAUNCH)) != 0;
         for (uint32_t t = 0; t < sh[S_NTENS]; ++t) seg_of[sh[S_TBASE] + t] = (uint8_t)s;
         at += sh[S_WORDS];
     }
-    for (uint32_t i = 0; i < ntens; ++i) ordered |= (w[PH_WORDS_N + i * TT_WORDS + TT_INFO] >> 24) != 0;
     // Segments of one launch run without order between them unless the bytecode says otherwise: see check_tensor_set
     const int n_sets = batch ? batch->n_sets : 1;
     for (int k = 0; k < n_sets; ++k) {
@@ -2620,11 +2685,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     const bool rotates = (w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL;
     if (grid_sync) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, (uint32_t)WS_SYNC_WORDS);
     hipError_t e;
-    // A softmax that runs apart (plain_softmax).  A smaller one, whose bits are the interpreter's, only where it is the whole program: in a batched
-    // stack its arithmetic hides behind the traffic of the other parts (a 32-layer step of 200 tokens 213 us, 219 with it apart).
-    auto softmax_of = [&](uint32_t s, dvm_softmax_args *sm) {
-        return plain_softmax(w + seg_at[s], w + PH_WORDS_N, tensors, n_sets, ntens, w[PH_NSEG] == 1, sm);
-    };
+    auto softmax_of = [&](uint32_t s, dvm_softmax_args *sm) { return runs_apart(w, seg_at[s], tensors, n_sets, sm); };
     dvm_rotary_args ra;
     if (w[PH_NSEG] == 1 && plain_rotary(w + segs_off, NR, w + PH_WORDS_N, tensors, n_sets, ntens, &ra)) {
         ra.sets = ka.sets;
@@ -2636,47 +2697,14 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         }
         return DVM_OK;
     }
-    // The kernel launches: segments in a run share one.  A segment starts a run of its own where it asks for one, and a softmax that runs apart is
-    // one.  Segments that are independent of each other go first, all but those, in one launch; softmaxes alike in all but their addresses share a
-    // launch, since few rows leave most of the chip idle (eight in a stack, one launch each and one for all, us: bf16 [32, 17000] 43 and 7, fp32 [128, 17000]
-    // 60 and 27, bf16 [6000, 751] 51 and 24; in the interpreter 20, 40 and 42).
-    uint32_t list[MAX_SEGMENTS], run_at[MAX_SEGMENTS + 1], n_runs = 0, n_list = 0;
-    bool apart_run[MAX_SEGMENTS];
-    dvm_softmax_args sm;
-    auto push = [&](uint32_t s, bool fresh, bool softmax) {
-        if (fresh || n_runs == 0) { apart_run[n_runs] = softmax; run_at[n_runs++] = n_list; }
-        list[n_list++] = s;
-    };
-    {
-        bool soft[MAX_SEGMENTS];
-        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) soft[s] = softmax_of(s, &sm);
-        if (ordered) {
-            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) push(s, soft[s] || (s > 0 && soft[s - 1]) || (w[seg_at[s] + S_FLAGS] & SF_NEW_LAUNCH), soft[s]);
-        } else {
-            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!soft[s]) push(s, false, false);
-            dvm_softmax_args last;
-            uint32_t n = 0;         // in the present run
-            for (uint32_t s = 0; s < w[PH_NSEG]; ++s) {
-                if (!soft[s]) continue;
-                memset(&sm, 0, sizeof sm);
-                softmax_of(s, &sm);
-                sm.a = sm.y = nullptr;
-                if (sm.b) sm.b = w;         // (there is one)
-                sm.ia = sm.ib = sm.iy = 0;
-                const bool joins = n > 0 && n < DVM_SOFTMAX_MAX_PARTS && n_sets == 1 && memcmp(&sm, &last, sizeof sm) == 0 &&
-                                   (uint64_t)sm.tiles * (n + 1) < (1ull << 31);
-                n = joins ? n + 1 : 1;
-                push(s, !joins, true);
-                last = sm;
-            }
-        }
-    }
-    run_at[n_runs] = n_list;
+    Runs runs;
+    plan_runs(w, tensors, n_sets, is_ordered(w), &runs);
     uint32_t vm_runs = 0;
-    for (uint32_t run = 0; run < n_runs; ++run) {
-        const uint32_t *segs = list + run_at[run];
-        const uint32_t n_segs = run_at[run + 1] - run_at[run];
-        if (apart_run[run]) {       // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
+    for (uint32_t run = 0; run < runs.n; ++run) {
+        const uint32_t *segs = runs.list + runs.at[run];
+        const uint32_t n_segs = runs.at[run + 1] - runs.at[run];
+        if (runs.softmax[run]) {    // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
+            dvm_softmax_args sm;
             softmax_of(segs[0], &sm);
             int n_cu = 256;
             dvm_ctx_planner_get(ctx, &n_cu, nullptr);
@@ -2696,10 +2724,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
                 sm.tiles *= n_segs;
             }
             sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets * n_segs >= STREAM_MIN_READS;
-            // (the kernel for long rows loads a workgroup's next row while it stores the one before: as many workgroups as are resident)
-            const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
-            const uint32_t grid = sm.in_long != 0 && sm.tiles > most ? most : sm.tiles;
-            e = (hipError_t)dvm_softmax_launch(&sm, grid, hip_stream);
+            e = (hipError_t)dvm_softmax_launch(&sm, softmax_grid(sm, n_cu), hip_stream);
             if (e != hipSuccess) {
                 t_last_hip_error = (int)e;
                 return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
@@ -2819,6 +2844,43 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
 }
 
 }  // namespace
+
+// The kernel launches that a run of `bytecode` over these tensors makes, without making them (for tests; no HIP call).
+extern "C" int dvm_launch_plan(const void *bytecode, size_t len, void *const *tensors, int n_sets, int n_cu, dvm_launch *out, int cap, int *n) {
+    if (!bytecode || !tensors || n_sets < 1 || !out || !n) return dvm_set_error(DVM_E_ARGS, "dvm_launch_plan: null argument");
+    const int st = dvm_validate(bytecode, len);
+    if (st != DVM_OK) return st;
+    const uint32_t *w = (const uint32_t *)bytecode;
+    if (w[PH_NSEG] > (uint32_t)MAX_SEGMENTS) return dvm_set_error(DVM_E_LIMIT, "dvm_launch_plan: bytecode exceeds the kernel-argument budget");
+    uint32_t seg_at[MAX_SEGMENTS];
+    for (uint32_t s = 0, at = PH_WORDS_N + w[PH_NTENS] * TT_WORDS; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) seg_at[s] = at;
+    Runs runs;
+    plan_runs(w, tensors, n_sets, is_ordered(w), &runs);
+    dvm_rotary_args ra;
+    const bool rotary = w[PH_NSEG] == 1 && plain_rotary(w + seg_at[0], (int)((w[PH_VARIANT] >> 8) & 0xFF), w + PH_WORDS_N, tensors, n_sets, w[PH_NTENS], &ra);
+    *n = (int)runs.n;
+    for (uint32_t r = 0; r < runs.n && (int)r < cap; ++r) {
+        dvm_launch &l = out[r];
+        l = dvm_launch{};
+        l.first_segment = runs.list[runs.at[r]];
+        l.n_segments = runs.at[r + 1] - runs.at[r];
+        dvm_softmax_args sm;
+        if (runs.softmax[r]) {
+            runs_apart(w, seg_at[l.first_segment], tensors, n_sets, &sm);
+            sm.tiles *= l.n_segments;
+            l.kind = sm.exact ? DVM_LAUNCH_SOFTMAX_EXACT : sm.in_long ? DVM_LAUNCH_SOFTMAX_LONG : DVM_LAUNCH_SOFTMAX;
+            l.grid = softmax_grid(sm, n_cu);
+            l.block = sm.exact || sm.lanes < 256 ? 256 : sm.lanes;
+            l.lanes = sm.lanes;
+            l.slots = sm.slots;
+        } else if (rotary) {
+            l.kind = DVM_LAUNCH_ROTARY;
+            l.grid = (ra.groups + 3) / 4;
+            l.block = 256;
+        }
+    }
+    return DVM_OK;
+}
 
 extern "C" int dvm_workspace_status(const void *workspace, void *hip_stream, int *gave_up) {
     if (!workspace || !gave_up) return dvm_set_error(DVM_E_ARGS, "dvm_workspace_status: null argument");

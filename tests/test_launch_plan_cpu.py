@@ -1,0 +1,54 @@
+"""Which kernel a run takes, and its launch: host rules, evaluated without a device over addresses that need not exist."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2603_24239_amd import binding as B
+from workloads import programs as W
+
+from . import launch_plan as L
+
+ES = {"f32": 4, "bf16": 2}
+FAR = 1 << 40       # between tensors
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = B.Context(-1)
+    c.set_planner(256)
+    return c
+
+
+def softmax(dt, masked=False):
+    if masked:
+        return B.Program(W._p(f"masked_{dt}", [("z", dt), ("m", dt)], [("s", "add", ["z", "m"], {}), ("p", "softmax", ["s"], {})], [("p", dt)]))
+    return B.Program(W.get_program(f"softmax_{dt}"))
+
+
+def encode(ctx, dt, shape, masked=False):
+    return B.dvm_encode(ctx, softmax(dt, masked), [B.make_shape(shape, align_bytes=4)] * (1 + masked), [B.make_shape(shape, align_bytes=4)])
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("cols", [25089, 30205, 65474, 131000])
+def test_long_rows_written_over_an_operand(ctx, dt, cols):
+    """Written over the first operand a row is read before it is stored.  The second one of a long bf16 row is read again beside the stores: such a call
+    stays with the interpreter."""
+    code = encode(ctx, dt, (100, cols), masked=True)
+    z, m, y = FAR, 2 * FAR, 3 * FAR
+    assert [l.kind for l in L.launches(code, [[z, m, y]])] == [L.SOFTMAX_LONG]
+    assert [l.kind for l in L.launches(code, [[z, m, z]])] == [L.SOFTMAX_LONG]
+    kept = L.INTERPRETER if dt == "bf16" else L.SOFTMAX_LONG
+    assert [l.kind for l in L.launches(code, [[z, m, m]])] == [kept]
+    assert [l.kind for l in L.launches(code, [[z, m, y], [z + 4096, m, m]])] == [kept]       # (in one set of a batch)
+    plain = encode(ctx, dt, (100, cols))
+    assert [l.kind for l in L.launches(plain, [[z, z]])] == [L.SOFTMAX_LONG]
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_shorter_rows_written_over_either_operand(ctx, dt):
+    code = encode(ctx, dt, (6000, 2600), masked=True)
+    for y in (FAR, 2 * FAR, 3 * FAR):
+        assert [l.kind for l in L.launches(code, [[FAR, 2 * FAR, y]])] == [L.SOFTMAX]
+    for y in (FAR + 2600 * ES[dt], 2 * FAR + ES[dt]):           # (any other overlap)
+        assert [l.kind for l in L.launches(code, [[FAR, 2 * FAR, y]])] == [L.INTERPRETER]
