@@ -56,7 +56,7 @@ def build(verbose: bool = True) -> str:
         os.remove(EXT)
     include = sysconfig.get_paths()["include"]
     if os.path.exists(os.path.join(include, "Python.h")):
-        jobs.append(([hipcc, "--no-hip-rt", "-x", "c", "-O2", "-std=c11", "-fPIC", "-Wall", "-shared", f"-I{include}", os.path.join(CSRC, "dvm_py.c")], EXT))
+        jobs.append(([hipcc, "-no-hip-rt", "-x", "c", "-O2", "-std=c11", "-fPIC", "-Wall", "-shared", f"-I{include}", os.path.join(CSRC, "dvm_py.c")], EXT))
     else:
         print(f"no Python.h in {include}: the binding's calls go through ctypes", flush=True)
     # every interpreter variant is a translation unit of its own, compiled side by side

@@ -34,7 +34,7 @@ using namespace dvmbc;
 namespace {
 
 constexpr int CODE_WORDS = DVM_CODE_MAX_BYTES / 4;
-constexpr int MAX_SEGMENTS = CODE_WORDS / SH_WORDS;
+[[maybe_unused]] constexpr int MAX_SEGMENTS = CODE_WORDS / SH_WORDS;
 
 struct KArgs {
     uint32_t code[CODE_WORDS];          // the segments of this launch (headers + bodies)
