@@ -2484,7 +2484,7 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
     const uint32_t rw = 64u >> a->log2_lanes;
     a->rows_per_lane = ext[0] % (4 * rw) == 0 && a->s[2][0] == 0 && a->s[3][0] == 0 ? 4 : 1;
     const uint64_t per = (uint64_t)rw * a->rows_per_lane, groups = (rows + per - 1) / per;
-    if (groups * (uint64_t)n_sets >= (1ull << 31)) return false;
+    if (groups * (uint64_t)n_sets >= (1ull << 26)) return false;       // (a wave each, and a launch has fewer than 2^32 threads)
     a->rows = (uint32_t)rows;
     a->set_groups = (uint32_t)groups;
     magic_of(a->set_groups, &a->set_m, &a->set_sh);
@@ -2499,10 +2499,12 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
 bool runs_apart(const uint32_t *w, uint32_t at, void *const *tensors, int n_sets, dvm_softmax_args *sm) {
     return plain_softmax(w + at, w + PH_WORDS_N, tensors, n_sets, w[PH_NTENS], w[PH_NSEG] == 1, sm);
 }
-// Workgroups of its launch.  The kernel for long rows loads a workgroup's next row while it stores the one before: as many as are resident.
+// Threads of a workgroup, and workgroups of its launch.  The kernel for long rows loads a workgroup's next row while it stores the one before: as many
+// as are resident.  The others take a tile each, as far as a launch may have that many threads (below 2^32), and the rest in turn.
+uint32_t softmax_block(const dvm_softmax_args &sm) { return sm.exact || sm.lanes < 256 ? 256 : sm.lanes; }
 uint32_t softmax_grid(const dvm_softmax_args &sm, int n_cu) {
-    const uint32_t most = (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u);
-    return sm.in_long != 0 && sm.tiles > most ? most : sm.tiles;
+    const uint32_t most = sm.in_long != 0 ? (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u) : UINT32_MAX / softmax_block(sm);
+    return sm.tiles > most ? most : sm.tiles;
 }
 
 // The kernel launches: segments in a run share one.  A segment starts a run of its own where it asks for one, and a softmax that runs apart is
@@ -2870,7 +2872,7 @@ extern "C" int dvm_launch_plan(const void *bytecode, size_t len, void *const *te
             sm.tiles *= l.n_segments;
             l.kind = sm.exact ? DVM_LAUNCH_SOFTMAX_EXACT : sm.in_long ? DVM_LAUNCH_SOFTMAX_LONG : DVM_LAUNCH_SOFTMAX;
             l.grid = softmax_grid(sm, n_cu);
-            l.block = sm.exact || sm.lanes < 256 ? 256 : sm.lanes;
+            l.block = softmax_block(sm);
             l.lanes = sm.lanes;
             l.slots = sm.slots;
         } else if (rotary) {

@@ -52,3 +52,23 @@ def test_shorter_rows_written_over_either_operand(ctx, dt):
         assert [l.kind for l in L.launches(code, [[FAR, 2 * FAR, y]])] == [L.SOFTMAX]
     for y in (FAR + 2600 * ES[dt], 2 * FAR + ES[dt]):           # (any other overlap)
         assert [l.kind for l in L.launches(code, [[FAR, 2 * FAR, y]])] == [L.INTERPRETER]
+
+
+@pytest.mark.parametrize("dt,rows,cols,kind", [("f32", 1 << 29, 32, L.SOFTMAX), ("bf16", 1 << 29, 64, L.SOFTMAX), ("bf16", (1 << 29) - 31, 100, L.SOFTMAX),
+                                               ("f32", (1 << 31) - 1, 3, L.SOFTMAX_EXACT), ("f32", 1 << 20, 1 << 13, L.SOFTMAX), ("f32", 1 << 13, 1 << 17, L.SOFTMAX_LONG)])
+def test_a_launch_has_fewer_threads_than_it_may(ctx, dt, rows, cols, kind):
+    """HIP takes fewer than 2^32 threads; the kernels stride over the tiles that are left."""
+    (l,) = L.launches(encode(ctx, dt, (rows, cols)), [[FAR, 2 * FAR]])
+    assert l.kind == kind and 0 < l.grid * l.block < 1 << 32
+
+
+@pytest.mark.parametrize("tokens,kind", [(1 << 20, L.ROTARY), (1 << 25, L.INTERPRETER)])
+def test_a_rotation_beyond_one_launch(ctx, tokens, kind):
+    """Three heads of 2 * 512 columns under shared tables: a wave takes one row."""
+    prog = B.Program(W.get_program("c5_rope"))
+    x = B.make_shape((tokens, 3, 512), (3072, 1024, 1), 16)
+    t = B.make_shape((tokens, 1, 512), (512, 512, 1), 16)
+    code = B.dvm_encode(ctx, prog, [x, x, t, t], [x, x])
+    q, c, s, y = FAR, 3 * FAR, 5 * FAR, 7 * FAR
+    (l,) = L.launches(code, [[q, q + 1024, c, s, y, y + 1024]])
+    assert l.kind == kind and l.grid * l.block < 1 << 32
