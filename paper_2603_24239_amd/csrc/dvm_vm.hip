@@ -2315,13 +2315,15 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
         const uint32_t at = (uint32_t)(ylo % 128) / es;
         if (at > shift) shift = at;
     }
-    if (!even) shift = line - 1;
-    a->shifted = shift != 0;
-    auto need = [&](uint32_t lanes) { return (uint32_t)((cols + shift + (uint64_t)lanes * V - 1) / ((uint64_t)lanes * V)); };
+    // Lanes and kernel follow from the strides alone, never from an address: the sums of a row depend on them, and a set of a batch keeps its bits
+    // whatever the others' addresses are.  Rows of whole lines in an output that starts inside one take the slots that the shift needs where their
+    // kernel has them, and stay where they are otherwise (the classes of columns, and with them the bits, are the same).
+    auto need = [&](uint32_t lanes, uint32_t by) { return (uint32_t)((cols + by + (uint64_t)lanes * V - 1) / ((uint64_t)lanes * V)); };
+    const uint32_t planned = even ? 0 : line - 1;
     if (!a->exact) a->lanes = 0;
     uint64_t best = a->exact ? 0 : UINT64_MAX;
     for (uint32_t lanes = 8; lanes <= 1024; lanes *= 2) {
-        const uint32_t n = need(lanes);
+        const uint32_t n = need(lanes, planned);
         if (n > (lanes == 1024 ? (dt ? 3u : 4u) : dt ? 6u : 8u)) continue;
         const uint64_t cost = (uint64_t)lanes * n * (n > 4 && (dt || lanes != 64) ? 18 : 16) * (lanes > 64 ? 17 : 16);
         if (cost < best) {
@@ -2331,9 +2333,19 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     }
     a->in_long = a->lanes == 0;
     if (a->in_long != 0 && dt && over_b) return false;
-    if (a->in_long != 0) a->lanes = need(512) <= (dt ? 16u : 24u) ? 512 : 1024;
-    if (!a->exact) a->slots = need(a->lanes);
-    if (a->slots > (dt ? 20u : 33u)) return false;
+    if (a->in_long != 0) a->lanes = need(512, planned) <= (dt ? 16u : 24u) ? 512 : 1024;
+    a->line_mask = 0;
+    if (!a->exact) {
+        const uint32_t most = a->in_long != 0 ? (a->lanes == 512 ? (dt ? 16u : 24u) : dt ? 20u : 33u) : a->lanes == 1024 ? 4u : dt ? 6u : 8u;
+        a->slots = need(a->lanes, planned);
+        if (a->slots > most) return false;
+        if (!even) shift = planned;
+        if (need(a->lanes, shift) <= most) {
+            a->slots = need(a->lanes, shift);
+            a->line_mask = 127;
+        }
+    }
+    a->shifted = shift != 0 && a->line_mask != 0;
     a->tail = (uint32_t)(cols / ((uint64_t)a->lanes * V));
     const uint64_t rp = a->lanes >= 256 ? 1 : 256 / a->lanes, tiles = (all + rp - 1) / rp;
     if (all >= (1ull << 32) || tiles * (uint64_t)n_sets >= (1ull << 31)) return false;

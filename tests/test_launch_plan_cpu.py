@@ -72,3 +72,22 @@ def test_a_rotation_beyond_one_launch(ctx, tokens, kind):
     q, c, s, y = FAR, 3 * FAR, 5 * FAR, 7 * FAR
     (l,) = L.launches(code, [[q, q + 1024, c, s, y, y + 1024]])
     assert l.kind == kind and l.grid * l.block < 1 << 32
+
+
+# widths of whole lines whose lanes or kernel a row that starts inside a line would change
+WHOLE_LINES = {"f32": [192, 448, 2048, 8160, 16384, 32768, 131072], "bf16": [448, 960, 1984, 16384, 24576, 65536, 163840]}
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_lanes_do_not_depend_on_addresses(ctx, dt):
+    """The sums of a row, and so its bits, follow from its lanes; the kernel must be the same too, apart from its slots of chunks."""
+    for cols in WHOLE_LINES[dt]:
+        rows = -(-(20 << 20) // (2 * ES[dt] * cols))
+        code = encode(ctx, dt, (rows, cols))
+        (on,) = L.launches(code, [[FAR, 2 * FAR]])
+        assert on.kind in (L.SOFTMAX, L.SOFTMAX_LONG)
+        for at in (ES[dt] if dt == "f32" else 4, 16, 124):
+            for sets in ([[FAR, 2 * FAR + at]], [[FAR + 64, 2 * FAR], [FAR, 2 * FAR + at], [FAR, 3 * FAR]]):
+                (off,) = L.launches(code, sets)
+                assert (off.kind, off.lanes, off.block) == (on.kind, on.lanes, on.block), (cols, at)
+                assert on.slots <= off.slots <= on.slots + 1
