@@ -380,7 +380,7 @@ def dvm_run(ctx: Context, code: Bytecode, tensor_ptrs: Sequence[int], stream: in
 def dvm_run_batched(ctx: Context, code: Bytecode, tensor_ptr_sets: Sequence[Sequence[int]], table_ptr: int, table_bytes: int,
                     stream: int = 0) -> None:
     """One launch over several sets of tensors (device pointers); `table_ptr`: device memory for the address table."""
-    tensor_ptr_sets[0]              # (at least one set)
+    len(tensor_ptr_sets[0])         # (at least one set, and of a known size; the others may be any iterables)
     status = _dvm.run_batched(ctx._h, code.raw, tensor_ptr_sets, table_ptr, table_bytes, stream)
     assert status is not None       # (sets of equal size)
     if status != 0:

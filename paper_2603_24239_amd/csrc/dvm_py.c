@@ -192,18 +192,21 @@ static PyObject *py_run_batched(PyObject *self, PyObject *const *a, Py_ssize_t n
     void **flat = NULL;
     PyObject *result = NULL;
     for (Py_ssize_t k = 0; k < n_sets; ++k) {
-        PyObject *set = PySequence_Fast_GET_ITEM(sets, k);
+        PyObject *set = PySequence_Fast(PySequence_Fast_GET_ITEM(sets, k), "a set of addresses");      /* (any iterable, taken once) */
+        if (!set) goto done;
         if (k == 0) {
-            n = PySequence_Size(set);
-            if (n < 0) goto done;
+            n = PySequence_Fast_GET_SIZE(set);
             flat = (void **)PyMem_Malloc(sizeof(void *) * (size_t)(n > 0 ? n : 1) * (size_t)n_sets);
-            if (!flat) { PyErr_NoMemory(); goto done; }
+            if (!flat) { PyErr_NoMemory(); Py_DECREF(set); goto done; }
         }
-        if (k > 0 && PySequence_Size(set) != n) {
-            if (!PyErr_Occurred()) { result = Py_None; Py_INCREF(result); }
+        const Py_ssize_t got = PySequence_Fast_GET_SIZE(set) == n ? addresses_from(set, flat + k * n, n) : n + 1;
+        Py_DECREF(set);
+        if (got < 0) goto done;
+        if (got != n) {
+            result = Py_None;
+            Py_INCREF(result);
             goto done;
         }
-        if (addresses_from(set, flat + k * n, n) < 0) goto done;
     }
     {
         int st;

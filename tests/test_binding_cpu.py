@@ -77,6 +77,34 @@ def test_buffers_are_checked(ctx):
         B.check_buffers(code, (whole[:0], whole))
 
 
+class Yields:
+    """A sequence that yields fewer addresses than its length says."""
+
+    def __init__(self, at):
+        self.at = at
+
+    def __len__(self):
+        return len(self.at) + 1
+
+    def __getitem__(self, i):
+        return self.at[i]
+
+    def __iter__(self):
+        return iter(self.at)
+
+
+def test_sets_are_iterables_of_addresses(ctx):
+    code = B.encode_for(ctx, B.Program(W.single_op_program("abs", 1, "f32")), [torch.zeros(16)])
+    for sets in ([[64, 64], iter([64, 64])], [(64, 64), (p for p in (64, None))], ([64, 64], {64: 0, 128: 0})):
+        with pytest.raises(B.DvmError, match="dvm_run_batched"):        # (a context without a device launches nothing)
+            B.dvm_run_batched(ctx, code, sets, 64, 4096)
+    for sets in ([[64, 64], iter([64])], [[64, 64], (p for p in range(64, 67))], [[64, 64], Yields([64])]):
+        with pytest.raises(AssertionError):
+            B.dvm_run_batched(ctx, code, sets, 64, 4096)
+    with pytest.raises(TypeError):
+        B.dvm_run_batched(ctx, code, [iter([64, 64])], 64, 4096)
+
+
 @pytest.mark.parametrize("built", ["*.so", "libdvm.so"])
 def test_a_build_in_the_process_that_uses_it(tmp_path, built):
     """A clean tree's build imports the package, compiles, and loads what it compiled, all in one process; without the extension module too."""
