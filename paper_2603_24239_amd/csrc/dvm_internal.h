@@ -51,8 +51,7 @@ typedef struct dvm_softmax_args {
     uint32_t slots;                 // 16-byte chunks of a lane
     uint32_t tail;                  // a row may end in this slot of chunks or behind it
     uint32_t stream;                // 1: larger than the last-level cache holds, read past it
-    uint32_t line_mask;             // 127: a row's chunks are laid on the 128-byte lines of the output, 0: they start with the row
-    uint32_t shifted;               // some row does not start with its first chunk
+    uint32_t shifted;               // 1: a row's chunks are laid on the 128-byte lines of the output, 0: they start with the row
     uint64_t parts[3 * 16];         // sets = DVM_SOFTMAX_PARTS: the addresses of up to 16 alike parts of a stack (n_tensors 3, in the order 0, 1, 2)
 } dvm_softmax_args;
 constexpr uint64_t DVM_SOFTMAX_PARTS = 1;

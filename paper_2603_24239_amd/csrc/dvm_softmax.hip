@@ -144,7 +144,8 @@ template <int BF16, bool MASK> DI Row place(const dvm_softmax_args &s, uint32_t 
     r.a = (const char *)pa + ((int64_t)i1 * s.a_s[0] + (int64_t)i2 * s.a_s[1] + (int64_t)i3 * s.a_s[2]) * ES;
     r.b = MASK ? (const char *)pb + ((int64_t)i1 * s.b_s[0] + (int64_t)i2 * s.b_s[1] + (int64_t)i3 * s.b_s[2]) * ES : nullptr;
     r.y = (char *)py + ((int64_t)i1 * s.y_s[0] + (int64_t)i2 * s.y_s[1] + (int64_t)i3 * s.y_s[2]) * ES;
-    r.shift = (int)(((uint32_t)(uintptr_t)r.y & s.line_mask) / ES);
+    r.shift = (int)(((uint32_t)(uintptr_t)r.y & 127u) / ES);
+    r.shift = s.shifted != 0 ? r.shift : 0;
     r.ok = ok;
     return r;
 }

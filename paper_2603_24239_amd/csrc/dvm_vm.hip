@@ -2334,7 +2334,7 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     a->in_long = a->lanes == 0;
     if (a->in_long != 0 && dt && over_b) return false;
     if (a->in_long != 0) a->lanes = need(512, planned) <= (dt ? 16u : 24u) ? 512 : 1024;
-    a->line_mask = 0;
+    a->shifted = 0;
     if (!a->exact) {
         const uint32_t most = a->in_long != 0 ? (a->lanes == 512 ? (dt ? 16u : 24u) : dt ? 20u : 33u) : a->lanes == 1024 ? 4u : dt ? 6u : 8u;
         a->slots = need(a->lanes, planned);
@@ -2342,10 +2342,9 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
         if (!even) shift = planned;
         if (need(a->lanes, shift) <= most) {
             a->slots = need(a->lanes, shift);
-            a->line_mask = 127;
+            a->shifted = shift != 0;
         }
     }
-    a->shifted = shift != 0 && a->line_mask != 0;
     a->tail = (uint32_t)(cols / ((uint64_t)a->lanes * V));
     const uint64_t rp = a->lanes >= 256 ? 1 : 256 / a->lanes, tiles = (all + rp - 1) / rp;
     if (all >= (1ull << 32) || tiles * (uint64_t)n_sets >= (1ull << 31)) return false;
