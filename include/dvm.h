@@ -214,7 +214,7 @@ int  dvm_encode(const dvm_ctx *ctx, const dvm_prog *prog,
  * depend on each other use dvm_stack_dependent.  Parts planned for the variant of 64 elements beside others whose tensors exceed 256 MB in
  * all make two kernel launches of one dvm_run (dvm_code_info.n_launches): each kind runs in its own variant.
  * A softmax along the row that moves 16 MB or more (over rows longer than a tile: 2 MB) runs in a kernel of its own, as a launch of
- * its own in its place among the parts (independent ones alike in all but their addresses share one), here, in dvm_stack_dependent and in dvm_run_batched; n_launches does not count those. */
+ * its own in its place among the parts (independent ones of one type and kernel share it), here, in dvm_stack_dependent and in dvm_run_batched; n_launches does not count those. */
 int  dvm_stack(const void *const *codes, const size_t *lens, int n,
                void *out, size_t cap, size_t *len);
 

@@ -52,12 +52,24 @@ typedef struct dvm_softmax_args {
     uint32_t tail;                  // a row may end in this slot of chunks or behind it
     uint32_t stream;                // 1: larger than the last-level cache holds, read past it
     uint32_t shifted;               // 1: a row's chunks are laid on the 128-byte lines of the output, 0: they start with the row
-    uint64_t parts[3 * 16];         // sets = DVM_SOFTMAX_PARTS: the addresses of up to 16 alike parts of a stack (n_tensors 3, in the order 0, 1, 2)
 } dvm_softmax_args;
-constexpr uint64_t DVM_SOFTMAX_PARTS = 1;
+// What a launch takes: one of them, or (sets = DVM_SOFTMAX_PARTS, n_tensors 3, in the order 0, 1, 2) several alike in all but their addresses
 constexpr uint32_t DVM_SOFTMAX_MAX_PARTS = 16;
+constexpr uint64_t DVM_SOFTMAX_PARTS = 1;
+typedef struct dvm_softmax_alike {
+    dvm_softmax_args s;
+    uint64_t parts[3 * DVM_SOFTMAX_MAX_PARTS];
+} dvm_softmax_alike;
+// or several alike in type, second tensor or none, and kernel (lanes up to 256; or the same lanes and in_long) only
+typedef struct dvm_softmax_mixed {
+    uint32_t n;
+    uint32_t first[DVM_SOFTMAX_MAX_PARTS + 1];          // tiles of the parts before each, and of all
+    dvm_softmax_args part[DVM_SOFTMAX_MAX_PARTS];
+} dvm_softmax_mixed;
+static_assert(sizeof(dvm_softmax_mixed) <= 4096, "a kernel's arguments");
 constexpr int64_t DVM_SOFTMAX_MIN_BYTES = 16 << 20;
-int dvm_softmax_launch(const dvm_softmax_args *a, unsigned grid, void *stream);
+int dvm_softmax_launch(const dvm_softmax_alike *a, unsigned grid, void *stream);
+int dvm_softmax_launch_mixed(const dvm_softmax_mixed *p, unsigned grid, void *stream);
 // A rotation of pairs over short rows as its own kernel takes it (dvm_rotary.hip): tensors in the order x1, x2, c, s, y1, y2; strides in elements.
 typedef struct dvm_rotary_args {
     uint64_t p[6];                  // addresses
@@ -80,7 +92,8 @@ typedef struct dvm_launch {
     uint32_t kind;                  // DVM_LAUNCH_*
     uint32_t first_segment, n_segments;
     uint32_t grid, block;
-    uint32_t lanes, slots;          // a softmax: lanes on a row, 16-byte chunks of a lane
+    uint32_t lanes, slots;          // a softmax: lanes on a row, 16-byte chunks of a lane (mixed: of the first part)
+    uint32_t mixed;                 // softmaxes of several shapes
 } dvm_launch;
 enum { DVM_LAUNCH_INTERPRETER = 0, DVM_LAUNCH_SOFTMAX, DVM_LAUNCH_SOFTMAX_LONG, DVM_LAUNCH_SOFTMAX_EXACT, DVM_LAUNCH_ROTARY };
 int dvm_launch_plan(const void *bytecode, size_t len, void *const *tensors, int n_sets, int n_cu, dvm_launch *out, int cap, int *n);

@@ -132,9 +132,9 @@ template <int BF16, bool MASK> DI Row place(const dvm_softmax_args &s, uint32_t 
     i1 = ok ? i1 : s.limit - 1u - i3 * s.d1;
     uint64_t pa = (uint64_t)(uintptr_t)s.a, pb = (uint64_t)(uintptr_t)s.b, py = (uint64_t)(uintptr_t)s.y;
     if (s.sets != 0) {
-        // (the addresses of a stack's parts are in the argument block, which is memory like any other)
+        // (the addresses of a stack's alike parts are in the argument block, which is memory like any other)
         uint64_t table = s.sets;
-        if (table == DVM_SOFTMAX_PARTS) table = (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(dvm_softmax_args, parts);
+        if (table == DVM_SOFTMAX_PARTS) table = (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(dvm_softmax_alike, parts);
         const GLOBAL_AS uint64_t *t = (const GLOBAL_AS uint64_t *)table + (uint64_t)set * s.n_tensors;
         pa = t[s.ia];
         if constexpr (MASK) pb = t[s.ib];
@@ -200,19 +200,20 @@ template <int V, int T> DI float in_order_narrow(float *acc, uint32_t tid, int s
 }
 
 // ---- rows of up to NR * T * V columns (less the shift), T lanes on a row --------------------------------------------------
-template <int BF16, int T, int NR, bool MASK>
-__global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_softmax_args s) {
+// Tiles `first` to `end`, `step` apart (one alone is written so too: outside a loop the compiler makes one vector of a lane's chunks and waits for
+// the first of them before it asks for the next, fp32 [1000, 16384] 28.0 -> 28.8 us).  rot: BLOCK * V floats of LDS, red: two for every wave.  HALF: a launch's rows have more than NR / 2 chunks a lane, so that many are not asked for.
+template <int BF16, int T, int NR, bool MASK, bool HALF> DI void rows_of(const dvm_softmax_args &s, uint32_t first, uint32_t end, uint32_t step, float *rot, float *red) {
     constexpr int V = BF16 ? 8 : 4, ES = BF16 ? 2 : 4, W = T * V, BLOCK = T < 256 ? 256 : T, RP = BLOCK / T;
     constexpr int GW = T > 64 ? T / 64 : 1;             // waves on a row
-    __shared__ __align__(16) float rot[BLOCK * V];
-    __shared__ float red[2][BLOCK / 64];
+    constexpr int SURE = HALF ? NR / 2 : 0;
+    float *red0 = red, *red1 = red + BLOCK / 64;
     const uint32_t tid = threadIdx.x;
     const uint32_t g = tid / T, l = tid % T;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
     const int cols = (int)s.cols, cmax = cols - V;
     const bool shifted = s.shifted != 0;
     const int at = (int)l * V;
-    for (uint32_t tile = blockIdx.x; tile < s.tiles; tile += gridDim.x) {
+    for (uint32_t tile = first; tile < end; tile += step) {
         const uint32_t set = s.sets != 0 ? magic_div(tile, s.set_m, s.set_sh) : 0u;
         uint32_t row = (tile - set * s.set_tiles) * RP + (T >= 64 ? wave / GW : g);
         const bool in = row < s.rows;
@@ -225,23 +226,23 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
         if (s.stream != 0) {        // (the same for every lane)
 #pragma unroll
             for (int j = 0; j < NR; ++j)
-                if (j < NR / 2 || j < (int)s.slots) raw[j] = load16<true>(r.a + (int64_t)col(c_first + j * W) * ES);
+                if (j < SURE || j < (int)s.slots) raw[j] = load16<true>(r.a + (int64_t)col(c_first + j * W) * ES);
             STREAMING();
         } else {
 #pragma unroll
             for (int j = 0; j < NR; ++j)
-                if (j < NR / 2 || j < (int)s.slots) raw[j] = load16<false>(r.a + (int64_t)col(c_first + j * W) * ES);
+                if (j < SURE || j < (int)s.slots) raw[j] = load16<false>(r.a + (int64_t)col(c_first + j * W) * ES);
         }
         if constexpr (MASK) {
 #pragma unroll
             for (int j = 0; j < NR; ++j)
-                if (j < NR / 2 || j < (int)s.slots) rawb[j] = load16<false>(r.b + (int64_t)col(c_first + j * W) * ES);
+                if (j < SURE || j < (int)s.slots) rawb[j] = load16<false>(r.b + (int64_t)col(c_first + j * W) * ES);
         }
         float v[NR][V];
         float m = NEG_INF;
 #pragma unroll
         for (int j = 0; j < NR; ++j)
-            if (j < NR / 2 || j < (int)s.slots) {
+            if (j < SURE || j < (int)s.slots) {
                 widen<BF16>(v[j], raw[j]);
                 if constexpr (MASK) {
                     float b[V];
@@ -254,9 +255,9 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
             }
         m = group_all<true, T>(m);
         if constexpr (T > 64) {
-            red[0][wave] = m;
+            red0[wave] = m;
             __syncthreads();
-            const float *w = red[0] + wave / GW * GW;
+            const float *w = red0 + wave / GW * GW;
             m = w[0];
 #pragma unroll
             for (int i = 1; i < GW; ++i) m = maxp(m, w[i]);
@@ -266,7 +267,7 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
         for (int e = 0; e < V; ++e) acc[e] = 0.0f;
 #pragma unroll
         for (int j = 0; j < NR; ++j)
-            if (j < NR / 2 || j < (int)s.slots) {
+            if (j < SURE || j < (int)s.slots) {
 #pragma unroll
                 for (int e = 0; e < V; ++e) v[j][e] = __builtin_amdgcn_exp2f((v[j][e] - m) * LOG2E);
                 if ((j == 0 && shifted) || j >= (int)s.tail) {        // (the same for every lane)
@@ -286,9 +287,9 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
         else sum = sum_of<V>(acc);
         sum = group_all<false, T>(sum);
         if constexpr (T > 64) {
-            red[1][wave] = sum;
+            red1[wave] = sum;
             __syncthreads();
-            const float *w = red[1] + wave / GW * GW;
+            const float *w = red1 + wave / GW * GW;
             sum = w[0];
 #pragma unroll
             for (int i = 1; i < GW; ++i) sum += w[i];
@@ -296,11 +297,18 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
         const float scale = __builtin_amdgcn_rcpf(sum);
 #pragma unroll
         for (int j = 0; j < NR; ++j)
-            if (j < NR / 2 || j < (int)s.slots) {
+            if (j < SURE || j < (int)s.slots) {
                 const int c0 = c_first + j * W;
                 if (ok && c0 > -V && c0 < cols) store16(r.y + (int64_t)col(c0) * ES, narrow<BF16>(v[j], scale));
             }
     }
+}
+template <int BF16, int T, int NR, bool MASK>
+__global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_softmax_alike a) {
+    constexpr int V = BF16 ? 8 : 4, BLOCK = T < 256 ? 256 : T;
+    __shared__ __align__(16) float rot[BLOCK * V];
+    __shared__ float red[2 * (BLOCK / 64)];
+    rows_of<BF16, T, NR, MASK, true>(a.s, blockIdx.x, a.s.tiles, gridDim.x, rot, red);
 }
 
 // ---- longer rows: a workgroup of T = 512 or 1024 threads holds one --------------------------------------------------------
@@ -308,48 +316,52 @@ __global__ void __launch_bounds__(T < 256 ? 256 : T) dvm_softmax_rows(const dvm_
 // stores slot by slot, so that only the exponentials of a row run without memory traffic of its own workgroup.
 // (fp32 rows of 33 slots leave LDS for one class of every lane at a time only; more barriers)
 constexpr bool long_narrow(bool bf16, int nr) { return !bf16 && nr == 24; }
-template <int BF16, int T, int NR, bool MASK>
-__global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_args s) {
+// Src: the launch's rows, of one softmax or of several.
+template <int BF16, int T, int NR, bool MASK, class Src> DI void long_rows(const Src &src, float *lds) {
     constexpr int V = BF16 ? 8 : 4, ES = BF16 ? 2 : 4, W = T * V, NW = T / 64;
     constexpr bool NARROW = long_narrow(BF16, NR);
     constexpr int ROT = NARROW ? 2 * T : W;
-    extern __shared__ __align__(16) float lds[];        // ROT floats for the classes, 32 for the waves, then the row's slots from NR on
+    // lds: ROT floats for the classes, 32 for the waves, then the row's slots from NR on
     float *rot = lds, *red = lds + ROT;
     u32x4 *stash = (u32x4 *)(lds + ROT + 32);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid) >> 6;
-    const int cols = (int)s.cols, cmax = cols - V, n_slots = (int)s.slots;
-    const bool shifted = s.shifted != 0;
     const int at = (int)tid * V;
-    auto col = [&](int c0) { const int c = c0 < cmax ? c0 : cmax; return c > 0 ? c : 0; };
-    auto placed = [&](uint32_t tile) {
+    auto col = [&](int c0, int cmax) { const int c = c0 < cmax ? c0 : cmax; return c > 0 ? c : 0; };
+    auto placed = [&](uint32_t part, uint32_t tile) {
+        const dvm_softmax_args &s = src.args(part);
+        tile -= src.first(part);
         const uint32_t set = s.sets != 0 ? magic_div(tile, s.set_m, s.set_sh) : 0u;
         return place<BF16, MASK>(s, set, tile - set * s.set_tiles);
     };
     // what a lane does with a chunk: its values (of the sum, where there is a second tensor)
-    auto values = [&](float *v, u32x4 raw, const Row &r, int c0) {
+    auto values = [&](float *v, u32x4 raw, const Row &r, int c0, int cmax) {
         widen<BF16>(v, raw);
         if constexpr (MASK) {
             float b[V];
-            widen<BF16>(b, load16<false>(r.b + (int64_t)col(c0) * ES));
+            widen<BF16>(b, load16<false>(r.b + (int64_t)col(c0, cmax) * ES));
 #pragma unroll
             for (int e = 0; e < V; ++e) v[e] += b[e];
         }
     };
     u32x4 raw[NR];
     uint32_t tile = blockIdx.x;
-    if (tile >= s.tiles) return;
-    Row r = placed(tile);
+    if (tile >= src.tiles()) return;
+    uint32_t part = src.part_of(tile, 0u);
+    Row r = placed(part, tile);
 #pragma unroll
     for (int j = 0; j < NR; ++j)
-        if (j < n_slots) raw[j] = load16<true>(r.a + (int64_t)col(at - r.shift + j * W) * ES);
+        if (j < (int)src.args(part).slots) raw[j] = load16<true>(r.a + (int64_t)col(at - r.shift + j * W, (int)src.args(part).cols - V) * ES);
     for (;;) {
+        const dvm_softmax_args &s = src.args(part);
+        const int cols = (int)s.cols, cmax = cols - V, n_slots = (int)s.slots;
+        const bool shifted = s.shifted != 0;
         const int c_first = at - r.shift;
         float m = NEG_INF;
         for (int j = NR; j < n_slots; ++j) {
-            const u32x4 w = load16<true>(r.a + (int64_t)col(c_first + j * W) * ES);
+            const u32x4 w = load16<true>(r.a + (int64_t)col(c_first + j * W, cmax) * ES);
             stash[(j - NR) * T + tid] = w;
             float v[V];
-            values(v, w, r, c_first + j * W);
+            values(v, w, r, c_first + j * W, cmax);
 #pragma unroll
             for (int e = 0; e < V; ++e) m = maxp(m, v[e]);
         }
@@ -357,7 +369,7 @@ __global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_args s) 
         for (int j = 0; j < NR; ++j)
             if (j < n_slots) {
                 float v[V];
-                values(v, raw[j], r, c_first + j * W);
+                values(v, raw[j], r, c_first + j * W, cmax);
 #pragma unroll
                 for (int e = 0; e < V; ++e) m = maxp(m, v[e]);
             }
@@ -381,14 +393,14 @@ __global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_args s) 
         for (int j = 0; j < NR; ++j)
             if (j < n_slots) {
                 float v[V];
-                values(v, raw[j], r, c_first + j * W);
+                values(v, raw[j], r, c_first + j * W, cmax);
                 exps(v);
                 if constexpr (!BF16) raw[j] = narrow<0>(v, 1.0f);       // (fp32 exponentials are kept, bf16 rows are taken from their inputs again)
                 take(v, j);
             }
         for (int j = NR; j < n_slots; ++j) {
             float v[V];
-            values(v, stash[(j - NR) * T + tid], r, c_first + j * W);
+            values(v, stash[(j - NR) * T + tid], r, c_first + j * W, cmax);
             exps(v);
             if constexpr (!BF16) stash[(j - NR) * T + tid] = narrow<0>(v, 1.0f);
             take(v, j);
@@ -404,27 +416,86 @@ __global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_args s) 
             const int c0 = c_first + j * W;
             float v[V];
             if constexpr (BF16) {
-                values(v, w, r, c0);
+                values(v, w, r, c0, cmax);
                 exps(v);
             } else {
                 widen<0>(v, w);
             }
-            if (r.ok && c0 > -V && c0 < cols) store16(r.y + (int64_t)col(c0) * ES, narrow<BF16>(v, scale));
+            if (r.ok && c0 > -V && c0 < cols) store16(r.y + (int64_t)col(c0, cmax) * ES, narrow<BF16>(v, scale));
         };
         for (int j = NR; j < n_slots; ++j) put(stash[(j - NR) * T + tid], j);
         const uint32_t next = tile + gridDim.x;
-        const bool last = next >= s.tiles;      // (the same for every lane)
-        const Row n = placed(last ? tile : next);
+        const bool last = next >= src.tiles();      // (the same for every lane)
+        const uint32_t next_part = last ? part : src.part_of(next, part);
+        const Row n = placed(next_part, last ? tile : next);
+        const int next_slots = last ? 0 : (int)src.args(next_part).slots, next_cmax = (int)src.args(next_part).cols - V;
 #pragma unroll
-        for (int j = 0; j < NR; ++j)
-            if (j < n_slots) {
-                put(raw[j], j);
-                if (!last) raw[j] = load16<true>(n.a + (int64_t)col(at - n.shift + j * W) * ES);
-            }
+        for (int j = 0; j < NR; ++j) {
+            if (j < n_slots) put(raw[j], j);
+            if (j < next_slots) raw[j] = load16<true>(n.a + (int64_t)col(at - n.shift + j * W, next_cmax) * ES);
+        }
         if (last) break;
         tile = next;
+        part = next_part;
         r = n;
     }
+}
+
+struct OneSoftmax {
+    const dvm_softmax_args &s;
+    DI uint32_t tiles() const { return s.tiles; }
+    DI uint32_t part_of(uint32_t, uint32_t) const { return 0; }
+    DI uint32_t first(uint32_t) const { return 0; }
+    DI const dvm_softmax_args &args(uint32_t) const { return s; }
+};
+template <int BF16, int T, int NR, bool MASK>
+__global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_alike a) {
+    extern __shared__ __align__(16) float lds[];
+    long_rows<BF16, T, NR, MASK>(OneSoftmax{a.s}, lds);
+}
+
+// ---- several softmaxes in one launch --------------------------------------------------------------------------------------
+// Independent parts of a stack.  Few rows leave most of the chip idle, and a launch for each is one after the other: eight unlike ones of fp32
+// [16, 100003] 156 us so, 48 in the interpreter and 25 here; bf16 [32, 17000] 43, 18 and 6.7; fp32 [600, 8192] 82, 65 and 55.  A workgroup takes its
+// tile's part from the argument block; the arithmetic of a row is that of a launch of its own.  One kernel for all rows of up to 256 lanes, with a lane's
+// most chunks (alike ones have the kernel for theirs: eight of bf16 [6000, 751] 24 there and 28 here), one for each lane count beyond.
+struct ManySoftmaxes {
+    const dvm_softmax_mixed &p;
+    DI uint32_t tiles() const { return p.first[p.n]; }
+    DI uint32_t part_of(uint32_t tile, uint32_t from) const {
+        while (tile >= p.first[from + 1]) ++from;
+        return from;
+    }
+    DI uint32_t first(uint32_t part) const { return p.first[part]; }
+    DI const dvm_softmax_args &args(uint32_t part) const { return p.part[part]; }
+};
+template <int BF16, bool MASK> __global__ void __launch_bounds__(256) dvm_softmax_mixed_rows(const dvm_softmax_mixed p) {
+    constexpr int V = BF16 ? 8 : 4, NR = BF16 ? 6 : 8;
+    __shared__ __align__(16) float rot[256 * V];
+    __shared__ float red[8];
+    const uint32_t part = ManySoftmaxes{p}.part_of(blockIdx.x, 0u), tile = blockIdx.x - p.first[part], all = p.first[p.n];
+    const dvm_softmax_args &s = p.part[part];
+    switch (s.lanes) {
+        case 8: rows_of<BF16, 8, NR, MASK, false>(s, tile, s.tiles, all, rot, red); break;
+        case 16: rows_of<BF16, 16, NR, MASK, false>(s, tile, s.tiles, all, rot, red); break;
+        case 32: rows_of<BF16, 32, NR, MASK, false>(s, tile, s.tiles, all, rot, red); break;
+        case 64: rows_of<BF16, 64, NR, MASK, false>(s, tile, s.tiles, all, rot, red); break;
+        case 128: rows_of<BF16, 128, NR, MASK, false>(s, tile, s.tiles, all, rot, red); break;
+        case 256: rows_of<BF16, 256, NR, MASK, false>(s, tile, s.tiles, all, rot, red); break;
+        default: break;
+    }
+}
+template <int BF16, int T, int NR, bool MASK> __global__ void __launch_bounds__(T) dvm_softmax_mixed_long(const dvm_softmax_mixed p) {
+    extern __shared__ __align__(16) float lds[];
+    long_rows<BF16, T, NR, MASK>(ManySoftmaxes{p}, lds);
+}
+template <int BF16, int T, bool MASK> __global__ void __launch_bounds__(T) dvm_softmax_mixed_wide(const dvm_softmax_mixed p) {
+    constexpr int V = BF16 ? 8 : 4, NR = T == 1024 ? 4 : BF16 ? 6 : 8;
+    __shared__ __align__(16) float rot[T * V];
+    __shared__ float red[2 * (T / 64)];
+    const uint32_t part = ManySoftmaxes{p}.part_of(blockIdx.x, 0u), tile = blockIdx.x - p.first[part], all = p.first[p.n];
+    const dvm_softmax_args &s = p.part[part];
+    rows_of<BF16, T, NR, MASK, false>(s, tile, s.tiles, all, rot, red);
 }
 
 // ---- rows as the interpreter lays them out --------------------------------------------------------------------------------
@@ -549,48 +620,82 @@ template <int BF16, bool MASK> int launch_exact(const dvm_softmax_args &s, unsig
     return (int)hipGetLastError();
 }
 
-template <int BF16, int T, bool MASK> int launch_rows(const dvm_softmax_args &s, unsigned grid, hipStream_t q) {
+template <int BF16, int T, bool MASK> int launch_rows(const dvm_softmax_alike &a, unsigned grid, hipStream_t q) {
     constexpr unsigned BLOCK = T < 256 ? 256 : T;
-    if (s.slots <= 2) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 2, MASK>), dim3(grid), dim3(BLOCK), 0, q, s);
-    else if (s.slots <= 4) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 4, MASK>), dim3(grid), dim3(BLOCK), 0, q, s);
-    else if constexpr (T < 1024) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, BF16 ? 6 : 8, MASK>), dim3(grid), dim3(BLOCK), 0, q, s);
+    const dvm_softmax_args &s = a.s;
+    if (s.slots <= 2) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 2, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
+    else if (s.slots <= 4) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 4, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
+    else if constexpr (T < 1024) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, BF16 ? 6 : 8, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
     return (int)hipGetLastError();
 }
-template <int BF16, int T, int NR, bool MASK> int launch_long(const dvm_softmax_args &s, unsigned grid, hipStream_t q) {
-    const unsigned lds = ((long_narrow(BF16, NR) ? 2 : BF16 ? 8 : 4) * T + 32) * 4u + (s.slots > NR ? (s.slots - NR) * (unsigned)T * 16u : 0u);
-    if (lds > 65536u) {
-        const hipError_t e = hipFuncSetAttribute((const void *)dvm_softmax_long<BF16, T, NR, MASK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return (int)e;
-    }
-    hipLaunchKernelGGL((dvm_softmax_long<BF16, T, NR, MASK>), dim3(grid), dim3(T), lds, q, s);
+// LDS of a launch whose longest rows have `slots`, and of the longest rows that its kernel takes
+template <int BF16, int T, int NR> constexpr unsigned long_lds(unsigned slots) {
+    return ((long_narrow(BF16, NR) ? 2 : BF16 ? 8 : 4) * T + 32) * 4u + (slots > NR ? (slots - NR) * (unsigned)T * 16u : 0u);
+}
+template <int BF16, int T, int NR> constexpr unsigned long_most() { return long_lds<BF16, T, NR>(BF16 ? NR : T == 512 ? (NR == 16 ? 16 : 24) : NR == 20 ? 28 : 33); }
+// (the bound on a kernel's LDS is the process's: always the same, whichever thread launches)
+template <unsigned MOST> int raise_lds(const void *kernel) {
+    if constexpr (MOST > 65536u) return (int)hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MOST);
+    return 0;
+}
+template <int BF16, int T, int NR, bool MASK> int launch_long(const dvm_softmax_alike &a, unsigned grid, hipStream_t q) {
+    const int e = raise_lds<long_most<BF16, T, NR>()>((const void *)dvm_softmax_long<BF16, T, NR, MASK>);
+    if (e != 0) return e;
+    hipLaunchKernelGGL((dvm_softmax_long<BF16, T, NR, MASK>), dim3(grid), dim3(T), (long_lds<BF16, T, NR>(a.s.slots)), q, a);
     return (int)hipGetLastError();
 }
-template <int BF16, bool MASK> int launch_any(const dvm_softmax_args &s, unsigned grid, hipStream_t q) {
-    if (s.lanes == 8) return launch_rows<BF16, 8, MASK>(s, grid, q);
-    if (s.lanes == 16) return launch_rows<BF16, 16, MASK>(s, grid, q);
-    if (s.lanes == 32) return launch_rows<BF16, 32, MASK>(s, grid, q);
-    if (s.lanes == 64) return launch_rows<BF16, 64, MASK>(s, grid, q);
-    if (s.lanes == 128) return launch_rows<BF16, 128, MASK>(s, grid, q);
-    if (s.lanes == 256) return launch_rows<BF16, 256, MASK>(s, grid, q);
-    if (s.in_long == 0) return s.lanes == 512 ? launch_rows<BF16, 512, MASK>(s, grid, q) : launch_rows<BF16, 1024, MASK>(s, grid, q);
+template <int BF16, int T, int NR, bool MASK> int launch_long(const dvm_softmax_mixed &p, unsigned slots, unsigned grid, hipStream_t q) {
+    const int e = raise_lds<long_most<BF16, T, NR>()>((const void *)dvm_softmax_mixed_long<BF16, T, NR, MASK>);
+    if (e != 0) return e;
+    hipLaunchKernelGGL((dvm_softmax_mixed_long<BF16, T, NR, MASK>), dim3(grid), dim3(T), (long_lds<BF16, T, NR>(slots)), q, p);
+    return (int)hipGetLastError();
+}
+template <int BF16, bool MASK> int launch_any(const dvm_softmax_alike &a, unsigned grid, hipStream_t q) {
+    const dvm_softmax_args &s = a.s;
+    if (s.lanes == 8) return launch_rows<BF16, 8, MASK>(a, grid, q);
+    if (s.lanes == 16) return launch_rows<BF16, 16, MASK>(a, grid, q);
+    if (s.lanes == 32) return launch_rows<BF16, 32, MASK>(a, grid, q);
+    if (s.lanes == 64) return launch_rows<BF16, 64, MASK>(a, grid, q);
+    if (s.lanes == 128) return launch_rows<BF16, 128, MASK>(a, grid, q);
+    if (s.lanes == 256) return launch_rows<BF16, 256, MASK>(a, grid, q);
+    if (s.in_long == 0) return s.lanes == 512 ? launch_rows<BF16, 512, MASK>(a, grid, q) : launch_rows<BF16, 1024, MASK>(a, grid, q);
     if (s.lanes == 512) {
-        if constexpr (BF16) if (s.slots <= 8) return launch_long<BF16, 512, 8, MASK>(s, grid, q);
-        if (s.slots <= 16) return launch_long<BF16, 512, 16, MASK>(s, grid, q);
-        if constexpr (!BF16) return launch_long<BF16, 512, 20, MASK>(s, grid, q);
+        if constexpr (BF16) if (s.slots <= 8) return launch_long<BF16, 512, 8, MASK>(a, grid, q);
+        if (s.slots <= 16) return launch_long<BF16, 512, 16, MASK>(a, grid, q);
+        if constexpr (!BF16) return launch_long<BF16, 512, 20, MASK>(a, grid, q);
     }
-    if (BF16 || s.slots <= 28) return launch_long<BF16, 1024, 20, MASK>(s, grid, q);
-    if constexpr (!BF16) return launch_long<BF16, 1024, 24, MASK>(s, grid, q);
+    if (BF16 || s.slots <= 28) return launch_long<BF16, 1024, 20, MASK>(a, grid, q);
+    if constexpr (!BF16) return launch_long<BF16, 1024, 24, MASK>(a, grid, q);
     return (int)hipErrorInvalidValue;
+}
+template <int BF16, bool MASK> int launch_mixed(const dvm_softmax_mixed &p, unsigned grid, hipStream_t q) {
+    const dvm_softmax_args &s = p.part[0];
+    unsigned slots = 0;
+    for (uint32_t i = 0; i < p.n; ++i) slots = p.part[i].slots > slots ? p.part[i].slots : slots;
+    if (s.lanes <= 256) hipLaunchKernelGGL((dvm_softmax_mixed_rows<BF16, MASK>), dim3(grid), dim3(256), 0, q, p);
+    else if (s.in_long == 0 && s.lanes == 512) hipLaunchKernelGGL((dvm_softmax_mixed_wide<BF16, 512, MASK>), dim3(grid), dim3(512), 0, q, p);
+    else if (s.in_long == 0) hipLaunchKernelGGL((dvm_softmax_mixed_wide<BF16, 1024, MASK>), dim3(grid), dim3(1024), 0, q, p);
+    else if (s.lanes == 512) return launch_long<BF16, 512, BF16 ? 16 : 20, MASK>(p, slots, grid, q);
+    else if (BF16 || slots <= 28) return launch_long<BF16, 1024, 20, MASK>(p, slots, grid, q);
+    else if constexpr (!BF16) return launch_long<BF16, 1024, 24, MASK>(p, slots, grid, q);
+    return (int)hipGetLastError();
 }
 
 }  // namespace
 
-extern "C" int dvm_softmax_launch(const dvm_softmax_args *s, unsigned grid, void *stream) {
+extern "C" int dvm_softmax_launch(const dvm_softmax_alike *a, unsigned grid, void *stream) {
     const hipStream_t q = (hipStream_t)stream;
-    if (s->exact) {
-        if (s->bf16) return s->b ? launch_exact<1, true>(*s, grid, q) : launch_exact<1, false>(*s, grid, q);
-        return s->b ? launch_exact<0, true>(*s, grid, q) : launch_exact<0, false>(*s, grid, q);
+    const dvm_softmax_args &s = a->s;
+    if (s.exact) {
+        if (s.bf16) return s.b ? launch_exact<1, true>(s, grid, q) : launch_exact<1, false>(s, grid, q);
+        return s.b ? launch_exact<0, true>(s, grid, q) : launch_exact<0, false>(s, grid, q);
     }
-    if (s->bf16) return s->b ? launch_any<1, true>(*s, grid, q) : launch_any<1, false>(*s, grid, q);
-    return s->b ? launch_any<0, true>(*s, grid, q) : launch_any<0, false>(*s, grid, q);
+    if (s.bf16) return s.b ? launch_any<1, true>(*a, grid, q) : launch_any<1, false>(*a, grid, q);
+    return s.b ? launch_any<0, true>(*a, grid, q) : launch_any<0, false>(*a, grid, q);
+}
+extern "C" int dvm_softmax_launch_mixed(const dvm_softmax_mixed *p, unsigned grid, void *stream) {
+    const hipStream_t q = (hipStream_t)stream;
+    const dvm_softmax_args &s = p->part[0];
+    if (s.bf16) return s.b ? launch_mixed<1, true>(*p, grid, q) : launch_mixed<1, false>(*p, grid, q);
+    return s.b ? launch_mixed<0, true>(*p, grid, q) : launch_mixed<0, false>(*p, grid, q);
 }

@@ -2505,6 +2505,14 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
     return true;
 }
 
+// Loads take the streaming hint in launches that read more than this.  Less may still be in the last-level cache (256 MB) from the program that
+// wrote it or the one that read it last, beside what others use; the hint then costs (RMSNorm bf16 [11000, 4096], 90 MB read, 30.8 us
+// without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
+// 2245 rows of 8192, 110 MB, 40.1 and 36.7).
+constexpr uint64_t STREAM_MIN_READS = 96ull << 20;
+constexpr uint64_t LARGE_MIN_BYTES = 256ull << 20;      // launches larger than the last-level cache
+constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut into column tiles
+
 // A softmax that runs apart (plain_softmax): the segment at word `at`.  A smaller one, whose bits are the interpreter's, only where it is the whole
 // program: in a batched stack its arithmetic hides behind the traffic of the other parts (a 32-layer step of 200 tokens 213 us, 219 with it apart).
 bool runs_apart(const uint32_t *w, uint32_t at, void *const *tensors, int n_sets, dvm_softmax_args *sm) {
@@ -2513,54 +2521,125 @@ bool runs_apart(const uint32_t *w, uint32_t at, void *const *tensors, int n_sets
 // Threads of a workgroup, and workgroups of its launch.  The kernel for long rows loads a workgroup's next row while it stores the one before: as many
 // as are resident.  The others take a tile each, as far as a launch may have that many threads (below 2^32), and the rest in turn.
 uint32_t softmax_block(const dvm_softmax_args &sm) { return sm.exact || sm.lanes < 256 ? 256 : sm.lanes; }
-uint32_t softmax_grid(const dvm_softmax_args &sm, int n_cu) {
+uint32_t softmax_grid(const dvm_softmax_args &sm, uint32_t tiles, int n_cu) {
     const uint32_t most = sm.in_long != 0 ? (uint32_t)n_cu * (sm.lanes == 1024 ? 1u : 2u) : UINT32_MAX / softmax_block(sm);
-    return sm.tiles > most ? most : sm.tiles;
+    return tiles > most ? most : tiles;
 }
 
 // The kernel launches: segments in a run share one.  A segment starts a run of its own where it asks for one, and a softmax that runs apart is
-// one.  Segments that are independent of each other go first, all but those, in one launch; softmaxes alike in all but their addresses share a
-// launch, since few rows leave most of the chip idle (eight in a stack, one launch each and one for all, us: bf16 [32, 17000] 43 and 7, fp32 [128, 17000]
-// 60 and 27, bf16 [6000, 751] 51 and 24; in the interpreter 20, 40 and 42).
+// one.  Segments that are independent of each other go first, all but those, in one launch.  Of independent softmaxes those alike in all but their addresses
+// share a launch of the kernel that each has alone, wherever they stand, as long as such a group fills the chip or there is no other to join; those of
+// smaller groups share one of the kernel for several shapes, since few rows leave most of the chip idle and launches follow each other (eight of fp32
+// [16, 100003], of two widths in turn: 25 us, each in its own launch 156, in the interpreter 48; bf16 [32, 17000] 6.6, 43 and 18; [6000, 751], where both
+// groups fill the chip, 29, 51 and 43).  A softmax that is alone among other programs pays its launch, 1 to 2 us: with an addition of its size, launch and
+// interpreter, bf16 [6000, 751] 13.9 and 12.3, fp32 [2100, 2049] 19.8 and 17.7, but bf16 [50000, 128] 14.5 and 27.6, fp32 [16, 100003] 28 and 49.
+enum : uint8_t { RUN_VM = 0, RUN_SOFTMAX, RUN_MIXED };
 struct Runs {
     uint32_t n = 0, n_list = 0;
     uint32_t list[MAX_SEGMENTS], at[MAX_SEGMENTS + 1];      // segments, run after run, and where the runs start
-    bool softmax[MAX_SEGMENTS];                             // the run is a softmax that runs apart
-    void push(uint32_t s, bool fresh, bool soft) {
-        if (fresh || n == 0) { softmax[n] = soft; at[n++] = n_list; }
+    uint8_t kind[MAX_SEGMENTS];
+    void push(uint32_t s, bool fresh, uint8_t k) {
+        if (fresh || n == 0) { kind[n] = k; at[n++] = n_list; }
         list[n_list++] = s;
     }
 };
 void plan_runs(const uint32_t *w, void *const *tensors, int n_sets, bool ordered, Runs *runs) {
     uint32_t seg_at[MAX_SEGMENTS];
-    bool soft[MAX_SEGMENTS];
-    dvm_softmax_args sm;
+    uint8_t which[MAX_SEGMENTS];            // 1 + a softmax that runs apart, 0: any other segment
+    static_assert(DVM_SOFTMAX_MAX_PARTS >= DVM_MAX_TENSORS / 2, "softmaxes of a launch");
+    dvm_softmax_args soft[DVM_MAX_TENSORS / 2];
+    uint32_t seg_of[DVM_MAX_TENSORS / 2], n_soft = 0;
     for (uint32_t s = 0, at = PH_WORDS_N + w[PH_NTENS] * TT_WORDS; s < w[PH_NSEG]; at += w[at + S_WORDS], ++s) {
         seg_at[s] = at;
-        soft[s] = runs_apart(w, at, tensors, n_sets, &sm);
+        which[s] = 0;
+        if (n_soft == DVM_MAX_TENSORS / 2) continue;
+        dvm_softmax_args &sm = soft[n_soft];
+        memset(&sm, 0, sizeof sm);
+        if (!runs_apart(w, at, tensors, n_sets, &sm)) continue;
+        seg_of[n_soft] = s;
+        which[s] = (uint8_t)++n_soft;
     }
-    if (ordered) {
-        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) runs->push(s, soft[s] || (s > 0 && soft[s - 1]) || (w[seg_at[s] + S_FLAGS] & SF_NEW_LAUNCH), soft[s]);
-    } else {
-        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!soft[s]) runs->push(s, false, false);
-        dvm_softmax_args last;
-        uint32_t n = 0;         // in the present run
-        for (uint32_t s = 0; s < w[PH_NSEG]; ++s) {
-            if (!soft[s]) continue;
-            memset(&sm, 0, sizeof sm);
-            runs_apart(w, seg_at[s], tensors, n_sets, &sm);
-            sm.a = sm.y = nullptr;
-            if (sm.b) sm.b = w;         // (there is one)
-            sm.ia = sm.ib = sm.iy = 0;
-            const bool joins = n > 0 && n < DVM_SOFTMAX_MAX_PARTS && n_sets == 1 && memcmp(&sm, &last, sizeof sm) == 0 &&
-                               (uint64_t)sm.tiles * (n + 1) < (1ull << 31);
-            n = joins ? n + 1 : 1;
-            runs->push(s, !joins, true);
-            last = sm;
+    if (ordered || n_soft < 2) {
+        if (!ordered) for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!which[s]) runs->push(s, false, RUN_VM);
+        for (uint32_t s = 0; s < w[PH_NSEG]; ++s)
+            if (ordered || which[s])
+                runs->push(s, which[s] || (s > 0 && which[s - 1]) || (w[seg_at[s] + S_FLAGS] & SF_NEW_LAUNCH), which[s] ? RUN_SOFTMAX : RUN_VM);
+        runs->at[runs->n] = runs->n_list;
+        return;
+    }
+    for (uint32_t s = 0; s < w[PH_NSEG]; ++s) if (!which[s]) runs->push(s, false, RUN_VM);
+    // groups of alike ones (alike[i]: the first that i is like), and the kernels they could share with others
+    uint32_t alike[DVM_MAX_TENSORS / 2], size[DVM_MAX_TENSORS / 2], kernel[DVM_MAX_TENSORS / 2];
+    for (uint32_t i = 0; i < n_soft; ++i) {
+        dvm_softmax_args &sm = soft[i];
+        kernel[i] = sm.bf16 | (sm.b ? 2u : 0u) | sm.in_long << 2 | (sm.lanes > 256 ? sm.lanes << 3 : 0u);
+        sm.a = sm.y = nullptr;
+        if (sm.b) sm.b = w;         // (there is one)
+        sm.ia = sm.ib = sm.iy = 0;
+        alike[i] = i;
+        size[i] = 1;
+        for (uint32_t j = 0; j < i && n_sets == 1; ++j)
+            if (alike[j] == j && memcmp(&sm, &soft[j], sizeof sm) == 0 && (uint64_t)sm.tiles * (size[j] + 1) < (1ull << 31)) {
+                alike[i] = j;
+                ++size[j];
+                break;
+            }
+    }
+    auto fills = [&](uint32_t i) { return (uint64_t)soft[i].tiles * size[i] >= (soft[i].lanes <= 256 ? 2048u : 1024u * 512u / soft[i].lanes); };
+    bool done[DVM_MAX_TENSORS / 2] = {};
+    for (uint32_t i = 0; i < n_soft; ++i) {
+        if (done[i]) continue;
+        // (i stands first in its group: the others of it are done with it)
+        auto joins = [&](uint32_t j) { return !done[j] && !fills(alike[j]) && kernel[j] == kernel[i]; };
+        bool mixed = false;
+        for (uint32_t j = i + 1; j < n_soft && !fills(i); ++j) mixed |= joins(j) && alike[j] != i;
+        uint32_t n = 0;
+        for (uint32_t j = i; j < n_soft; ++j) {
+            if (done[j] || !(mixed ? joins(j) : alike[j] == i)) continue;
+            runs->push(seg_of[j], n++ == 0, mixed ? RUN_MIXED : RUN_SOFTMAX);
+            done[j] = true;
         }
     }
     runs->at[runs->n] = runs->n_list;
 }
+// The arguments of a run's launch; its tiles
+uint32_t softmax_args(const uint32_t *w, const uint32_t *seg_at, const uint32_t *segs, uint32_t n, void *const *tensors, int n_sets, uint64_t sets, dvm_softmax_alike *a) {
+    dvm_softmax_args &sm = a->s;
+    if (n > 1) {
+        for (uint32_t i = 0; i < n; ++i) {
+            runs_apart(w, seg_at[segs[i]], tensors, n_sets, &sm);
+            a->parts[3 * i] = (uint64_t)(uintptr_t)sm.a;
+            a->parts[3 * i + 1] = (uint64_t)(uintptr_t)sm.b;
+            a->parts[3 * i + 2] = (uint64_t)(uintptr_t)sm.y;
+        }
+        sm.sets = DVM_SOFTMAX_PARTS;
+        sm.n_tensors = 3;
+        sm.ia = 0, sm.ib = 1, sm.iy = 2;
+        sm.tiles *= n;
+    } else {
+        runs_apart(w, seg_at[segs[0]], tensors, n_sets, &sm);
+        sm.sets = sets;
+        sm.n_tensors = w[PH_NTENS];
+    }
+    sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets * n >= STREAM_MIN_READS;
+    return sm.tiles;
+}
+uint32_t softmax_args(const uint32_t *w, const uint32_t *seg_at, const uint32_t *segs, uint32_t n, void *const *tensors, int n_sets, uint64_t sets, dvm_softmax_mixed *p) {
+    uint64_t bytes = 0;
+    p->n = n;
+    p->first[0] = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        dvm_softmax_args &sm = p->part[i];
+        runs_apart(w, seg_at[segs[i]], tensors, n_sets, &sm);
+        sm.sets = sets;
+        sm.n_tensors = w[PH_NTENS];
+        p->first[i + 1] = p->first[i] + sm.tiles;
+        bytes += (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets;
+    }
+    for (uint32_t i = 0; i < n; ++i) p->part[i].stream = bytes >= STREAM_MIN_READS;
+    return p->first[n];
+}
+
 // Segments that may depend on each other
 bool is_ordered(const uint32_t *w) {
     bool r = (w[PH_TYPE] & 0xFFFF) == KT_STACK_SPATIAL;
@@ -2569,14 +2648,6 @@ bool is_ordered(const uint32_t *w) {
         r |= (w[at + S_FLAGS] & (SF_SYNC_WG | SF_SYNC_GRID | SF_NEW_LAUNCH)) != 0;
     return r;
 }
-
-// Loads take the streaming hint in launches that read more than this.  Less may still be in the last-level cache (256 MB) from the program that
-// wrote it or the one that read it last, beside what others use; the hint then costs (RMSNorm bf16 [11000, 4096], 90 MB read, 30.8 us
-// without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
-// 2245 rows of 8192, 110 MB, 40.1 and 36.7).
-constexpr uint64_t STREAM_MIN_READS = 96ull << 20;
-constexpr uint64_t LARGE_MIN_BYTES = 256ull << 20;      // launches larger than the last-level cache
-constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut into column tiles
 
 int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *tensors_in, int n_tensors, void *hip_stream, bool static_ws,
              const Batch *batch) {
@@ -2698,7 +2769,6 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     const bool rotates = (w[PH_NSEG] > 1 || n_sets > 1) && !wg_sync && (w[PH_TYPE] & 0xFFFF) != KT_STACK_SPATIAL;
     if (grid_sync) hipLaunchKernelGGL(dvm_ws_clear, dim3(1), dim3(64), 0, (hipStream_t)hip_stream, (uint32_t *)(uintptr_t)ka.ws, (uint32_t)WS_SYNC_WORDS);
     hipError_t e;
-    auto softmax_of = [&](uint32_t s, dvm_softmax_args *sm) { return runs_apart(w, seg_at[s], tensors, n_sets, sm); };
     dvm_rotary_args ra;
     if (w[PH_NSEG] == 1 && plain_rotary(w + segs_off, NR, w + PH_WORDS_N, tensors, n_sets, ntens, &ra)) {
         ra.sets = ka.sets;
@@ -2716,28 +2786,18 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
     for (uint32_t run = 0; run < runs.n; ++run) {
         const uint32_t *segs = runs.list + runs.at[run];
         const uint32_t n_segs = runs.at[run + 1] - runs.at[run];
-        if (runs.softmax[run]) {    // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
-            dvm_softmax_args sm;
-            softmax_of(segs[0], &sm);
+        if (runs.kind[run] != RUN_VM) {     // (the launch boundaries are what orders it behind the parts it depends on, and those behind it)
             int n_cu = 256;
             dvm_ctx_planner_get(ctx, &n_cu, nullptr);
-            sm.sets = ka.sets;
-            sm.n_tensors = ntens;
-            if (n_segs > 1) {
-                for (uint32_t i = 0; i < n_segs; ++i) {
-                    dvm_softmax_args one;
-                    softmax_of(segs[i], &one);
-                    sm.parts[3 * i] = (uint64_t)(uintptr_t)one.a;
-                    sm.parts[3 * i + 1] = (uint64_t)(uintptr_t)one.b;
-                    sm.parts[3 * i + 2] = (uint64_t)(uintptr_t)one.y;
-                }
-                sm.sets = DVM_SOFTMAX_PARTS;
-                sm.n_tensors = 3;
-                sm.ia = 0, sm.ib = 1, sm.iy = 2;
-                sm.tiles *= n_segs;
+            if (runs.kind[run] == RUN_MIXED) {
+                dvm_softmax_mixed sm;
+                const uint32_t tiles = softmax_args(w, seg_at, segs, n_segs, tensors, n_sets, ka.sets, &sm);
+                e = (hipError_t)dvm_softmax_launch_mixed(&sm, softmax_grid(sm.part[0], tiles, n_cu), hip_stream);
+            } else {
+                dvm_softmax_alike sm;
+                const uint32_t tiles = softmax_args(w, seg_at, segs, n_segs, tensors, n_sets, ka.sets, &sm);
+                e = (hipError_t)dvm_softmax_launch(&sm, softmax_grid(sm.s, tiles, n_cu), hip_stream);
             }
-            sm.stream = (uint64_t)sm.rows * sm.cols * (sm.bf16 ? 2u : 4u) * (uint64_t)n_sets * n_segs >= STREAM_MIN_READS;
-            e = (hipError_t)dvm_softmax_launch(&sm, softmax_grid(sm, n_cu), hip_stream);
             if (e != hipSuccess) {
                 t_last_hip_error = (int)e;
                 return dvm_set_error(DVM_E_HIP, hipGetErrorString(e));
@@ -2877,12 +2937,16 @@ extern "C" int dvm_launch_plan(const void *bytecode, size_t len, void *const *te
         l = dvm_launch{};
         l.first_segment = runs.list[runs.at[r]];
         l.n_segments = runs.at[r + 1] - runs.at[r];
-        dvm_softmax_args sm;
-        if (runs.softmax[r]) {
-            runs_apart(w, seg_at[l.first_segment], tensors, n_sets, &sm);
-            sm.tiles *= l.n_segments;
+        if (runs.kind[r] != RUN_VM) {
+            dvm_softmax_alike sa;
+            dvm_softmax_mixed sx;
+            const bool mixed = runs.kind[r] == RUN_MIXED;
+            const uint32_t *segs = runs.list + runs.at[r];
+            const uint32_t tiles = mixed ? softmax_args(w, seg_at, segs, l.n_segments, tensors, n_sets, 0, &sx) : softmax_args(w, seg_at, segs, l.n_segments, tensors, n_sets, 0, &sa);
+            const dvm_softmax_args &sm = mixed ? sx.part[0] : sa.s;
+            l.mixed = mixed;
             l.kind = sm.exact ? DVM_LAUNCH_SOFTMAX_EXACT : sm.in_long ? DVM_LAUNCH_SOFTMAX_LONG : DVM_LAUNCH_SOFTMAX;
-            l.grid = softmax_grid(sm, n_cu);
+            l.grid = softmax_grid(sm, tiles, n_cu);
             l.block = softmax_block(sm);
             l.lanes = sm.lanes;
             l.slots = sm.slots;

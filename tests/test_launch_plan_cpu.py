@@ -91,3 +91,27 @@ def test_lanes_do_not_depend_on_addresses(ctx, dt):
                 (off,) = L.launches(code, sets)
                 assert (off.kind, off.lanes, off.block) == (on.kind, on.lanes, on.block), (cols, at)
                 assert on.slots <= off.slots <= on.slots + 1
+
+
+def stacked(ctx, parts):
+    codes = [encode(ctx, dt, shape, masked) for dt, shape, masked in parts]
+    ptrs, at = [], FAR
+    for _, _, masked in parts:
+        for _ in range(2 + masked):
+            ptrs.append(at)
+            at += FAR
+    return [(l.kind, l.n_segments, l.mixed) for l in L.launches(B.dvm_stack(codes), [ptrs])]
+
+
+def test_softmaxes_of_a_stack_share_launches(ctx):
+    """Groups of alike ones; groups too small to fill the chip together where type, second tensor and kernel are the same, wherever they stand."""
+    a, b = ("f32", (16, 100003), False), ("f32", (17, 100011), False)
+    assert stacked(ctx, [a, b, a, b]) == [(L.SOFTMAX_LONG, 4, 1)]
+    assert stacked(ctx, [a, a, a]) == [(L.SOFTMAX_LONG, 3, 0)]
+    short = ("bf16", (6000, 751), False), ("bf16", (14900, 300), False), ("bf16", (1500, 3000), False)
+    add = ("bf16", (9, 64), False)                              # (small: with the interpreter, first)
+    assert stacked(ctx, [short[0], add, short[1], a, short[2]]) == [(L.INTERPRETER, 1, 0), (L.SOFTMAX, 3, 1), (L.SOFTMAX_LONG, 1, 0)]
+    large = ("bf16", (60000, 751), False)                       # (fills the chip)
+    assert stacked(ctx, [short[0], large, short[1]]) == [(L.SOFTMAX, 2, 1), (L.SOFTMAX, 1, 0)]
+    assert stacked(ctx, [short[0], short[1], short[0], short[1], short[0]]) == [(L.SOFTMAX, 3, 0), (L.SOFTMAX, 2, 0)]
+    assert stacked(ctx, [a, ("bf16", (64, 40003), False), ("f32", (16, 100003), True), ("f32", (64, 17000), False)]) == [(L.SOFTMAX_LONG, 1, 0)] * 4
