@@ -254,7 +254,7 @@ int run_stacked(dvm_fuser *f) {
             if (st == DVM_OK) st = dvm_code_tensor(f->code, f->code_len, info.n_tensors - 1, nullptr, &is_ws, nullptr, nullptr);
             if (st != DVM_OK) return st;
             if (is_ws == 2) tensors[n_t++] = f->workspace;
-            n_launches = info.n_launches;
+            n_launches = dvm_launch_count((const uint32_t *)f->code);        // (info.n_launches leaves out the softmaxes that run apart)
         }
         if (dvm_ctx_device(f->ctx) >= 0) {
             st = dvm_run(f->ctx, f->code, f->code_len, tensors, n_t, f->stream);

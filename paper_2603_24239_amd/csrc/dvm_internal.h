@@ -96,6 +96,7 @@ typedef struct dvm_launch {
     uint32_t mixed;                 // softmaxes of several shapes
 } dvm_launch;
 enum { DVM_LAUNCH_INTERPRETER = 0, DVM_LAUNCH_SOFTMAX, DVM_LAUNCH_SOFTMAX_LONG, DVM_LAUNCH_SOFTMAX_EXACT, DVM_LAUNCH_ROTARY };
+int dvm_launch_count(const uint32_t *program);
 int dvm_launch_plan(const void *bytecode, size_t len, void *const *tensors, int n_sets, int n_cu, dvm_launch *out, int cap, int *n);
 // Implemented in the device file so that the encoder object stays free of HIP calls.
 int dvm_ctx_query_device(int hip_device, int *n_cu);

@@ -2354,9 +2354,9 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     a->set_tiles = (uint32_t)tiles;
     magic_of(a->set_tiles, &a->set_m, &a->set_sh);
     a->tiles = (uint32_t)(tiles * (uint64_t)n_sets);
-    a->a = tensors[a->ia];
-    a->b = lb ? tensors[a->ib] : nullptr;
-    a->y = tensors[a->iy];
+    a->a = tensors ? tensors[a->ia] : nullptr;
+    a->b = lb ? (tensors ? tensors[a->ib] : sh) : nullptr;         // (where only the launches are counted: there is one)
+    a->y = tensors ? tensors[a->iy] : nullptr;
     return true;
 }
 
@@ -2578,7 +2578,7 @@ void plan_runs(const uint32_t *w, void *const *tensors, int n_sets, bool ordered
         sm.ia = sm.ib = sm.iy = 0;
         alike[i] = i;
         size[i] = 1;
-        for (uint32_t j = 0; j < i && n_sets == 1; ++j)
+        for (uint32_t j = 0; j < i && n_sets <= 1; ++j)
             if (alike[j] == j && memcmp(&sm, &soft[j], sizeof sm) == 0 && (uint64_t)sm.tiles * (size[j] + 1) < (1ull << 31)) {
                 alike[i] = j;
                 ++size[j];
@@ -2917,6 +2917,14 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
 }
 
 }  // namespace
+
+// The number of kernel launches that a run of valid bytecode makes over tensors that start on a line and apart from each other (no HIP call).
+extern "C" int dvm_launch_count(const uint32_t *w) {
+    if (w[PH_NSEG] > (uint32_t)MAX_SEGMENTS) return 1;      // (none: dvm_run refuses it)
+    Runs runs;
+    plan_runs(w, nullptr, 0, is_ordered(w), &runs);
+    return runs.n > 1 ? (int)runs.n : 1;
+}
 
 // The kernel launches that a run of `bytecode` over these tensors makes, without making them (for tests; no HIP call).
 extern "C" int dvm_launch_plan(const void *bytecode, size_t len, void *const *tensors, int n_sets, int n_cu, dvm_launch *out, int cap, int *n) {

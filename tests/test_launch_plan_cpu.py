@@ -115,3 +115,17 @@ def test_softmaxes_of_a_stack_share_launches(ctx):
     assert stacked(ctx, [short[0], large, short[1]]) == [(L.SOFTMAX, 2, 1), (L.SOFTMAX, 1, 0)]
     assert stacked(ctx, [short[0], short[1], short[0], short[1], short[0]]) == [(L.SOFTMAX, 3, 0), (L.SOFTMAX, 2, 0)]
     assert stacked(ctx, [a, ("bf16", (64, 40003), False), ("f32", (16, 100003), True), ("f32", (64, 17000), False)]) == [(L.SOFTMAX_LONG, 1, 0)] * 4
+
+
+def test_the_fuser_counts_what_it_launches():
+    """A softmax that runs apart among the pieces is a launch, though the bytecode does not ask for one (dvm_code_info.n_launches)."""
+    ctx = B.Context(-1)
+    ctx.set_limits(16, 2)           # (one interpreter variant for both pieces)
+    for rows, launches in ((6000, 2), (600, 1)):
+        f = B.Fuser(ctx)
+        f.set_workspace(5 * FAR, 256)
+        p = f.op("softmax", [f.tensor(FAR, "bf16", B.make_shape((rows, 751)))], "bf16", 2 * FAR)
+        q = f.op("exp", [f.tensor(3 * FAR, "bf16", B.make_shape((rows, 753)))], "bf16", 4 * FAR)
+        f.flush()
+        assert f.last_code().info().n_segments == 2 and f.last_code().info().n_launches == 1 and p != q
+        assert f.stats()["launches"] == launches, rows
