@@ -94,6 +94,7 @@ typedef struct dvm_launch {
     uint32_t grid, block;
     uint32_t lanes, slots;          // a softmax: lanes on a row, 16-byte chunks of a lane (mixed: of the first part)
     uint32_t mixed;                 // softmaxes of several shapes
+    uint32_t stream;                // the interpreter: loads take the streaming hint
 } dvm_launch;
 enum { DVM_LAUNCH_INTERPRETER = 0, DVM_LAUNCH_SOFTMAX, DVM_LAUNCH_SOFTMAX_LONG, DVM_LAUNCH_SOFTMAX_EXACT, DVM_LAUNCH_ROTARY };
 int dvm_launch_count(const uint32_t *program);

@@ -2510,8 +2510,38 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
 // without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
 // 2245 rows of 8192, 110 MB, 40.1 and 36.7).
 constexpr uint64_t STREAM_MIN_READS = 96ull << 20;
+// A program that reads several tensors past the caches gains earlier, and loses nothing where they are in the last-level cache: us without and with the
+// hint, inputs in memory (in the cache), the chain (three tensors) reading 16 MB 15.5 14.6 (11.7 12.5), 48 MB 24.2 20.4 (20.1 19.4), fp32 add (two) 32 MB 12.7
+// 11.8 (9.2 9.9), 64 MB 21.4 19.7 (17.9 17.7); but RMSNorm (one) 48 MB 22.2 20.8 (18.5 19.1), 80 MB 33.9 31.7 (27.7 30.0).
+constexpr uint64_t STREAM_MIN_READS_OF_TWO = 32ull << 20, STREAM_MIN_READS_OF_THREE = 16ull << 20;
 constexpr uint64_t LARGE_MIN_BYTES = 256ull << 20;      // launches larger than the last-level cache
 constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut into column tiles
+
+// Bytes of a launch of some segments, over one set of tensors
+struct LaunchBytes {
+    uint64_t spans = 0, touched = 0, reads = 0;     // the last two: without what lies between the rows of views
+    uint32_t streams = 0;                           // of a segment alone: tensors that it reads past the caches if it may
+    bool stream(int n_sets) const {
+        return reads * (uint64_t)n_sets >= (streams > 2 ? STREAM_MIN_READS_OF_THREE : streams == 2 ? STREAM_MIN_READS_OF_TWO : STREAM_MIN_READS);
+    }
+};
+LaunchBytes launch_bytes(const uint32_t *w, const uint32_t *seg_at, const uint32_t *segs, uint32_t n_segs) {
+    LaunchBytes b;
+    for (uint32_t i = 0; i < n_segs; ++i) {
+        const uint32_t *sh = w + seg_at[segs[i]];
+        for (uint32_t t = 0; t < sh[S_NTENS]; ++t) {
+            const uint32_t *te = w + PH_WORDS_N + (sh[S_TBASE] + t) * TT_WORDS;
+            const uint64_t span = (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
+            const uint64_t whole = (uint64_t)sh[S_NROWS] * ((uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32)) * ((te[TT_INFO] & 0xFF) == DVM_BF16 ? 2u : 4u);
+            b.spans += span;
+            b.touched += whole < span ? whole : span;
+            if (!(te[TT_INFO] & TI_OUTPUT)) b.reads += whole < span ? whole : span;
+        }
+        for (uint32_t pc = SH_WORDS; n_segs == 1 && pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF)
+            b.streams += ((sh[pc] & 0xFF) == I_LOAD || (sh[pc] & 0xFF) == I_VLOAD) && ((sh[pc + 1] >> 16) & MF_STREAM);
+    }
+    return b;
+}
 
 // A softmax that runs apart (plain_softmax): the segment at word `at`.  A smaller one, whose bits are the interpreter's, only where it is the whole
 // program: in a batched stack its arithmetic hides behind the traffic of the other parts (a 32-layer step of 200 tokens 213 us, 219 with it apart).
@@ -2807,7 +2837,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         ka.nseg = n_segs;
         ka.set_tiles = 0;
         Needs need;
-        uint64_t total = 0, bytes = 0, touched = 0, reads = 0;     // of this launch (the last two: without what lies between the rows of views)
+        uint64_t total = 0;                 // tiles of this launch
         uint32_t k_need = 0;                // elements per lane its segments use
         bool round_robin = true;
         for (uint32_t i = 0; i < n_segs; ++i) {
@@ -2817,17 +2847,10 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
             round_robin &= (sh[S_FLAGS] & SF_INTERLEAVED) != 0;
             const uint32_t k = (sh[S_GEOM] >> 24) * ((sh[S_GEOM] >> 16) & 0xFF);
             if (k > k_need) k_need = k;
-            for (uint32_t t = 0; t < sh[S_NTENS]; ++t) {
-                const uint32_t *te = w + PH_WORDS_N + (sh[S_TBASE] + t) * TT_WORDS;
-                const uint64_t span = (uint64_t)te[TT_BYTES_LO] | ((uint64_t)te[TT_BYTES_HI] << 32);
-                const uint64_t whole = (uint64_t)sh[S_NROWS] * ((uint64_t)sh[S_D0LO] | ((uint64_t)sh[S_D0HI] << 32)) * ((te[TT_INFO] & 0xFF) == DVM_BF16 ? 2u : 4u);
-                bytes += span;
-                touched += whole < span ? whole : span;
-                if (!(te[TT_INFO] & TI_OUTPUT)) reads += whole < span ? whole : span;
-            }
         }
         // (streaming loads go past the last-level cache)
-        const bool stream = reads * (uint64_t)n_sets >= STREAM_MIN_READS;
+        const LaunchBytes bytes = launch_bytes(w, seg_at, segs, n_segs);
+        const bool stream = bytes.stream(n_sets);
         for (uint32_t i = 0, to = 0; i < n_segs; ++i) {
             const uint32_t *sh = w + seg_at[segs[i]];
             memcpy(ka.code + to, sh, (size_t)sh[S_WORDS] * 4);
@@ -2846,7 +2869,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         // The instantiations that pass over foreign sets and segments are some 8 % slower per tile; the others spend 1.1 us on each.
         // They pay where that is more than 8 % of the time the launch's bytes take at 5 TB/s, i.e. below 69 MB per segment and set
         // (32 layers of five programs at 512 tokens, 18 MB each: 604 us against 639; eight RMSNorms of 285 MB: the other way round).
-        const bool skip = ka.rotate == 1 && bytes < (uint64_t)n_segs * (69ull << 20);
+        const bool skip = ka.rotate == 1 && bytes.spans < (uint64_t)n_segs * (69ull << 20);
         const bool narrow = apart && k_need <= 32;
         const int K_l = narrow ? 32 : K, NR_l = narrow ? 2 : NR;
         vm_launch_t launch = nullptr;
@@ -2899,7 +2922,7 @@ int run_impl(const dvm_ctx *ctx, const void *bytecode, size_t len, void *const *
         // RMSNorm bf16 [42648, 4096] 127 -> 119).  A prologue (pinned operands) runs in every workgroup: each of its records wants two and a
         // half tiles behind it (LayerNorm bf16 [163840, 2048] 250 -> 241, but [81920, 1024], with one tile behind two, 63 -> 68).  Flat programs, whose tiles
         // cost the same, gain from 64 MB on, where their last round is not full (fp32 add over 15M elements 34.0 -> 31.9, over 10M 23.1 -> 23.3).
-        if (w[PH_NSEG] == 1 && n_sets == 1 && !cred && !longrow && touched >= (first_sh[S_NCT] > 1 ? FLAT_MIN_BYTES : LARGE_MIN_BYTES) && (first_sh[S_FLAGS] & SF_INTERLEAVED) && !(first_sh[S_FLAGS] & SF_LDS)) {
+        if (w[PH_NSEG] == 1 && n_sets == 1 && !cred && !longrow && bytes.touched >= (first_sh[S_NCT] > 1 ? FLAT_MIN_BYTES : LARGE_MIN_BYTES) && (first_sh[S_FLAGS] & SF_INTERLEAVED) && !(first_sh[S_FLAGS] & SF_LDS)) {
             uint32_t records = 0;
             for (uint32_t pc = SH_WORDS; pc < SH_WORDS + first_sh[S_PROLOG]; pc += (first_sh[pc] >> 8) & 0xFF) ++records;
             if (records == 0 || 2 * total >= 5ull * records * 8u * grid) grid = total < 8ull * grid ? (uint32_t)total : 8u * grid;
@@ -2958,7 +2981,9 @@ extern "C" int dvm_launch_plan(const void *bytecode, size_t len, void *const *te
             l.block = softmax_block(sm);
             l.lanes = sm.lanes;
             l.slots = sm.slots;
-        } else if (rotary) {
+        } else if (!rotary) {
+            l.stream = launch_bytes(w, seg_at, runs.list + runs.at[r], l.n_segments).stream(n_sets);
+        } else {
             l.kind = DVM_LAUNCH_ROTARY;
             l.grid = (ra.groups + 3) / 4;
             l.block = 256;

@@ -10,7 +10,7 @@ INTERPRETER, SOFTMAX, SOFTMAX_LONG, SOFTMAX_EXACT, ROTARY = range(5)
 
 
 class Launch(C.Structure):
-    _fields_ = [(n, C.c_uint32) for n in ("kind", "first_segment", "n_segments", "grid", "block", "lanes", "slots", "mixed")]
+    _fields_ = [(n, C.c_uint32) for n in ("kind", "first_segment", "n_segments", "grid", "block", "lanes", "slots", "mixed", "stream")]
 
 
 def launches(code: B.Bytecode, sets: Sequence[Sequence[int]], n_cu: int = 256) -> List[Launch]:

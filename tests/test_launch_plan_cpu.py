@@ -129,3 +129,16 @@ def test_the_fuser_counts_what_it_launches():
         f.flush()
         assert f.last_code().info().n_segments == 2 and f.last_code().info().n_launches == 1 and p != q
         assert f.stats()["launches"] == launches, rows
+
+
+@pytest.mark.parametrize("name,cols,n,reads", [("c2_rmsnorm", 4096, 2, 1), ("c4_chain", 8192, 6, 3), ("add_f16like", 4096, 2, 2)])
+def test_streaming_hint(ctx, name, cols, n, reads):
+    """By the bytes that a launch reads: 96 MB of one tensor, 32 of two, 16 of three."""
+    bound = {1: 96, 2: 32, 3: 16}[reads] << 20
+    desc = W.get_program(name)
+    for rows, hint in ((bound // (reads * 2 * cols) - 3, 0), (bound // (reads * 2 * cols) + 1, 1)):
+        shapes = [B.make_shape((cols,) if n_ in ("w", "gamma", "beta", "bias") else (rows, cols)) for n_, _ in desc.inputs]
+        assert len(shapes) == n
+        code = B.dvm_encode(ctx, B.Program(desc), shapes)
+        (l,) = L.launches(code, [[FAR * (k + 1) for k in range(n + 1)]])
+        assert l.kind == L.INTERPRETER and l.stream == hint, (rows, l.stream)
