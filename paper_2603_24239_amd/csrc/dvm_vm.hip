@@ -2510,9 +2510,10 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
 // without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
 // 2245 rows of 8192, 110 MB, 40.1 and 36.7).
 constexpr uint64_t STREAM_MIN_READS = 96ull << 20;
-// A program that reads several tensors past the caches gains earlier, and loses nothing where they are in the last-level cache: us without and with the
-// hint, inputs in memory (in the cache), the chain (three tensors) reading 16 MB 15.5 14.6 (11.7 12.5), 48 MB 24.2 20.4 (20.1 19.4), fp32 add (two) 32 MB 12.7
-// 11.8 (9.2 9.9), 64 MB 21.4 19.7 (17.9 17.7); but RMSNorm (one) 48 MB 22.2 20.8 (18.5 19.1), 80 MB 33.9 31.7 (27.7 30.0).
+// A bf16 program that reads several tensors so gains earlier: us without and with the hint, inputs in memory (in the cache), the chain (three tensors)
+// reading 16 MB 15.5 14.6 (11.7 12.5), 48 MB 24.2 20.4 (20.1 19.4), add (two) 32 MB 13.1 12.0 (9.2 9.9), 64 MB 21.4 19.6 (18.5 17.6); but RMSNorm (one) 48 MB
+// 22.2 20.8 (18.5 19.1), 80 MB 33.9 31.7 (27.7 30.0).  In fp32 what the hint drops from a cache that is nearly full costs more than it gives: an addition
+// beside a softmax of its size, 34 MB read by each, 19.8 and 24.4, alone 64 MB 21.4 19.7 (17.9 17.7).
 constexpr uint64_t STREAM_MIN_READS_OF_TWO = 32ull << 20, STREAM_MIN_READS_OF_THREE = 16ull << 20;
 constexpr uint64_t LARGE_MIN_BYTES = 256ull << 20;      // launches larger than the last-level cache
 constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut into column tiles
@@ -2520,7 +2521,7 @@ constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut
 // Bytes of a launch of some segments, over one set of tensors
 struct LaunchBytes {
     uint64_t spans = 0, touched = 0, reads = 0;     // the last two: without what lies between the rows of views
-    uint32_t streams = 0;                           // of a segment alone: tensors that it reads past the caches if it may
+    uint32_t streams = 0;                           // of a segment alone, all of bf16: tensors that it reads past the caches if it may
     bool stream(int n_sets) const {
         return reads * (uint64_t)n_sets >= (streams > 2 ? STREAM_MIN_READS_OF_THREE : streams == 2 ? STREAM_MIN_READS_OF_TWO : STREAM_MIN_READS);
     }
@@ -2537,8 +2538,13 @@ LaunchBytes launch_bytes(const uint32_t *w, const uint32_t *seg_at, const uint32
             b.touched += whole < span ? whole : span;
             if (!(te[TT_INFO] & TI_OUTPUT)) b.reads += whole < span ? whole : span;
         }
-        for (uint32_t pc = SH_WORDS; n_segs == 1 && pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF)
-            b.streams += ((sh[pc] & 0xFF) == I_LOAD || (sh[pc] & 0xFF) == I_VLOAD) && ((sh[pc + 1] >> 16) & MF_STREAM);
+        bool bf16 = n_segs == 1;
+        for (uint32_t pc = SH_WORDS; pc < sh[S_WORDS]; pc += (sh[pc] >> 8) & 0xFF) {
+            if (((sh[pc] & 0xFF) != I_LOAD && (sh[pc] & 0xFF) != I_VLOAD) || !((sh[pc + 1] >> 16) & MF_STREAM)) continue;
+            bf16 &= ((sh[pc + 1] >> 8) & 0xFF) == DVM_BF16;
+            ++b.streams;
+        }
+        if (!bf16) b.streams = 0;
     }
     return b;
 }

@@ -131,12 +131,13 @@ def test_the_fuser_counts_what_it_launches():
         assert f.stats()["launches"] == launches, rows
 
 
-@pytest.mark.parametrize("name,cols,n,reads", [("c2_rmsnorm", 4096, 2, 1), ("c4_chain", 8192, 6, 3), ("add_f16like", 4096, 2, 2)])
+@pytest.mark.parametrize("name,cols,n,reads", [("c2_rmsnorm", 4096, 2, 1), ("c4_chain", 8192, 6, 3), ("add_f16like", 4096, 2, 2), ("add_sqrt", 4096, 2, 2)])
 def test_streaming_hint(ctx, name, cols, n, reads):
-    """By the bytes that a launch reads: 96 MB of one tensor, 32 of two, 16 of three."""
-    bound = {1: 96, 2: 32, 3: 16}[reads] << 20
+    """By the bytes that a launch reads: 96 MB, in bf16 32 of two tensors, 16 of three."""
     desc = W.get_program(name)
-    for rows, hint in ((bound // (reads * 2 * cols) - 3, 0), (bound // (reads * 2 * cols) + 1, 1)):
+    es = ES[desc.inputs[0][1]]
+    bound = {1: 96, 2: 32, 3: 16}[reads if es == 2 else 1] << 20
+    for rows, hint in ((bound // (reads * es * cols) - 3, 0), (bound // (reads * es * cols) + 1, 1)):
         shapes = [B.make_shape((cols,) if n_ in ("w", "gamma", "beta", "bias") else (rows, cols)) for n_, _ in desc.inputs]
         assert len(shapes) == n
         code = B.dvm_encode(ctx, B.Program(desc), shapes)
