@@ -46,7 +46,7 @@ typedef struct dvm_softmax_args {
     uint32_t set_tiles, set_m, set_sh;      // of one set
     uint32_t exact;                 // 1: rows laid out and added up as the interpreter does
     uint32_t ragged;                // exact: the row does not fill the tile
-    uint32_t lanes, log2_lanes;     // lanes on a row: a power of two from 8 to 1024 (exact: from 1 to 64, log2 given)
+    uint32_t lanes, log2_lanes;     // lanes on a row: a power of two from 8 to 512, in long rows 512 or 1024 (exact: from 1 to 64, log2 given)
     uint32_t in_long;               // 1: the kernel for long rows (lanes: 512 or 1024)
     uint32_t slots;                 // 16-byte chunks of a lane
     uint32_t tail;                  // a row may end in this slot of chunks or behind it

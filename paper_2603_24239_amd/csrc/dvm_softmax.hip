@@ -12,7 +12,7 @@
 // Interpreter and this kernel, rotating inputs, us: masked softmax fp32 [64, 2048, 2048] 420 -> 367 (5.9 TB/s), [96, 1411, 1411] 343 -> 267,
 // softmax bf16 [192224, 751] 129 -> 94 (6.1 TB/s), fp32 [31250, 4096] 196 -> 161, fp32 [671, 100003] 141 -> 113 (4.7 TB/s), bf16 [1279, 100003]
 // 165 -> 120.  What is left in the last two is one row per compute unit: nothing is loaded while its exponentials are taken.
-// A row is T lanes wide (8 to 64 lanes of a wave, or a workgroup of up to 1024 threads), a lane holds NR chunks of 16 bytes.
+// A row is T lanes wide (8 to 64 lanes of a wave, or 2 to 16 waves of a workgroup), a lane holds NR chunks of 16 bytes.
 //
 // The bits of a row do not depend on where it stands, although the shift does: column c is summed in the class (c mod T * V); a class
 // is one lane's running sum at any shift, over ascending columns, and the classes are brought into their order through LDS before they are
@@ -201,7 +201,7 @@ template <int V, int T> DI float in_order_narrow(float *acc, uint32_t tid, int s
 
 // ---- rows of up to NR * T * V columns (less the shift), T lanes on a row --------------------------------------------------
 // Tiles `first` to `end`, `step` apart (one alone is written so too: outside a loop the compiler makes one vector of a lane's chunks and waits for
-// the first of them before it asks for the next, fp32 [1000, 16384] 28.0 -> 28.8 us).  rot: BLOCK * V floats of LDS, red: two for every wave.  HALF: a launch's rows have more than NR / 2 chunks a lane, so that many are not asked for.
+// the first of them before it asks for the next, fp32 [1000, 16384] in 1024 lanes of 4 chunks 28.0 -> 28.8 us).  rot: BLOCK * V floats of LDS, red: two for every wave.  HALF: a launch's rows have more than NR / 2 chunks a lane, so that many are not asked for.
 template <int BF16, int T, int NR, bool MASK, bool HALF> DI void rows_of(const dvm_softmax_args &s, uint32_t first, uint32_t end, uint32_t step, float *rot, float *red) {
     constexpr int V = BF16 ? 8 : 4, ES = BF16 ? 2 : 4, W = T * V, BLOCK = T < 256 ? 256 : T, RP = BLOCK / T;
     constexpr int GW = T > 64 ? T / 64 : 1;             // waves on a row
@@ -458,7 +458,7 @@ __global__ void __launch_bounds__(T) dvm_softmax_long(const dvm_softmax_alike a)
 // Independent parts of a stack.  Few rows leave most of the chip idle, and a launch for each is one after the other: eight unlike ones of fp32
 // [16, 100003] 156 us so, 48 in the interpreter and 25 here; bf16 [32, 17000] 43, 18 and 6.7; fp32 [600, 8192] 82, 65 and 55.  A workgroup takes its
 // tile's part from the argument block; the arithmetic of a row is that of a launch of its own.  One kernel for all rows of up to 256 lanes, with a lane's
-// most chunks (alike ones have the kernel for theirs: eight of bf16 [6000, 751] 24 there and 28 here), one for each lane count beyond.
+// most chunks (alike ones have the kernel for theirs: eight of bf16 [6000, 751] 24 there and 28 here), one for 512 lanes, and those for long rows.
 struct ManySoftmaxes {
     const dvm_softmax_mixed &p;
     DI uint32_t tiles() const { return p.first[p.n]; }
@@ -489,8 +489,8 @@ template <int BF16, int T, int NR, bool MASK> __global__ void __launch_bounds__(
     extern __shared__ __align__(16) float lds[];
     long_rows<BF16, T, NR, MASK>(ManySoftmaxes{p}, lds);
 }
-template <int BF16, int T, bool MASK> __global__ void __launch_bounds__(T) dvm_softmax_mixed_wide(const dvm_softmax_mixed p) {
-    constexpr int V = BF16 ? 8 : 4, NR = T == 1024 ? 4 : BF16 ? 6 : 8;
+template <int BF16, bool MASK> __global__ void __launch_bounds__(512) dvm_softmax_mixed_wide(const dvm_softmax_mixed p) {
+    constexpr int V = BF16 ? 8 : 4, NR = BF16 ? 6 : 8, T = 512;
     __shared__ __align__(16) float rot[T * V];
     __shared__ float red[2 * (T / 64)];
     const uint32_t part = ManySoftmaxes{p}.part_of(blockIdx.x, 0u), tile = blockIdx.x - p.first[part], all = p.first[p.n];
@@ -625,7 +625,7 @@ template <int BF16, int T, bool MASK> int launch_rows(const dvm_softmax_alike &a
     const dvm_softmax_args &s = a.s;
     if (s.slots <= 2) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 2, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
     else if (s.slots <= 4) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, 4, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
-    else if constexpr (T < 1024) hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, BF16 ? 6 : 8, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
+    else hipLaunchKernelGGL((dvm_softmax_rows<BF16, T, BF16 ? 6 : 8, MASK>), dim3(grid), dim3(BLOCK), 0, q, a);
     return (int)hipGetLastError();
 }
 // LDS of a launch whose longest rows have `slots`, and of the longest rows that its kernel takes
@@ -658,7 +658,7 @@ template <int BF16, bool MASK> int launch_any(const dvm_softmax_alike &a, unsign
     if (s.lanes == 64) return launch_rows<BF16, 64, MASK>(a, grid, q);
     if (s.lanes == 128) return launch_rows<BF16, 128, MASK>(a, grid, q);
     if (s.lanes == 256) return launch_rows<BF16, 256, MASK>(a, grid, q);
-    if (s.in_long == 0) return s.lanes == 512 ? launch_rows<BF16, 512, MASK>(a, grid, q) : launch_rows<BF16, 1024, MASK>(a, grid, q);
+    if (s.in_long == 0) return launch_rows<BF16, 512, MASK>(a, grid, q);
     if (s.lanes == 512) {
         if constexpr (BF16) if (s.slots <= 8) return launch_long<BF16, 512, 8, MASK>(a, grid, q);
         if (s.slots <= 16) return launch_long<BF16, 512, 16, MASK>(a, grid, q);
@@ -673,8 +673,7 @@ template <int BF16, bool MASK> int launch_mixed(const dvm_softmax_mixed &p, unsi
     unsigned slots = 0;
     for (uint32_t i = 0; i < p.n; ++i) slots = p.part[i].slots > slots ? p.part[i].slots : slots;
     if (s.lanes <= 256) hipLaunchKernelGGL((dvm_softmax_mixed_rows<BF16, MASK>), dim3(grid), dim3(256), 0, q, p);
-    else if (s.in_long == 0 && s.lanes == 512) hipLaunchKernelGGL((dvm_softmax_mixed_wide<BF16, 512, MASK>), dim3(grid), dim3(512), 0, q, p);
-    else if (s.in_long == 0) hipLaunchKernelGGL((dvm_softmax_mixed_wide<BF16, 1024, MASK>), dim3(grid), dim3(1024), 0, q, p);
+    else if (s.in_long == 0) hipLaunchKernelGGL((dvm_softmax_mixed_wide<BF16, MASK>), dim3(grid), dim3(512), 0, q, p);
     else if (s.lanes == 512) return launch_long<BF16, 512, BF16 ? 16 : 20, MASK>(p, slots, grid, q);
     else if (BF16 || slots <= 28) return launch_long<BF16, 1024, 20, MASK>(p, slots, grid, q);
     else if constexpr (!BF16) return launch_long<BF16, 1024, 24, MASK>(p, slots, grid, q);

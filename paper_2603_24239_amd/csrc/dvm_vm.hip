@@ -2187,7 +2187,9 @@ void magic_of(uint32_t d, uint32_t *m, uint32_t *sh) {
 // Lanes on a row: those that leave the fewest idle, lanes * chunks being what a row costs, over up to 8 chunks of 16 bytes a lane (bf16: 6,
 // for the registers).  More than 4 cost an eighth for the waves they displace (not in fp32 rows of one wave), a row of several waves a
 // sixteenth for its barriers: bf16 [64000, 2000] 141 us in 256 lanes of 2 chunks, 99 in 128 of 3, 82 in 64 of 5; fp32 [31250, 4096] 169 in 128 of
-// 8, 161 in 256 of 4.  Longer rows go to the kernel that keeps one per workgroup.
+// 8, 161 in 256 of 4.  512 at most: 1024 leave one or two workgroups to a compute unit and were slower than 512 of twice the chunks, and than the
+// interpreter (fp32 [1000, 16384] 27.7 and 24.6 us, interpreter 27.0; [1100, 15000] from the cache 28.4, 21.3 and 25.7; bf16 [1500, 24500] 41.2 and 30.3).
+// Longer rows go to the kernel that keeps one per workgroup.
 bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tensors, int n_sets, uint32_t n_tensors, bool may_exact,
                    dvm_softmax_args *a) {
     if (sh[S_INNER] != 0 || sh[S_NWG] != 0 || (sh[S_FLAGS] & (SF_LDS | SF_CSTREAM)) || sh[S_NROWS] == 0) return false;
@@ -2322,9 +2324,9 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     const uint32_t planned = even ? 0 : line - 1;
     if (!a->exact) a->lanes = 0;
     uint64_t best = a->exact ? 0 : UINT64_MAX;
-    for (uint32_t lanes = 8; lanes <= 1024; lanes *= 2) {
+    for (uint32_t lanes = 8; lanes <= 512; lanes *= 2) {
         const uint32_t n = need(lanes, planned);
-        if (n > (lanes == 1024 ? (dt ? 3u : 4u) : dt ? 6u : 8u)) continue;
+        if (n > (dt ? 6u : 8u)) continue;
         const uint64_t cost = (uint64_t)lanes * n * (n > 4 && (dt || lanes != 64) ? 18 : 16) * (lanes > 64 ? 17 : 16);
         if (cost < best) {
             best = cost;
@@ -2336,7 +2338,7 @@ bool plain_softmax(const uint32_t *sh, const uint32_t *table, void *const *tenso
     if (a->in_long != 0) a->lanes = need(512, planned) <= (dt ? 16u : 24u) ? 512 : 1024;
     a->shifted = 0;
     if (!a->exact) {
-        const uint32_t most = a->in_long != 0 ? (a->lanes == 512 ? (dt ? 16u : 24u) : dt ? 20u : 33u) : a->lanes == 1024 ? 4u : dt ? 6u : 8u;
+        const uint32_t most = a->in_long != 0 ? (a->lanes == 512 ? (dt ? 16u : 24u) : dt ? 20u : 33u) : dt ? 6u : 8u;
         a->slots = need(a->lanes, planned);
         if (a->slots > most) return false;
         if (!even) shift = planned;
