@@ -87,7 +87,8 @@ template <int BF16> DI u32x4 narrow(const float *v, float scale) {
     return r;
 }
 // (closes a branch of loads with the streaming hint, which the compiler would otherwise merge with the branch of those without it, dropping
-// the hint)
+// the hint.  It still asks for the slots that every row has before the branch, without the hint: with it on all of them fp32 [30000, 2048] took
+// 79 us instead of 71, bf16 [60000, 2048] 77 instead of 70, under a mask fp32 [1, 32, 3000, 3000] 413 instead of 427.)
 #define STREAMING() asm volatile("; streaming" ::: "memory")
 template <bool NT> DI u32x4 load16(const char *p) {
     if constexpr (NT) return __builtin_nontemporal_load((const GLOBAL_AS u32x4_a2 *)p);

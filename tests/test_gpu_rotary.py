@@ -10,6 +10,7 @@ from workloads import gen
 from workloads import programs as W
 
 from . import harness as H
+from . import launch_plan as L
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -100,11 +101,17 @@ def test_batched_and_written_inputs():
     B.dvm_run_batched(ctx, code, [[t.data_ptr() for t in s] for s in ins], table.data_ptr(), table.numel() * 8, stream)
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(outs, refs))
-    print("[case] rotation written over its inputs", flush=True)        # (stays with the interpreter)
-    d = sets[0]
-    whole = refs[0]
-    try:
-        H.run_vm(desc, d, outputs={"y1": d["x1"], "y2": d["x2"]}, ctx=ctx)
-    except B.DvmError:
-        return
-    assert torch.equal(d["x1"], whole[..., :64]) and torch.equal(d["x2"], whole[..., 64:])
+    # Written over its inputs, in the form that allows it (all products first): the interpreter's, whose plan loads before it stores
+    print("[case] rotation written over its inputs", flush=True)
+    products = [("a", "mul", ["x1", "c"], {}), ("b", "mul", ["x2", "s"], {}), ("d", "mul", ["x2", "c"], {}), ("e", "mul", ["x1", "s"], {})]
+    desc, d = W._p("rope_late", desc.inputs, products + [("y1", "sub", ["a", "b"], {}), ("y2", "add", ["d", "e"], {})], desc.outputs), sets[0]
+    ins, whole = [d[k] for k in ("x1", "x2", "c", "s")], torch.empty_like(refs[0])
+    views = [whole[..., :64], whole[..., 64:]]
+    ctx.set_copies_in_flight(1)
+    apart, over = B.encode_for(ctx, H.program(desc), ins, views), B.encode_for(ctx, H.program(desc), ins, ins[:2])
+    assert [l.kind for l in L.launches(apart, [[t.data_ptr() for t in ins + views]])] == [L.ROTARY]
+    assert [l.kind for l in L.launches(over, [[t.data_ptr() for t in ins + ins[:2]]])] == [L.INTERPRETER]
+    B.run_on(ctx, apart, ins + views)
+    B.run_on(ctx, over, ins + ins[:2])
+    torch.cuda.synchronize()
+    assert torch.equal(d["x1"], views[0]) and torch.equal(d["x2"], views[1])

@@ -14,13 +14,14 @@ from . import harness as H
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 INF = float("inf")
-MIN_BYTES = 16 << 20        # below, such a program runs in the interpreter
+MIN_BYTES = 16 << 20        # below, a program that is nothing else runs in the kernel with the interpreter's bits, a part of a stack in the interpreter
 TORCH_DT = {"f32": torch.float32, "bf16": torch.bfloat16}
-# lanes on a row change behind 97, 225, 481 (193, 449, 961, 1985 in bf16), 2017, 8161 (16321); slots in registers and LDS behind
-# 32737, 114657, and the kernel ends at 131041 columns that start anywhere in a line
-EDGES = {"f32": [4, 5, 31, 33, 65, 97, 98, 225, 226, 481, 482, 1000, 1411, 2017, 2018, 2048, 4096, 8161, 8162, 8192, 32737, 32738, 60011, 114657, 114658,
-                 131041, 131042, 131072],
-         "bf16": [8, 9, 63, 65, 193, 194, 257, 449, 450, 751, 961, 962, 1985, 1986, 4096, 16321, 16322, 65473, 65474, 131071, 163777, 163778]}
+# lanes on a row change behind 258, 578, 1218 (bf16; in fp32 back and forth, 128 behind 2018) and on up to 512; a workgroup keeps a row behind 16353 (24513),
+# of 1024 lanes behind 49121 (65473); its slots leave the registers behind 32737, change their kernel behind 114657, and the kernel ends at 135137 (163777)
+# columns that start anywhere in a line
+EDGES = {"f32": [4, 5, 31, 33, 65, 97, 98, 225, 226, 481, 482, 1000, 1411, 2017, 2018, 2048, 4096, 8161, 8162, 8192, 16353, 16354, 32737, 32738, 49121, 49122, 60011, 114657, 114658,
+                 131041, 131042, 131072, 135137, 135138],
+         "bf16": [8, 9, 63, 65, 193, 194, 257, 449, 450, 751, 961, 962, 1985, 1986, 4096, 16321, 16322, 24513, 24514, 65473, 65474, 131071, 163777, 163778]}
 
 
 def rows_for(cols, dt):
