@@ -2510,13 +2510,14 @@ bool plain_rotary(const uint32_t *sh, int nr, const uint32_t *table, void *const
 // Loads take the streaming hint in launches that read more than this.  Less may still be in the last-level cache (256 MB) from the program that
 // wrote it or the one that read it last, beside what others use; the hint then costs (RMSNorm bf16 [11000, 4096], 90 MB read, 30.8 us
 // without and 36.5 with it, RoPE over 8111 tokens, 66 MB, 31.6 and 38.1), and pays beyond (fp32 add, 128 MB, 34.0 and 31.5, the 12-op chain over
-// 2245 rows of 8192, 110 MB, 40.1 and 36.7).
+// 2245 rows of 8192, 110 MB, 40.1 and 36.7), where the inputs are in memory: RMSNorm reading 128 MB 51.8 and 48.6 us, from the cache 42.4 and 47.1.
 constexpr uint64_t STREAM_MIN_READS = 96ull << 20;
 // A bf16 program that reads several tensors so gains earlier: us without and with the hint, inputs in memory (in the cache), the chain (three tensors)
-// reading 16 MB 15.5 14.6 (11.7 12.5), 48 MB 24.2 20.4 (20.1 19.4), add (two) 32 MB 13.1 12.0 (9.2 9.9), 64 MB 21.4 19.6 (18.5 17.6); but RMSNorm (one) 48 MB
+// reading 16 MB 15.4 14.6 (11.6 13.0), 24 MB 18.8 16.1 (12.7 14.3), 48 MB 24.2 20.4 (20.1 19.4), add (two) 16 MB 8.8 8.4 (6.0 7.4), 32 MB 13.1 12.0 (9.2 9.9),
+// 64 MB 21.4 19.6 (18.5 17.6); but RMSNorm (one) 48 MB
 // 22.2 20.8 (18.5 19.1), 80 MB 33.9 31.7 (27.7 30.0).  In fp32 what the hint drops from a cache that is nearly full costs more than it gives: an addition
 // beside a softmax of its size, 34 MB read by each, 19.8 and 24.4, alone 64 MB 21.4 19.7 (17.9 17.7).
-constexpr uint64_t STREAM_MIN_READS_OF_TWO = 32ull << 20, STREAM_MIN_READS_OF_THREE = 16ull << 20;
+constexpr uint64_t STREAM_MIN_READS_OF_SEVERAL = 32ull << 20;
 constexpr uint64_t LARGE_MIN_BYTES = 256ull << 20;      // launches larger than the last-level cache
 constexpr uint64_t FLAT_MIN_BYTES = 64ull << 20;        // the same for rows cut into column tiles
 
@@ -2525,7 +2526,7 @@ struct LaunchBytes {
     uint64_t spans = 0, touched = 0, reads = 0;     // the last two: without what lies between the rows of views
     uint32_t streams = 0;                           // of a segment alone, all of bf16: tensors that it reads past the caches if it may
     bool stream(int n_sets) const {
-        return reads * (uint64_t)n_sets >= (streams > 2 ? STREAM_MIN_READS_OF_THREE : streams == 2 ? STREAM_MIN_READS_OF_TWO : STREAM_MIN_READS);
+        return reads * (uint64_t)n_sets >= (streams > 1 ? STREAM_MIN_READS_OF_SEVERAL : STREAM_MIN_READS);
     }
 };
 LaunchBytes launch_bytes(const uint32_t *w, const uint32_t *seg_at, const uint32_t *segs, uint32_t n_segs) {

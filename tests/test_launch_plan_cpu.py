@@ -133,10 +133,10 @@ def test_the_fuser_counts_what_it_launches():
 
 @pytest.mark.parametrize("name,cols,n,reads", [("c2_rmsnorm", 4096, 2, 1), ("c4_chain", 8192, 6, 3), ("add_f16like", 4096, 2, 2), ("add_sqrt", 4096, 2, 2)])
 def test_streaming_hint(ctx, name, cols, n, reads):
-    """By the bytes that a launch reads: 96 MB, in bf16 32 of two tensors, 16 of three."""
+    """By the bytes that a launch reads: 96 MB, in bf16 32 of several tensors."""
     desc = W.get_program(name)
     es = ES[desc.inputs[0][1]]
-    bound = {1: 96, 2: 32, 3: 16}[reads if es == 2 else 1] << 20
+    bound = (32 if reads > 1 and es == 2 else 96) << 20
     for rows, hint in ((bound // (reads * es * cols) - 3, 0), (bound // (reads * es * cols) + 1, 1)):
         shapes = [B.make_shape((cols,) if n_ in ("w", "gamma", "beta", "bias") else (rows, cols)) for n_, _ in desc.inputs]
         assert len(shapes) == n
