@@ -41,6 +41,15 @@ ALL_WORKLOADS = ["c1_gelu", "c2_rmsnorm", "c3_masked_softmax", "c4_chain", "c5_l
 PROFILE_SUMMARY = {w: f"profiles/dvm_vm_kernel_{w}.md" for w in ALL_WORKLOADS}
 
 
+# What the launches of a workload run in beside, or instead of, the interpreter
+OTHER_KERNELS = {"c3_masked_softmax": "dvm_softmax_rows", "c5_layers": "dvm_vm_kernel, dvm_rotary, dvm_softmax_rows", "column_sum": "dvm_colreduce, dvm_vm_kernel"}
+
+
+def kernel_names(workloads) -> str:
+    names = {w: OTHER_KERNELS.get(w, "dvm_vm_kernel (bytecode interpreter)") for w in workloads}
+    return next(iter(names.values())) if len(set(names.values())) == 1 else "; ".join(f"{w}: {k}" for w, k in names.items())
+
+
 def measured_traffic_ratio(workload: str):
     """HBM bytes / algorithmic bytes of the interpreter launches of a workload, from the committed counter summary
     (two rocprofv3 --pmc runs of this command, FETCH_SIZE and WRITE_SIZE, each scaled by what the same counter
@@ -872,7 +881,7 @@ def run(args, names, cpu) -> int:
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "; ".join(dtypes), "data": "synthetic", "config": wl,
         "pct_of_hbm_peak": round(100.0 * value / HBM_PEAK_GBS, 2),
-        "roofline": {"bound": "hbm", "kernel": "dvm_vm_kernel (bytecode interpreter)", "achieved": round(achieved, 2),
+        "roofline": {"bound": "hbm", "kernel": kernel_names(head), "achieved": round(achieved, 2),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "bytes_per_launch": int(tot_bytes_step / launches_step), "avg_launch_ms": round(kern_step_ms / launches_step, 5),
                      "launches": launches_step * args.steps,

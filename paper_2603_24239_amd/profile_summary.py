@@ -82,11 +82,12 @@ def main() -> int:
                                                                     r["Percentage"]))
     tot_ns = sum(float(r["TotalDurationNs"]) for r in vm)
     calls = sum(int(r["Calls"]) for r in vm)
-    avg_us = tot_ns / calls / 1e3
+    runs = 3 * pc["launches_per_pass"]          # a call may launch several kernels: softmaxes that run apart have their own
+    avg_us = tot_ns / runs / 1e3
     bpl = roof["bytes_per_launch"]
     out.append("")
-    out.append("Launches of the library (all instantiations together): %d, average %.2f us.  Algorithmic bytes per launch (mean over the launches;"
-               % (calls, avg_us))
+    out.append("Calls of the library: %d, %d kernels (all instantiations together), average %.2f us a call.  Algorithmic bytes per call (mean over the calls;"
+               % (runs, calls, avg_us))
     out.append("one read of every input element and one write of every output element): %.1f MB -> %.2f TB/s, %.1f %% of the 8 TB/s HBM peak."
                % (bpl / 1e6, bpl / avg_us / 1e6, 100 * bpl / avg_us / 1e6 / 8))
     out.append("The same command without a profiler (HIP events on the launch stream) reported avg_launch_ms %.5f (%.2f TB/s, frac %.4f),"
@@ -102,18 +103,19 @@ def main() -> int:
         KIB = 256 * 1024
         ff, wf = KIB / (sum(fcp) / len(fcp)), KIB / (sum(wcp) / len(wcp))
         fvm, wvm = f_all["vm"], w_all["vm"]
-        fb, wb = sum(fvm) / len(fvm) * ff * 1024, sum(wvm) / len(wvm) * wf * 1024
+        runs = pc["launches_per_pass"]
+        fb, wb = sum(fvm) / runs * ff * 1024, sum(wvm) / runs * wf * 1024
         out.append("## HBM traffic counters\n")
         out.append(f"    rocprofv3 --pmc FETCH_SIZE --output-format csv -d <dir>/pmcF -o p -- {cmd} --steps 1 --warmup 0 --no-cpu-baseline --skip-unstacked --calibrate-copy")
         out.append(f"    rocprofv3 --pmc WRITE_SIZE --output-format csv -d <dir>/pmcW -o p -- {cmd} --steps 1 --warmup 0 --no-cpu-baseline --skip-unstacked --calibrate-copy\n")
         out.append("`--calibrate-copy` appends three plain 256 MiB device-to-device copies (`__amd_rocclr_copyBuffer`): a kernel that is known to")
         out.append("read 262144 KiB and write 262144 KiB; its counter readings give the factor from counter units to KiB.\n")
-        out.append("| counter | copy kernel reads (mean of %d) | factor to KiB | interpreter kernel (mean of %d launches) | scaled bytes per launch |\n|---|---|---|---|---|"
-                   % (len(fcp), len(fvm)))
-        out.append("| FETCH_SIZE | %.1f | %.5f | %.1f | %.0f |" % (sum(fcp) / len(fcp), ff, sum(fvm) / len(fvm), fb))
-        out.append("| WRITE_SIZE | %.1f | %.5f | %.1f | %.0f |" % (sum(wcp) / len(wcp), wf, sum(wvm) / len(wvm), wb))
+        out.append("| counter | copy kernel reads (mean of %d) | factor to KiB | kernels of the library (mean of %d calls) | scaled bytes per call |\n|---|---|---|---|---|"
+                   % (len(fcp), runs))
+        out.append("| FETCH_SIZE | %.1f | %.5f | %.1f | %.0f |" % (sum(fcp) / len(fcp), ff, sum(fvm) / runs, fb))
+        out.append("| WRITE_SIZE | %.1f | %.5f | %.1f | %.0f |" % (sum(wcp) / len(wcp), wf, sum(wvm) / runs, wb))
         out.append("")
-        out.append("Read + written per launch: %.0f bytes against %d algorithmic bytes." % (fb + wb, bpl))
+        out.append("Read + written per call: %.0f bytes against %d algorithmic bytes." % (fb + wb, bpl))
         out.append("")
         out.append("traffic_bytes_per_launch: %d" % round(fb + wb))
         out.append("traffic_ratio: %.4f" % ((fb + wb) / bpl))
@@ -128,7 +130,7 @@ def main() -> int:
             tot = {c: sum(v) for c, v in vals.items()}
             out.append("## Shader-sequencer counters (issue limits)\n")
             out.append(f"    rocprofv3 --pmc {' '.join(SQ)} --output-format csv -d <dir>/pmcSQ -o p -- {cmd} --steps 1 --warmup 0 --no-cpu-baseline --skip-unstacked\n")
-            out.append("Sums over the %d interpreter launches of one pass (SQ_WAVE_CYCLES, SQ_WAIT_INST_ANY and SQ_ACTIVE_INST_ANY count in units of four cycles).\n" % n)
+            out.append("Sums over the %d kernels of one pass (SQ_WAVE_CYCLES, SQ_WAIT_INST_ANY and SQ_ACTIVE_INST_ANY count in units of four cycles).\n" % n)
             out.append("| counter | total | per wave |\n|---|---|---|")
             for c in SQ:
                 out.append("| %s | %.4g | %.1f |" % (c, tot[c], tot[c] / tot["SQ_WAVES"]))
@@ -139,7 +141,7 @@ def main() -> int:
                           4 * wc / tot["SQ_WAVES"]))
             out.append("instruction to complete (memory, mostly) %.0f %% and issues %.0f %% of the time.  Scalar instructions per vector instruction: %.2f."
                        % (100 * tot["SQ_WAIT_INST_ANY"] / wc, 100 * tot["SQ_ACTIVE_INST_ANY"] / wc, tot["SQ_INSTS_SALU"] / max(1.0, tot["SQ_INSTS_VALU"])))
-            out.append("Algorithmic bytes per scalar instruction: %.1f." % (bpl * n / max(1.0, tot["SQ_INSTS_SALU"])))
+            out.append("Algorithmic bytes per scalar instruction: %.1f." % (bpl * pc["launches_per_pass"] / max(1.0, tot["SQ_INSTS_SALU"])))
             out.append("")
     text = "\n".join(out) + "\n"
     path = os.path.join(ROOT, "profiles", f"dvm_vm_kernel_{W}.md")
