@@ -270,9 +270,9 @@ int  dvm_stack_spatial(const void *const *codes, const size_t *lens, int n,
  * buffer ran, and that no later piece reads, is a pure intermediate and is never written to memory.
  * A piece that needs all of an earlier piece (not only what its own workgroup wrote) starts a kernel launch of
  * its own inside that one dvm_run call (DVM_ORDER_BY_LAUNCH), or, when dvm_fuser_set_workspace has lent a workspace,
- * waits inside the single kernel launch (DVM_ORDER_IN_KERNEL).  When the pieces do not fit one program (tensor
+ * waits inside the single kernel launch (DVM_ORDER_IN_KERNEL; large softmaxes have launches of their own, see dvm_stack).  When the pieces do not fit one program (tensor
  * table, bytecode size, interpreter variant), every piece is run on its own, in order.  dvm_fuser_stats counts
- * kernel launches.
+ * kernel launches, those that large softmaxes have of their own (dvm_stack) among them.
  *
  * All calls are host calls.  The fuser owns no device memory: every tensor and every result buffer
  * is the caller's (device pointers), and must stay valid until the buffer that uses it has run.

@@ -1,14 +1,14 @@
 // Softmax along the row, plain or of a sum of two tensors (attention scores and their mask), outside the interpreter.
 //
-// A meta-kernel whose body is load [, load, add], max, exp(. - max), 1 / sum, store times that, over at least DVM_SOFTMAX_MIN_BYTES, has
-// a launch of its own wherever it stands (alone, in a stack, in a batched launch: the same kernel, the same bits).  It is bound by
+// A meta-kernel whose body is load [, load, add], max, exp(. - max), 1 / sum, store times that, over at least DVM_SOFTMAX_MIN_BYTES, leaves
+// the interpreter wherever it stands (alone, in a stack, in a batched launch: the same arithmetic, the same bits).  It is bound by
 // memory, and what the interpreter lost there was not arithmetic (its vector units are busy 30 % of the time) but the way it meets memory:
 //   - Rows that are no whole number of 128-byte lines.  A wave's 1 KiB store then begins and ends inside a line, each such line is
 //     written in two parts, and the traffic of writes grows by a tenth.  Here the chunk grid of a row is shifted to the lines of the
 //     output: every store but a row's first and last covers whole lines (masked softmax fp32 [96, 1411, 1411] 308 -> 285 us).
 //   - Workgroups that walk a long list of tiles drift apart and the memory in use with them.  A workgroup here takes one tile; the
 //     dispatcher keeps the front together (softmax bf16 [192224, 751] 112 us in 4 workgroups per compute unit, 99 in one per tile).
-//   - Rows longer than a tile were read twice.  Here a workgroup holds one in its registers and LDS.
+//   - Rows longer than a tile were read twice.  Here a workgroup holds one in its registers and LDS (a second tensor is read again in each pass).
 // Interpreter and this kernel, rotating inputs, us: masked softmax fp32 [64, 2048, 2048] 420 -> 367 (5.9 TB/s), [96, 1411, 1411] 343 -> 267,
 // softmax bf16 [192224, 751] 129 -> 94 (6.1 TB/s), fp32 [31250, 4096] 196 -> 161, fp32 [671, 100003] 141 -> 113 (4.7 TB/s), bf16 [1279, 100003]
 // 165 -> 120.  What is left in the last two is one row per compute unit: nothing is loaded while its exponentials are taken.

@@ -2182,8 +2182,8 @@ void magic_of(uint32_t d, uint32_t *m, uint32_t *sh) {
 // DVM_SOFTMAX_MIN_BYTES in a layout of its own (rows longer than a tile, which the interpreter reads twice: an eighth of that): below, a launch
 // is bound by its own cost, and in a stack an extra one (2 us) would cost more than it gives.  Rows of less than a line and smaller segments
 // go to the kernel with the interpreter's bits where they are the whole program (fp32 [400000, 9] 12.4 us in the interpreter and 18.0 in the
-// layout here).  The rule looks at the segment alone, so that its bits are the same alone, in a stack and in a batched launch (in a
-// spatial stack, whose parts share one launch, it stays with the interpreter).
+// layout here).  The rule looks at the segment alone, so that its bits are the same alone, in a stack and in a batched launch (apart from outputs that
+// overlap an operand, see below; in a spatial stack, whose parts share one launch, it stays with the interpreter).
 // Lanes on a row: those that leave the fewest idle, lanes * chunks being what a row costs, over up to 8 chunks of 16 bytes a lane (bf16: 6,
 // for the registers).  More than 4 cost an eighth for the waves they displace (not in fp32 rows of one wave), a row of several waves a
 // sixteenth for its barriers: bf16 [64000, 2000] 141 us in 256 lanes of 2 chunks, 99 in 128 of 3, 82 in 64 of 5; fp32 [31250, 4096] 169 in 128 of
